@@ -76,6 +76,24 @@ __device__ __forceinline__ float halves_sum(float x) {
     return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
+// One wave-wide global -> LDS copy, 16 bytes per lane: lane l's bytes land at lds_base + 16 l.
+// Issued as inline asm so that the compiler does not serialise later LDS reads of OTHER stages
+// behind it; completion is awaited explicitly with wait_vm<n>() before the stage is published by
+// a barrier.  lds_base must be wave-uniform.  The statement overwrites m0, which the compiler reserves and does
+// not accept on a clobber list; the kernels here contain nothing else that lives in m0 (no indirect register
+// indexing, no LDS-direct or message instructions), and a host-side test checks the generated assembly for that.
+__device__ __forceinline__ void dma16(const void* gbase, uint32_t voff, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(gbase) : "memory");
+}
+// s_waitcnt vmcnt(CNT) with the other counters left alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14,
+// expcnt 6:4, lgkmcnt 11:8).  Emitted through the builtin so that the compiler's own wait bookkeeping
+// sees it.
+template <int CNT>
+__device__ __forceinline__ void wait_vm() {
+    static_assert(CNT >= 0 && CNT < 64, "vmcnt is a 6-bit counter");
+    __builtin_amdgcn_s_waitcnt((CNT & 15) | ((CNT >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
 // XCD-aware remap of a 1-D grid.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs;
 // this makes each XCD own a contiguous range of logical ids, so that the workgroups sharing one
 // head's K/V also share one L2.

@@ -1,301 +1,404 @@
 // Fused attention forward for gfx950 in fp32 throughout (fp32 MFMA 32x32x2, fp32 probabilities).
 // Same dataflow as the bf16 kernel (paper sections 4-5: one pass over blocks of query rows with
-// Logit, softmax and Attend interleaved), sized for small problems: 4 wavefronts x 32 query rows
-// per workgroup, 32 keys per tile, one LDS stage fed from a register prefetch of the next tile; small problems
-// take a second form that splits the keys over the wavefronts of a workgroup (fwd_f32_splitkeys_kernel).
+// Logit, softmax and Attend interleaved).
 #include "flat_common.hpp"
 #include "flat_launch.hpp"
 
+#include <math.h>
+
+#include <type_traits>
+
 namespace flat {
 
-// One 32-key tile for one wavefront (32 query rows): Logit, exact online softmax, Attend.  Ks holds the tile's
-// keys with row pitch D + 1, Vs its values with row pitch D.
-template <int D, bool CAUSAL>
-__device__ __forceinline__ void f32_tile(const float* Ks, const float* Vs, int jbase, int N, int q0w, int qrow, float c,
-                                         const float (&qf)[D / 2], floatx16 (&oacc)[D / 32], float& m, float& lsum, int l32,
-                                         int half) {
-    constexpr int BC = 32, KS = D / 2, DB = D / 32, KLD = D + 1;
-    // Logit: S^T[key, query]
-    floatx16 s;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) s = mfma_f32_32x32x2(Ks[l32 * KLD + 2 * ks + half], qf[ks], s);
+// One workgroup owns 32 query rows and its NW wavefronts divide the KEYS: wavefront w takes the 32-key tiles w, w + NW, ...
+// and keeps a running result (reference maximum m, row sum l, unnormalised O) of its own; the partial results are merged
+// through LDS at the end.
+//
+// What bounds it: the fp32 matrix pipe.  A 32x32x2 MFMA takes 64 cycles for 4096 flops and a 32 x 32 block of logits needs D of
+// them, against about 110 vector instructions, so one wavefront per SIMD keeps the pipe busy if nothing it waits for
+// stands between two MFMAs.  Hence:
+//   - Tiles are private to a wavefront (no barrier in the loop): 32 keys of K and of V in LDS, one buffer each, filled by
+//     global_load_lds.  A buffer is free as soon as its operands sit in registers, so the next tile's loads go out at the
+//     start of the phase that multiplies them and have almost two phases (7000 cycles at D = 128) to land.
+//   - Two phases per tile: A = Logit(i + 1) with the exponentials of tile i between its MFMAs, B = Attend(i) with the row
+//     maximum of tile i + 1 between its MFMAs.  The second half of a phase reads the operands of the other one from LDS.
+//   - The contraction index of a product may be permuted, if both operands agree, and so may the rows of its result.  Half h of
+//     a wavefront takes head-dim elements 8 g + 4 h .. + 3 of K and Q for four Logit MFMAs (one ds_read_b128 per operand), and
+//     row i of accumulator db is head-dim column DB i + db, so one read of DB consecutive values of V serves the DB Attend
+//     MFMAs of a key.
+//   - The row maximum is exact but lazy: O and l are rescaled only when a row's maximum rises more than 2^8 above the
+//     reference (fp32 has the range; the quotient O / l does not depend on the reference).
+// LDS: chunk c (16 bytes) of K row r lives in slot c ^ (r & 15): a ds_read_b128 touches 16 rows at one chunk index per clock and
+// then meets 16 different slots.  V rows are read along the row and need no swizzle.
+// Measured: 16 heads of 8192 positions at d = 128 without a mask 128 TFLOP/s, 32 heads of 4096 at d = 64 130 (a large fp32
+// matrix product reaches 154 on this card; this loop with loads, operand reads and exponentials taken out 145).  Before, with
+// 128-row workgroups around one shared LDS tile and operands read a float at a time: 110 and 113; and short of 1024 such
+// workgroups, where the keys were split over unpipelined wavefronts: 16 causal heads of 2049 positions at d = 128 351 -> 162 us,
+// 12 heads of 512 at d = 64 21 -> 12 us.
+template <int D>
+struct F32Cfg {
+    static constexpr int ROWB = D * 4;             // bytes of a row
+    static constexpr int TILE = 32 * ROWB;         // one 32-key tile of K or V
+    static constexpr int CHUNKS = ROWB / 16;
+    static constexpr int RPL = 1024 / ROWB;        // rows filled by one wave-wide load
+    static constexpr int LOADS = 32 / RPL;         // loads per tile and tensor
+    static constexpr int G = D / 8;                // groups of four Logit MFMAs
+    static constexpr int DB = D / 32;              // accumulator blocks
+    static constexpr int WAVE_LDS = 2 * TILE;
+    static constexpr int WAVES_PER_CU = D == 64 ? 8 : 4;                     // two and one per SIMD
+    static constexpr int LDS_RESERVED = 160 * 1024 / WAVES_PER_CU;           // of a wavefront: no third one on some SIMDs
+};
 
-    const bool masked = (jbase + BC > N) || (CAUSAL && jbase + BC - 1 > q0w);
-    uint32_t okmask = 0xffffu;
-    if (masked) {
-        okmask = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = jbase + acc_row(r, half);
-            const bool ok = key < N && (!CAUSAL || key <= qrow);
-            okmask |= ok ? (1u << r) : 0u;
-            s[r] = ok ? s[r] : -INFINITY;
-        }
+constexpr float kF32LazyMax = 8.0f;  // log2 units
+
+template <int D, int NW, bool CAUSAL>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                                          const float* __restrict__ V, float* __restrict__ O, int N,
+                                                                          int n_qtiles, int n_blocks, int blocks_per_xcd, float c) {
+    using C = F32Cfg<D>;
+    constexpr int G = C::G, DB = C::DB, LOADS = C::LOADS;
+    typedef float floatdb __attribute__((ext_vector_type(DB)));
+    typedef const floatx4 __attribute__((address_space(3))) * lds_f4_ptr;
+    typedef const floatdb __attribute__((address_space(3))) * lds_fdb_ptr;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    // Without a mask an XCD takes a contiguous range of (head, row block) pairs, so that a head's K and V stay in one L2; with the
+    // causal mask the blocks are ranked heaviest first over all heads and dealt to the XCDs in turn.
+    int bh, qt;
+    if (!CAUSAL) {
+        const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
+        if (logical >= n_blocks) return;
+        bh = logical / n_qtiles;
+        qt = logical - bh * n_qtiles;
+    } else {
+        const int rank = blockIdx.x;
+        if (rank >= n_blocks) return;
+        const int heads = n_blocks / n_qtiles;
+        const int from_end = rank / heads;
+        bh = rank - from_end * heads;
+        qt = n_qtiles - 1 - from_end;
     }
-    float mx = s[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = __builtin_fmaxf(mx, s[r]);
-    mx = halves_max(mx);
-    const float m_new = __builtin_fmaxf(m, mx * c);
-    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-    lsum *= alpha;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-    m = m_new;
-    float p[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        float x = __builtin_fmaf(s[r], c, -m_new);
-        if (masked) x = (okmask >> r) & 1u ? x : -INFINITY;
-        p[r] = __builtin_amdgcn_exp2f(x);
-        lsum += p[r];
-    }
-    // Attend: O^T[dcol, query] += V^T[dcol, key] P^T[key, query]; step r contracts the two keys
-    // acc_row(r, 0) and acc_row(r, 1) held by the two wave halves.
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int key_local = acc_row(r, half);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) oacc[db] = mfma_f32_32x32x2(Vs[key_local * D + 32 * db + l32], p[r], oacc[db]);
-    }
-}
 
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                      const float* __restrict__ V, float* __restrict__ O, int N,
-                                                      int n_qtiles, int n_blocks, int blocks_per_xcd, float c) {
-    constexpr int BR = 128, BC = 32, KS = D / 2, DB = D / 32, KLD = D + 1;  // KLD: odd row pitch, conflict-free column reads
-    __shared__ float Ks[BC * KLD];
-    __shared__ __attribute__((aligned(16))) float Vs[BC * D];
-
-    const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
-    if (logical >= n_blocks) return;
-    const int bh = logical / n_qtiles;
-    int qt = logical - bh * n_qtiles;
-    if (CAUSAL) qt = n_qtiles - 1 - qt;
-
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t head = (size_t)bh * N * D;
-    const float* Qh = Q + head;
-    const float* Kh = K + head;
-    const float* Vh = V + head;
-    float* Oh = O + head;
-    const int q0w = qt * BR + wave * 32;
-    const int qrow = q0w + l32;
+    const char* const Kh = (const char*)(K + head);
+    const char* const Vh = (const char*)(V + head);
+    const int q0 = qt * 32, qrow = q0 + l32;
 
-    float qf[KS];
+    const int kv_len = CAUSAL ? min(N, q0 + 32) : N;
+    const int n_tiles = (kv_len + 31) / 32;
+    const int n_mine = (n_tiles - wave + NW - 1) / NW;  // tiles wave, wave + NW, ... of this wavefront
+
+    // ---- global -> LDS.  Load i of a tile fills rows RPL i .. of it; lane l fills slot l % CHUNKS of row RPL i + l / CHUNKS.
+    // Keys beyond N are clamped to the last one: their logits are masked and their values meet a zero probability.
+    const uint32_t lds_k = (uint32_t)(uintptr_t)smem + (uint32_t)wave * C::WAVE_LDS, lds_v = lds_k + C::TILE;
+    const int ld_row = lane / C::CHUNKS, ld_slot = lane % C::CHUNKS;
+    const int ld_kchunk = (ld_slot ^ ld_row) * 16, ld_vchunk = ld_slot * 16;
+    auto load_part = [&](bool is_k, int tile, int i) __attribute__((always_inline)) {
+        const int jbase = tile * 32;
+        const int row = min(C::RPL * i + ld_row, N - 1 - jbase);
+        const char* base = (is_k ? Kh : Vh) + (size_t)jbase * C::ROWB;
+        const uint32_t voff = (uint32_t)row * C::ROWB + (uint32_t)(is_k ? ld_kchunk ^ (((C::RPL * i) & 15) * 16) : ld_vchunk);
+        dma16(base, voff, (is_k ? lds_k : lds_v) + (uint32_t)i * 1024);
+    };
+    auto tile_of = [&](int i) __attribute__((always_inline)) { return wave + NW * i; };
+
+    // ---- operands
+    floatx4 qf[G], kf[G];
+    floatdb vf[16];
+    int koff[8];  // lane part of the K reads: chunk 2 g + half of row l32, for g mod 8
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = qrow < N ? Qh[(size_t)qrow * D + 2 * ks + half] : 0.f;
+    for (int g = 0; g < 8; ++g) koff[g] = (int)lds_k + l32 * C::ROWB + (((2 * g + half) ^ (l32 & 15)) << 4);
+    const int voff = (int)lds_v + 4 * half * C::ROWB + l32 * DB * 4;
+    auto read_k = [&](int g) __attribute__((always_inline)) { kf[g] = *(lds_f4_ptr)(uintptr_t)(uint32_t)(koff[g & 7] + (g >> 3) * 256); };
+    auto read_v = [&](int r) __attribute__((always_inline)) {
+        vf[r] = *(lds_fdb_ptr)(uintptr_t)(uint32_t)(voff + (8 * (r >> 2) + (r & 3)) * C::ROWB);
+    };
+    auto fence = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    constexpr int kLgkm0 = (63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8);  // s_waitcnt lgkmcnt(0), the rest left alone
 
-    floatx16 oacc[DB];
+    floatx16 oacc[DB], xn;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
     float m = -INFINITY, lsum = 0.f;
+    float x[16], p[16];  // logits (an array: the vector ALU's copy of an accumulator) and probabilities of the current tile
 
-    int kv_len = N;
-    if (CAUSAL) kv_len = min(N, qt * BR + BR);
-    const int n_tiles = (kv_len + BC - 1) / BC;
-
-    // K/V tiles are fetched one tile ahead into registers and written to LDS once the previous tile's readers
-    // are done, so the global-memory latency overlaps the MFMAs of the tile before.
-    constexpr int LD = BC * D / 4 / 256;  // float4 loads per thread, tile and tensor
-    floatx4 kreg[LD], vreg[LD];
-    auto fetch_tile = [&](int jbase) __attribute__((always_inline)) {
+    auto logit_group = [&](int g, floatx16& s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            const int ch = tid + 256 * i;
-            const int row = ch / (D / 4), col = (ch % (D / 4)) * 4;
-            kreg[i] = floatx4{0, 0, 0, 0};
-            vreg[i] = floatx4{0, 0, 0, 0};
-            if (jbase + row < N) {
-                kreg[i] = *(const floatx4*)(Kh + (size_t)(jbase + row) * D + col);
-                vreg[i] = *(const floatx4*)(Vh + (size_t)(jbase + row) * D + col);
+        for (int e = 0; e < 4; ++e) s = mfma_f32_32x32x2(kf[g][e], qf[g][e], s);
+    };
+    auto attend_key = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) oacc[db] = mfma_f32_32x32x2(vf[r][db], p[r], oacc[db]);
+    };
+    auto exponentiate = [&](int r) __attribute__((always_inline)) {
+        p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], c, -m));
+        lsum += p[r];
+        asm volatile("" : "+v"(p[r]), "+v"(lsum));  // here, between the MFMAs, not where p is used
+    };
+    auto mask = [&](int tile, floatx16& s) __attribute__((always_inline)) {
+        const int jbase = tile * 32;
+        if (jbase + 32 > N || (CAUSAL && jbase + 31 > q0)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = jbase + acc_row(r, half);
+                s[r] = key < N && (!CAUSAL || key <= qrow) ? s[r] : -INFINITY;
             }
         }
     };
-    if (n_tiles > 0) fetch_tile(0);
-
-    for (int j = 0; j < n_tiles; ++j) {
-        const int jbase = j * BC;
-        __syncthreads();
+    // With 512 registers the MFMA accumulators live in the upper half of the file; kept there by name, or the compiler
+    // carries them through the lower half around every trip.
+    auto keep_high = [&]() __attribute__((always_inline)) {
+        if (D == 128) {
 #pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            const int ch = tid + 256 * i;
-            const int row = ch / (D / 4), col = (ch % (D / 4)) * 4;
-            Ks[row * KLD + col] = kreg[i][0];
-            Ks[row * KLD + col + 1] = kreg[i][1];
-            Ks[row * KLD + col + 2] = kreg[i][2];
-            Ks[row * KLD + col + 3] = kreg[i][3];
-            *(floatx4*)(Vs + row * D + col) = vreg[i];
+            for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[db]));
         }
-        __syncthreads();
-        if (j + 1 < n_tiles) fetch_tile(jbase + BC);
-        if (CAUSAL && jbase > q0w + 31) continue;  // every key of this tile is masked for this wavefront
-
-        f32_tile<D, CAUSAL>(Ks, Vs, jbase, N, q0w, qrow, c, qf, oacc, m, lsum, l32, half);
-    }
-
-    const float inv = 1.0f / halves_sum(lsum);
-    if (qrow < N) {
+    };
+    // raise the reference maximum to `top` (log2 units) where that is higher, and bring O and l to it
+    auto rescale = [&](float top) __attribute__((always_inline)) {
+        const float m_new = __builtin_fmaxf(m, top);
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        lsum *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                floatx4 w = {oacc[db][4 * rq] * inv, oacc[db][4 * rq + 1] * inv, oacc[db][4 * rq + 2] * inv,
-                             oacc[db][4 * rq + 3] * inv};
-                *(floatx4*)(Oh + (size_t)qrow * D + 32 * db + 8 * rq + 4 * half) = w;
-            }
-    }
-}
+            for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+        keep_high();
+        m = m_new;
+    };
 
-// Small problems: with 128 rows per workgroup a short sequence leaves most of the chip idle (B*H*N/32 wavefronts
-// in all).  This form gives a workgroup only 32 query rows and lets its four wavefronts split the KEYS: wavefront
-// w takes the 32-key tiles w, w+4, ... through an LDS region of its own (no workgroup barrier in the loop), and
-// the four partial results (running max, sum, unnormalised output) are merged through LDS at the end with the
-// same rescaling as a step of the online softmax.
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void fwd_f32_splitkeys_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                                const float* __restrict__ V, float* __restrict__ O, int N,
-                                                                int n_qtiles, int n_blocks, int blocks_per_xcd, float c) {
-    constexpr int BC = 32, KS = D / 2, DB = D / 32, KLD = D + 1, WAVE_LDS = BC * KLD + BC * D;  // floats per wavefront
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-
-    const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
-    if (logical >= n_blocks) return;
-    const int bh = logical / n_qtiles;
-    int qt = logical - bh * n_qtiles;
-    if (CAUSAL) qt = n_qtiles - 1 - qt;
-
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-    const size_t head = (size_t)bh * N * D;
-    const float* Qh = Q + head;
-    const float* Kh = K + head;
-    const float* Vh = V + head;
-    float* Oh = O + head;
-    const int q0w = qt * 32;  // all four wavefronts work on the same 32 rows
-    const int qrow = q0w + l32;
-    float* Ks = lds + wave * WAVE_LDS;
-    float* Vs = Ks + BC * KLD;  // BC * KLD * 4 bytes is a multiple of 16
-
-    float qf[KS];
+    if (n_mine > 0) {
+        // ---- prologue: tile 0 and Q arrive together; Logit of tile 0; operands of the first two phases
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = qrow < N ? Qh[(size_t)qrow * D + 2 * ks + half] : 0.f;
-    floatx16 oacc[DB];
+        for (int i = 0; i < LOADS; ++i) load_part(true, tile_of(0), i);
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int i = 0; i < LOADS; ++i) load_part(false, tile_of(0), i);
+        const float* Qr = Q + head + (size_t)min(qrow, N - 1) * D + 4 * half;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
-    float m = -INFINITY, lsum = 0.f;
-
-    int kv_len = N;
-    if (CAUSAL) kv_len = min(N, q0w + 32);
-    const int n_tiles = (kv_len + BC - 1) / BC;
-    constexpr int LD = BC * D / 4 / 64;  // float4 loads per lane, tile and tensor
-    for (int j = wave; j < n_tiles; j += 4) {
-        const int jbase = j * BC;
+        for (int g = 0; g < G; ++g) qf[g] = *(const floatx4*)(Qr + 8 * g);
+        wait_vm<0>();
+        fence();
 #pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            const int ch = lane + 64 * i;
-            const int row = ch / (D / 4), col = (ch % (D / 4)) * 4;
-            floatx4 kv = {0, 0, 0, 0}, vv = {0, 0, 0, 0};
-            if (jbase + row < N) {
-                kv = *(const floatx4*)(Kh + (size_t)(jbase + row) * D + col);
-                vv = *(const floatx4*)(Vh + (size_t)(jbase + row) * D + col);
-            }
-            Ks[row * KLD + col] = kv[0];
-            Ks[row * KLD + col + 1] = kv[1];
-            Ks[row * KLD + col + 2] = kv[2];
-            Ks[row * KLD + col + 3] = kv[3];
-            *(floatx4*)(Vs + row * D + col) = vv;
+        for (int g = 0; g < G; ++g) read_k(g);
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        fence();
+        if (n_mine > 1) {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) load_part(true, tile_of(1), i);
         }
-        // The region is private to this wavefront, but lanes read what other lanes wrote: order the wavefront's
-        // LDS stores before its reads, and the reads before the next tile's stores.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        f32_tile<D, CAUSAL>(Ks, Vs, jbase, N, q0w, qrow, c, qf, oacc, m, lsum, l32, half);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
+        fence();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xn[r] = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) logit_group(g, xn);
+        mask(tile_of(0), xn);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            x[r] = xn[r];
+            asm volatile("" : "+v"(x[r]));
+            mx = __builtin_fmaxf(mx, x[r]);
+        }
+        m = halves_max(mx) * c;
+        if (n_mine > 1) {
+            wait_vm<0>();
+            fence();
+#pragma unroll
+            for (int g = 0; g < G; ++g) read_k(g);
+        }
 
-    // merge: wavefronts 1..3 publish (m, l, O) in their own regions (layout [value][lane], conflict-free)
-    lsum = halves_sum(lsum);
-    if (wave != 0) {
+        // One trip: the two phases of tile i.  `more`: there is a tile i + 2 to fetch K of; without it tile i + 1 is the last
+        // one, the only one that can be partly masked.
+        auto trip = [&](int i, auto more) __attribute__((always_inline)) {
+            // ---- A: Logit of tile i + 1, exponentials of tile i
+            __builtin_amdgcn_s_waitcnt(kLgkm0);
+            fence();
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+            for (int r = 0; r < 16; ++r) xn[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) Ks[(db * 16 + r) * 64 + lane] = oacc[db][r];
-        Ks[DB * 16 * 64 + lane] = m;
-        Ks[(DB * 16 + 1) * 64 + lane] = lsum;
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    float mw[4], lw[4], M = m;
-    mw[0] = m;
-    lw[0] = lsum;
+            for (int g = 0; g < G; ++g) {
+                logit_group(g, xn);
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
-        const float* part = lds + w * WAVE_LDS;
-        mw[w] = part[DB * 16 * 64 + lane];
-        lw[w] = part[(DB * 16 + 1) * 64 + lane];
-        M = __builtin_fmaxf(M, mw[w]);
-    }
-    float L = 0.f, sc[4];
+                for (int r = g * 16 / G; r < (g + 1) * 16 / G; ++r) exponentiate(r);
+                if (more && g < G / 2) {
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        sc[w] = __builtin_amdgcn_exp2f(mw[w] - M);  // a wavefront that saw no key has m = -inf: weight 0
-        L += lw[w] * sc[w];
-    }
-    const float inv = 1.0f / L;  // wavefront 0 always sees key 0, so L > 0
-    if (qrow < N) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                floatx4 w4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int r = 4 * rq + e;
-                    float acc = oacc[db][r] * sc[0];
-#pragma unroll
-                    for (int w = 1; w < 4; ++w) acc += (lds + w * WAVE_LDS)[(db * 16 + r) * 64 + lane] * sc[w];
-                    w4[e] = acc * inv;
+                    for (int k = g * LOADS / (G / 2); k < (g + 1) * LOADS / (G / 2); ++k) load_part(true, tile_of(i + 2), k);
                 }
-                *(floatx4*)(Oh + (size_t)qrow * D + 32 * db + 8 * rq + 4 * half) = w4;
+                if (g == G / 2 - 1) {  // V of tile i has landed
+                    wait_vm<more ? LOADS : 0>();
+                    fence();
+                }
+                if (g >= G / 2 && g < G * 3 / 4) {
+                    constexpr int PER = 16 / (G / 4);
+#pragma unroll
+                    for (int r = 0; r < PER; ++r) read_v((g - G / 2) * PER + r);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
+            if (!more) mask(tile_of(i + 1), xn);
+            // ---- B: Attend of tile i, row maximum of tile i + 1
+            __builtin_amdgcn_s_waitcnt(kLgkm0);
+            fence();
+            keep_high();
+            float mx = -INFINITY, top = 0.f;
+            bool risen = false;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                attend_key(r);
+                if (r >= 4 && r < 12) {  // the first keys' MFMAs cover the latency of the last Logit MFMA
+#pragma unroll
+                    for (int k = 2 * (r - 4); k < 2 * (r - 3); ++k) {
+                        x[k] = xn[k];
+                        asm volatile("" : "+v"(x[k]));
+                        mx = __builtin_fmaxf(mx, x[k]);
+                    }
+                }
+                if (r == 13) {
+                    top = halves_max(mx) * c;
+                    risen = __builtin_amdgcn_ballot_w64(top > m + kF32LazyMax) != 0;
+                }
+                if (r < 8) {
+#pragma unroll
+                    for (int k = r * LOADS / 8; k < (r + 1) * LOADS / 8; ++k) load_part(false, tile_of(i + 1), k);
+                }
+                if (more && r == 7) {  // K of tile i + 2 has landed
+                    wait_vm<LOADS>();
+                    fence();
+                }
+                if (more && r >= 8 && r < 12) {
+#pragma unroll
+                    for (int g = (r - 8) * G / 4; g < (r - 7) * G / 4; ++g) read_k(g);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (risen) rescale(top);
+        };
+        int i = 0;
+#pragma unroll 1
+        for (; i + 2 < n_mine; ++i) trip(i, std::true_type{});
+        if (i + 1 < n_mine) trip(i, std::false_type{});
+        // ---- the last tile: nothing left to fetch
+        wait_vm<0>();
+        fence();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) read_v(r);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) exponentiate(r);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) attend_key(r);
+    }
+
+    // ---- merge: every wavefront leaves (O, m, l) in its own region (layout [value][lane], conflict-free), then each sums
+    // a share of the accumulator registers over all wavefronts.  A wavefront without a tile has m = -inf: weight 0.
+    lsum = halves_sum(lsum);
+    constexpr int SHARE = 16 / NW;  // registers per accumulator block and wavefront
+    float inv = 1.0f / lsum;
+    floatdb out[SHARE];
+    if (NW > 1) {
+        constexpr int REGION = C::WAVE_LDS / 4;
+        float* const all = (float*)smem;
+        float* const mine = all + wave * REGION;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mine[(db * 16 + r) * 64 + lane] = oacc[db][r];
+        mine[DB * 16 * 64 + lane] = m;
+        mine[(DB * 16 + 1) * 64 + lane] = lsum;
+        __syncthreads();
+        float M = -INFINITY, L = 0.f, w[NW];
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            w[v] = all[v * REGION + DB * 16 * 64 + lane];
+            M = __builtin_fmaxf(M, w[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            w[v] = __builtin_amdgcn_exp2f(w[v] - M);
+            L += w[v] * all[v * REGION + (DB * 16 + 1) * 64 + lane];
+        }
+        inv = 1.0f / L;
+#pragma unroll
+        for (int s = 0; s < SHARE; ++s)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                float acc = 0.f;
+#pragma unroll
+                for (int v = 0; v < NW; ++v) acc += w[v] * all[v * REGION + (db * 16 + wave * SHARE + s) * 64 + lane];
+                out[s][db] = acc * inv;
+            }
+    } else {
+#pragma unroll
+        for (int s = 0; s < SHARE; ++s)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) out[s][db] = oacc[db][s % 16] * inv;
+    }
+    if (qrow < N) {
+        float* const Or = O + head + (size_t)qrow * D;
+#pragma unroll
+        for (int s = 0; s < SHARE; ++s) {
+            const int r = wave * SHARE + s;
+            *(floatdb*)(Or + DB * acc_row(r, half)) = out[s];
+        }
     }
 }
 
-template <int D, bool CAUSAL>
-static hipError_t launch_cfg(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale,
-                             hipStream_t stream) {
-    // 128 rows per workgroup fill the chip (256 compute units, a few workgroups each) only from about 1024 row
-    // blocks on; below that, 32 rows per workgroup with the keys split over its wavefronts.
-    const int n_qtiles_big = (N + 127) / 128;
-    if ((long long)BH * n_qtiles_big < 1024 && N > 128) {
-        const int n_qtiles = (N + 31) / 32;
-        const int n_blocks = BH * n_qtiles;
-        const int blocks_per_xcd = (n_blocks + 7) / 8;
-        constexpr int lds = 4 * (32 * (D + 1) + 32 * D) * (int)sizeof(float);
-        auto kern = fwd_f32_splitkeys_kernel<D, CAUSAL>;
-        static std::atomic<uint64_t> attr_done{0};
-        hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(blocks_per_xcd * 8), dim3(256), lds, stream, Q, K, V, O, N, n_qtiles, n_blocks,
-                           blocks_per_xcd, scale * kLog2e);
-        return hipGetLastError();
-    }
-    const int n_qtiles = n_qtiles_big;
+template <int D, int NW, bool CAUSAL>
+static hipError_t launch_shape(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream) {
+    const int n_qtiles = (N + 31) / 32;
+    if ((long long)BH * n_qtiles > 0x7ffffff0LL) return hipErrorInvalidValue;
     const int n_blocks = BH * n_qtiles;
     const int blocks_per_xcd = (n_blocks + 7) / 8;
-    hipLaunchKernelGGL((fwd_f32_kernel<D, CAUSAL>), dim3(blocks_per_xcd * 8), dim3(256), 0, stream, Q, K, V, O, N,
-                       n_qtiles, n_blocks, blocks_per_xcd, scale * kLog2e);
+    constexpr int lds = NW * F32Cfg<D>::LDS_RESERVED;
+    auto kern = fwd_f32_kernel<D, NW, CAUSAL>;
+    static std::atomic<uint64_t> attr_done{0};
+    hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(blocks_per_xcd * 8), dim3(64 * NW), lds, stream, Q, K, V, O, N, n_qtiles, n_blocks, blocks_per_xcd,
+                       scale * kLog2e);
     return hipGetLastError();
+}
+
+// Wavefronts per workgroup (1, 2 or 4) by the time each would take, in units of one 32-key tile of a wavefront on a chip whose
+// slots are full: a workgroup takes ceil(tiles / NW) units plus its start and merge (1.5 units at d = 128, 0.7 at d = 64 where a
+// second wavefront on the SIMD hides half of it), and
+//   without a mask all workgroups are equal and run in whole rounds;
+//   with the causal mask they run heaviest first, so the time is their mean times their number, or the heaviest one alone.
+// With fewer wavefronts than SIMDs a d = 64 wavefront has its SIMD to itself and takes half a unit per tile.
+// Measured with 1 / 2 / 4 wavefronts (us; the rule's choice in brackets): d = 128, heads x positions: 16 x 8192 4322 / 4321 /
+// 4346 [1]; 16 x 2049 causal 274 / 164 / 175 [2], without a mask 551 / 425 / 375 [4]; 128 x 512 causal 85 / 97 / 128 [1]; 128 x
+// 128 22 / 17 / 20 [2]; 1024 x 33 33 / 36 / 63 [1].  d = 64: 12 x 512 37 / 20 / 13 [4]; 128 x 512 88 / 87 / 77 [4]; 1024 x 128
+// 45 / 48 / 56 [1]; 1024 x 200 causal 85 / 92 / 110 [1].
+template <int D>
+static int wavefronts_per_workgroup(int BH, int N, bool causal) {
+    constexpr double kUnitsPerGroup = D == 128 ? 1.5 : 0.7, kSlots = 256.0 * F32Cfg<D>::WAVES_PER_CU;
+    const double tiles = (N + 31) / 32, groups = BH * tiles;
+    int best = 1;
+    double best_time = 0.0;
+    for (int nw = 1; nw <= 4; nw *= 2) {
+        const double load = groups * nw / kSlots, longest = ceil(tiles / nw) + kUnitsPerGroup;
+        double time = causal ? fmax(load * ((tiles / nw + 1.0) * 0.5 + kUnitsPerGroup), longest) : ceil(load) * longest;
+        if (D == 64) time *= fmin(1.0, fmax(0.5, load));
+        if (nw == 1 || time < best_time) {
+            best = nw;
+            best_time = time;
+        }
+    }
+    return best;
+}
+
+template <int D, bool CAUSAL>
+static hipError_t launch_cfg(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream) {
+    switch (wavefronts_per_workgroup<D>(BH, N, CAUSAL)) {
+        case 1: return launch_shape<D, 1, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
+        case 2: return launch_shape<D, 2, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
+        default: return launch_shape<D, 4, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
+    }
 }
 
 hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale,

@@ -1,0 +1,33 @@
+"""fp32 path at the sizes where its key split can go wrong: one to a few 32-key tiles per wavefront, tails of a tile, wavefronts
+without a tile, and enough or too few heads for each number of wavefronts per workgroup (1, 2, 4)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2107_06419_amd as fa
+from paper_2107_06419_amd import synth
+from helpers import check_close, to_device, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+HEADS = {1: 1100, 2: 150, 4: 3}  # enough heads for whole rounds of one-wavefront workgroups ... so few that the keys are split in four
+
+
+@pytest.mark.parametrize("heads", sorted(HEADS.values()))
+@pytest.mark.parametrize("N", [1, 31, 32, 33, 64, 65, 96, 129, 160, 289])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("mask", [0, 1])
+def test_f32_key_split_edges(heads, N, d, mask):
+    import torch
+    q, k, v = (synth.tensor_f32((1, heads, N, d), 900 + N + d + mask, t, "normal", 1.0) for t in range(3))
+    if N > 64:  # logits that grow along the keys: the reference maximum is passed by less and by more than its slack of 2^8
+        k = k * np.linspace(0.1, 8.0, N, dtype=np.float32)[None, None, :, None]
+    dq, dk, dv = (to_device(x, "f32") for x in (q, k, v))
+    out = torch.full_like(dq, float("nan"))
+    print(f"case f32 key split heads={heads} N={N} d={d} mask={mask}", flush=True)
+    fa.flat_attn_fwd_f32(dq, dk, dv, out, float(np.float32(d ** -0.5)), mask)
+    torch.cuda.synchronize()
+    some = sorted({0, 1, heads // 2, heads - 1} & set(range(heads)))
+    ref = oracle.attention(q[:, some], k[:, some], v[:, some], float(np.float32(d ** -0.5)), mask)
+    check_close(to_host_f64(out[:, some]), ref, "f32", f"heads={heads} N={N} d={d} mask={mask}")
+    assert torch.isfinite(out).all()
