@@ -44,9 +44,9 @@ constexpr bool kSyncEveryPhase = true;
 constexpr bool kSyncEveryPhase = false;
 #endif
 
-// Head dimensions.  D is the head dimension of the tensors in memory (32, 64, 96, 128 or 256); the tiles in LDS
-// and the matrix products use DP = D rounded up to a power of two (96 -> 128: the missing columns of Q are zero,
-// so whatever the padded K columns hold drops out of the logits, and the padded output columns are not stored).
+// Head dimensions.  D is the head dimension of the tensors in memory (32, 64, 96, 128 or 256); rows in LDS are DP = D rounded
+// up to a power of two (96 -> 128, for the swizzle and the streaming loads), the matrix products touch the D columns that
+// exist.  (At d = 96, multiplying the padded columns as well, as zeros, cost: 16 heads x 8192 432 us against 402.)
 // A tile holds BC keys: 64 (two 32-key blocks), or 32 at d = 256, where 64 keys of K and V would take 64 KiB; a tile
 // shape may ask for another multiple of 32 (BCX: 32, 64 or 128) so that this axis of the map space can be measured too.
 //
@@ -59,7 +59,7 @@ constexpr bool kSyncEveryPhase = false;
 template <int D, int STAGES, int NW, int BCX = 0>
 struct Bf16Cfg {
     static_assert(D == 32 || D == 64 || D == 96 || D == 128 || D == 256, "head dimension not built");
-    static constexpr int DP = D == 96 ? 128 : D;      // head dimension of the tiles and products
+    static constexpr int DP = D == 96 ? 128 : D;      // row length of the tiles in LDS
     static constexpr int BC = BCX ? BCX : (D == 256 ? 32 : 64);  // keys per tile
     static constexpr int ROWB = DP * 2;               // bytes per row in LDS
     static constexpr int GROWB = D * 2;               // bytes per row in global memory
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
                                                           int blocks_per_xcd, float c) {
     using C = Bf16Cfg<D, STAGES, NW, BCX>;
     constexpr bool SPARSE = MODE == kSparse, SPLIT = MODE == kSplit;
-    constexpr int DP = C::DP, QW = 32 * QB, BR = NW * QW, BC = C::BC, DS = DP / 16, DB = DP / 32;
+    constexpr int DP = C::DP, QW = 32 * QB, BR = NW * QW, BC = C::BC, DS = D / 16, DB = D / 32;
     constexpr int KB = BC / 32;    // 32-key blocks per tile
     constexpr int KB64 = 64 / BC;  // tiles per 64 keys (the unit of a block-sparse list)
     static_assert(KB == 1 || KB == 2 || KB == 4, "a tile is one, two or four 32-key blocks");
@@ -164,8 +164,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         const int row = q0w + 32 * qb + l32;
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) {
-            uint4v z = {0, 0, 0, 0};  // rows past the end and the padded head-dim columns are zero
-            if (row < Nq && ds * 16 + half * 8 < D) z = *(const uint4v*)(Qh + (size_t)row * D + ds * 16 + half * 8);
+            uint4v z = {0, 0, 0, 0};  // rows past the end are zero
+            if (row < Nq) z = *(const uint4v*)(Qh + (size_t)row * D + ds * 16 + half * 8);
             qf[qb][ds] = __builtin_bit_cast(bf16x8, z);
         }
     }
@@ -383,8 +383,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         const int first_key = SPLIT ? min(t0 * BC, N - 1) : (SPARSE && sp_count > 0) ? sp_ids[0] * 64 : 0;
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) {
-            uint4v kv = {0, 0, 0, 0};
-            if (ds * 16 + half * 8 < D) kv = *(const uint4v*)(Kh + (size_t)first_key * C::GROWB + ds * 32 + half * 16);
+            const uint4v kv = *(const uint4v*)(Kh + (size_t)first_key * C::GROWB + ds * 32 + half * 16);
             const bf16x8 kb8 = __builtin_bit_cast(bf16x8, kv);
 #pragma unroll
             for (int e = 0; e < 8; ++e) k0[ds][e] = (float)kb8[e];
@@ -723,7 +722,6 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
 #pragma unroll
                 for (int rq = 0; rq < 4; ++rq) {
                     const int dcol = 32 * db + 8 * rq + 4 * half;
-                    if (32 * db + 8 * rq >= D) continue;  // padded head-dim columns
                     floatx2 w;
                     w[0] = __builtin_bit_cast(float, pack_bf16(oacc[qb][db][4 * rq] * inv, oacc[qb][db][4 * rq + 1] * inv));
                     w[1] = __builtin_bit_cast(float, pack_bf16(oacc[qb][db][4 * rq + 2] * inv, oacc[qb][db][4 * rq + 3] * inv));
