@@ -177,14 +177,16 @@ int flat_attn_unfused(const void* Q, const void* K, const void* V, void* O,
  * flat_attn_fwd uses index 0, except where the 128-row shape (d = 64: index 7, d = 128: index 2, d = 32 and 96:
  * index 1) measures ahead: launches of few row blocks (at most 128 blocks of 256 query rows; 256 with the causal
  * mask at d = 32 and 64, 192 at d = 96 and 128: 1.3-1.5 times faster), d = 64 with the causal mask up to 4096
- * positions and 1024 row blocks, and d = 32 for short sequences.  flat_attn_fwd_tile runs any shape so that the
- * choice can be re-timed.
+ * positions and 1024 row blocks, d = 32 for short sequences, and up to 128 query rows.  Launches of few rows further
+ * run a key-group form of their shape, in which the wavefronts of a workgroup share the keys of 32 to 128 rows;
+ * flat_attn_fwd_tile runs any shape so that the choice can be re-timed: index 0 and the others as they are, the 128-row
+ * index of the choice above with its key-group forms, as flat_attn_fwd does.
  *   flat_attn_tile_shape_count(d): number of shapes for head dimension d (0 if d is not one of 32, 64, 96, 128, 256).
  *   flat_attn_tile_shape_get: fills *out (HOST pointer) for 0 <= index < count; FLAT_ERR_SHAPE otherwise.
  *   flat_attn_tile_shape_occupancy: workgroups of that shape resident per compute unit on the current
  *     device (registers and LDS permitting), or a negative flat_status; the only one of the three that
  *     needs a GPU.
- *   flat_attn_tile_shape_default: the index flat_attn_fwd (N = Nq) and flat_attn_fwd_cross (Nq query rows) take for a
+ *   flat_attn_tile_shape_default: the index (base shape) flat_attn_fwd (N = Nq) and flat_attn_fwd_cross (Nq query rows) take for a
  *     problem, or a negative flat_status; host arithmetic only.
  *   flat_attn_fwd_tile: flat_attn_fwd with the shape chosen by the caller; same arguments, checks and
  *     result tolerance (different shapes sum in different orders, so results differ in the last bits).

@@ -1,0 +1,14 @@
+// Key-group forms of the fused bf16 kernel, d = 32 and 64: 32 or 64 rows over four groups, 64 or 128 rows over two
+// (chosen by predicted time in flat_tiles.hip).
+#include "flat_fwd_bf16_kernel.hpp"
+
+namespace flat {
+
+FLAT_INSTANTIATE_BF16_GROUPS(64, 1, 4, 2, 128, 4)
+FLAT_INSTANTIATE_BF16_GROUPS(64, 1, 8, 2, 128, 4)
+FLAT_INSTANTIATE_BF16_GROUPS(64, 1, 4, 2, 64, 2)
+FLAT_INSTANTIATE_BF16_GROUPS(32, 1, 4, 4, 128, 4)
+FLAT_INSTANTIATE_BF16_GROUPS(32, 1, 8, 4, 128, 4)
+FLAT_INSTANTIATE_BF16_GROUPS(32, 1, 4, 4, 64, 2)
+
+}  // namespace flat

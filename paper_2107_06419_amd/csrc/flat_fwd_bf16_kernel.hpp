@@ -87,24 +87,33 @@ constexpr int kMaxSparseTiles = 2048;  // block-sparse: listed tiles per row blo
 // Two wavefronts per SIMD (256 registers each), except 64 rows per wavefront at d = 128 and every shape at d = 256,
 // whose accumulators alone need more: those run one wavefront per SIMD with the full 512 registers.
 
+// Key groups (KG > 1): NW / KG wavefronts' worth of rows per workgroup, the keys of every tile divided over KG wavefronts per row
+// block.  For launches of few rows, which are bound by the chain of steps of one workgroup: KG times fewer steps, paid for
+// with K and V read from L2 KG times as often per flop and a merge through LDS (about 1 us).
 // kSplit = the keys of one row block are divided over prob.n_splits workgroups, each of which leaves its
 // unnormalised result (reference maximum, row sum, accumulators) in a workspace for split_merge_kernel.
 constexpr int kDense = 0, kSparse = 1, kSplit = 2;
 
-template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0>
+template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0, int KG = 1>
 __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 2) void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                           const bf16* __restrict__ V, bf16* __restrict__ O,
                                                           const Bf16Problem prob, int n_qtiles, int n_blocks,
                                                           int blocks_per_xcd, float c) {
     using C = Bf16Cfg<D, STAGES, NW, BCX>;
     constexpr bool SPARSE = MODE == kSparse, SPLIT = MODE == kSplit;
-    constexpr int DP = C::DP, QW = 32 * QB, BR = NW * QW, BC = C::BC, DS = D / 16, DB = D / 32;
-    constexpr int KB = BC / 32;    // 32-key blocks per tile
+    constexpr int DP = C::DP, QW = 32 * QB, BR = NW / KG * QW, BC = C::BC, DS = D / 16, DB = D / 32;
+    constexpr int KBT = BC / 32, KB = KBT / KG;  // 32-key blocks per tile, and of those per wavefront
     constexpr int KB64 = 64 / BC;  // tiles per 64 keys (the unit of a block-sparse list)
-    static_assert(KB == 1 || KB == 2 || KB == 4, "a tile is one, two or four 32-key blocks");
+    static_assert(NW % KG == 0 && KBT % KG == 0 && D / 8 % KG == 0, "key groups share wavefronts, keys and output columns evenly");
+    static_assert(KG == 1 || (!SPARSE && BC % 64 == 0), "the block-sparse variant has one key group");
+    static_assert(KB == 1 || KB == 2 || KB == 4, "a wavefront takes one, two or four 32-key blocks of a tile");
     static_assert(KB != 1 || STAGES % 2 == 0, "with one block per tile the unrolled loop needs an even ring");
     static_assert(!SPARSE || KB64 >= 1, "block-sparse lists name 64-key tiles");
     constexpr int LOADS_PER_TILE = 2 * C::LOADS;  // DMA instructions per wavefront per tile (K and V)
+    // With one block per wavefront and tile, a step is done with its V tile and with the NEXT K tile, so K runs one tile
+    // ahead of V in the ring: one more tile in flight for the same LDS, and two stages are enough.
+    constexpr bool kStagger = KB == 1;
+    static_assert(STAGES >= (kStagger ? 2 : 3), "the ring is too short to keep a tile in flight");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // Which (head, row block) this workgroup takes.  Workgroup ids are dealt round-robin to the 8 XCDs, so XCD x
@@ -155,7 +164,9 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     const char* Kh = (const char*)(K + head_k);
     const char* Vh = (const char*)(V + head_k);
     bf16* Oh = O + head_q;
-    const int q0w = qt * BR + wave * QW;
+    // Key groups: wavefronts rg * KG + kg, kg = 0 .. KG-1, own the same QW query rows and take KB of every tile's blocks each.
+    const int kg = KG == 1 ? 0 : wave % KG, rg = KG == 1 ? wave : wave / KG;
+    const int q0w = qt * BR + rg * QW;
 
     // Q^T fragments (B operand of S^T = K Q^T): column = query, 8 consecutive head-dim elements
     bf16x8 qf[QB][DS];
@@ -225,7 +236,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         const int chunk = (lane % C::CHUNKS) ^ C::swz(ld_row[i]);
         ld_chunk_off[i] = (chunk < C::GCHUNKS ? chunk : chunk - (C::CHUNKS - C::GCHUNKS)) * 16;
     }
-    auto issue_tile_loads = [&](int j, int stage) __attribute__((always_inline)) {  // j-th visited tile, stage = j % STAGES
+    auto issue_tile_loads = [&](int j, int stage, bool k_tile = true, bool v_tile = true) __attribute__((always_inline)) {  // j-th visited tile, stage = j % STAGES
         const uint32_t stage_base = smem_base + (uint32_t)stage * C::STAGE;
         const int tile = tile_of(j);
 #pragma unroll
@@ -233,8 +244,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
             const int key = min(tile * BC + ld_row[i], N - 1);
             const uint32_t voff = (uint32_t)key * C::GROWB + ld_chunk_off[i];
             const uint32_t lds_k = __builtin_amdgcn_readfirstlane(stage_base + (NW * i + wave) * 1024);
-            dma16(Kh, voff, lds_k);
-            dma16(Vh, voff, lds_k + C::KBYTES);
+            if (k_tile) dma16(Kh, voff, lds_k);
+            if (v_tile) dma16(Vh, voff, lds_k + C::KBYTES);
         }
     };
 
@@ -242,7 +253,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // compile-time chunk index
     int koff[DS];
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) koff[ds] = (int)smem_base + l32 * C::ROWB + (((2 * ds + half) ^ C::swz(l32)) << 4);
+    for (int ds = 0; ds < DS; ++ds) koff[ds] = (int)smem_base + (kg * KB * 32 + l32) * C::ROWB + (((2 * ds + half) ^ C::swz(l32)) << 4);
     const int i16 = lane & 15, g16 = lane >> 4;
     int voff[DB][2];
 #pragma unroll
@@ -251,7 +262,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         for (int hi = 0; hi < 2; ++hi) {
             const int r = 8 * hi + 4 * (g16 >> 1) + (i16 >> 2);         // row within a 16-key step
             const int ch = 4 * db + 2 * (g16 & 1) + ((i16 >> 1) & 1);  // 16-byte chunk holding this lane's 4 columns
-            voff[db][hi] = (int)smem_base + r * C::ROWB + ((ch ^ C::swz(r)) << 4) + (i16 & 1) * 8;
+            voff[db][hi] = (int)smem_base + (kg * KB * 32 + r) * C::ROWB + ((ch ^ C::swz(r)) << 4) + (i16 & 1) * 8;
         }
     const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
 
@@ -376,6 +387,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
 #pragma unroll
     for (int t = 0; t < STAGES - 1; ++t)
         if (t < n_tiles) issue_tile_loads(t, t);
+    if (kStagger && STAGES - 1 < n_tiles) issue_tile_loads(STAGES - 1, STAGES - 1, true, false);
     // reference max of each row = c * (q . k_first), k_first = the first key the row block sees (key 0 unless
     // block-sparse or split), from the Q fragments already in registers
     {
@@ -584,12 +596,22 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // flight only STAGES-3 may still be outstanding), barrier (every wavefront is then also past its last read of
     // tile j-1), and start streaming tile j+STAGES-1 into the stage that held tile j-1.
     auto sync_and_stream = [&](int j, int sj) __attribute__((always_inline)) {
-        if (kSyncEveryPhase || j + STAGES - 2 >= n_tiles)
-            wait_vm<0>();
-        else
-            wait_vm<(STAGES - 3) * LOADS_PER_TILE>();
-        __syncthreads();
-        if (j + STAGES - 1 < n_tiles) issue_tile_loads(j + STAGES - 1, sj == 0 ? STAGES - 1 : sj - 1);
+        if (kStagger) {  // the step needs V of tile j and K of tile j+1, which were started together
+            if (kSyncEveryPhase || j + STAGES - 1 >= n_tiles)
+                wait_vm<0>();
+            else
+                wait_vm<(STAGES - 2) * LOADS_PER_TILE>();
+            __syncthreads();
+            if (j + STAGES - 1 < n_tiles) issue_tile_loads(j + STAGES - 1, sj == 0 ? STAGES - 1 : sj - 1, false, true);
+            if (j + STAGES < n_tiles) issue_tile_loads(j + STAGES, sj, true, false);
+        } else {
+            if (kSyncEveryPhase || j + STAGES - 2 >= n_tiles)
+                wait_vm<0>();
+            else
+                wait_vm<(STAGES < 3 ? 0 : STAGES - 3) * LOADS_PER_TILE>();
+            __syncthreads();
+            if (j + STAGES - 1 < n_tiles) issue_tile_loads(j + STAGES - 1, sj == 0 ? STAGES - 1 : sj - 1);
+        }
         if (kSyncEveryPhase) {  // every wavefront runs this the same number of times, so the barrier is safe here
             wait_vm<0>();
             __syncthreads();
@@ -601,7 +623,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     auto tile_steps = [&](int j, int sj, bool masked, bool odd) __attribute__((always_inline)) {  // sj = j % STAGES
         const int sn = sj + 1 == STAGES ? 0 : sj + 1;       // stage of tile j+1
         // first 32-key block of the tile, as a key position / 32 (only the masked form of a step looks at it)
-        const int kb0 = KB * (((SPARSE && masked) || SPLIT) ? tile_of(j) : j);
+        const int kb0 = KBT * (((SPARSE && masked) || SPLIT) ? tile_of(j) : j) + kg * KB;
         if (KB >= 2) {
 #pragma unroll
             for (int i = 0; i < KB; i += 2) {
@@ -635,11 +657,13 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // Per wavefront the tiles fall into three consecutive ranges: fully visible, partly masked
     // (sequence tail or causal diagonal), and not visible at all (the wavefront then only keeps
     // streaming and synchronising for the others).
-    const int n_vis_blocks = (N + 31) / 32;
     // (block-sparse: the list is ascending, so only its last 64 keys can hold the ragged end of the sequence)
     // (split keys: the same ranges, counted from the first tile of the split and cut to its length)
-    const int n_unm_all = (CAUSAL ? min((q0w + off + 1) / 32, N / 32) : N / 32) / KB;
-    const int n_act_all = ((CAUSAL ? min(n_vis_blocks, (q0w + QW - 1 + off) / 32 + 1) : n_vis_blocks) + KB - 1) / KB;
+    // A tile is fully visible to a key group when the last key of its share is, and active when the first one is.
+    const int first_of_share = kg * KB * 32, end_of_share = first_of_share + KB * 32;
+    const int all_see = CAUSAL ? min(q0w + off + 1, N) : N, any_sees = CAUSAL ? min(q0w + QW + off, N) : N;  // keys seen by all / any of the rows
+    const int n_unm_all = all_see < end_of_share ? 0 : (all_see - end_of_share) / BC + 1;
+    const int n_act_all = any_sees <= first_of_share ? 0 : (any_sees - first_of_share - 1) / BC + 1;
     const int n_unm_tiles = SPARSE ? max(n_tiles - KB64, 0) : max(0, min(n_unm_all - t0, n_tiles));
     const int n_act_tiles = SPARSE ? n_tiles : max(0, min(n_act_all - t0, n_tiles));
     int j = 0;
@@ -684,6 +708,73 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     for (; j < n_tiles; ++j) {
         sync_and_stream(j, sj);
         sj = sj + 1 == STAGES ? 0 : sj + 1;
+    }
+
+    // ---- key groups: the partial results (reference maximum, row sum, accumulators) of a row's wavefronts meet in the ring's
+    // LDS, in the lane layout they have; each wavefront then merges and writes its share of the output columns.
+    if (KG > 1) {
+        constexpr int QUADS = D / 8, OQ = QUADS / KG;  // accumulator quads of a lane per row block, and of those per wavefront
+        floatx4* const part = (floatx4*)smem + lane;
+        float* const stat = (float*)(smem + NW * QB * QUADS * 1024) + lane;
+        auto slot = [&](int k, int qb) __attribute__((always_inline)) { return (rg * KG + k) * QB + qb; };
+        __syncthreads();  // every wavefront is past its last read of the ring
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const float total = halves_sum(lsum[qb]);
+            stat[slot(kg, qb) * 64] = half ? total : m[qb];
+#pragma unroll
+            for (int q = 0; q < QUADS; ++q) {
+                const int db = q / 4, rq = q % 4;
+                part[(slot(kg, qb) * QUADS + q) * 64] =
+                    floatx4{oacc[qb][db][4 * rq], oacc[qb][db][4 * rq + 1], oacc[qb][db][4 * rq + 2], oacc[qb][db][4 * rq + 3]};
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            float mk[KG], w[KG], M = -INFINITY, L = 0.f;
+#pragma unroll
+            for (int k = 0; k < KG; ++k) {
+                mk[k] = stat[slot(k, qb) * 64 - 32 * half];
+                M = __builtin_fmaxf(M, mk[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < KG; ++k) {
+                w[k] = __builtin_amdgcn_exp2f(mk[k] - M);
+                L += w[k] * stat[slot(k, qb) * 64 + 32 * (1 - half)];
+            }
+            const int r_wg = rg * QW + 32 * qb + l32, row = qt * BR + r_wg;
+            const float inv = SPLIT ? 1.f : 1.0f / L;
+            float* ws = nullptr;
+            if (SPLIT) {
+                ws = prob.split_ws + ((size_t)(bh * (n_qtiles / prob.n_splits) + qt) * prob.n_splits + split) * (size_t)(BR * (DP + 2));
+                if (row < Nq && kg == 0 && half == 0) {
+                    ws[BR * DP + r_wg] = M;
+                    ws[BR * DP + BR + r_wg] = L;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < OQ; ++i) {
+                const int q = kg * OQ + i, dcol = 8 * q + 4 * half;
+                float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < KG; ++k) {
+                    const floatx4 o = part[(slot(k, qb) * QUADS + q) * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(w[k], o[e], a[e]);
+                }
+                if (row >= Nq) continue;
+                if (SPLIT) {
+                    *(floatx4*)(ws + (size_t)r_wg * DP + dcol) = floatx4{a[0], a[1], a[2], a[3]};
+                } else {
+                    floatx2 w2;
+                    w2[0] = __builtin_bit_cast(float, pack_bf16(a[0] * inv, a[1] * inv));
+                    w2[1] = __builtin_bit_cast(float, pack_bf16(a[2] * inv, a[3] * inv));
+                    *(floatx2*)(Oh + (size_t)row * D + dcol) = w2;
+                }
+            }
+        }
+        return;
     }
 
     // ---- split keys: leave the unnormalised partial result in the workspace.  Per (head, row block, split):
@@ -731,16 +822,19 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     }
 }
 
-template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0>
+template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0, int KG = 1>
 inline hipError_t launch_cfg(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, float scale,
                              hipStream_t stream) {
-    constexpr int BR = 32 * QB * NW;
+    constexpr int BR = 32 * QB * (NW / KG);
     // split keys: the kernel sees (row block, split) pairs where the other modes see row blocks
     const int n_qtiles = (prob.Nq + BR - 1) / BR * (MODE == kSplit ? prob.n_splits : 1);
     const int n_blocks = BH * n_qtiles;
     const int blocks_per_xcd = (n_blocks + 7) / 8;
-    auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, CAUSAL, MODE, BCX>;
-    constexpr int lds = Bf16Cfg<D, STAGES, NW, BCX>::LDS_BYTES + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
+    auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, CAUSAL, MODE, BCX, KG>;
+    constexpr int ring = Bf16Cfg<D, STAGES, NW, BCX>::LDS_BYTES;
+    constexpr int merge = KG > 1 ? NW * QB * (D * 128 + 256) : 0;  // the key groups' partial results, in the ring's place
+    constexpr int lds = (ring > merge ? ring : merge) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
+    static_assert(lds <= 160 * 1024, "more LDS than a compute unit has");
     static std::atomic<uint64_t> attr_done{0};  // one flag per kernel instantiation
     hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
     if (e != hipSuccess) return e;
@@ -756,6 +850,14 @@ hipError_t launch_fwd_bf16_shape(const void* Q, const void* K, const void* V, vo
                                  int causal, hipStream_t stream) {
     return causal ? launch_cfg<D, QB, NW, STAGES, true, kDense, BCX>(Q, K, V, O, BH, prob, scale, stream)
                   : launch_cfg<D, QB, NW, STAGES, false, kDense, BCX>(Q, K, V, O, BH, prob, scale, stream);
+}
+
+// Key-group form: KG groups of wavefronts share the keys of 32 QB NW / KG query rows.
+template <int D, int QB, int NW, int STAGES, int BC, int KG>
+hipError_t launch_fwd_bf16_groups(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, float scale,
+                                  int causal, hipStream_t stream) {
+    return causal ? launch_cfg<D, QB, NW, STAGES, true, kDense, BC, KG>(Q, K, V, O, BH, prob, scale, stream)
+                  : launch_cfg<D, QB, NW, STAGES, false, kDense, BC, KG>(Q, K, V, O, BH, prob, scale, stream);
 }
 
 // Workgroups of this shape that fit one compute unit at a time (registers and LDS), as the runtime reports it.
@@ -779,6 +881,9 @@ hipError_t launch_fwd_bf16_sparse_shape(const void* Q, const void* K, const void
     template hipError_t launch_fwd_bf16_shape<D, QB, NW, STAGES, BCX>(const void*, const void*, const void*, void*, int,    \
                                                                       const Bf16Problem&, float, int, hipStream_t);        \
     template hipError_t fwd_bf16_shape_occupancy<D, QB, NW, STAGES, BCX>(int*);
+#define FLAT_INSTANTIATE_BF16_GROUPS(D, QB, NW, STAGES, BC, KG)                                                              \
+    template hipError_t launch_fwd_bf16_groups<D, QB, NW, STAGES, BC, KG>(const void*, const void*, const void*, void*, int, \
+                                                                          const Bf16Problem&, float, int, hipStream_t);
 #define FLAT_INSTANTIATE_BF16_SHAPE(D, QB, NW, STAGES) FLAT_INSTANTIATE_BF16_SHAPE_BC(D, QB, NW, STAGES, 0)
 
 }  // namespace flat

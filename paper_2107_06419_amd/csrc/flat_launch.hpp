@@ -78,6 +78,7 @@ struct TileShape {
     int lds_bytes;           // dynamic LDS per workgroup
 };
 int tile_shape_count(int d);
+int small_launch_shape(int d);                                // the 128-row shape of a head size, 0 if there is none
 int default_tile_shape(int BH, int Nq, int d, int causal);  // index launch_fwd_bf16 uses for this problem
 bool tile_shape(int d, int index, TileShape* out);
 hipError_t tile_shape_occupancy(int d, int index, int* workgroups_per_cu);
@@ -88,6 +89,10 @@ hipError_t launch_fwd_bf16_tile(const void* Q, const void* K, const void* V, voi
 template <int D, int QB, int NW, int STAGES, int BCX = 0>  // BCX: keys per tile, 0 = the head dimension's usual tile
 hipError_t launch_fwd_bf16_shape(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, float scale,
                                  int causal, hipStream_t stream);
+// The same with the keys of 32 QB NW / KG rows divided over KG key groups of wavefronts (flat_fwd_bf16_groups_*.hip).
+template <int D, int QB, int NW, int STAGES, int BC, int KG>
+hipError_t launch_fwd_bf16_groups(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, float scale,
+                                  int causal, hipStream_t stream);
 template <int D, int QB, int NW, int STAGES, int BCX = 0>
 hipError_t fwd_bf16_shape_occupancy(int* workgroups_per_cu);
 
