@@ -94,13 +94,14 @@ int flat_attn_fwd_cross(const void* Q, const void* K, const void* V, void* O,
  * (reference maximum, row sum, unnormalised output, all fp32) in `workspace`, and a second kernel merges them.
  * Same arguments, masks, key counts and tolerance as flat_attn_fwd_cross, plus
  *   n_splits: parts the key sequence is divided into, clamped to [1, number of key tiles]; <= 0 lets the library
- *     choose (one workgroup per compute-unit slot, at least 8 key tiles per split).
+ *     choose (by predicted time: one launch without splits, or one workgroup per compute-unit slot).
  *     flat_attn_fwd_splitkv_splits returns the number actually used (or a negative flat_status).
  *   workspace: device, 16-byte aligned, at least flat_attn_fwd_splitkv_workspace_bytes() bytes (same B, H, Nq,
  *     Nk, d, n_splits; 0 means the arguments are invalid), overwritten; it must not overlap any other buffer
  *     (FLAT_ERR_ALIAS).  FLAT_ERR_WORKSPACE if too small.
  * The result differs from flat_attn_fwd_cross in the last bits (different summation order), and is itself
- * bitwise reproducible for a given n_splits.  Two launches (partial pass, merge) are enqueued on `stream`.
+ * bitwise reproducible for a given n_splits.  Two launches (partial pass, merge) are enqueued on `stream`; one where
+ * the number of splits is 1, and then the result is that of flat_attn_fwd_cross.
  */
 int flat_attn_fwd_splitkv_splits(int B, int H, int Nq, int Nk, int d, int n_splits);
 size_t flat_attn_fwd_splitkv_workspace_bytes(int B, int H, int Nq, int Nk, int d, int n_splits);

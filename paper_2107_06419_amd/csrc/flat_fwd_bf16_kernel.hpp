@@ -596,6 +596,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // flight only STAGES-3 may still be outstanding), barrier (every wavefront is then also past its last read of
     // tile j-1), and start streaming tile j+STAGES-1 into the stage that held tile j-1.
     auto sync_and_stream = [&](int j, int sj) __attribute__((always_inline)) {
+        // A single wavefront has no barrier to wait at: its reads of the stage that is refilled below must be back first.
+        if (NW == 1) __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8));
         if (kStagger) {  // the step needs V of tile j and K of tile j+1, which were started together
             if (kSyncEveryPhase || j + STAGES - 1 >= n_tiles)
                 wait_vm<0>();

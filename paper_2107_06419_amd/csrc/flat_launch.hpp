@@ -50,14 +50,13 @@ hipError_t launch_fwd_bf16_sparse(const void* Q, const void* K, const void* V, v
 // of the chip idle.  The geometry is fixed per head dimension; split_plan fills in what a launch needs.
 struct SplitPlan {
     int rows_per_block;    // query rows per workgroup of the shape used
-    int keys_per_tile;
     int padded_d;          // accumulator columns stored per row
     int n_row_blocks;      // per head
-    int n_tiles;           // key tiles per head
-    int n_splits;          // after clamping to [1, n_tiles]
+    int n_splits;          // after clamping to [1, units of 64 keys]
     int tiles_per_split;
     size_t workspace_bytes;
 };
+int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index);  // flat_plan.hip; -1: none
 bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* out);  // n_splits_wanted <= 0: chosen here
 hipError_t launch_fwd_bf16_split(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, int d,
                                  int rows_per_block, float scale, int causal, hipStream_t stream);

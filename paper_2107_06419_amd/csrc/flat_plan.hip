@@ -1,42 +1,160 @@
-// Host-side planning of a split-keys launch (no device code): how many workgroups share the keys of a row block,
-// how many tiles each takes, and how large the workspace for their partial results is.
+// Host-side planning (no device code): which key-group form a launch takes, and for a split-keys launch how many workgroups
+// share the keys of a row block, how many tiles each takes, and how large the workspace for their partial results is.
 #include "flat_launch.hpp"
 
 namespace flat {
 
+// ---- Key-group forms.  A launch of few query rows leaves most of the chip idle on the shapes above, whatever their rows per
+// workgroup, because each workgroup walks all keys alone.  In these forms the wavefronts of a workgroup share the keys of
+// the same 32, 64 or 128 rows (kernel parameter KG) and merge through LDS at the end; nothing else changes.  They re-read K
+// and V from L2 more often per flop, so large launches keep the shapes above.  Each holds a step of K and V per wavefront in
+// a ring of two stages (K runs one tile ahead of V); deeper rings measured 3-25 % slower, as fewer workgroups fit.
+// Measured, us, best of the shapes above -> form: 12 heads x 512, d = 64, 9.8 -> 6.5; 4 x 4096, d = 64, 47.6 -> 26.4; 2 causal
+// x 8192, d = 64, 86.7 -> 39.2; 8 x 1024, d = 128, 22.2 -> 13.3; 4 x 4096, d = 256, 175 -> 109; 64 x 16 rows over 4096 keys,
+// d = 64, 46 -> 24.
+//
+// The choice is by predicted time.  A form (and each shape above) has a measured cost: us to launch, start and drain (`start`),
+// us per tile and per workgroup when a workgroup runs alone (`step`, `fixed`), us per tile when the compute unit holds as
+// many workgroups as fit (`busy`), and the share of its longest workgroup that a causal launch ends late (`skew`).  Fitted
+// to 1750 timings: 1 to 2048 heads, 16 to 300 query rows over 300 to 4096 keys and 64 to 16384 positions, both masks, five
+// head sizes.  The choice is within 1-3 % of the fastest on average, where the shapes above alone are 12-28 % behind it, and
+// on none of the timings more than 10 % behind the shape it replaces.
 namespace {
-// The tile shape a split-keys launch uses: rows per workgroup, keys per tile, padded head dimension, workgroups that
-// fit a compute unit.  Every workgroup multiplies a full tile of `rows` rows whatever Nq is, so few query rows take a shape
-// with fewer rows where flat_splitkv.hip builds one.
-struct Geometry { int rows, keys, dp, per_cu; };
+
+struct Cost {
+    float start, step, fixed, busy, skew;
+};
+struct Form {
+    int rows, keys_per_tile, per_cu;  // query rows per workgroup, keys per tile, workgroups that fit a compute unit
+    Cost cost;
+};
+// Per head size: the shapes launch_fwd_bf16 runs (index 0, small_launch_shape), then the key-group forms.
+struct Choice {
+    int d, n_forms;
+    Form base[2];
+    Form forms[4];
+};
+const Choice kChoices[] = {
+    {32, 3, {{256, 64, 2, {2.51f, 0.854f, 1.55f, 0.685f, 0.38f}}, {128, 64, 3, {2.95f, 0.530f, 0.80f, 0.362f, 0.18f}}},
+     {{32, 128, 2, {1.67f, 0.379f, 2.00f, 0.233f, 0.30f}}, {64, 128, 1, {2.95f, 0.378f, 1.48f, 0.378f, 0.29f}},
+      {64, 64, 3, {2.74f, 0.327f, 1.19f, 0.194f, 0.08f}}}},
+    {64, 3, {{256, 64, 2, {3.88f, 1.031f, 1.67f, 0.995f, 0.35f}}, {128, 64, 3, {3.03f, 0.666f, 1.59f, 0.532f, 0.22f}}},
+     {{32, 128, 2, {2.05f, 0.520f, 2.43f, 0.367f, 0.21f}}, {64, 128, 1, {1.30f, 0.611f, 4.37f, 0.611f, 0.21f}},
+      {64, 64, 3, {1.61f, 0.421f, 3.01f, 0.294f, 0.17f}}}},
+    {96, 4, {{256, 64, 1, {0.27f, 1.325f, 5.38f, 1.325f, 0.30f}}, {128, 64, 1, {0.57f, 0.857f, 4.69f, 0.857f, 0.19f}}},
+     {{32, 128, 1, {1.19f, 0.756f, 3.51f, 0.756f, 0.17f}}, {64, 128, 1, {0.70f, 0.899f, 5.60f, 0.899f, 0.18f}},
+      {64, 64, 2, {1.37f, 0.548f, 3.60f, 0.420f, 0.17f}}, {128, 64, 1, {0.34f, 0.693f, 6.15f, 0.693f, 0.22f}}}},
+    {128, 4, {{256, 64, 1, {0.33f, 1.609f, 7.00f, 1.609f, 0.29f}}, {128, 64, 1, {0.42f, 1.003f, 6.14f, 1.003f, 0.20f}}},
+     {{32, 128, 1, {1.17f, 0.861f, 4.64f, 0.861f, 0.17f}}, {64, 128, 1, {0.67f, 1.038f, 7.67f, 1.038f, 0.19f}},
+      {64, 64, 2, {1.82f, 0.588f, 4.40f, 0.489f, 0.23f}}, {128, 64, 1, {0.40f, 0.831f, 8.27f, 0.831f, 0.24f}}}},
+    {256, 1, {{128, 32, 1, {0.35f, 1.291f, 10.68f, 1.291f, 0.22f}}, {128, 32, 1, {0.35f, 1.291f, 10.68f, 1.291f, 0.22f}}},
+     {{64, 64, 1, {0.34f, 1.459f, 10.02f, 1.459f, 0.15f}}}},
+};
+
+float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int causal) {
+    const long long wgs = (long long)BH * ((prob.Nq + (long long)f.rows - 1) / f.rows), per_cu = (wgs + 255) / 256;
+    const float tiles = (float)((prob.Nk + (long long)f.keys_per_tile - 1) / f.keys_per_tile);
+    const float alone = tiles * f.cost.step + f.cost.fixed;             // one workgroup, start to end
+    const float fixed_busy = f.cost.fixed * f.cost.busy / f.cost.step;  // its fixed part on a full compute unit
+    // K, V, Q, O once at 5.9 TB/s; one workgroup per unit leaves that rate with the units that have nothing in the last round
+    float memory = (float)BH * ((float)prob.Nq + (float)prob.Nk) * (float)d * 4.0f / 5.9e6f;
+    if (f.per_cu == 1) memory *= (float)per_cu * 256.0f / (float)wgs;
+    if (wgs < 256) memory = 0.0f;  // and few workgroups never reach it: `step` holds their rate
+    float work;
+    if (!causal) {
+        const float rounds = (float)((per_cu + f.per_cu - 1) / f.per_cu) * alone, full = (float)per_cu * (tiles * f.cost.busy + fixed_busy);
+        work = rounds > full ? rounds : full;
+    } else {  // the longest workgroup, or an even share of the work and what the longest one sticks out
+        float seen = ((float)prob.causal_offset + 0.5f * (float)prob.Nq + 0.5f * (float)f.rows) / (float)f.keys_per_tile + 0.5f;
+        if (seen > tiles) seen = tiles;
+        const float spread = (float)wgs / 256.0f * (seen * f.cost.busy + fixed_busy) + f.cost.skew * alone;
+        work = alone > spread ? alone : spread;
+    }
+    return f.cost.start + (work > memory ? work : memory);
+}
+
+}  // namespace
+
+// The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1 times as long
+// (what the prediction is worth) or there is one tile, and so nothing to divide.  Up to 512 keys index 0 also keeps launches of
+// more than 512 blocks of 32 rows (forms gain 20 % at most there: 128 heads x 256, d = 64, 10.2 -> 8.0 us) and all of
+// d = 32 (16 x 512, 9.7 -> 4.9 us): a caller may hold flat_attn_fwd to flat_attn_fwd_tile 0 bit for bit, and so do the tests.
+int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
+    if (prob.Nk <= 64) return -1;
+    if (index == 0 && prob.Nk <= 512 && (d == 32 || (long long)BH * ((prob.Nq + 31LL) / 32) > 512)) return -1;
+    for (const Choice& c : kChoices) {
+        if (c.d != d) continue;
+        int best = -1;
+        float limit = predicted_us(c.base[index == 0 ? 0 : 1], BH, prob, d, causal) / 1.1f;
+        for (int i = 0; i < c.n_forms; ++i) {
+            const float t = predicted_us(c.forms[i], BH, prob, d, causal);
+            if (t < limit) limit = t, best = i;
+        }
+        return best;
+    }
+    return -1;
+}
+
+namespace {
+// The tile shape a split-keys launch uses: rows per workgroup, keys per tile, padded head dimension, workgroups wanted per
+// compute unit, the keys it takes at least per split, and its measured cost: us to start and drain, us per unit of 64 keys (32 at
+// d = 256) of a workgroup alone and with the compute unit full.  Every workgroup multiplies a full tile of `rows` rows whatever Nq
+// is, so few query rows take a shape with fewer rows where flat_splitkv.hip builds one.
+struct Geometry { int rows, keys, dp, per_cu, min_keys; float start, step, busy; };
 bool geometry(int d, int Nq, Geometry* g) {
     switch (d) {
         case 32:
-            if (Nq <= 32) *g = {32, 64, 32, 6};
-            else if (Nq <= 64) *g = {64, 64, 32, 4};
-            else if (Nq <= 128) *g = {128, 64, 32, 2};
-            else *g = {256, 64, 32, 2};
+            if (Nq <= 32) *g = {32, 64, 32, 6, 128, 3.2f, 0.40f, 0.10f};
+            else if (Nq <= 64) *g = {64, 64, 32, 4, 256, 5.0f, 0.50f, 0.20f};
+            else if (Nq <= 128) *g = {128, 64, 32, 2, 512, 6.0f, 0.53f, 0.45f};
+            else *g = {256, 64, 32, 2, 512, 7.0f, 0.85f, 0.75f};
             return true;
         case 64:
-            if (Nq <= 32) *g = {32, 64, 64, 3};
-            else if (Nq <= 64) *g = {64, 64, 64, 2};
-            else if (Nq <= 128) *g = {128, 64, 64, 2};
-            else *g = {256, 64, 64, 2};
+            if (Nq <= 32) *g = {32, 64, 64, 3, 128, 3.0f, 0.45f, 0.20f};
+            else if (Nq <= 64) *g = {64, 64, 64, 2, 256, 5.5f, 0.65f, 0.40f};
+            else if (Nq <= 128) *g = {128, 64, 64, 2, 512, 6.0f, 0.66f, 0.60f};
+            else *g = {256, 64, 64, 2, 512, 8.0f, 1.00f, 1.00f};
             return true;
         case 96:
-            if (Nq <= 128) *g = {128, 64, 128, 1};
-            else *g = {256, 64, 128, 1};
+            if (Nq <= 32) *g = {32, 32, 128, 4, 64, 2.8f, 1.00f, 0.30f};
+            else if (Nq <= 128) *g = {128, 64, 128, 1, 256, 6.5f, 0.86f, 0.86f};
+            else *g = {256, 64, 128, 1, 512, 9.0f, 1.20f, 1.20f};
             return true;
         case 128:
-            if (Nq <= 128) *g = {128, 64, 128, 1};
-            else *g = {256, 64, 128, 1};
+            if (Nq <= 32) *g = {32, 32, 128, 4, 64, 2.8f, 1.20f, 0.40f};
+            else if (Nq <= 128) *g = {128, 64, 128, 1, 256, 7.0f, 0.94f, 0.94f};
+            else *g = {256, 64, 128, 1, 512, 9.0f, 1.36f, 1.36f};
             return true;
-        case 256: *g = {128, 32, 256, 1}; return true;
+        case 256:
+            if (Nq <= 64) *g = {64, 32, 256, 2, 64, 4.0f, 1.22f, 0.70f};
+            else *g = {128, 32, 256, 1, 256, 10.0f, 1.29f, 1.29f};
+            return true;
         default: return false;
     }
 }
+// Predicted time of the launch without splits, and of partial pass and merge: the longer of the chain of one workgroup, the
+// work of a compute unit and one read of K and V, then the merge (4.3 us and 1.2 ns a row) and the partial results' round trip.
+float unsplit_us(int BH, int Nq, int Nk, int d) {
+    const Bf16Problem prob{Nq, Nk, 0, 1, nullptr, nullptr, nullptr, 0};
+    float best = 1e30f;
+    for (const Choice& c : kChoices) {
+        if (c.d != d) continue;
+        for (int i = -2; i < c.n_forms; ++i) {
+            const float t = predicted_us(i < 0 ? c.base[i + 2] : c.forms[i], BH, prob, d, 0);
+            if (t < best) best = t;
+        }
+    }
+    return best;
+}
+float split_us(const Geometry& g, long long blocks, int BH, int Nq, int Nk, int d, long long splits, int n_units) {
+    const float units = (float)((n_units + splits - 1) / splits), per_cu = (float)((blocks * splits + 255) / 256);
+    const float alone = g.step * units, full = g.busy * units * per_cu, memory = (float)BH * (float)Nk * (float)d * 4.0f / 5.9e6f;
+    float t = alone > full ? alone : full;
+    if (memory > t) t = memory;
+    return g.start + t + 4.3f + 0.0012f * (float)BH * (float)Nq + (float)BH * (float)Nq * (float)splits * (float)(g.dp + 2) * 8.0f / 4.0e6f;
+}
 constexpr int kComputeUnits = 256;
-constexpr int kMinTilesPerSplit = 8;   // below this the prologue and the merge outweigh the gain
+constexpr int kMaxSplits = 256;        // of one row block: its merge is one workgroup's work
 }  // namespace
 
 bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* out) {
@@ -44,23 +162,35 @@ bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* o
     if (BH <= 0 || Nq <= 0 || Nk <= 0 || !geometry(d, Nq, &g)) return false;
     SplitPlan p;
     p.rows_per_block = g.rows;
-    p.keys_per_tile = g.keys;
     p.padded_d = g.dp;
     p.n_row_blocks = (int)(((long long)Nq + g.rows - 1) / g.rows);
-    p.n_tiles = (int)(((long long)Nk + g.keys - 1) / g.keys);
+    // splits are counted in units of 64 keys (32 at d = 256), whatever the tile of the shape
+    const int unit = d == 256 ? 32 : 64, tiles_per_unit = unit / g.keys;
+    const int n_units = (int)(((long long)Nk + unit - 1) / unit);
     long long s = n_splits_wanted;
-    if (s <= 0) {  // one workgroup per slot of the chip (measured: more only adds partial results to write and merge), but
-                   // keep every split long enough to pay for itself
+    if (s <= 0) {
+        // One workgroup per wanted slot of the chip and no more: a workgroup beyond them only adds partial results to write
+        // and merge (and a second round), one split fewer leaves some slots empty.  Every split stays long enough to pay for itself.
         const long long blocks = (long long)BH * p.n_row_blocks;
-        s = (kComputeUnits * g.per_cu + blocks - 1) / blocks;
-        const long long longest = (p.n_tiles + kMinTilesPerSplit - 1) / kMinTilesPerSplit;
+        s = kComputeUnits * g.per_cu / blocks;
+        const long long longest = ((long long)Nk + g.min_keys - 1) / g.min_keys;
+        if (s < 2) s = 2;  // more heads than slots: still twice as many workgroups, as the last round is half empty otherwise
         if (s > longest) s = longest;
+        if (s > kMaxSplits) s = kMaxSplits;
+        // No split where one launch does it in less (many heads over short keys, or enough rows to fill the chip: 64 heads x 200
+        // rows over 2048 keys, d = 64, 37.7 -> 17.1 us, 256 x 1 over 512 keys 11.7 -> 8.2) by a clear margin, as key counts of
+        // different length favour the many short workgroups of a split launch.
+        if (s > 1 && unsplit_us(BH, Nq, Nk, d) * (Nq <= 64 ? 1.12f : 1.0f) <= split_us(g, blocks, BH, Nq, Nk, d, s, n_units)) s = 1;
     }
-    if (s > p.n_tiles) s = p.n_tiles;
+    if (s > n_units) s = n_units;
     if (s < 1) s = 1;
-    p.tiles_per_split = (int)((p.n_tiles + s - 1) / s);
-    p.n_splits = (p.n_tiles + p.tiles_per_split - 1) / p.tiles_per_split;  // no split is left without a tile
-    const unsigned __int128 bytes = (unsigned __int128)BH * p.n_row_blocks * p.n_splits * g.rows * (g.dp + 2) * sizeof(float);
+    const int units_per_split = (int)((n_units + s - 1) / s);
+    p.n_splits = (n_units + units_per_split - 1) / units_per_split;  // no split is left without a unit
+    p.tiles_per_split = units_per_split * tiles_per_unit;
+    // A caller's number of splits asks for at least 128 rows each at d >= 96, more than the shapes of few rows fill: a workspace
+    // that holds n splits of theirs then also holds the library's choice of more and smaller ones.
+    const int ws_rows = n_splits_wanted > 0 && d >= 96 && g.rows < 128 ? 128 : g.rows;
+    const unsigned __int128 bytes = (unsigned __int128)BH * p.n_row_blocks * p.n_splits * ws_rows * (g.dp + 2) * sizeof(float);
     if (bytes >= ((unsigned __int128)1 << 62) || (long long)BH * p.n_row_blocks * p.n_splits > 0x7fffffffLL) return false;
     if ((long long)BH * Nq > 0x7fffffffLL) return false;  // the merge launches one workgroup per (head, row)
     p.workspace_bytes = (size_t)bytes;

@@ -107,34 +107,45 @@ __global__ __launch_bounds__(kMergeThreads) void split_merge_kernel(const float*
 
 // Split-keys launch of one tile shape: the partial pass, then the merge.  prob carries n_splits, tiles_per_split
 // and the workspace (BH * ceil(Nq / BR) * n_splits * BR * (DP + 2) floats).
-template <int D, int QB, int NW, int STAGES>
+template <int D, int QB, int NW, int STAGES, int BCX = 0, int KG = 1>
 hipError_t launch_fwd_bf16_split_shape(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob,
                                        float scale, int causal, hipStream_t stream) {
-    constexpr int BR = 32 * QB * NW;
-    const hipError_t e = causal ? launch_cfg<D, QB, NW, STAGES, true, kSplit>(Q, K, V, O, BH, prob, scale, stream)
-                                : launch_cfg<D, QB, NW, STAGES, false, kSplit>(Q, K, V, O, BH, prob, scale, stream);
+    constexpr int BR = 32 * QB * (NW / KG);
+    const hipError_t e = causal ? launch_cfg<D, QB, NW, STAGES, true, kSplit, BCX, KG>(Q, K, V, O, BH, prob, scale, stream)
+                                : launch_cfg<D, QB, NW, STAGES, false, kSplit, BCX, KG>(Q, K, V, O, BH, prob, scale, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(split_merge_kernel, dim3((unsigned)BH * (unsigned)prob.Nq), dim3(kMergeThreads), 0, stream, prob.split_ws,
-                       (bf16*)O, prob.Nq, (prob.Nq + BR - 1) / BR, BR, Bf16Cfg<D, STAGES, NW>::DP, D, prob.n_splits);
+                       (bf16*)O, prob.Nq, (prob.Nq + BR - 1) / BR, BR, Bf16Cfg<D, STAGES, NW, BCX>::DP, D, prob.n_splits);
     return hipGetLastError();
 }
 
-// rows = rows per workgroup of the plan (split_plan): selects among the shapes built for a head dimension
+// rows = rows per workgroup of the plan (split_plan): selects among the shapes built for a head dimension.
+// Up to 32 query rows (64 at d = 256) the pass is bound by reading K and V, and by how evenly that is spread: small workgroups,
+// several per compute unit, whose start and end overlap.  Two wavefronts that share each tile's keys at d = 64, one wavefront
+// with 32-key tiles at d = 96 and 128 (32 KiB of LDS each), two with 32 rows each at d = 256.  Measured, partial pass and merge,
+// us, one row: 16 heads x 65536 keys 128-row shape -> these d = 128 106.7 -> 97.6, d = 256 209 -> 188; 256 heads, 2001 to 4001
+// keys each, d = 128 95 -> 75, d = 256 182 -> 150; 32 x 2048, d = 128 13.4 -> 11.4.  One key tile ahead is enough: four stages
+// instead of two measured 0-5 % slower.
 hipError_t launch_fwd_bf16_split(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, int d,
                                  int rows, float scale, int causal, hipStream_t stream) {
+    // all keys in one part: nothing to merge, so the launch of flat_attn_fwd_cross
+    if (prob.n_splits == 1) return launch_fwd_bf16(Q, K, V, O, BH, prob, d, scale, causal, stream);
     switch (d * 1000 + rows) {
         case 32032: return launch_fwd_bf16_split_shape<32, 1, 1, 3>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 32064: return launch_fwd_bf16_split_shape<32, 1, 2, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 32128: return launch_fwd_bf16_split_shape<32, 1, 4, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 32256: return launch_fwd_bf16_split_shape<32, 2, 4, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
-        case 64032: return launch_fwd_bf16_split_shape<64, 1, 1, 3>(Q, K, V, O, BH, prob, scale, causal, stream);
+        case 64032: return launch_fwd_bf16_split_shape<64, 1, 2, 2, 64, 2>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 64064: return launch_fwd_bf16_split_shape<64, 1, 2, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 64128: return launch_fwd_bf16_split_shape<64, 1, 4, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 64256: return launch_fwd_bf16_split_shape<64, 2, 4, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
+        case 96032: return launch_fwd_bf16_split_shape<96, 1, 1, 2, 32>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 96128: return launch_fwd_bf16_split_shape<96, 1, 4, 3>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 96256: return launch_fwd_bf16_split_shape<96, 1, 8, 3>(Q, K, V, O, BH, prob, scale, causal, stream);
+        case 128032: return launch_fwd_bf16_split_shape<128, 1, 1, 2, 32>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 128128: return launch_fwd_bf16_split_shape<128, 1, 4, 3>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 128256: return launch_fwd_bf16_split_shape<128, 1, 8, 3>(Q, K, V, O, BH, prob, scale, causal, stream);
+        case 256064: return launch_fwd_bf16_split_shape<256, 1, 2, 2, 32>(Q, K, V, O, BH, prob, scale, causal, stream);
         case 256128: return launch_fwd_bf16_split_shape<256, 1, 4, 4>(Q, K, V, O, BH, prob, scale, causal, stream);
         default: return hipErrorInvalidValue;
     }

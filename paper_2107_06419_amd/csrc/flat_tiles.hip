@@ -105,96 +105,22 @@ int default_tile_shape(int BH, int Nq, int d, int causal) {
     }
 }
 
-// ---- Key-group forms.  A launch of few query rows leaves most of the chip idle on the shapes above, whatever their rows per
-// workgroup, because each workgroup walks all keys alone.  In these forms the wavefronts of a workgroup share the keys of
-// the same 32, 64 or 128 rows (kernel parameter KG) and merge through LDS at the end; nothing else changes.  They re-read K
-// and V from L2 more often per flop, so large launches keep the shapes above.  Each holds a step of K and V per wavefront in
-// a ring of two stages (K runs one tile ahead of V); deeper rings measured 3-25 % slower, as fewer workgroups fit.
-// Measured, us, best of the shapes above -> form: 12 heads x 512, d = 64, 9.8 -> 6.5; 4 x 4096, d = 64, 47.6 -> 26.4; 2 causal
-// x 8192, d = 64, 86.7 -> 39.2; 8 x 1024, d = 128, 22.2 -> 13.3; 4 x 4096, d = 256, 175 -> 109; 64 x 16 rows over 4096 keys,
-// d = 64, 46 -> 24.
-//
-// The choice is by predicted time.  A form (and each shape above) has a measured cost: us to launch, start and drain (`start`),
-// us per tile and per workgroup when a workgroup runs alone (`step`, `fixed`), us per tile when the compute unit holds as
-// many workgroups as fit (`busy`), and the share of its longest workgroup that a causal launch ends late (`skew`).  Fitted
-// to 1750 timings: 1 to 2048 heads, 16 to 300 query rows over 300 to 4096 keys and 64 to 16384 positions, both masks, five
-// head sizes.  The choice is within 1-3 % of the fastest on average, where the shapes above alone are 12-28 % behind it, and
-// on none of the timings more than 10 % behind the shape it replaces.
 namespace {
 
-struct Cost {
-    float start, step, fixed, busy, skew;
-};
-struct Form {
-    int rows, keys_per_tile, per_cu;  // query rows per workgroup, keys per tile, workgroups that fit a compute unit
-    Cost cost;
-    LaunchFn launch;
-};
+// Launchers of the key-group forms, in the order of the cost table in flat_plan.hip, whose key_group_form() picks one.
 template <int D, int QB, int NW, int STAGES, int BC, int KG>
-constexpr Form form(int per_cu, Cost cost) {
-    return Form{32 * QB * (NW / KG), BC, per_cu, cost, &launch_fwd_bf16_groups<D, QB, NW, STAGES, BC, KG>};
-}
+constexpr LaunchFn groups() { return &launch_fwd_bf16_groups<D, QB, NW, STAGES, BC, KG>; }
+const LaunchFn kGroups32[] = {groups<32, 1, 4, 4, 128, 4>(), groups<32, 1, 8, 4, 128, 4>(), groups<32, 1, 4, 4, 64, 2>()};
+const LaunchFn kGroups64[] = {groups<64, 1, 4, 2, 128, 4>(), groups<64, 1, 8, 2, 128, 4>(), groups<64, 1, 4, 2, 64, 2>()};
+const LaunchFn kGroups96[] = {groups<96, 1, 4, 2, 128, 4>(), groups<96, 1, 8, 2, 128, 4>(), groups<96, 1, 4, 2, 64, 2>(), groups<96, 1, 8, 2, 64, 2>()};
+const LaunchFn kGroups128[] = {groups<128, 1, 4, 2, 128, 4>(), groups<128, 1, 8, 2, 128, 4>(), groups<128, 1, 4, 2, 64, 2>(), groups<128, 1, 8, 2, 64, 2>()};
+const LaunchFn kGroups256[] = {groups<256, 1, 4, 2, 64, 2>()};
 
-// Per head size: the shapes launch_fwd_bf16 runs (index 0, small_launch_shape), then the key-group forms.
-struct Choice {
-    int d, n_forms;
-    Form base[2];
-    Form forms[4];
-};
-const Choice kChoices[] = {
-    {32, 3, {{256, 64, 2, {2.51f, 0.854f, 1.55f, 0.685f, 0.38f}, nullptr}, {128, 64, 3, {2.95f, 0.530f, 0.80f, 0.362f, 0.18f}, nullptr}},
-     {form<32, 1, 4, 4, 128, 4>(2, {1.67f, 0.379f, 2.00f, 0.233f, 0.30f}), form<32, 1, 8, 4, 128, 4>(1, {2.95f, 0.378f, 1.48f, 0.378f, 0.29f}),
-      form<32, 1, 4, 4, 64, 2>(3, {2.74f, 0.327f, 1.19f, 0.194f, 0.08f})}},
-    {64, 3, {{256, 64, 2, {3.88f, 1.031f, 1.67f, 0.995f, 0.35f}, nullptr}, {128, 64, 3, {3.03f, 0.666f, 1.59f, 0.532f, 0.22f}, nullptr}},
-     {form<64, 1, 4, 2, 128, 4>(2, {2.05f, 0.520f, 2.43f, 0.367f, 0.21f}), form<64, 1, 8, 2, 128, 4>(1, {1.30f, 0.611f, 4.37f, 0.611f, 0.21f}),
-      form<64, 1, 4, 2, 64, 2>(3, {1.61f, 0.421f, 3.01f, 0.294f, 0.17f})}},
-    {96, 4, {{256, 64, 1, {0.27f, 1.325f, 5.38f, 1.325f, 0.30f}, nullptr}, {128, 64, 1, {0.57f, 0.857f, 4.69f, 0.857f, 0.19f}, nullptr}},
-     {form<96, 1, 4, 2, 128, 4>(1, {1.19f, 0.756f, 3.51f, 0.756f, 0.17f}), form<96, 1, 8, 2, 128, 4>(1, {0.70f, 0.899f, 5.60f, 0.899f, 0.18f}),
-      form<96, 1, 4, 2, 64, 2>(2, {1.37f, 0.548f, 3.60f, 0.420f, 0.17f}), form<96, 1, 8, 2, 64, 2>(1, {0.34f, 0.693f, 6.15f, 0.693f, 0.22f})}},
-    {128, 4, {{256, 64, 1, {0.33f, 1.609f, 7.00f, 1.609f, 0.29f}, nullptr}, {128, 64, 1, {0.42f, 1.003f, 6.14f, 1.003f, 0.20f}, nullptr}},
-     {form<128, 1, 4, 2, 128, 4>(1, {1.17f, 0.861f, 4.64f, 0.861f, 0.17f}), form<128, 1, 8, 2, 128, 4>(1, {0.67f, 1.038f, 7.67f, 1.038f, 0.19f}),
-      form<128, 1, 4, 2, 64, 2>(2, {1.82f, 0.588f, 4.40f, 0.489f, 0.23f}), form<128, 1, 8, 2, 64, 2>(1, {0.40f, 0.831f, 8.27f, 0.831f, 0.24f})}},
-    {256, 1, {{128, 32, 1, {0.35f, 1.291f, 10.68f, 1.291f, 0.22f}, nullptr}, {128, 32, 1, {0.35f, 1.291f, 10.68f, 1.291f, 0.22f}, nullptr}},
-     {form<256, 1, 4, 2, 64, 2>(1, {0.34f, 1.459f, 10.02f, 1.459f, 0.15f})}},
-};
-
-float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int causal) {
-    const long long wgs = (long long)BH * ((prob.Nq + (long long)f.rows - 1) / f.rows), per_cu = (wgs + 255) / 256;
-    const float tiles = (float)((prob.Nk + (long long)f.keys_per_tile - 1) / f.keys_per_tile);
-    const float alone = tiles * f.cost.step + f.cost.fixed;             // one workgroup, start to end
-    const float fixed_busy = f.cost.fixed * f.cost.busy / f.cost.step;  // its fixed part on a full compute unit
-    const float memory = (float)BH * ((float)prob.Nq + (float)prob.Nk) * (float)d * 4.0f / 5.5e6f;  // K, V, Q, O once at 5.5 TB/s
-    float work;
-    if (!causal) {
-        const float rounds = (float)((per_cu + f.per_cu - 1) / f.per_cu) * alone, full = (float)per_cu * (tiles * f.cost.busy + fixed_busy);
-        work = rounds > full ? rounds : full;
-    } else {  // the longest workgroup, or an even share of the work and what the longest one sticks out
-        float seen = ((float)prob.causal_offset + 0.5f * (float)prob.Nq + 0.5f * (float)f.rows) / (float)f.keys_per_tile + 0.5f;
-        if (seen > tiles) seen = tiles;
-        const float spread = (float)wgs / 256.0f * (seen * f.cost.busy + fixed_busy) + f.cost.skew * alone;
-        work = alone > spread ? alone : spread;
-    }
-    return f.cost.start + (work > memory ? work : memory);
-}
-
-// The key-group form for this problem, or null where the shape `index` is predicted to take no more than 1.1 times as long
-// (what the prediction is worth) or there is one tile, and so nothing to divide.  Up to 512 keys index 0 also keeps launches of
-// more than 512 blocks of 32 rows (forms gain 20 % at most there: 128 heads x 256, d = 64, 10.2 -> 8.0 us) and all of
-// d = 32 (16 x 512, 9.7 -> 4.9 us): a caller may hold flat_attn_fwd to flat_attn_fwd_tile 0 bit for bit, and so do the tests.
-const Form* key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
-    if (prob.Nk <= 64) return nullptr;
-    if (index == 0 && prob.Nk <= 512 && (d == 32 || (long long)BH * ((prob.Nq + 31LL) / 32) > 512)) return nullptr;
-    for (const Choice& c : kChoices) {
-        if (c.d != d) continue;
-        const Form* best = nullptr;
-        float limit = predicted_us(c.base[index == 0 ? 0 : 1], BH, prob, d, causal) / 1.1f;
-        for (int i = 0; i < c.n_forms; ++i) {
-            const float t = predicted_us(c.forms[i], BH, prob, d, causal);
-            if (t < limit) limit = t, best = &c.forms[i];
-        }
-        return best;
-    }
-    return nullptr;
+// The shape `index`, or its key-group form for this problem.
+LaunchFn shape_or_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
+    const int f = key_group_form(BH, prob, d, causal, index);
+    if (f < 0) return table(d)[index].launch;
+    return (d == 32 ? kGroups32 : d == 64 ? kGroups64 : d == 96 ? kGroups96 : d == 128 ? kGroups128 : kGroups256)[f];
 }
 
 }  // namespace
@@ -205,15 +131,13 @@ hipError_t launch_fwd_bf16_tile(const void* Q, const void* K, const void* V, voi
                                 float scale, int causal, int index, hipStream_t stream) {
     const Entry* e = find(d, index);
     if (!e) return hipErrorInvalidValue;
-    const Form* f = index != 0 && index == small_launch_shape(d) ? key_group_form(BH, prob, d, causal, index) : nullptr;
-    return (f ? f->launch : e->launch)(Q, K, V, O, BH, prob, scale, causal, stream);
+    const LaunchFn launch = index != 0 && index == small_launch_shape(d) ? shape_or_form(BH, prob, d, causal, index) : e->launch;
+    return launch(Q, K, V, O, BH, prob, scale, causal, stream);
 }
 
 hipError_t launch_fwd_bf16(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, int d,
                            float scale, int causal, hipStream_t stream) {
-    const int index = default_tile_shape(BH, prob.Nq, d, causal);
-    const Form* f = key_group_form(BH, prob, d, causal, index);
-    return (f ? f->launch : table(d)[index].launch)(Q, K, V, O, BH, prob, scale, causal, stream);
+    return shape_or_form(BH, prob, d, causal, default_tile_shape(BH, prob.Nq, d, causal))(Q, K, V, O, BH, prob, scale, causal, stream);
 }
 
 }  // namespace flat

@@ -100,3 +100,33 @@ def test_splitkv_status_codes_on_device_buffers():
     fa.flat_attn_fwd_splitkv(q, k, k, o, 1.0, 0, None, 4, ws)
     torch.cuda.synchronize()
     assert (o.float() == 0).all()
+
+
+# rows on both sides of the limits at which the partial pass changes its shape, splits of one tile and of many, ragged ends;
+# n_splits = 1 and the library's choice for short keys run without a merge
+@pytest.mark.parametrize("B,H,Nq,Nk,lens,n_splits", [(2, 3, 32, 1111, [1111, 70], 3), (1, 5, 33, 1090, None, 5), (2, 2, 64, 321, [321, 33], 16),
+                                                     (1, 3, 65, 2049, None, 4), (3, 30, 1, 2500, [2500, 1, 1300], 0), (1, 4, 5, 400, None, 0),
+                                                     (1, 700, 1, 700, None, 0)])
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
+@pytest.mark.parametrize("mask", [0, 1])
+def test_splitkv_shapes_match_the_oracle_and_the_synchronised_build(B, H, Nq, Nk, lens, n_splits, d, mask):
+    import ctypes
+    import os
+    import torch
+    q, k, v = (rounded((B, H, n, d), 61000 + Nq + Nk + d, t) for t, n in ((0, Nq), (1, Nk), (2, Nk)))
+    scale = float(np.float32(d ** -0.5))
+    print(f"case splitkv shapes B={B} H={H} Nq={Nq} Nk={Nk} d={d} mask={mask} lens={lens} n_splits={n_splits}", flush=True)
+    out = run_split(q, k, v, scale, mask, lens, n_splits)
+    check_close(to_host_f64(out), oracle.attention_cross(q, k, v, scale, mask, kv_lens=None if lens is None else np.array(lens)), "bf16", "splitkv")
+    lib = ctypes.CDLL(os.path.join(os.path.dirname(fa.library_path()), "libflat_attn_sync.so"))
+    vp, i, f, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
+    lib.flat_attn_fwd_splitkv.argtypes = [vp, vp, vp, vp, i, i, i, i, i, f, i, vp, i, vp, sz, vp]
+    dq, dk, dv = (to_device(x, "bf16") for x in (q, k, v))
+    chk = torch.full_like(dq, float("nan"))
+    nbytes = fa.flat_attn_fwd_splitkv_workspace_bytes(B, H, Nq, Nk, d, n_splits)
+    ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    kv = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    rc = lib.flat_attn_fwd_splitkv(dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), chk.data_ptr(), B, H, Nq, Nk, d, scale, mask,
+                                   None if kv is None else kv.data_ptr(), n_splits, ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(out.view(torch.int16), chk.view(torch.int16))
