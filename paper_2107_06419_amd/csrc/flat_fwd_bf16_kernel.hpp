@@ -680,6 +680,11 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     bool owed_in_a = false;  // one block per tile only: the last step left its probabilities in pA, not pB
     if (KB >= 2) {
 #pragma unroll 1
+        for (; j < n_unm_tiles; ++j) {
+            tile_steps(j, sj, false, false);
+            sj = sj + 1 == STAGES ? 0 : sj + 1;
+        }
+#pragma unroll 1
         for (; j < n_act_tiles; ++j) {
             tile_steps(j, sj, true, false);
             sj = sj + 1 == STAGES ? 0 : sj + 1;
