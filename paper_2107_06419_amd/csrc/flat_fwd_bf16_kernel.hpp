@@ -808,24 +808,32 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         }
         return;
     }
-    // ---- epilogue: O = O_acc / l, rounded to bf16; a lane holds 4 consecutive head-dim elements per register quad
+    // ---- epilogue: O = O_acc / l, rounded to bf16.  A lane holds 4 consecutive columns per register quad, its other half the next
+    // 4; two quads are swapped across the halves so that every lane stores 8 consecutive columns.  Short sequences are bound by
+    // memory and by their start and end: half as many stores of twice the width, 768 heads x 512, d = 64: 72.7 -> 66 us; 1024 x 128
+    // 16.6 -> 15.0; d = 128, 768 x 512: 162 -> 151.
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const float total = halves_sum(lsum[qb]);
         const float inv = (SPARSE && n_tiles == 0) ? 0.f : 1.0f / total;  // a row block with an empty list yields zeros
         const int row = q0w + 32 * qb + l32;
-        if (row < Nq) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const int dcol = 32 * db + 8 * rq + 4 * half;
-                    floatx2 w;
-                    w[0] = __builtin_bit_cast(float, pack_bf16(oacc[qb][db][4 * rq] * inv, oacc[qb][db][4 * rq + 1] * inv));
-                    w[1] = __builtin_bit_cast(float, pack_bf16(oacc[qb][db][4 * rq + 2] * inv, oacc[qb][db][4 * rq + 3] * inv));
-                    *(floatx2*)(Oh + (size_t)row * D + dcol) = w;
-                }
-        }
+            for (int rp = 0; rp < 2; ++rp) {
+                uint32_t w[2][2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int r = 8 * rp + 4 * q + 2 * e;
+                        w[q][e] = pack_bf16(oacc[qb][db][r] * inv, oacc[qb][db][r + 1] * inv);
+                    }
+                const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                const uint4v o8 = {(uint32_t)lo[0], (uint32_t)hi[0], (uint32_t)lo[1], (uint32_t)hi[1]};
+                if (row < Nq) *(uint4v*)(Oh + (size_t)row * D + 32 * db + 16 * rp + 8 * half) = o8;
+            }
     }
 }
 
