@@ -160,26 +160,13 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     int N = prob.Nk;
     if (prob.kv_lens) N = max(1, min(prob.Nk, prob.kv_lens[bh / prob.heads_per_batch]));
     const size_t head_q = (size_t)bh * Nq * D, head_k = (size_t)bh * prob.Nk * D;
-    const bf16* Qh = Q + head_q;
+    const char* Qh = (const char*)(Q + head_q);
     const char* Kh = (const char*)(K + head_k);
     const char* Vh = (const char*)(V + head_k);
     bf16* Oh = O + head_q;
     // Key groups: wavefronts rg * KG + kg, kg = 0 .. KG-1, own the same QW query rows and take KB of every tile's blocks each.
     const int kg = KG == 1 ? 0 : wave % KG, rg = KG == 1 ? wave : wave / KG;
     const int q0w = qt * BR + rg * QW;
-
-    // Q^T fragments (B operand of S^T = K Q^T): column = query, 8 consecutive head-dim elements
-    bf16x8 qf[QB][DS];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int row = q0w + 32 * qb + l32;
-#pragma unroll
-        for (int ds = 0; ds < DS; ++ds) {
-            uint4v z = {0, 0, 0, 0};  // rows past the end are zero
-            if (row < Nq) z = *(const uint4v*)(Qh + (size_t)row * D + ds * 16 + half * 8);
-            qf[qb][ds] = __builtin_bit_cast(bf16x8, z);
-        }
-    }
 
     // Block-sparse: copy this row block's tile list into LDS (ids forced into range; a wrong list can give a
     // wrong result but no stray access).
@@ -205,7 +192,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         return KB64 == 1 ? sp_ids[j] : sp_ids[j / KB64] * KB64 + j % KB64;
     };
 
-    float m[QB];  // reference max of each row, set in the prologue below
+    float m[QB];          // reference max of each row, set in the prologue below
+    bf16x8 qf[QB][DS];    // Q^T fragments (B operand of S^T = K Q^T): column = query, 8 consecutive head-dim elements
 
     floatx16 oacc[QB][DB];
     float lsum[QB];
@@ -380,23 +368,62 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
                 for (int r = 0; r < 16; ++r) oacc[qb][db][r] *= alpha;
         }
     };
-    // ---- prologue: fill STAGES-1 stages.  The full wait at its end also retires the Q loads above, so that no
-    // wait on them is left inside the loops (it would drain the prefetch ring every iteration).  The streaming
-    // loads go out before the first-key loads below are waited for, so that a workgroup's start is one memory round
-    // trip, not two in a row (short sequences consist of little else).
+    // ---- prologue.  The workgroup's Q rows arrive through LDS like the tiles: whole rows, 1024 contiguous bytes per load, where
+    // fragments straight from memory touch 32 bytes of each of 32 rows per load.  They lie at the end of the ring, and what
+    // they leave free in front is filled with the first tiles at once; the rest of the ring follows when the fragments are in
+    // registers.  So a workgroup starts after one round trip of Q and the first tile.  768 heads x 512, d = 64: 67 -> 66 us, d = 128
+    // 154 -> 148, d = 96 125 -> 117; 8 x 1001, d = 128, 13.4 -> 12.3; 4 x 4096, d = 64, 26.6 -> 24.9.  At d = 256 the 64 KiB of Q take
+    // longer into LDS and out again (2 x 8 causal heads of 3001: 130 us straight to registers, 132 through LDS), so they go
+    // straight to registers, with the whole ring filled behind them.
+    constexpr bool kQThroughLds = D != 256;
+    constexpr int kQBytes = kQThroughLds ? BR * C::ROWB : 0;
+    constexpr int kQAt = C::LDS_BYTES - kQBytes >= C::STAGE ? C::LDS_BYTES - kQBytes : C::STAGE;
+    constexpr int kEarlyTiles = kQAt / C::STAGE < STAGES - 1 ? kQAt / C::STAGE : STAGES - 1;
+    if (kQThroughLds) {
+        constexpr int kQLoads = BR / C::ROWS_PER_LOAD;
 #pragma unroll
-    for (int t = 0; t < STAGES - 1; ++t)
-        if (t < n_tiles) issue_tile_loads(t, t);
-    if (kStagger && STAGES - 1 < n_tiles) issue_tile_loads(STAGES - 1, STAGES - 1, true, false);
-    // reference max of each row = c * (q . k_first), k_first = the first key the row block sees (key 0 unless
-    // block-sparse or split), from the Q fragments already in registers
+        for (int i = 0; i < (kQLoads + NW - 1) / NW; ++i) {
+            const int blk = NW * i + wave;  // 1024-byte block of the Q rows
+            if (kQLoads % NW != 0 && blk >= kQLoads) break;
+            const int r = blk * C::ROWS_PER_LOAD + lane / C::CHUNKS, chunk = (lane % C::CHUNKS) ^ C::swz(r);
+            const int row = min(qt * BR + r, Nq - 1);  // rows past the end repeat the last one; they are never stored
+            const uint32_t off_q = (uint32_t)row * C::GROWB + (chunk < C::GCHUNKS ? chunk : chunk - (C::CHUNKS - C::GCHUNKS)) * 16;
+            dma16(Qh, off_q, __builtin_amdgcn_readfirstlane(smem_base + kQAt + blk * 1024));
+        }
+    } else {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) {
+                const int row = q0w + 32 * qb + l32;
+                uint4v z = {0, 0, 0, 0};
+                if (row < Nq) z = *(const uint4v*)(Qh + (size_t)row * C::GROWB + ds * 32 + half * 16);
+                qf[qb][ds] = __builtin_bit_cast(bf16x8, z);
+            }
+    }
+    auto fill = [&](int t) __attribute__((always_inline)) {
+        if (t >= n_tiles) return;
+        if (kStagger) {  // K first, in the order the loop goes on with and its wait counts: K(t), V(t), K(t+1), ...
+            issue_tile_loads(t, t, true, false);
+            if (t < STAGES - 1) issue_tile_loads(t, t, false, true);
+        } else {
+            issue_tile_loads(t, t);
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < kEarlyTiles; ++t) fill(t);
+    if (kQThroughLds && !kSyncEveryPhase && n_tiles >= kEarlyTiles)
+        wait_vm<(kEarlyTiles - 1) * LOADS_PER_TILE>();
+    else
+        wait_vm<0>();
+    __syncthreads();
+    // Reference max of each row = c * (q . k_first), k_first = the first key the row block sees: row 0 of its first tile.
     {
+        typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
         float k0[DS][8];
-        const int first_key = SPLIT ? min(t0 * BC, N - 1) : (SPARSE && sp_count > 0) ? sp_ids[0] * 64 : 0;
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) {
-            const uint4v kv = *(const uint4v*)(Kh + (size_t)first_key * C::GROWB + ds * 32 + half * 16);
-            const bf16x8 kb8 = __builtin_bit_cast(bf16x8, kv);
+            const bf16x8 kb8 = *(lds_frag_ptr)(uintptr_t)(smem_base + (2 * ds + half) * 16);
 #pragma unroll
             for (int e = 0; e < 8; ++e) k0[ds][e] = (float)kb8[e];
         }
@@ -404,14 +431,17 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         for (int qb = 0; qb < QB; ++qb) {
             float dot = 0.f;
 #pragma unroll
-            for (int ds = 0; ds < DS; ++ds)
+            for (int ds = 0; ds < DS; ++ds) {
+                if (kQThroughLds) qf[qb][ds] = *(lds_frag_ptr)(uintptr_t)(smem_base + kQAt + (rg * QW + 32 * qb + l32) * C::ROWB + (((2 * ds + half) ^ C::swz(l32)) << 4));
 #pragma unroll
                 for (int e = 0; e < 8; ++e) dot = __builtin_fmaf((float)qf[qb][ds][e], k0[ds][e], dot);
-            m[qb] = halves_sum(dot) * c;
+            }
+            m[qb] = n_tiles > 0 ? halves_sum(dot) * c : 0.f;
         }
     }
-    wait_vm<0>();
-    __syncthreads();
+    if (kQThroughLds) __syncthreads();  // every wavefront has its fragments: the ring takes their place
+#pragma unroll
+    for (int t = kEarlyTiles; t < STAGES - (kStagger ? 0 : 1); ++t) fill(t);
 
     // With d = 128 two sets of V fragments do not fit the register file next to the accumulators: then one
     // set is used, refilled in the middle of each step right after the MFMAs that consumed it were issued.
@@ -848,7 +878,8 @@ inline hipError_t launch_cfg(const void* Q, const void* K, const void* V, void* 
     auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, CAUSAL, MODE, BCX, KG>;
     constexpr int ring = Bf16Cfg<D, STAGES, NW, BCX>::LDS_BYTES;
     constexpr int merge = KG > 1 ? NW * QB * (D * 128 + 256) : 0;  // the key groups' partial results, in the ring's place
-    constexpr int lds = (ring > merge ? ring : merge) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
+    constexpr int with_q = D == 256 ? 0 : Bf16Cfg<D, STAGES, NW, BCX>::STAGE + BR * Bf16Cfg<D, STAGES, NW, BCX>::ROWB;  // the first tile and Q
+    constexpr int lds = (ring > merge ? (ring > with_q ? ring : with_q) : (merge > with_q ? merge : with_q)) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
     static_assert(lds <= 160 * 1024, "more LDS than a compute unit has");
     static std::atomic<uint64_t> attr_done{0};  // one flag per kernel instantiation
     hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
