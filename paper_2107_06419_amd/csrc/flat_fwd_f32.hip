@@ -142,14 +142,17 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
         lsum += p[r];
         asm volatile("" : "+v"(p[r]), "+v"(lsum));  // here, between the MFMAs, not where p is used
     };
+    // Masked logits leave the row maximum here and the sums in the last tile's exponentials: scaled, -infinity need not stay what
+    // it is (scale 0 makes it a NaN).
+    auto partly_masked = [&](int tile) __attribute__((always_inline)) { return tile * 32 + 32 > N || (CAUSAL && tile * 32 + 31 > q0); };
+    auto visible = [&](int tile, int r) __attribute__((always_inline)) {
+        const int key = tile * 32 + acc_row(r, half);
+        return key < N && (!CAUSAL || key <= qrow);
+    };
     auto mask = [&](int tile, floatx16& s) __attribute__((always_inline)) {
-        const int jbase = tile * 32;
-        if (jbase + 32 > N || (CAUSAL && jbase + 31 > q0)) {
+        if (partly_masked(tile)) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = jbase + acc_row(r, half);
-                s[r] = key < N && (!CAUSAL || key <= qrow) ? s[r] : -INFINITY;
-            }
+            for (int r = 0; r < 16; ++r) s[r] = visible(tile, r) ? s[r] : -INFINITY;
         }
     };
     // With 512 registers the MFMA accumulators live in the upper half of the file; kept there by name, or the compiler
@@ -288,8 +291,14 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
         fence();
 #pragma unroll
         for (int r = 0; r < 16; ++r) read_v(r);
+        const int last = tile_of(n_mine - 1);
+        const bool masked = partly_masked(last);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) exponentiate(r);
+        for (int r = 0; r < 16; ++r) {
+            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], c, -m));
+            if (masked) p[r] = visible(last, r) ? p[r] : 0.f;
+            lsum += p[r];
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) attend_key(r);
     }

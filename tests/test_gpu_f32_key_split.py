@@ -31,3 +31,21 @@ def test_f32_key_split_edges(heads, N, d, mask):
     ref = oracle.attention(q[:, some], k[:, some], v[:, some], float(np.float32(d ** -0.5)), mask)
     check_close(to_host_f64(out[:, some]), ref, "f32", f"heads={heads} N={N} d={d} mask={mask}")
     assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("heads", sorted(HEADS.values()))
+@pytest.mark.parametrize("N", [1, 33, 128, 289])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("mask", [0, 1])
+def test_f32_scale_zero_gives_uniform_weights(heads, N, d, mask):
+    """scale = 0 is accepted: every visible key weighs the same, masked keys (the diagonal tile, the tail) nothing."""
+    import torch
+    q, k, v = (synth.tensor_f32((1, heads, N, d), 1700 + N + d + mask, t, "normal", 1.0) for t in range(3))
+    dq, dk, dv = (to_device(x, "f32") for x in (q, k, v))
+    out = torch.full_like(dq, float("nan"))
+    print(f"case f32 scale 0 heads={heads} N={N} d={d} mask={mask}", flush=True)
+    fa.flat_attn_fwd_f32(dq, dk, dv, out, 0.0, mask)
+    torch.cuda.synchronize()
+    some = sorted({0, heads - 1})
+    check_close(to_host_f64(out[:, some]), oracle.attention(q[:, some], k[:, some], v[:, some], 0.0, mask), "f32", f"scale 0 N={N} d={d}")
+    assert torch.isfinite(out).all()
