@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
     const int n_mine = (n_tiles - wave + NW - 1) / NW;  // tiles wave, wave + NW, ... of this wavefront
 
     // ---- global -> LDS.  Load i of a tile fills rows RPL i .. of it; lane l fills slot l % CHUNKS of row RPL i + l / CHUNKS.
-    // Keys beyond N are clamped to the last one: their logits are masked and their values meet a zero probability.
+    // Keys beyond N are clamped to the last one; their logits are masked and their values replaced by zeros when the last tile is used.
     const uint32_t lds_k = (uint32_t)(uintptr_t)smem + (uint32_t)wave * C::WAVE_LDS, lds_v = lds_k + C::TILE;
     const int ld_row = lane / C::CHUNKS, ld_slot = lane % C::CHUNKS;
     const int ld_kchunk = (ld_slot ^ ld_row) * 16, ld_vchunk = ld_slot * 16;
@@ -298,6 +298,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
             p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], c, -m));
             if (masked) p[r] = visible(last, r) ? p[r] : 0.f;
             lsum += p[r];
+        }
+        if (last * 32 + 32 > N) {  // keys past N add nothing, also where the last row, which their loads were clamped to, is infinite
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) vf[r][db] = last * 32 + acc_row(r, half) < N ? vf[r][db] : 0.f;
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) attend_key(r);

@@ -49,3 +49,22 @@ def test_f32_scale_zero_gives_uniform_weights(heads, N, d, mask):
     some = sorted({0, heads - 1})
     check_close(to_host_f64(out[:, some]), oracle.attention(q[:, some], k[:, some], v[:, some], 0.0, mask), "f32", f"scale 0 N={N} d={d}")
     assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("heads", sorted(HEADS.values()))
+@pytest.mark.parametrize("N", [1, 31, 65, 127])
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_infinity_in_the_last_value_row_reaches_its_column_only(heads, N, d):
+    """The last tile is filled up with keys that do not exist: they add nothing, whatever the last value row holds."""
+    import torch
+    q, k, v = (synth.tensor_f32((1, heads, N, d), 1900 + N + d, t, "normal", 1.0) for t in range(3))
+    dq, dk, dv = (to_device(x, "f32") for x in (q, k, v))
+    dv[:, :, N - 1, 3] = float("inf")
+    out = torch.full_like(dq, float("nan"))
+    print(f"case f32 infinite value heads={heads} N={N} d={d}", flush=True)
+    fa.flat_attn_fwd_f32(dq, dk, dv, out, float(np.float32(d ** -0.5)), 0)
+    torch.cuda.synchronize()
+    assert torch.isposinf(out[..., 3]).all()
+    some, rest = sorted({0, heads - 1}), [c for c in range(d) if c != 3]
+    ref = oracle.attention(q[:, some], k[:, some], v[:, some], float(np.float32(d ** -0.5)), 0)
+    check_close(to_host_f64(out[:, some])[..., rest], ref[..., rest], "f32", f"infinite value N={N} d={d}")
