@@ -26,8 +26,11 @@ namespace flat {
 //     a wavefront takes head-dim elements 8 g + 4 h .. + 3 of K and Q for four Logit MFMAs (one ds_read_b128 per operand), and
 //     row i of accumulator db is head-dim column DB i + db, so one read of DB consecutive values of V serves the DB Attend
 //     MFMAs of a key.
-//   - The row maximum is exact but lazy: O and l are rescaled only when a row's maximum rises more than 2^8 above the
-//     reference (fp32 has the range; the quotient O / l does not depend on the reference).
+//   - The row maximum is exact but lazy: a reference maximum is set 2^4 above the row maximum, and O and l are rescaled only
+//     when that is passed (the quotient O / l does not depend on the reference).  So probabilities are at most 1, as with the row
+//     maximum itself, and O and l overflow no earlier; and they are at least 2^-4 at the maximum, so values down to the smallest
+//     normal floats lose nothing (relative error at values of 2e-38: 1.3e-7, with 2^8 1.2e-6).  Measured against the row maximum
+//     as the reference: 16 causal heads of 2049, d = 128, 170.6 -> 163.0 us; 128 x 512 causal 91.6 -> 86.1.
 // LDS: chunk c (16 bytes) of K row r lives in slot c ^ (r & 15): a ds_read_b128 touches 16 rows at one chunk index per clock and
 // then meets 16 different slots.  V rows are read along the row and need no swizzle.
 // Measured: 16 heads of 8192 positions at d = 128 without a mask 128 TFLOP/s, 32 heads of 4096 at d = 64 130 (a large fp32
@@ -49,7 +52,7 @@ struct F32Cfg {
     static constexpr int LDS_RESERVED = 160 * 1024 / WAVES_PER_CU;           // of a wavefront: no third one on some SIMDs
 };
 
-constexpr float kF32LazyMax = 8.0f;  // log2 units
+constexpr float kF32Headroom = 4.0f;  // of the reference maximum above the row maximum, log2 units
 
 template <int D, int NW, bool CAUSAL>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
@@ -163,9 +166,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
             for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[db]));
         }
     };
-    // raise the reference maximum to `top` (log2 units) where that is higher, and bring O and l to it
+    // raise the reference maximum where the row maximum `top` (log2 units) is above it, and bring O and l to it
     auto rescale = [&](float top) __attribute__((always_inline)) {
-        const float m_new = __builtin_fmaxf(m, top);
+        const float m_new = top > m ? top + kF32Headroom : m;
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         lsum *= alpha;
 #pragma unroll
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
             asm volatile("" : "+v"(x[r]));
             mx = __builtin_fmaxf(mx, x[r]);
         }
-        m = halves_max(mx) * c;
+        m = halves_max(mx) * c + kF32Headroom;
         if (n_mine > 1) {
             wait_vm<0>();
             fence();
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
                 }
                 if (r == 13) {
                     top = halves_max(mx) * c;
-                    risen = __builtin_amdgcn_ballot_w64(top > m + kF32LazyMax) != 0;
+                    risen = __builtin_amdgcn_ballot_w64(top > m) != 0;
                 }
                 if (r < 8) {
 #pragma unroll

@@ -68,3 +68,26 @@ def test_f32_infinity_in_the_last_value_row_reaches_its_column_only(heads, N, d)
     some, rest = sorted({0, heads - 1}), [c for c in range(d) if c != 3]
     ref = oracle.attention(q[:, some], k[:, some], v[:, some], float(np.float32(d ** -0.5)), 0)
     check_close(to_host_f64(out[:, some])[..., rest], ref[..., rest], "f32", f"infinite value N={N} d={d}")
+
+
+@pytest.mark.parametrize("heads", sorted(HEADS.values()))
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("magnitude", [1e36, 1e-37])
+def test_f32_large_and_small_values_stay_in_range(heads, d, magnitude):
+    """Probabilities never exceed 1 against the reference maximum, also while it lags behind the row maximum: the first tile's
+    logits lie 7.5 powers of two below the others', and 160 values of 1e36 still sum to less than the largest float.  Nor do they
+    become so small that values near the smallest normal float are lost."""
+    import torch
+    N = 160
+    q, k = np.zeros((1, heads, N, d), np.float32), np.zeros((1, heads, N, d), np.float32)
+    q[..., 0] = 1.0
+    k[:, :, 32:, 0] = 7.5 * np.log(2.0)
+    v = (1.0 + 0.1 * synth.tensor_f32((1, heads, N, d), 77, 2, "normal", 1.0)).astype(np.float32)
+    dq, dk, dv = (to_device(x, "f32") for x in (q, k, v * np.float32(magnitude)))
+    out = torch.full_like(dq, float("nan"))
+    print(f"case f32 range heads={heads} d={d} magnitude={magnitude}", flush=True)
+    fa.flat_attn_fwd_f32(dq, dk, dv, out, 1.0, 0)
+    torch.cuda.synchronize()
+    some = sorted({0, heads - 1})
+    check_close(to_host_f64(out[:, some]) / float(np.float32(magnitude)), oracle.attention(q[:, some], k[:, some], v[:, some], 1.0, 0), "f32", "range")
+    assert torch.isfinite(out).all()
