@@ -4,6 +4,7 @@
 #include "flat_common.hpp"
 #include "flat_launch.hpp"
 
+#include <float.h>
 #include <math.h>
 
 #include <type_traits>
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
             asm volatile("" : "+v"(x[r]));
             mx = __builtin_fmaxf(mx, x[r]);
         }
-        m = halves_max(mx) * c + kF32Headroom;
+        m = __builtin_fmaxf(halves_max(mx) * c + kF32Headroom, -FLT_MAX);  // finite, so that a first tile of -infinity only has weight 0
         if (n_mine > 1) {
             wait_vm<0>();
             fence();

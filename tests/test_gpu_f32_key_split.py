@@ -91,3 +91,21 @@ def test_f32_large_and_small_values_stay_in_range(heads, d, magnitude):
     some = sorted({0, heads - 1})
     check_close(to_host_f64(out[:, some]) / float(np.float32(magnitude)), oracle.attention(q[:, some], k[:, some], v[:, some], 1.0, 0), "f32", "range")
     assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("heads", sorted(HEADS.values()))
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_keys_at_minus_infinity_weigh_nothing(heads, d):
+    """A wavefront whose own tiles hold only logits of -inf (here every tile but the first) adds nothing to the others' result."""
+    import torch
+    N, scale = 128, float(np.float32(d ** -0.5))
+    q, k, v = (synth.tensor_f32((1, heads, N, d), 2300 + d, t, "normal", 1.0) for t in range(3))
+    q = np.abs(q) + 0.1
+    dq, dk, dv = (to_device(x, "f32") for x in (q, k, v))
+    dk[:, :, 32:] = float("-inf")
+    out = torch.full_like(dq, float("nan"))
+    print(f"case f32 keys at -inf heads={heads} d={d}", flush=True)
+    fa.flat_attn_fwd_f32(dq, dk, dv, out, scale, 0)
+    torch.cuda.synchronize()
+    some = sorted({0, heads - 1})
+    check_close(to_host_f64(out[:, some]), oracle.attention_cross(q[:, some], k[:, some, :32], v[:, some, :32], scale, 0), "f32", "keys at -inf")
