@@ -60,7 +60,7 @@ template <int D, int STAGES, int NW, int BCX = 0>
 struct Bf16Cfg {
     static_assert(D == 32 || D == 64 || D == 96 || D == 128 || D == 256, "head dimension not built");
     static constexpr int DP = D == 96 ? 128 : D;      // row length of the tiles in LDS
-    static constexpr int BC = BCX ? BCX : (D == 256 ? 32 : 64);  // keys per tile
+    static constexpr int BC = BCX ? BCX : bf16_keys_per_tile(D);  // keys per tile
     static constexpr int ROWB = DP * 2;               // bytes per row in LDS
     static constexpr int GROWB = D * 2;               // bytes per row in global memory
     static constexpr int CHUNKS = ROWB / 16;          // 16-byte chunks per LDS row
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         bh = logical / n_qtiles;
         qt = logical - bh * n_qtiles;
     } else {
-        constexpr int kByLds = (160 * 1024) / C::LDS_BYTES, kByRegs = 8 / NW;  // two wavefronts per SIMD
+        constexpr int kByLds = (160 * 1024) / bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG), kByRegs = 8 / NW;  // two wavefronts per SIMD
         constexpr bool kTwoPerUnit = (kByLds < kByRegs ? kByLds : kByRegs) == 2;
         const int x = blockIdx.x & 7, t = blockIdx.x >> 3;
         int r = t;
@@ -378,6 +378,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     constexpr bool kQThroughLds = D != 256;
     constexpr int kQBytes = kQThroughLds ? BR * C::ROWB : 0;
     constexpr int kQAt = C::LDS_BYTES - kQBytes >= C::STAGE ? C::LDS_BYTES - kQBytes : C::STAGE;
+    static_assert(kQAt + kQBytes <= bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG), "the Q rows must fit the LDS a launch asks for");
+    static_assert(!SPARSE || kQAt + kQBytes <= C::LDS_BYTES, "the Q rows must not reach the block-sparse list behind the ring");
     constexpr int kEarlyTiles = kQAt / C::STAGE < STAGES - 1 ? kQAt / C::STAGE : STAGES - 1;
     if (kQThroughLds) {
         constexpr int kQLoads = BR / C::ROWS_PER_LOAD;
@@ -876,10 +878,7 @@ inline hipError_t launch_cfg(const void* Q, const void* K, const void* V, void* 
     const int n_blocks = BH * n_qtiles;
     const int blocks_per_xcd = (n_blocks + 7) / 8;
     auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, CAUSAL, MODE, BCX, KG>;
-    constexpr int ring = Bf16Cfg<D, STAGES, NW, BCX>::LDS_BYTES;
-    constexpr int merge = KG > 1 ? NW * QB * (D * 128 + 256) : 0;  // the key groups' partial results, in the ring's place
-    constexpr int with_q = D == 256 ? 0 : Bf16Cfg<D, STAGES, NW, BCX>::STAGE + BR * Bf16Cfg<D, STAGES, NW, BCX>::ROWB;  // the first tile and Q
-    constexpr int lds = (ring > merge ? (ring > with_q ? ring : with_q) : (merge > with_q ? merge : with_q)) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
+    constexpr int lds = bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
     static_assert(lds <= 160 * 1024, "more LDS than a compute unit has");
     static std::atomic<uint64_t> attr_done{0};  // one flag per kernel instantiation
     hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
@@ -910,7 +909,7 @@ hipError_t launch_fwd_bf16_groups(const void* Q, const void* K, const void* V, v
 template <int D, int QB, int NW, int STAGES, int BCX>
 hipError_t fwd_bf16_shape_occupancy(int* workgroups_per_cu) {
     auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, false, kDense, BCX>;
-    constexpr int lds = Bf16Cfg<D, STAGES, NW, BCX>::LDS_BYTES;
+    constexpr int lds = bf16_lds_bytes(D, QB, NW, STAGES, BCX, 1);  // as launched: the limit set here holds for launches too
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, kern, 64 * NW, lds);

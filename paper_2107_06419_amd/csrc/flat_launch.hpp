@@ -66,6 +66,17 @@ constexpr size_t kSplitStaticScratchBytes = (size_t)64 << 20;
 hipError_t launch_fwd_bf16_split_static(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob,
                                         int d, int rows_per_block, float scale, int causal, hipStream_t stream);
 
+// Keys per tile where a shape does not ask for another number, and the dynamic LDS of a launch of the fused bf16 kernel: the ring, or
+// what lies in its place before the loop (the first tile and the workgroup's Q rows; none at d = 256) and after it (the key
+// groups' partial results).  The one place this is computed: launch, occupancy query and tile table use it.
+constexpr int bf16_keys_per_tile(int d) { return d == 256 ? 32 : 64; }
+constexpr int bf16_lds_bytes(int d, int row_blocks, int wavefronts, int stages, int keys_per_tile, int key_groups) {
+    const int row_bytes = (d == 96 ? 128 : d) * 2, stage = 2 * (keys_per_tile ? keys_per_tile : bf16_keys_per_tile(d)) * row_bytes;
+    const int ring = stages * stage, with_q = d == 256 ? 0 : stage + 32 * row_blocks * (wavefronts / key_groups) * row_bytes;
+    const int merge = key_groups > 1 ? wavefronts * row_blocks * (d * 128 + 256) : 0;
+    return ring > with_q ? (ring > merge ? ring : merge) : (with_q > merge ? with_q : merge);
+}
+
 // Tile shapes of the fused bf16 kernel (flat_tiles.hip).  Index 0 is the default of launch_fwd_bf16.
 struct TileShape {
     int d;                   // head dimension the shape is built for

@@ -20,8 +20,7 @@ struct Entry {
 
 template <int D, int QB, int NW, int STAGES, int BCX = 0>
 constexpr Entry entry() {
-    constexpr int DP = D == 96 ? 128 : D, BC = BCX ? BCX : (D == 256 ? 32 : 64);  // as in Bf16Cfg: padded row length, keys per tile
-    return Entry{TileShape{D, 32 * QB * NW, BC, NW, 32 * QB, STAGES, STAGES * 2 * BC * DP * 2},
+    return Entry{TileShape{D, 32 * QB * NW, BCX ? BCX : bf16_keys_per_tile(D), NW, 32 * QB, STAGES, bf16_lds_bytes(D, QB, NW, STAGES, BCX, 1)},
                  &launch_fwd_bf16_shape<D, QB, NW, STAGES, BCX>, &fwd_bf16_shape_occupancy<D, QB, NW, STAGES, BCX>};
 }
 
