@@ -140,7 +140,7 @@ int flat_attn_fwd_splitkv_static(const void* Q, const void* K, const void* V, vo
  *   tile_ids: device, n_tile_ids ints in [0, ceil(N/64)), ascending and distinct within a row block.
  *   The lists live on the device and are not validated by the host: out-of-range offsets and ids are clamped
  *     (never a stray access), duplicate or unsorted ids give a wrong result.  A row block with an empty list
- *     produces zeros.  Listing every tile for every row block reproduces flat_attn_fwd bit for bit.
+ *     produces zeros.  Listing every tile for every row block reproduces flat_attn_fwd_tile of index 0 bit for bit.
  */
 #define FLAT_SPARSE_BLOCK_ROWS 256
 #define FLAT_SPARSE_BLOCK_KEYS 64
@@ -178,17 +178,17 @@ int flat_attn_unfused(const void* Q, const void* K, const void* V, void* O,
  * flat_attn_fwd uses index 0, except where the 128-row shape (d = 64: index 7, d = 128: index 2, d = 32 and 96:
  * index 1) measures ahead: launches of few row blocks (at most 128 blocks of 256 query rows; 256 with the causal
  * mask at d = 32 and 64, 192 at d = 96 and 128: 1.3-1.5 times faster), d = 64 with the causal mask up to 4096
- * positions and 1024 row blocks, d = 32 for short sequences, and up to 128 query rows.  Launches of few rows further
- * run a key-group form of their shape, in which the wavefronts of a workgroup share the keys of 32 to 128 rows;
- * flat_attn_fwd_tile runs any shape so that the choice can be re-timed: index 0 and the others as they are, the 128-row
- * index of the choice above with its key-group forms, as flat_attn_fwd does.
+ * positions and 1024 row blocks, d = 32 for short sequences, and up to 128 query rows; and except where a key-group form
+ * (the last indices of a head size), in which the wavefronts of a workgroup share the keys of the same 32 to 128 rows, is
+ * predicted to be faster: launches of few rows.  flat_attn_fwd_tile runs any index as it is, so that the choice can be re-timed.
  *   flat_attn_tile_shape_count(d): number of shapes for head dimension d (0 if d is not one of 32, 64, 96, 128, 256).
  *   flat_attn_tile_shape_get: fills *out (HOST pointer) for 0 <= index < count; FLAT_ERR_SHAPE otherwise.
  *   flat_attn_tile_shape_occupancy: workgroups of that shape resident per compute unit on the current
  *     device (registers and LDS permitting), or a negative flat_status; the only one of the three that
  *     needs a GPU.
- *   flat_attn_tile_shape_default: the index (base shape) flat_attn_fwd (N = Nq) and flat_attn_fwd_cross (Nq query rows) take for a
- *     problem, or a negative flat_status; host arithmetic only.
+ *   flat_attn_tile_shape_default: the index flat_attn_fwd (N = Nq) runs for a problem, and flat_attn_fwd_cross for Nq query rows
+ *     over as many keys (with another number of keys a key-group form may be the faster one, or not), or a negative
+ *     flat_status; host arithmetic only.
  *   flat_attn_fwd_tile: flat_attn_fwd with the shape chosen by the caller; same arguments, checks and
  *     result tolerance (different shapes sum in different orders, so results differ in the last bits).
  */
@@ -197,7 +197,8 @@ typedef struct {
     int rows_per_workgroup; /* query rows per workgroup (the paper's R of R-Gran) */
     int keys_per_tile;      /* keys staged in LDS per ring stage */
     int wavefronts;         /* wavefronts per workgroup */
-    int rows_per_wavefront; /* query rows owned by one wavefront */
+    int rows_per_wavefront; /* query rows of one wavefront; in a key-group form of KG groups, KG wavefronts share them:
+                               rows_per_workgroup * KG = wavefronts * rows_per_wavefront (KG = 1 otherwise) */
     int lds_stages;         /* depth of the K/V ring in LDS */
     int lds_bytes;          /* LDS bytes per workgroup */
 } flat_tile_shape;

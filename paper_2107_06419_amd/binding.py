@@ -300,7 +300,8 @@ def flat_attn_tile_shape_occupancy(d: int, index: int) -> int:
 
 
 def flat_attn_tile_shape_default(B: int, H: int, Nq: int, d: int, mask_kind: int = FLAT_MASK_NONE) -> int:
-    """Index of the tile shape flat_attn_fwd / flat_attn_fwd_cross take for this problem (host arithmetic only)."""
+    """Index of the tile shape flat_attn_fwd runs for this problem, and flat_attn_fwd_cross for as many keys as queries (host
+    arithmetic only)."""
     n = int(load_library().flat_attn_tile_shape_default(int(B), int(H), int(Nq), int(d), int(mask_kind)))
     if n < 0:
         _check(n)

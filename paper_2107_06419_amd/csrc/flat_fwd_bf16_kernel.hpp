@@ -906,10 +906,10 @@ hipError_t launch_fwd_bf16_groups(const void* Q, const void* K, const void* V, v
 }
 
 // Workgroups of this shape that fit one compute unit at a time (registers and LDS), as the runtime reports it.
-template <int D, int QB, int NW, int STAGES, int BCX>
+template <int D, int QB, int NW, int STAGES, int BCX, int KG>
 hipError_t fwd_bf16_shape_occupancy(int* workgroups_per_cu) {
-    auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, false, kDense, BCX>;
-    constexpr int lds = bf16_lds_bytes(D, QB, NW, STAGES, BCX, 1);  // as launched: the limit set here holds for launches too
+    auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, false, kDense, BCX, KG>;
+    constexpr int lds = bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG);  // as launched: the limit set here holds for launches too
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, kern, 64 * NW, lds);
@@ -928,7 +928,8 @@ hipError_t launch_fwd_bf16_sparse_shape(const void* Q, const void* K, const void
     template hipError_t fwd_bf16_shape_occupancy<D, QB, NW, STAGES, BCX>(int*);
 #define FLAT_INSTANTIATE_BF16_GROUPS(D, QB, NW, STAGES, BC, KG)                                                              \
     template hipError_t launch_fwd_bf16_groups<D, QB, NW, STAGES, BC, KG>(const void*, const void*, const void*, void*, int, \
-                                                                          const Bf16Problem&, float, int, hipStream_t);
+                                                                          const Bf16Problem&, float, int, hipStream_t);       \
+    template hipError_t fwd_bf16_shape_occupancy<D, QB, NW, STAGES, BC, KG>(int*);
 #define FLAT_INSTANTIATE_BF16_SHAPE(D, QB, NW, STAGES) FLAT_INSTANTIATE_BF16_SHAPE_BC(D, QB, NW, STAGES, 0)
 
 }  // namespace flat

@@ -56,7 +56,6 @@ struct SplitPlan {
     int tiles_per_split;
     size_t workspace_bytes;
 };
-int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index);  // flat_plan.hip; -1: none
 bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* out);  // n_splits_wanted <= 0: chosen here
 hipError_t launch_fwd_bf16_split(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, int d,
                                  int rows_per_block, float scale, int causal, hipStream_t stream);
@@ -87,9 +86,12 @@ struct TileShape {
     int lds_stages;          // depth of the K/V ring
     int lds_bytes;           // dynamic LDS per workgroup
 };
+// After the shapes whose wavefronts own rows of their own come the key-group forms, whose wavefronts share the keys of a row: this is
+// the index of the first one, in the order of the cost table of flat_plan.hip.
+constexpr int first_key_group_form(int d) { return d == 64 ? 12 : d == 128 ? 4 : d == 32 || d == 96 ? 2 : 1; }
 int tile_shape_count(int d);
-int small_launch_shape(int d);                                // the 128-row shape of a head size, 0 if there is none
-int default_tile_shape(int BH, int Nq, int d, int causal);  // index launch_fwd_bf16 uses for this problem
+int chosen_tile_shape(int BH, const Bf16Problem& prob, int d, int causal);  // flat_plan.hip: index launch_fwd_bf16 runs
+int default_tile_shape(int BH, int Nq, int d, int causal);  // the same for as many keys as queries
 bool tile_shape(int d, int index, TileShape* out);
 hipError_t tile_shape_occupancy(int d, int index, int* workgroups_per_cu);
 hipError_t launch_fwd_bf16_tile(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, int d,
@@ -103,7 +105,7 @@ hipError_t launch_fwd_bf16_shape(const void* Q, const void* K, const void* V, vo
 template <int D, int QB, int NW, int STAGES, int BC, int KG>
 hipError_t launch_fwd_bf16_groups(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, float scale,
                                   int causal, hipStream_t stream);
-template <int D, int QB, int NW, int STAGES, int BCX = 0>
+template <int D, int QB, int NW, int STAGES, int BCX = 0, int KG = 1>
 hipError_t fwd_bf16_shape_occupancy(int* workgroups_per_cu);
 
 hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale,

@@ -4,6 +4,42 @@
 
 namespace flat {
 
+namespace {
+
+// The 128-row shape of a head size, for launches of few query rows (0: there is none).
+int small_launch_shape(int d) { return d == 64 ? 7 : d == 128 ? 2 : d == 32 || d == 96 ? 1 : 0; }
+
+// The shape a launch takes if none of its key-group forms is faster: index 0, except where a measured sweep (python -m
+// paper_2107_06419_amd.tile_sweep --small: 1 to 512 heads of 128 to 8192 positions, both masks, several machines)
+// shows the 128-row shape of the head dimension ahead:
+//   * launches too small to give every compute unit a 256-row workgroup - at most 128 blocks of 256 query rows (causal:
+//     256 at d = 32 / 64, 192 at d = 96 / 128): 1.3-1.5 times faster, simply because twice as many compute units work;
+//   * d = 64 with the causal mask, up to 4096 positions and 1024 row blocks: ahead by up to 15 %, never behind;
+//   * d = 32 (the vector side is the longer pole there and three workgroups per compute unit hide more of it): with
+//     the causal mask up to 8192 positions (4-18 %), without it up to 4096 positions and 1024 row blocks (6 %).
+//   * up to 128 query rows, where half of a 256-row workgroup or more would be padding (256 heads of 16 rows over 1024
+//     keys, d = 64: 23 us on 256 rows, 16 on 128; 2048 heads of 100 rows: 162 and 119 us).
+// Beyond these ranges the 128-row shapes lose 1-15 %.  No other shape is ahead of index 0 by more than the
+// run-to-run spread (the 512-row shape leads by 3 % for d = 64, causal, when B*H*ceil(N/512) is exactly 512, and
+// trails by 2-15 % with more or fewer row blocks: no rule is built on that).
+int base_tile_shape(int BH, int Nq, int d, int causal) {
+    const long long blocks = (long long)BH * (((long long)Nq + 255) / 256);  // 256-row blocks in the launch
+    if (Nq <= 128 && d != 256) return small_launch_shape(d);  // a 256-row workgroup would be at least half padding
+    switch (d) {
+        case 32:
+            if (causal) return Nq <= 8192 ? 1 : 0;
+            return (Nq > 512 && ((Nq <= 4096 && blocks <= 1024) || blocks <= 128)) ? 1 : 0;
+        case 64:
+            if (causal) return (Nq > 256 && blocks <= (Nq <= 4096 ? 1024 : 256)) ? 7 : 0;
+            return (Nq > 256 && blocks <= 128) ? 7 : 0;
+        case 96: return blocks <= (causal ? 192 : 128) ? 1 : 0;
+        case 128: return blocks <= (causal ? 192 : 128) ? 2 : 0;
+        default: return 0;
+    }
+}
+
+}  // namespace
+
 // ---- Key-group forms.  A launch of few query rows leaves most of the chip idle on the shapes above, whatever their rows per
 // workgroup, because each workgroup walks all keys alone.  In these forms the wavefronts of a workgroup share the keys of
 // the same 32, 64 or 128 rows (kernel parameter KG) and merge through LDS at the end; nothing else changes.  They re-read K
@@ -73,8 +109,6 @@ float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int ca
     return f.cost.start + (work > memory ? work : memory);
 }
 
-}  // namespace
-
 // The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1 times as long
 // (what the prediction is worth) or there is one tile, and so nothing to divide.  Up to 512 keys index 0 also keeps launches of
 // more than 512 blocks of 32 rows (forms gain 20 % at most there: 128 heads x 256, d = 64, 10.2 -> 8.0 us) and all of
@@ -93,6 +127,14 @@ int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index
         return best;
     }
     return -1;
+}
+
+}  // namespace
+
+// The index flat_attn_fwd / flat_attn_fwd_cross run: a base shape or its key-group form.
+int chosen_tile_shape(int BH, const Bf16Problem& prob, int d, int causal) {
+    const int base = base_tile_shape(BH, prob.Nq, d, causal), form = key_group_form(BH, prob, d, causal, base);
+    return form < 0 ? base : first_key_group_form(d) + form;
 }
 
 namespace {

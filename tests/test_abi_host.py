@@ -95,26 +95,33 @@ def test_validation_happens_before_any_gpu_work():
 
 
 def test_tile_shape_table_is_consistent():
-    """The shape table is host data: index 0 is the default, every entry describes a launchable shape, and
-    out-of-range queries are refused without touching a GPU."""
+    """The shape table is host data: index 0 is the default, every entry describes a launchable shape, the key-group forms
+    (KG wavefronts share the keys of the same rows) come last, and out-of-range queries are refused without touching a GPU."""
     lib = fa.load_library()
     assert fa.flat_attn_tile_shape_count(48) == 0 and fa.flat_attn_tile_shape_count(512) == 0
     for d in (32, 64, 96, 128, 256):
         n = fa.flat_attn_tile_shape_count(d)
-        assert n >= (2 if d in (64, 128) else 1)
+        n_base = n - {32: 3, 64: 3, 96: 4, 128: 4, 256: 1}[d]  # and as many key-group forms
+        assert n_base >= (2 if d in (64, 128) else 1)
         seen = set()
         for idx in range(n):
             t = fa.flat_attn_tile_shape_get(d, idx).as_dict()
-            assert t["d"] == d and t["keys_per_tile"] in ((32, 64, 128) if d == 64 else (32,) if d == 256 else (64,))
+            groups = t["wavefronts"] * t["rows_per_wavefront"] // t["rows_per_workgroup"]
+            assert t["rows_per_workgroup"] * groups == t["wavefronts"] * t["rows_per_wavefront"]
+            if idx < n_base:
+                assert t["d"] == d and t["keys_per_tile"] in ((32, 64, 128) if d == 64 else (32,) if d == 256 else (64,))
+                assert groups == 1 and t["lds_stages"] >= 3
+            else:  # a 32-key block of every tile per group
+                assert t["d"] == d and groups in (2, 4) and t["keys_per_tile"] == 32 * groups and t["lds_stages"] >= 2
             if idx == 0:
                 assert t["keys_per_tile"] == (32 if d == 256 else 64)
-            assert t["rows_per_workgroup"] == t["wavefronts"] * t["rows_per_wavefront"]
             assert t["rows_per_wavefront"] in (32, 64) and 1 <= t["wavefronts"] <= 16
-            assert t["lds_stages"] >= 3
             d_lds = 128 if d == 96 else d  # rows of 96 elements are padded to 128 in LDS
-            # K and V tiles, bf16; before the loop the first of them and the Q rows lie in the same place (d = 256: no Q)
+            # K and V tiles, bf16; before the loop the first of them and the Q rows lie in the same place (d = 256: no Q),
+            # after it what each wavefront of a key-group form brings: its accumulators, maxima and sums, fp32
             tile, q_rows = 2 * t["keys_per_tile"] * d_lds * 2, (0 if d == 256 else t["rows_per_workgroup"] * d_lds * 2)
-            assert t["lds_bytes"] == max(t["lds_stages"] * tile, tile + q_rows) <= 160 * 1024
+            merge = t["wavefronts"] * t["rows_per_wavefront"] * (d + 2) * 4 if groups > 1 else 0
+            assert t["lds_bytes"] == max(t["lds_stages"] * tile, tile + q_rows, merge) <= 160 * 1024
             assert 256 % t["rows_per_workgroup"] == 0 or t["rows_per_workgroup"] % 256 == 0
             key = (t["rows_per_workgroup"], t["wavefronts"], t["lds_stages"], t["keys_per_tile"])
             assert key not in seen
@@ -127,16 +134,17 @@ def test_tile_shape_table_is_consistent():
             assert lib.flat_attn_tile_shape_occupancy(d, bad) == -2
     assert lib.flat_attn_tile_shape_get(64, 0, None) == -1
     assert lib.flat_attn_tile_shape_occupancy(80, 0) == -3
-    # the default shape is host arithmetic: large launches take index 0, small ones the 128-row shape
+    # the default shape is host arithmetic: large launches take index 0, smaller ones the 128-row shape or a key-group form
     assert fa.flat_attn_tile_shape_default(1, 16, 16384, 64, 0) == 0 and fa.flat_attn_tile_shape_default(2, 8, 8192, 128, 1) == 0
-    assert fa.flat_attn_tile_shape_default(1, 12, 512, 64, 0) == 7 and fa.flat_attn_tile_shape_default(1, 12, 512, 128, 1) == 2
-    assert fa.flat_attn_tile_shape_default(1, 12, 256, 64, 0) == 0 and fa.flat_attn_tile_shape_default(1, 129, 512, 64, 0) == 0
+    assert fa.flat_attn_tile_shape_default(2, 64, 512, 64, 1) == 7 and fa.flat_attn_tile_shape_default(1, 48, 1024, 128, 1) == 2
+    assert fa.flat_attn_tile_shape_default(1, 12, 512, 64, 0) == 12 and fa.flat_attn_tile_shape_default(1, 12, 512, 128, 1) == 4
+    assert fa.flat_attn_tile_shape_default(1, 1, 64, 64, 0) == 7 and fa.flat_attn_tile_shape_default(1, 129, 512, 64, 0) == 0
     for d in (32, 64, 96, 128, 256):
         for B, H, N, mask in ((1, 1, 1, 0), (3, 7, 300, 1), (1, 12, 512, 0), (64, 12, 512, 1), (1, 16, 16384, 0), (2147483, 1000, 77, 1)):
             idx = fa.flat_attn_tile_shape_default(B, H, N, d, mask)
             assert 0 <= idx < fa.flat_attn_tile_shape_count(d)
             if idx:
-                assert fa.flat_attn_tile_shape_get(d, idx).as_dict()["rows_per_workgroup"] == 128
+                assert fa.flat_attn_tile_shape_get(d, idx).as_dict()["rows_per_workgroup"] in (32, 64, 128)
     assert lib.flat_attn_tile_shape_default(0, 1, 1, 64, 0) == -2 and lib.flat_attn_tile_shape_default(1, 1, 1, 80, 0) == -3
     assert lib.flat_attn_tile_shape_default(1, 1, 1, 64, 2) == -3 and lib.flat_attn_tile_shape_default(65536, 65536, 1, 64, 0) == -2
     d64, d128 = fa.flat_attn_tile_shape_get(64, 0).as_dict(), fa.flat_attn_tile_shape_get(128, 0).as_dict()

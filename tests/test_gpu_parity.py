@@ -183,13 +183,16 @@ def test_long_causal_d64_default_and_512_row_shape_match_the_oracle():
             check_close(to_host_f64(explicit[:, :, drows, :]), ref, "bf16", f"{w.name} shape {index}")
 
 
-@pytest.mark.parametrize("d,B,H,N,mask,index", [(64, 1, 12, 512, 0, 7), (64, 2, 64, 512, 1, 7), (64, 1, 129, 512, 0, 0), (64, 8, 16, 256, 0, 0),
-                                                (128, 1, 12, 1024, 0, 2), (128, 1, 48, 1024, 1, 2), (128, 1, 40, 1024, 0, 0),
-                                                (32, 1, 12, 1024, 0, 1), (32, 1, 12, 512, 0, 0), (96, 1, 12, 640, 1, 1), (96, 1, 70, 700, 0, 0),
-                                                (64, 1, 128, 2048, 1, 7), (64, 1, 96, 4096, 1, 0), (32, 2, 16, 8192, 1, 1), (32, 1, 40, 8192, 0, 0)])
-def test_small_launches_take_the_128_row_shape(d, B, H, N, mask, index):
-    """flat_attn_fwd's choice of tile shape for launches of few row blocks, shown by bitwise equality with that shape
-    run explicitly, and the result compared with the oracle."""
+@pytest.mark.parametrize("d,B,H,N,mask,index,wg_rows", [
+    (64, 2, 64, 512, 1, 7, 128), (64, 1, 129, 512, 0, 0, 256), (64, 8, 16, 256, 0, 0, 256), (64, 1, 128, 2048, 1, 7, 128), (64, 1, 96, 4096, 1, 0, 256),
+    (128, 1, 48, 1024, 1, 2, 128), (128, 1, 40, 1024, 0, 0, 256), (32, 1, 12, 512, 0, 0, 256), (32, 2, 16, 8192, 1, 1, 128), (32, 1, 40, 8192, 0, 0, 256),
+    (96, 1, 70, 700, 0, 0, 256), (96, 1, 60, 512, 1, 1, 128),
+    # key-group forms: four groups on 32 and on 64 rows, two groups on 64 and on 128 rows
+    (64, 1, 12, 512, 0, 12, 32), (96, 1, 12, 640, 1, 2, 32), (32, 1, 12, 1024, 0, 3, 64), (64, 1, 16, 777, 0, 13, 64),
+    (128, 1, 12, 1024, 0, 6, 64), (256, 1, 8, 512, 1, 1, 64), (96, 1, 48, 2048, 0, 5, 128), (128, 1, 48, 2048, 0, 7, 128)])
+def test_launches_take_the_shape_the_dispatch_names(d, B, H, N, mask, index, wg_rows):
+    """flat_attn_fwd's choice of tile shape, from the 256-row shape of large launches to the key-group forms of small ones,
+    shown by bitwise equality with that shape run explicitly, and the result compared with the oracle."""
     import torch
     import paper_2107_06419_amd as fa
     w = synth.custom(f"small_{d}_{B}_{H}_{N}_{mask}", B, H, N, d, "bf16", mask, seed=3100 + H + N + mask)
@@ -201,7 +204,7 @@ def test_small_launches_take_the_128_row_shape(d, B, H, N, mask, index):
     explicit = torch.full_like(dq, float("nan"))
     fa.flat_attn_fwd_tile(dq, dk, dv, explicit, w.scale, w.mask, index)
     torch.cuda.synchronize()
-    assert fa.flat_attn_tile_shape_get(d, index).as_dict()["rows_per_workgroup"] == (256 if index == 0 else 128)
+    assert fa.flat_attn_tile_shape_get(d, index).as_dict()["rows_per_workgroup"] == wg_rows
     assert fa.flat_attn_tile_shape_default(B, H, N, d, mask) == index
     assert torch.equal(out.view(torch.int16), explicit.view(torch.int16))
 
