@@ -109,13 +109,10 @@ float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int ca
     return f.cost.start + (work > memory ? work : memory);
 }
 
-// The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1 times as long
-// (what the prediction is worth) or there is one tile, and so nothing to divide.  Up to 512 keys index 0 also keeps launches of
-// more than 512 blocks of 32 rows (forms gain 20 % at most there: 128 heads x 256, d = 64, 10.2 -> 8.0 us) and all of
-// d = 32 (16 x 512, 9.7 -> 4.9 us): a caller may hold flat_attn_fwd to flat_attn_fwd_tile 0 bit for bit, and so do the tests.
+// The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1
+// times as long (what the prediction is worth) or there is one tile, and so nothing to divide.
 int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
     if (prob.Nk <= 64) return -1;
-    if (index == 0 && prob.Nk <= 512 && (d == 32 || (long long)BH * ((prob.Nq + 31LL) / 32) > 512)) return -1;
     for (const Choice& c : kChoices) {
         if (c.d != d) continue;
         int best = -1;
