@@ -1,4 +1,4 @@
-"""Measured tile-shape sweep of the fused bf16 kernel:  python -m paper_2107_06419_amd.tile_sweep [--small] [--out FILE]
+"""Measured tile-shape sweep of the fused bf16 kernel:  python -m paper_2107_06419_amd.tile_sweep [--small | --forms] [--out FILE]
 
 The paper chooses tile sizes by exhaustive search over a cost model (section 6.1, map-space exploration)
 and names the trade-off of the row granularity (section 5.3).  This tool does the search by timing: every
@@ -7,6 +7,8 @@ flat_attn_fwd_tile, and the table of times is printed as Markdown.  Each shape's
 the default shape's (index 0) on the same input, so a row in the table is also a consistency check.
 With --small it times launches of few row blocks instead (1 to 128 heads of 128 to 4096 positions), the 256-row
 default shape against the 128-row shapes: the table the small-launch rule of flat_attn_fwd was read off.
+With --forms it times the base shapes and the key-group forms of launches of few rows, and says how far the index that
+flat_attn_fwd runs is behind the fastest: what the cost table of csrc/flat_plan.hip is worth on the kernels as they are.
 Needs a GPU; inputs are the seeded synthetic tensors of paper_2107_06419_amd.synth.
 """
 from __future__ import annotations
@@ -115,14 +117,95 @@ def small_launches(reps: int) -> str:
     return "\n".join(lines)
 
 
+FORM_POSITIONS = (65, 100, 128, 200, 256, 333, 512, 777, 1024, 2048, 3001, 4096, 8192)
+FORM_HEADS = (1, 4, 12, 16, 32, 64, 128, 256, 512, 1024)
+FORM_MAX_FLOPS = 1.5e11  # of a problem without a mask
+SMALL_LAUNCH_SHAPE = {32: 1, 64: 7, 96: 1, 128: 2}  # the 128-row shape of a head size
+
+
+def graph_us(fn, launches: int, replays: int = 5) -> float:
+    """Median microseconds per launch of a captured graph of `launches` launches: no host time between them."""
+    import statistics
+
+    import torch
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        fn()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(launches):
+                fn()
+        graph.replay()
+        ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(replays)]
+        for a, b in ev:
+            a.record()
+            graph.replay()
+            b.record()
+    torch.cuda.synchronize()
+    return statistics.median(a.elapsed_time(b) for a, b in ev) * 1e3 / launches
+
+
+def form_times():
+    """(d, mask, heads, positions, {index: us}) of the base shapes and key-group forms over the grid above."""
+    import torch
+
+    import paper_2107_06419_amd as fa
+    for d in (32, 64, 96, 128, 256):
+        shapes = [fa.flat_attn_tile_shape_get(d, i).as_dict() for i in range(fa.flat_attn_tile_shape_count(d))]
+        forms = [i for i, t in enumerate(shapes) if t["wavefronts"] * t["rows_per_wavefront"] > t["rows_per_workgroup"]]
+        indices = sorted({0, SMALL_LAUNCH_SHAPE.get(d, 0), *forms})
+        for mask in (0, 1):
+            for N in FORM_POSITIONS:
+                for heads in FORM_HEADS:
+                    if 4.0 * heads * N * N * d > FORM_MAX_FLOPS:
+                        continue
+                    gen = torch.Generator(device="cuda").manual_seed(N + heads)
+                    q, k, v = (torch.randn(1, heads, N, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+                    out = torch.empty_like(q)
+                    launches = 20 if heads * N * N < 1e9 else 5
+                    yield d, mask, heads, N, {i: graph_us(lambda: fa.flat_attn_fwd_tile(q, k, v, out, d ** -0.5, mask, i), launches) for i in indices}
+
+
+def form_choice() -> str:
+    """Table of those times with the index flat_attn_fwd runs, and per head size and mask how far it is behind the fastest."""
+    import math
+
+    import paper_2107_06419_amd as fa
+    lines, summary, group = [], [], None
+    behind: list = []
+
+    def close():
+        if behind:
+            summary.append(f"| {group[0]} | {'causal' if group[1] else 'none'} | {len(behind)} | {math.exp(sum(math.log(b) for b, _ in behind) / len(behind)):.3f} | "
+                           f"{math.exp(sum(math.log(o) for _, o in behind) / len(behind)):.3f} | {max(b for b, _ in behind):.2f} |")
+
+    for d, mask, heads, N, us in form_times():
+        if group != (d, mask):
+            close()
+            behind, group = [], (d, mask)
+            lines += ["", f"### d = {d}, {'causal' if mask else 'no mask'}", "",
+                      "| heads x positions | " + " | ".join(f"index {i}" for i in us) + " | runs | behind the fastest |", "|" + "---|" * (len(us) + 3)]
+        chosen, best = fa.flat_attn_tile_shape_default(1, heads, N, d, mask), min(us.values())
+        behind.append((us[chosen] / best, min(us[i] for i in (0, SMALL_LAUNCH_SHAPE.get(d, 0))) / best))
+        lines.append(f"| {heads} x {N} | " + " | ".join(f"{t:.1f}" for t in us.values()) + f" | {chosen} | {us[chosen] / best:.2f} |")
+        print(f"d={d} mask={mask} {lines[-1]}", file=sys.stderr, flush=True)
+    close()
+    head = ["Microseconds per launch (captured graphs, median of 5 replays) of the base shapes and the key-group forms, and the index that",
+            "flat_attn_fwd runs.  Summary: geometric mean of (what runs / the fastest) and of (the better base shape / the fastest).", "",
+            "| d | mask | problems | runs / fastest | better base shape / fastest | worst |", "|---|---|---|---|---|---|"]
+    return "\n".join(head + summary + lines)
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--out", default="", help="also write the Markdown table to this file")
     ap.add_argument("--reps", type=int, default=30)
     ap.add_argument("--small", action="store_true", help="time small launches (default shape against the 128-row shapes) instead")
+    ap.add_argument("--forms", action="store_true", help="time base shapes and key-group forms of launches of few rows instead")
     args = ap.parse_args()
-    if args.small:
-        text = small_launches(max(args.reps, 40))
+    if args.small or args.forms:
+        text = form_choice() if args.forms else small_launches(max(args.reps, 40))
         print(text)
         if args.out:
             with open(args.out, "w") as f:
