@@ -98,7 +98,8 @@ int flat_attn_fwd_cross(const void* Q, const void* K, const void* V, void* O,
  *     flat_attn_fwd_splitkv_splits returns the number actually used (or a negative flat_status).
  *   workspace: device, 16-byte aligned, at least flat_attn_fwd_splitkv_workspace_bytes() bytes (same B, H, Nq,
  *     Nk, d, n_splits; 0 means the arguments are invalid), overwritten; it must not overlap any other buffer
- *     (FLAT_ERR_ALIAS).  FLAT_ERR_WORKSPACE if too small.
+ *     (FLAT_ERR_ALIAS).  FLAT_ERR_WORKSPACE if the partial results do not fit.  With n_splits <= 0 the size never falls as
+ *     Nk grows: a workspace for the longest cache serves every shorter one.
  * The result differs from flat_attn_fwd_cross in the last bits (different summation order), and is itself
  * bitwise reproducible for a given n_splits.  Two launches (partial pass, merge) are enqueued on `stream`; one where
  * the number of splits is 1, and then the result is that of flat_attn_fwd_cross.

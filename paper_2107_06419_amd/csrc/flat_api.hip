@@ -119,11 +119,11 @@ int flat_attn_fwd_splitkv(const void* Q, const void* K, const void* V, void* O, 
     if (!aligned16(workspace)) return FLAT_ERR_ALIGN;
     flat::SplitPlan plan;
     if (!flat::split_plan(B * H, Nq, Nk, d, n_splits, &plan)) return FLAT_ERR_SHAPE;
-    if (workspace_bytes < plan.workspace_bytes) return FLAT_ERR_WORKSPACE;
-    if (overlaps(workspace, plan.workspace_bytes, Q, qbytes) || overlaps(workspace, plan.workspace_bytes, K, kbytes) ||
-        overlaps(workspace, plan.workspace_bytes, V, kbytes) || overlaps(workspace, plan.workspace_bytes, O, qbytes))
+    if (workspace_bytes < plan.used_bytes) return FLAT_ERR_WORKSPACE;
+    if (overlaps(workspace, plan.used_bytes, Q, qbytes) || overlaps(workspace, plan.used_bytes, K, kbytes) ||
+        overlaps(workspace, plan.used_bytes, V, kbytes) || overlaps(workspace, plan.used_bytes, O, qbytes))
         return FLAT_ERR_ALIAS;
-    if (kv_lens && overlaps(workspace, plan.workspace_bytes, kv_lens, (size_t)B * sizeof(int))) return FLAT_ERR_ALIAS;
+    if (kv_lens && overlaps(workspace, plan.used_bytes, kv_lens, (size_t)B * sizeof(int))) return FLAT_ERR_ALIAS;
     flat::Bf16Problem prob{Nq, Nk, mask_kind == FLAT_MASK_CAUSAL ? Nk - Nq : 0, H, kv_lens, nullptr, nullptr, 0};
     prob.n_splits = plan.n_splits;
     prob.tiles_per_split = plan.tiles_per_split;
@@ -140,12 +140,12 @@ int flat_attn_fwd_splitkv_static(const void* Q, const void* K, const void* V, vo
     if (rc != FLAT_OK) return rc;
     flat::SplitPlan plan;
     if (!flat::split_plan(B * H, Nq, Nk, d, n_splits, &plan)) return FLAT_ERR_SHAPE;
-    if (plan.workspace_bytes > flat::kSplitStaticScratchBytes) {
+    if (plan.used_bytes > flat::kSplitStaticScratchBytes) {
         if (n_splits > 0) return FLAT_ERR_WORKSPACE;  // the caller's choice does not fit the built-in scratch buffer
         // the library's choice: as many splits as the buffer holds
-        const size_t per_split = plan.workspace_bytes / (size_t)plan.n_splits;
+        const size_t per_split = plan.used_bytes / (size_t)plan.n_splits;
         const size_t fit = flat::kSplitStaticScratchBytes / per_split;
-        if (fit < 1 || !flat::split_plan(B * H, Nq, Nk, d, (int)fit, &plan) || plan.workspace_bytes > flat::kSplitStaticScratchBytes)
+        if (fit < 1 || !flat::split_plan(B * H, Nq, Nk, d, (int)fit, &plan) || plan.used_bytes > flat::kSplitStaticScratchBytes)
             return FLAT_ERR_WORKSPACE;
     }
     flat::Bf16Problem prob{Nq, Nk, mask_kind == FLAT_MASK_CAUSAL ? Nk - Nq : 0, H, kv_lens, nullptr, nullptr, 0};

@@ -54,13 +54,14 @@ struct SplitPlan {
     int n_row_blocks;      // per head
     int n_splits;          // after clamping to [1, units of 64 keys]
     int tiles_per_split;
-    size_t workspace_bytes;
+    size_t used_bytes;       // of the partial results
+    size_t workspace_bytes;  // what a caller is asked for: at least that, and with the library's choice no less for more keys
 };
 bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* out);  // n_splits_wanted <= 0: chosen here
 hipError_t launch_fwd_bf16_split(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob, int d,
                                  int rows_per_block, float scale, int causal, hipStream_t stream);
 // The same launch with the partial results in a scratch array inside the library's device image (prob.split_ws is
-// ignored): nothing is allocated.  The plan's workspace_bytes must not exceed kSplitStaticScratchBytes.
+// ignored): nothing is allocated.  The plan's used_bytes must not exceed kSplitStaticScratchBytes.
 constexpr size_t kSplitStaticScratchBytes = (size_t)64 << 20;
 hipError_t launch_fwd_bf16_split_static(const void* Q, const void* K, const void* V, void* O, int BH, const Bf16Problem& prob,
                                         int d, int rows_per_block, float scale, int causal, hipStream_t stream);

@@ -206,7 +206,7 @@ bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* o
     // splits are counted in units of 64 keys (32 at d = 256), whatever the tile of the shape
     const int unit = d == 256 ? 32 : 64, tiles_per_unit = unit / g.keys;
     const int n_units = (int)(((long long)Nk + unit - 1) / unit);
-    long long s = n_splits_wanted;
+    long long s = n_splits_wanted, reserved = 0;
     if (s <= 0) {
         // One workgroup per wanted slot of the chip and no more: a workgroup beyond them only adds partial results to write
         // and merge (and a second round), one split fewer leaves some slots empty.  Every split stays long enough to pay for itself.
@@ -216,6 +216,7 @@ bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* o
         if (s < 2) s = 2;  // more heads than slots: still twice as many workgroups, as the last round is half empty otherwise
         if (s > longest) s = longest;
         if (s > kMaxSplits) s = kMaxSplits;
+        reserved = s < n_units ? s : n_units;
         // No split where one launch does it in less (many heads over short keys, or enough rows to fill the chip: 64 heads x 200
         // rows over 2048 keys, d = 64, 37.7 -> 17.1 us, 256 x 1 over 512 keys 11.7 -> 8.2) by a clear margin, as key counts of
         // different length favour the many short workgroups of a split launch.
@@ -232,7 +233,10 @@ bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* o
     const unsigned __int128 bytes = (unsigned __int128)BH * p.n_row_blocks * p.n_splits * ws_rows * (g.dp + 2) * sizeof(float);
     if (bytes >= ((unsigned __int128)1 << 62) || (long long)BH * p.n_row_blocks * p.n_splits > 0x7fffffffLL) return false;
     if ((long long)BH * Nq > 0x7fffffffLL) return false;  // the merge launches one workgroup per (head, row)
-    p.workspace_bytes = (size_t)bytes;
+    p.used_bytes = (size_t)bytes;
+    // The number of splits falls and rises with the keys, by rounding and by the choice of one launch; what the caller is asked to
+    // hold never falls, so that a workspace for the longest cache serves every shorter one.
+    p.workspace_bytes = reserved > p.n_splits ? p.used_bytes / p.n_splits * reserved : p.used_bytes;
     *out = p;
     return true;
 }

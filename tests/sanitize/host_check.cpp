@@ -124,6 +124,21 @@ static void check_validation() {
     EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 1, lens_storage, 4, big_ws, need, nullptr) == FLAT_OK);
     EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 0, nullptr, 0, big_ws, need, nullptr) == FLAT_OK);
 
+    // a workspace sized for the longest cache is accepted for every shorter one (library's choice of splits)
+    {
+        void *Qc = fake(1ull << 44), *Kc = fake(2ull << 44), *Vc = fake(3ull << 44), *Oc = fake(4ull << 44), *wsc = fake(5ull << 44);
+        int refused = 0;
+        for (int d : {32, 64, 96, 128, 256})
+            for (int heads : {1, 3, 8, 16, 64, 300, 2000})
+                for (int Nq : {1, 16, 40, 200})
+                    for (int longest : {700, 5000, 20000, 40000}) {
+                        const size_t held = flat_attn_fwd_splitkv_workspace_bytes(1, heads, Nq, longest, d, 0);
+                        for (int Nk = longest; Nk >= 200; Nk -= 61)
+                            refused += flat_attn_fwd_splitkv(Qc, Kc, Vc, Oc, 1, heads, Nq, Nk, d, 1.f, 0, nullptr, 0, wsc, held, nullptr) != FLAT_OK;
+                    }
+        EXPECT(refused == 0);
+    }
+
     // the allocation-free form: the plan must fit the built-in buffer
     EXPECT(flat_attn_fwd_splitkv_static(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 1, lens_storage, 4, nullptr) == FLAT_OK && g_static_splits == 4);
     EXPECT(flat_attn_fwd_splitkv_static(Q, fake(1ull << 40), fake(2ull << 40), O, 1, 16, 256, 65536, 64, 1.f, 1, nullptr, 0, nullptr) == FLAT_OK);
