@@ -227,10 +227,7 @@ bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* o
     const int units_per_split = (int)((n_units + s - 1) / s);
     p.n_splits = (n_units + units_per_split - 1) / units_per_split;  // no split is left without a unit
     p.tiles_per_split = units_per_split * tiles_per_unit;
-    // A caller's number of splits asks for at least 128 rows each at d >= 96, more than the shapes of few rows fill: a workspace
-    // that holds n splits of theirs then also holds the library's choice of more and smaller ones.
-    const int ws_rows = n_splits_wanted > 0 && d >= 96 && g.rows < 128 ? 128 : g.rows;
-    const unsigned __int128 bytes = (unsigned __int128)BH * p.n_row_blocks * p.n_splits * ws_rows * (g.dp + 2) * sizeof(float);
+    const unsigned __int128 bytes = (unsigned __int128)BH * p.n_row_blocks * p.n_splits * g.rows * (g.dp + 2) * sizeof(float);
     if (bytes >= ((unsigned __int128)1 << 62) || (long long)BH * p.n_row_blocks * p.n_splits > 0x7fffffffLL) return false;
     if ((long long)BH * Nq > 0x7fffffffLL) return false;  // the merge launches one workgroup per (head, row)
     p.used_bytes = (size_t)bytes;

@@ -122,7 +122,12 @@ static void check_validation() {
     EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 1, lens_storage, 4, O, need, nullptr) == FLAT_ERR_ALIAS);
     EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 17, 16, 96, 1.f, 1, lens_storage, 4, big_ws, need, nullptr) == FLAT_ERR_UNSUPPORTED);
     EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 1, lens_storage, 4, big_ws, need, nullptr) == FLAT_OK);
-    EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 0, nullptr, 0, big_ws, need, nullptr) == FLAT_OK);
+    EXPECT(flat_attn_fwd_splitkv(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 0, nullptr, 0, big_ws,
+                                 flat_attn_fwd_splitkv_workspace_bytes(2, 2, 16, 900, 96, 0), nullptr) == FLAT_OK);
+    // few rows: parts of 32 rows (64 at d = 256), whoever chooses their number
+    EXPECT(need == (size_t)4 * 4 * 32 * 130 * 4);
+    EXPECT(flat_attn_fwd_splitkv_workspace_bytes(1, 1, 1, 65536, 128, 8) == (size_t)8 * 32 * 130 * 4);
+    EXPECT(flat_attn_fwd_splitkv_workspace_bytes(1, 1, 1, 65536, 256, 8) == (size_t)8 * 64 * 258 * 4);
 
     // a workspace sized for the longest cache is accepted for every shorter one (library's choice of splits)
     {
@@ -145,6 +150,13 @@ static void check_validation() {
     EXPECT(g_static_splits >= 1 && (size_t)16 * g_static_splits * 256 * 66 * 4 <= FLAT_SPLITKV_STATIC_BYTES);
     EXPECT(flat_attn_fwd_splitkv_static(Q, fake(1ull << 40), fake(2ull << 40), O, 1, 16, 256, 65536, 64, 1.f, 1, nullptr, 64, nullptr) == FLAT_ERR_WORKSPACE);
     EXPECT(flat_attn_fwd_splitkv_static(Q, fake(1ull << 40), fake(2ull << 40), fake(3ull << 40), 64, 64, 256, 4096, 256, 1.f, 0, nullptr, 0, nullptr) == FLAT_ERR_WORKSPACE);
+    // many heads: the library's choice is cut to the splits that fit, as long as one does
+    for (int d : {96, 128, 256})
+        for (int heads : {500, 900, 2000, 4000, 8000}) {
+            const size_t one = (size_t)heads * (d == 256 ? 64 * 258 : 32 * 130) * 4;
+            EXPECT(flat_attn_fwd_splitkv_static(fake(1ull << 44), fake(2ull << 44), fake(3ull << 44), fake(4ull << 44), 1, heads, 1, 4096, d, 1.f, 0, nullptr,
+                                                0, nullptr) == (one <= FLAT_SPLITKV_STATIC_BYTES ? FLAT_OK : FLAT_ERR_WORKSPACE));
+        }
     EXPECT(flat_attn_fwd_splitkv_static(nullptr, K, V, O, 2, 2, 16, 900, 96, 1.f, 1, lens_storage, 4, nullptr) == FLAT_ERR_NULL);
 
     EXPECT(flat_attn_fwd_f32((const float*)Q, (const float*)K, (const float*)V, (float*)O, 1, 1, 8, 32, 1.f, 0, nullptr) == FLAT_ERR_UNSUPPORTED);
