@@ -105,6 +105,19 @@ float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int ca
         if (seen > tiles) seen = tiles;
         const float spread = (float)wgs / 256.0f * (seen * f.cost.busy + fixed_busy) + f.cost.skew * alone;
         work = alone > spread ? alone : spread;
+        // No less than whole rounds of the shortest workgroup: the rows of a short segment behind many keys all see nearly the
+        // same number of them, and then a workgroup too many costs a round (86 heads, 142 rows over 5726 keys, d = 256: 351 us in
+        // 258 workgroups of 64 rows, 243 in 172 of 128).
+        float least = ((float)prob.causal_offset + (float)f.rows) / (float)f.keys_per_tile;
+        if (least > tiles) least = tiles;
+        const float rounds = (float)((per_cu + f.per_cu - 1) / f.per_cu) * (least * f.cost.step + f.cost.fixed);
+        const float full = (float)per_cu * (least * f.cost.busy + fixed_busy), even = rounds > full ? rounds : full;
+        if (even > work) work = even;
+        // Causal launches deal a head's row blocks over the XCDs, so the first few of them fetch its keys each for itself, at 6.5 TB/s
+        // (162 heads, 194 rows over 5060 keys, d = 64: 142 us in 64-row workgroups, 90 in 128-row ones).
+        const long long blocks = wgs / BH;
+        const float fetched = (float)BH * (float)(blocks < 8 ? blocks : 8) * seen * (float)f.keys_per_tile * (float)d * 4.0f / 6.5e6f;
+        if (blocks > 1 && fetched > memory) memory = fetched;
     }
     return f.cost.start + (work > memory ? work : memory);
 }
@@ -112,7 +125,10 @@ float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int ca
 // The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1
 // times as long (what the prediction is worth) or there is one tile, and so nothing to divide.
 int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
-    if (prob.Nk <= 64) return -1;
+    // At d = 256 three tiles of the base shape are no more work than two of the form's: 8 x 65 without a mask 10.6 us, in the form
+    // 12.0, 7 causal heads, 55 rows over 80 keys, 10.8 and 12.1.  In causal self-attention the form wins there too (2 x 75: 10.5 and 11.4).
+    const bool triangle = causal && prob.causal_offset == 0;
+    if (prob.Nk <= (d == 256 && !triangle ? 96 : 64)) return -1;
     for (const Choice& c : kChoices) {
         if (c.d != d) continue;
         int best = -1;

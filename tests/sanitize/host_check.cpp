@@ -98,6 +98,16 @@ static void check_validation() {
     EXPECT(flat_attn_fwd_cross(Q, K, V, O, 2, 2, 16, 900, 96, 1.f, 1, lens_storage, nullptr) == FLAT_OK);
     EXPECT(flat_attn_fwd_cross(Q, K, V, O, 1, 1, 2147483647, 2147483647, 256, 1.f, 0, nullptr, nullptr) == FLAT_ERR_SHAPE);
 
+    // the choice of a tile shape is real host code too: a short causal segment behind many keys keeps to whole rounds of workgroups and
+    // to shapes that fetch its keys few times; small launches take key-group forms
+    auto chosen = [](int BH, int Nq, int Nk, int d, int causal) {
+        return flat::chosen_tile_shape(BH, flat::Bf16Problem{Nq, Nk, causal ? Nk - Nq : 0, 1, nullptr, nullptr, nullptr, 0}, d, causal);
+    };
+    EXPECT(chosen(86, 142, 5726, 256, 1) == 0 && chosen(93, 172, 500, 256, 1) == 0);
+    EXPECT(chosen(162, 194, 5060, 64, 1) < flat::first_key_group_form(64));
+    EXPECT(chosen(8, 65, 65, 256, 0) == 0 && chosen(8, 97, 97, 256, 0) == 1);
+    EXPECT(chosen(12, 512, 512, 64, 0) == 12 && chosen(2, 8192, 8192, 64, 1) >= 12 && chosen(16, 1, 700, 64, 1) == 12);
+
     // split keys: the plan is real host code (csrc/flat_plan.hip), the launch is a stub
     EXPECT(flat_attn_fwd_splitkv_splits(1, 16, 256, 65536, 64, 0) == 32);      // 512 slots for 16 row blocks
     EXPECT(flat_attn_fwd_splitkv_splits(1, 16, 256, 65536, 64, 7) == 7);
