@@ -234,9 +234,14 @@ bool split_plan(int BH, int Nq, int Nk, int d, int n_splits_wanted, SplitPlan* o
         if (s > kMaxSplits) s = kMaxSplits;
         reserved = s < n_units ? s : n_units;
         // No split where one launch does it in less (many heads over short keys, or enough rows to fill the chip: 64 heads x 200
-        // rows over 2048 keys, d = 64, 37.7 -> 17.1 us, 256 x 1 over 512 keys 11.7 -> 8.2) by a clear margin, as key counts of
-        // different length favour the many short workgroups of a split launch.
-        if (s > 1 && unsplit_us(BH, Nq, Nk, d) * (Nq <= 64 ? 1.12f : 1.0f) <= split_us(g, blocks, BH, Nq, Nk, d, s, n_units)) s = 1;
+        // rows over 2048 keys, d = 64, 37.7 -> 17.1 us, 256 x 1 over 512 keys 11.7 -> 8.2) by a clear margin: key counts of different
+        // length favour the many short workgroups of a split launch, and over many keys that no cache holds the few long
+        // workgroups of one launch take longer than predicted (12 heads x 250 rows over 5597 keys, d = 64, in one launch 42.8 us,
+        // 27.4 predicted; 11 splits 25.5, 28.3 predicted).  Margins by the keys, on 1817 random problems: 31 calls are more than
+        // 3 % slower than with the rule before key-group forms (every slot, at least 8 tiles per split), 58 with margins of 1.12
+        // up to 64 rows and none above.
+        const float margin = Nk < 2048 ? 1.12f : Nk < 4096 ? 1.25f : 1.6f;
+        if (s > 1 && unsplit_us(BH, Nq, Nk, d) * margin <= split_us(g, blocks, BH, Nq, Nk, d, s, n_units)) s = 1;
     }
     if (s > n_units) s = n_units;
     if (s < 1) s = 1;

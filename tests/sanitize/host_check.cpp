@@ -116,6 +116,9 @@ static void check_validation() {
     EXPECT(flat_attn_fwd_splitkv_splits(1, 16, 1, 65536, 32, 0) == 94);      // d = 32: 6 per compute unit, 96 wanted,
     EXPECT(flat_attn_fwd_splitkv_splits(1, 16, 1, 65536, 64, 96) == 94);     // 11 tiles each, and 94 such splits cover the 1024 tiles
     EXPECT(flat_attn_fwd_splitkv_workspace_bytes(1, 16, 1, 65536, 64, 96) == (size_t)16 * 94 * 32 * 66 * 4);
+    // few workgroups over many keys are split, many over few keys are not
+    EXPECT(flat_attn_fwd_splitkv_splits(1, 12, 250, 5597, 64, 0) == 11 && flat_attn_fwd_splitkv_splits(1, 111, 2, 11398, 64, 0) > 1);
+    EXPECT(flat_attn_fwd_splitkv_splits(1, 256, 1, 512, 64, 0) == 1 && flat_attn_fwd_splitkv_splits(1, 64, 200, 2000, 64, 0) == 1);
     EXPECT(flat_attn_fwd_splitkv_splits(1, 1, 1, 100, 80, 0) == FLAT_ERR_UNSUPPORTED);
     EXPECT(flat_attn_fwd_splitkv_splits(0, 1, 1, 100, 64, 0) == FLAT_ERR_SHAPE);
     EXPECT(flat_attn_fwd_splitkv_splits(2147483647, 2147483647, 2147483647, 2147483647, 256, 0) == FLAT_ERR_SHAPE);
