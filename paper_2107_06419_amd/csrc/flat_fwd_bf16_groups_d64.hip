@@ -1,5 +1,5 @@
 // Key-group forms of the fused bf16 kernel, d = 32 and 64: 32 or 64 rows over four groups, 64 or 128 rows over two
-// (chosen by predicted time in flat_tiles.hip).
+// (chosen by predicted time in flat_plan.hip).
 #include "flat_fwd_bf16_kernel.hpp"
 
 namespace flat {

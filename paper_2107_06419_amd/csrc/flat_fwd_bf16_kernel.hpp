@@ -371,8 +371,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // ---- prologue.  The workgroup's Q rows arrive through LDS like the tiles: whole rows, 1024 contiguous bytes per load, where
     // fragments straight from memory touch 32 bytes of each of 32 rows per load.  They lie at the end of the ring, and what
     // they leave free in front is filled with the first tiles at once; the rest of the ring follows when the fragments are in
-    // registers.  So a workgroup starts after one round trip of Q and the first tile.  768 heads x 512, d = 64: 67 -> 66 us, d = 128
-    // 154 -> 148, d = 96 125 -> 117; 8 x 1001, d = 128, 13.4 -> 12.3; 4 x 4096, d = 64, 26.6 -> 24.9.  At d = 256 the 64 KiB of Q take
+    // registers.  So a workgroup starts after one round trip of Q and the first tile.  768 heads x 512, d = 64: 62 -> 61 us, d = 128
+    // 147 -> 139, d = 96 112 -> 109; 8 x 1001, d = 128, 12.6 -> 11.9; 4 x 4096, d = 64, 25.7 -> 24.5.  At d = 256 the 64 KiB of Q take
     // longer into LDS and out again (2 x 8 causal heads of 3001: 130 us straight to registers, 132 through LDS), so they go
     // straight to registers, with the whole ring filled behind them.
     constexpr bool kQThroughLds = D != 256;
@@ -842,8 +842,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     }
     // ---- epilogue: O = O_acc / l, rounded to bf16.  A lane holds 4 consecutive columns per register quad, its other half the next
     // 4; two quads are swapped across the halves so that every lane stores 8 consecutive columns.  Short sequences are bound by
-    // memory and by their start and end: half as many stores of twice the width, 768 heads x 512, d = 64: 72.7 -> 66 us; 1024 x 128
-    // 16.6 -> 15.0; d = 128, 768 x 512: 162 -> 151.
+    // memory and by their start and end: half as many stores of twice the width, 768 heads x 512, d = 64: 66 -> 62 us; 1024 x 128
+    // 16.3 -> 15.0; d = 128, 768 x 512: 158 -> 147.
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const float total = halves_sum(lsum[qb]);

@@ -37,8 +37,8 @@ namespace flat {
 // Measured: 16 heads of 8192 positions at d = 128 without a mask 128 TFLOP/s, 32 heads of 4096 at d = 64 130 (a large fp32
 // matrix product reaches 154 on this card; this loop with loads, operand reads and exponentials taken out 145).  Before, with
 // 128-row workgroups around one shared LDS tile and operands read a float at a time: 110 and 113; and short of 1024 such
-// workgroups, where the keys were split over unpipelined wavefronts: 16 causal heads of 2049 positions at d = 128 351 -> 162 us,
-// 12 heads of 512 at d = 64 21 -> 12 us.
+// workgroups, where the keys were split over unpipelined wavefronts: 16 causal heads of 2049 positions at d = 128 344 -> 163 us,
+// 12 heads of 512 at d = 64 21 -> 13 us.
 template <int D>
 struct F32Cfg {
     static constexpr int ROWB = D * 4;             // bytes of a row

@@ -77,7 +77,7 @@ constexpr int bf16_lds_bytes(int d, int row_blocks, int wavefronts, int stages, 
     return ring > with_q ? (ring > merge ? ring : merge) : (with_q > merge ? with_q : merge);
 }
 
-// Tile shapes of the fused bf16 kernel (flat_tiles.hip).  Index 0 is the default of launch_fwd_bf16.
+// Tile shapes of the fused bf16 kernel (flat_tiles.hip); flat_plan.hip chooses the index launch_fwd_bf16 runs.
 struct TileShape {
     int d;                   // head dimension the shape is built for
     int rows_per_workgroup;  // query rows per workgroup

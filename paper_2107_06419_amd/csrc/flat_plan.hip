@@ -40,31 +40,34 @@ int base_tile_shape(int BH, int Nq, int d, int causal) {
 
 }  // namespace
 
-// ---- Key-group forms.  A launch of few query rows leaves most of the chip idle on the shapes above, whatever their rows per
+// ---- Key-group forms.  A launch of few query rows leaves most of the chip idle on the base shapes, whatever their rows per
 // workgroup, because each workgroup walks all keys alone.  In these forms the wavefronts of a workgroup share the keys of
 // the same 32, 64 or 128 rows (kernel parameter KG) and merge through LDS at the end; nothing else changes.  They re-read K
-// and V from L2 more often per flop, so large launches keep the shapes above.  Each holds a step of K and V per wavefront in
-// a ring of two stages (K runs one tile ahead of V); deeper rings measured 3-25 % slower, as fewer workgroups fit.
-// Measured, us, best of the shapes above -> form: 12 heads x 512, d = 64, 9.8 -> 6.5; 4 x 4096, d = 64, 47.6 -> 26.4; 2 causal
+// and V from L2 more often per flop, so large launches keep the base shapes.  Each holds a step of K and V per wavefront in
+// a ring of two stages (K runs one tile ahead of V); deeper rings measured 3-25 % slower where they cost a workgroup per
+// compute unit, so only d = 32, whose tiles are small, has four.
+// Measured, us, best base shape -> form: 12 heads x 512, d = 64, 9.8 -> 6.5; 4 x 4096, d = 64, 47.6 -> 26.4; 2 causal
 // x 8192, d = 64, 86.7 -> 39.2; 8 x 1024, d = 128, 22.2 -> 13.3; 4 x 4096, d = 256, 175 -> 109; 64 x 16 rows over 4096 keys,
 // d = 64, 46 -> 24.
 //
-// The choice is by predicted time.  A form (and each shape above) has a measured cost: us to launch, start and drain (`start`),
+// The choice is by predicted time.  A form (and each base shape) has five measured costs: us to launch, start and drain (`start`),
 // us per tile and per workgroup when a workgroup runs alone (`step`, `fixed`), us per tile when the compute unit holds as
-// many workgroups as fit (`busy`), and the share of its longest workgroup that a causal launch ends late (`skew`).  Fitted
-// to 1750 timings: 1 to 2048 heads, 16 to 300 query rows over 300 to 4096 keys and 64 to 16384 positions, both masks, five
-// head sizes.  The choice is within 1-3 % of the fastest on average, where the shapes above alone are 12-28 % behind it, and
-// on none of the timings more than 10 % behind the shape it replaces.
+// many workgroups as fit (`busy`), and the share of its longest workgroup that a causal launch ends late (`skew`).  They were
+// fitted by hand-run least squares to 1750 timings (1 to 2048 heads, 16 to 300 query rows over 300 to 4096 keys and 64 to 16384
+// positions, both masks, five head sizes, inputs that stay in the caches), before the epilogue and the start of a workgroup
+// took their present form.  What the choice is worth on the kernels as they are, python -m paper_2107_06419_amd.tile_sweep --forms
+// says: over 1050 self-attention problems it is 0-2 % behind the fastest on average, 32 % at worst, where the better base
+// shape is 13-22 % behind on average, and no form that runs is more than 8 % slower than the base shape it replaces.
 namespace {
 
 struct Cost {
     float start, step, fixed, busy, skew;
 };
 struct Form {
-    int rows, keys_per_tile, per_cu;  // query rows per workgroup, keys per tile, workgroups that fit a compute unit
+    int rows, keys_per_tile, per_cu;  // query rows per workgroup, keys per tile, workgroups per compute unit the costs were fitted with
     Cost cost;
 };
-// Per head size: the shapes launch_fwd_bf16 runs (index 0, small_launch_shape), then the key-group forms.
+// Per head size: the base shapes (index 0, small_launch_shape), then the key-group forms in the order of the tile table.
 struct Choice {
     int d, n_forms;
     Form base[2];
@@ -189,6 +192,8 @@ bool geometry(int d, int Nq, Geometry* g) {
 }
 // Predicted time of the launch without splits, and of partial pass and merge: the longer of the chain of one workgroup, the
 // work of a compute unit and one read of K and V, then the merge (4.3 us and 1.2 ns a row) and the partial results' round trip.
+// The former is that of the fastest shape or form, without a mask, which the plan does not know; the launch may take another
+// one.  (Predicting the one that is launched moved 125 of 28900 plans; of 96 timed, 62 got slower, by up to 15 %.)
 float unsplit_us(int BH, int Nq, int Nk, int d) {
     const Bf16Problem prob{Nq, Nk, 0, 1, nullptr, nullptr, nullptr, 0};
     float best = 1e30f;

@@ -1,6 +1,6 @@
-// Table of the tile shapes the fused bf16 kernel is built for, and the dispatch by index.  Index 0 of each head
-// dimension is the shape large launches use, flat_plan.hip chooses; all are here so that the choice can be re-measured (the
-// paper's map-space exploration, section 6.1, done by timing instead of a cost model; the trade-off being
+// Table of the tile shapes the fused bf16 kernel is built for, and the dispatch by index.  Index 0 of each head dimension is
+// the shape large launches use; flat_plan.hip chooses the index of a launch, and the others are here so that the choice can
+// be re-measured (the paper's map-space exploration, section 6.1, done by timing instead of a cost model; the trade-off being
 // explored is the row granularity of section 5.3: fewer rows per workgroup re-fetch K and V more often and
 // fill the matrix units less, more rows need more on-chip state).
 #include "flat_launch.hpp"

@@ -11,7 +11,8 @@ import sys
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--workload", default="cfg2_long_16k")
-    ap.add_argument("--shape", default="", help="B,H,N,d,mask of a bf16 problem to run instead of a named workload")
+    ap.add_argument("--shape", default="", help="B,H,N,d,mask of a problem to run instead of a named workload")
+    ap.add_argument("--f32", action="store_true", help="with --shape: run it through flat_attn_fwd_f32 instead of bf16")
     ap.add_argument("--reps", type=int, default=3)
     ap.add_argument("--unfused", action="store_true")
     ap.add_argument("--copy-mib", type=int, default=1024, help="size of the calibration copy (MiB read + MiB written)")
@@ -69,18 +70,20 @@ def main() -> int:
         return 0
     if args.shape:
         B, H, N, d, mask = (int(t) for t in args.shape.split(","))
-        w = synth.custom("shape_" + args.shape.replace(",", "_"), B, H, N, d, "bf16", mask, seed=1)
+        w = synth.custom("shape_" + args.shape.replace(",", "_"), B, H, N, d, "f32" if args.f32 else "bf16", mask, seed=1)
     else:
         w = synth.WORKLOADS[args.workload]
     q, k, v = synth.make_qkv(w)
 
     def dev(x):
+        if w.dtype == "f32":
+            return torch.from_numpy(np.ascontiguousarray(x)).cuda()
         return torch.from_numpy(synth.f32_to_bf16_bits(x).reshape(x.shape).view(np.int16)).cuda().view(torch.bfloat16)
 
     dq, dk, dv = dev(q), dev(k), dev(v)
     out = torch.empty_like(dq)
     for _ in range(args.reps):
-        fa.flat_attn_fwd(dq, dk, dv, out, w.scale, w.mask)
+        (fa.flat_attn_fwd_f32 if w.dtype == "f32" else fa.flat_attn_fwd)(dq, dk, dv, out, w.scale, w.mask)
     torch.cuda.synchronize()
     if args.unfused:
         ws = torch.empty(fa.flat_attn_unfused_workspace_bytes(w.B, w.H, w.N, w.d) // 4, dtype=torch.float32, device="cuda")
