@@ -456,8 +456,8 @@ def test_blocksparse_lists_out_of_range_are_clamped_not_followed():
 
 @pytest.mark.parametrize("mask", [0, 1])
 def test_f32_large_problem_sampled_rows(mask):
-    """fp32 path on a problem big enough for its 128-rows-per-workgroup form (1024 row blocks); the small shapes
-    above run the form that splits the keys over the wavefronts of a workgroup."""
+    """fp32 path on a problem of many whole rounds of workgroups, over which the keys need not be divided; in the small shapes
+    above the wavefronts of a workgroup share them."""
     import torch
     w = synth.custom("f32_large", 4, 8, 4096 + 40, 64, "f32", mask, seed=123 + mask)
     q, k, v = synth.make_qkv(w)

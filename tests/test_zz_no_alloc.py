@@ -85,3 +85,17 @@ def test_static_scratch_form_replays_from_a_hip_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), eager.view(torch.int16)), f"replay {rep}"
+
+
+@pytest.mark.parametrize("heads,d,n_splits", [(2000, 96, 0), (1800, 96, 2), (2000, 128, 0), (1800, 128, 2), (900, 256, 0), (500, 256, 2)])
+def test_static_scratch_form_takes_many_heads_of_few_rows(heads, d, n_splits):
+    """Parts are sized by the rows their workgroups have: two of 1800 heads fit the built-in buffer, and of 2000 one does, to which
+    the library's choice is cut."""
+    import torch
+    q, k, v = (rounded((1, heads, n, d), 40 + d, t) for t, n in ((0, 1), (1, 200), (2, 200)))
+    dq, dk, dv = (to_device(x, "bf16") for x in (q, k, v))
+    out, scale = torch.full_like(dq, float("nan")), float(np.float32(d ** -0.5))
+    print(f"case no-alloc many heads={heads} d={d} n_splits={n_splits}", flush=True)
+    fa.flat_attn_fwd_splitkv_static(dq, dk, dv, out, scale, 0, None, n_splits)
+    torch.cuda.synchronize()
+    check_close(to_host_f64(out), oracle.attention_cross(q, k, v, scale, 0), "bf16", "no-alloc many heads")
