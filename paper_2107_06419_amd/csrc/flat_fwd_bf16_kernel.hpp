@@ -32,6 +32,7 @@
 
 namespace flat {
 
+constexpr int kLgkm0 = (63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8);  // s_waitcnt: lgkmcnt(0), the other counters left alone
 constexpr float kSumJump = 16384.0f;  // per lane and 32-key block: 16 probabilities
 
 // Checking build (-DFLAT_SYNC_EVERY_PHASE): nothing is left in flight across a phase of the ring.  Every
@@ -68,6 +69,10 @@ struct Bf16Cfg {
     static constexpr int KBYTES = BC * ROWB;
     static constexpr int VBYTES = BC * ROWB;
     static constexpr int STAGE = KBYTES + VBYTES;
+    // Where the tiles of a ring stage lie: K beside V, or (d = 256) the K tiles of all stages before the V tiles: each lot is then within the
+    // 64 KiB that the offset field of an LDS read reaches, and no address is computed in the loop.
+    static constexpr bool SPLIT_RING = DP == 256;
+    static constexpr int K_STEP = SPLIT_RING ? KBYTES : STAGE, V_AT = SPLIT_RING ? STAGES * KBYTES : KBYTES;
     static constexpr int ROWS_PER_LOAD = 1024 / ROWB; // rows covered by one wave-wide 16-byte-per-lane load
     static constexpr int LOADS = BC / ROWS_PER_LOAD / NW; // such loads per wavefront per tensor per tile
     static_assert(LOADS >= 1 && LOADS * ROWS_PER_LOAD * NW == BC, "the wavefronts must share a tile's rows evenly");
@@ -225,7 +230,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         ld_chunk_off[i] = (chunk < C::GCHUNKS ? chunk : chunk - (C::CHUNKS - C::GCHUNKS)) * 16;
     }
     auto issue_tile_loads = [&](int j, int stage, bool k_tile = true, bool v_tile = true) __attribute__((always_inline)) {  // j-th visited tile, stage = j % STAGES
-        const uint32_t stage_base = smem_base + (uint32_t)stage * C::STAGE;
+        const uint32_t stage_base = smem_base + (uint32_t)stage * C::K_STEP;
         const int tile = tile_of(j);
 #pragma unroll
         for (int i = 0; i < C::LOADS; ++i) {
@@ -233,7 +238,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
             const uint32_t voff = (uint32_t)key * C::GROWB + ld_chunk_off[i];
             const uint32_t lds_k = __builtin_amdgcn_readfirstlane(stage_base + (NW * i + wave) * 1024);
             if (k_tile) dma16(Kh, voff, lds_k);
-            if (v_tile) dma16(Vh, voff, lds_k + C::KBYTES);
+            if (v_tile) dma16(Vh, voff, lds_k + C::V_AT);
         }
     };
 
@@ -250,7 +255,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         for (int hi = 0; hi < 2; ++hi) {
             const int r = 8 * hi + 4 * (g16 >> 1) + (i16 >> 2);         // row within a 16-key step
             const int ch = 4 * db + 2 * (g16 & 1) + ((i16 >> 1) & 1);  // 16-byte chunk holding this lane's 4 columns
-            voff[db][hi] = (int)smem_base + (kg * KB * 32 + r) * C::ROWB + ((ch ^ C::swz(r)) << 4) + (i16 & 1) * 8;
+            voff[db][hi] = (int)smem_base + (C::SPLIT_RING ? C::V_AT : 0) + (kg * KB * 32 + r) * C::ROWB + ((ch ^ C::swz(r)) << 4) + (i16 & 1) * 8;
         }
     const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
 
@@ -261,7 +266,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // both are compile-time constants and fold into the immediate offsets of the LDS reads.
     auto read_k = [&](int stage, int kb, bf16x8 (&kf)[DS]) __attribute__((always_inline)) {  // K fragments (A operand of S^T = K Q^T) of one block
         typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
-        const int block_off = stage * C::STAGE + kb * 32 * C::ROWB;
+        const int block_off = stage * C::K_STEP + kb * 32 * C::ROWB;
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) {
             // Declaring the lane offset "modified" keeps (offset + constant) from being hoisted out of the loop
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         }
     };
     auto read_v = [&](int stage, int kb, bf16x8 (&vf)[2][DB]) __attribute__((always_inline)) {  // V^T fragments (A operand of O^T += V^T P^T)
-        const int block_off = stage * C::STAGE + C::KBYTES + kb * 32 * C::ROWB;
+        const int block_off = stage * C::K_STEP + (C::SPLIT_RING ? 0 : C::V_AT) + kb * 32 * C::ROWB;
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             asm volatile("" : "+v"(voff[db][0]), "+v"(voff[db][1]));
@@ -448,11 +453,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // With d = 128 two sets of V fragments do not fit the register file next to the accumulators: then one
     // set is used, refilled in the middle of each step right after the MFMAs that consumed it were issued.
     constexpr bool kTwoVSets = (DP <= 64);
-    // d = 256 (one wavefront per SIMD, accumulators in the upper half of its 512 registers): the other half has to
-    // hold everything the vector ALU touches, so K fragments are kept 8 at a time and V fragments one 16-key half
-    // at a time, and the Attend of a block follows its softmax in the same step instead of being owed to the next.
+    // d = 256 (one wavefront per SIMD, the accumulators and Q in the upper half of its 512 registers) has steps of its own, wide_step below.
     constexpr bool kWide = (DP == 256);
-    constexpr int KFN = kWide ? DS / 2 : DS;
     // Pipeline state: xA/xB hold the logits of the current / next block, pA/pB and vfA/vfB the
     // probabilities and V fragments of the block whose Attend is still owed.
     floatx16 xA[QB], xB[QB];
@@ -468,53 +470,40 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int db = 0; db < DB; ++db) vfA[t][db] = vfB[t][db] = __builtin_bit_cast(bf16x8, (uint4v){0, 0, 0, 0});
-    // wide form: K fragments ds = h KFN .. of one block, and the V fragments of one 16-key half t
-    auto read_k_half = [&](int stage, int kb, int h) __attribute__((always_inline)) {
+    // ---- pieces of a d = 256 step
+    float xv[16];  // logits of the current block, the vector ALU's copy of an accumulator
+    // Kept in the upper half of the register file by name: left to itself the compiler carries all 128 accumulators through the lower half
+    // in every step, for the rescaling that hardly ever happens.
+    auto keep_high = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[0][db]));
+    };
+    auto wide_visible = [&](int blk, int r) __attribute__((always_inline)) {
+        const int key = blk * 32 + acc_row(r, half);
+        return key < N && (!CAUSAL || key <= q0w + l32 + off);
+    };
+    // V^T fragments of 32 columns (both 16-key halves), and two of the sixteen K fragments
+    auto read_v_block = [&](int stage, int db) __attribute__((always_inline)) {
+        const int at = stage * C::K_STEP;
+        asm volatile("" : "+v"(voff[db][0]), "+v"(voff[db][1]));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int off = at + t * 16 * C::ROWB;
+            vfA[t][db] = concat(lds_read_tr16_at(voff[db][0] + off), lds_read_tr16_at(voff[db][1] + off));
+        }
+        if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
+    };
+    auto read_k_pair = [&](int stage, int g) __attribute__((always_inline)) {
         typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
-        const int block_off = stage * C::STAGE + kb * 32 * C::ROWB;
 #pragma unroll
-        for (int i = 0; i < KFN; ++i) {
-            asm volatile("" : "+v"(koff[h * KFN + i]));
-            kf[i] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[h * KFN + i] + block_off);
+        for (int ds = 2 * g; ds < 2 * g + 2; ++ds) {
+            asm volatile("" : "+v"(koff[ds]));
+            kf[ds] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[ds] + stage * C::K_STEP);
         }
+        if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
     };
-    auto read_v_half = [&](int stage, int kb, int t) __attribute__((always_inline)) {
-        const int off = stage * C::STAGE + C::KBYTES + kb * 32 * C::ROWB + t * 16 * C::ROWB;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            asm volatile("" : "+v"(voff[db][0]), "+v"(voff[db][1]));
-            vfA[0][db] = concat(lds_read_tr16_at(voff[db][0] + off), lds_read_tr16_at(voff[db][1] + off));
-        }
-    };
-    auto logits_half = [&](int h, floatx16 (&x)[QB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < KFN; ++i)
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) x[qb] = mfma_bf16_32x32x16(kf[i], qf[qb][h * KFN + i], x[qb]);
-    };
-    auto attend_half = [&](int t, const uint32_t (&p)[QB][8]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                uint4v pw = {p[qb][4 * t], p[qb][4 * t + 1], p[qb][4 * t + 2], p[qb][4 * t + 3]};
-                oacc[qb][db] = mfma_bf16_32x32x16(vfA[0][db], __builtin_bit_cast(bf16x8, pw), oacc[qb][db]);
-            }
-    };
-    if (kWide) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) xA[qb][r] = 0.f;
-        read_k_half(0, 0, 0);
-        logits_half(0, xA);
-        __builtin_amdgcn_sched_barrier(0);
-        read_k_half(0, 0, 1);
-        logits_half(1, xA);
-    } else {
-        read_k(0, 0, kf);
-        logits(kf, xA);
-    }
+    read_k(0, 0, kf);
+    logits(kf, xA);
 
     // One step = one block b:   matrix pipe: Attend(b-1) and S(b+1);   vector ALU: softmax(b).
     // Stage bookkeeping (tile j = blocks 2j, 2j+1; reads of step b touch K of block b+1 and V of block b):
@@ -522,59 +511,9 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     //   before step 2j+1: start streaming tile j+STAGES-1 into the stage that held tile j-1
     auto step = [&](int blk, int stage, int next_stage, bool masked, floatx16 (&xc)[QB], floatx16 (&xn)[QB], const uint32_t (&pp)[QB][8],
                     const bf16x8 (&vp)[2][DB], uint32_t (&pc)[QB][8], bf16x8 (&vc)[2][DB]) __attribute__((always_inline)) {
-        if (kWide) {
-            // Wide head: S(b+1) in two halves with the softmax of block b spread under them, then Attend(b) in its
-            // two key halves; every batch of LDS reads has eight MFMAs (256 matrix-pipe cycles) ahead of its use.
-            constexpr auto kLgkm0 = (63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8);
-            float bs[QB];
-            read_k_half(next_stage, 0, 0);
-            read_v_half(stage, 0, 0);
-            if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) xn[qb][r] = 0.f;
-            logits_half(0, xn);
-            shift(blk, masked, xc);
-#pragma unroll
-            for (int g = 0; g < QB * KFN; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, (QB * 16) / (QB * KFN), 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            read_k_half(next_stage, 0, 1);
-            if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
-            __builtin_amdgcn_sched_barrier(0);
-            logits_half(1, xn);
-            softmax_b(xc, pc, bs);
-#pragma unroll
-            for (int g = 0; g < QB * KFN; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, (QB * 32) / (QB * KFN), 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            bool jumped = false;
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) jumped |= !(bs[qb] <= kSumJump);
-            if (__builtin_amdgcn_ballot_w64(jumped) != 0) {  // exact path, before this block's Attend
-                row_max(xc, mx);
-                rescale(xc, mx);
-                softmax_b(xc, pc, bs);
-            }
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) lsum[qb] += bs[qb];
-            attend_half(0, pc);
-            __builtin_amdgcn_sched_barrier(0);
-            read_v_half(stage, 0, 1);
-            if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
-            __builtin_amdgcn_sched_barrier(0);
-            attend_half(1, pc);
-            return;
-        }
         read_k(next_stage, (blk + 1) & (KB - 1), kf);
         if (kTwoVSets) read_v(stage, blk & (KB - 1), vc);
-        if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0) only
+        if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
         __builtin_amdgcn_sched_barrier(0);  // keep the LDS reads at the top: they have a whole step to land
         float bsum[QB];
         constexpr int kMfmaPerStep = 2 * QB * DB + QB * DS, kValuPerMfma = (QB * 48) / kMfmaPerStep;
@@ -600,7 +539,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
             }
             __builtin_amdgcn_sched_barrier(0);
             read_v(stage, blk & (KB - 1), vc);
-            if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8));
+            if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
             __builtin_amdgcn_sched_barrier(0);
             logits(kf, xn);
             softmax_b(xc, pc, bsum);
@@ -629,7 +568,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // tile j-1), and start streaming tile j+STAGES-1 into the stage that held tile j-1.
     auto sync_and_stream = [&](int j, int sj) __attribute__((always_inline)) {
         // A single wavefront has no barrier to wait at: its reads of the stage that is refilled below must be back first.
-        if (NW == 1) __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8));
+        if (NW == 1) __builtin_amdgcn_s_waitcnt(kLgkm0);
         if (kStagger) {  // the step needs V of tile j and K of tile j+1, which were started together
             if (kSyncEveryPhase || j + STAGES - 1 >= n_tiles)
                 wait_vm<0>();
@@ -649,6 +588,78 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         if (kSyncEveryPhase) {  // every wavefront runs this the same number of times, so the barrier is safe here
             wait_vm<0>();
             __syncthreads();
+        }
+    };
+    // d = 256.  One wavefront per SIMD has nobody to hide its waits behind, so a step is two phases, each multiplying operands that are
+    // in registers already while the operands of the other one are read from LDS:
+    //   A: S(b+1), sixteen MFMAs over kf, with the softmax of block b and the reads of V(b) between them;
+    //   B: Attend(b), sixteen MFMAs over vfA, with the reads of K(b+2) and the logits of b+1 on their way to the vector ALU.
+    // The ring moves on between the phases: V(b) and K(b+1) have left LDS by then.  Between two MFMAs (32 cycles) at most three vector
+    // instructions and four LDS reads are issued, so the matrix pipe is what bounds a step (1024 cycles), and then power: 16 heads of 8192
+    // positions without a mask 1340 -> 1010-1030 us (1070-1090 TFLOP/s), 2 x 8 causal heads of 3001 130 -> 93 us.  Before, a step read its
+    // operands at its start and moved the accumulators twice between the halves of the register file.
+    auto wide_step = [&](int blk, int j, int stage, bool masked) __attribute__((always_inline)) {
+        const int stage1 = (stage + 1) % STAGES, stage2 = (stage + 2) % STAGES;
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xA[0][r] = 0.f;
+        uint32_t(&p)[8] = pA[0];
+        float bsum = 0.f, e = 0.f;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            asm volatile("" : "+a"(qf[0][g]));
+            xA[0] = mfma_bf16_32x32x16(kf[g], qf[0][g], xA[0]);
+            if (g < 8) read_v_block(stage, g);
+            xv[g] = __builtin_fmaf(xv[g], c, -m[0]);
+            if (masked) xv[g] = wide_visible(blk, g) ? xv[g] : -INFINITY;
+            if (g & 1) {
+                p[g >> 1] = pack_bf16(e, __builtin_amdgcn_exp2f(xv[g]));
+                bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[g >> 1]), ones, bsum, false);
+            } else {
+                e = __builtin_amdgcn_exp2f(xv[g]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (__builtin_amdgcn_ballot_w64(!(bsum <= kSumJump)) != 0) {  // exact path, before this block's Attend
+            float top = xv[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, xv[r]);
+            const float delta = __builtin_fmaxf(halves_max(top), 0.f), alpha = __builtin_amdgcn_exp2f(-delta);
+            m[0] += delta;
+            lsum[0] *= alpha;
+            keep_high();
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[0][db][r] *= alpha;
+            keep_high();
+            bsum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                p[r >> 1] = pack_bf16(__builtin_amdgcn_exp2f(xv[r] - delta), __builtin_amdgcn_exp2f(xv[r + 1] - delta));
+                bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[r >> 1]), ones, bsum, false);
+            }
+        }
+        lsum[0] += bsum;
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        sync_and_stream(j + 1, stage1);
+        keep_high();
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            const int t = g / DB, db = g % DB;
+            const uint4v pw = {p[4 * t], p[4 * t + 1], p[4 * t + 2], p[4 * t + 3]};
+            oacc[0][db] = mfma_bf16_32x32x16(vfA[t][db], __builtin_bit_cast(bf16x8, pw), oacc[0][db]);
+            if (g < 8) read_k_pair(stage2, g);
+            if (g == 4) asm volatile("" : "+a"(xA[0]));  // the copies below stay below: the last MFMA of S has its latency behind it
+            if (g >= 4 && g < 12) {
+#pragma unroll
+                for (int r = 2 * (g - 4); r < 2 * (g - 3); ++r) {
+                    xv[r] = xA[0][r];
+                    asm volatile("" : "+v"(xv[r]));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     // Two or four blocks per tile: the last step already reads K of the next tile, so the synchronisation sits
@@ -672,6 +683,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
                 else
                     step(kb0 + i + 1, sj, last ? sn : sj, masked, xB, xA, pA, vfA, pB, vfA);
             }
+        } else if (kWide) {
+            wide_step(kb0, j, sj, masked);
         } else {
             sync_and_stream(j, sj);
             if (!odd) {
@@ -701,6 +714,13 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     const int n_unm_tiles = SPARSE ? max(n_tiles - KB64, 0) : max(0, min(n_unm_all - t0, n_tiles));
     const int n_act_tiles = SPARSE ? n_tiles : max(0, min(n_act_all - t0, n_tiles));
     int j = 0;
+    if (kWide) {
+        sync_and_stream(0, 0);
+        read_k(1, 0, kf);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xv[r] = xA[0][r];
+        __builtin_amdgcn_sched_barrier(0);
+    }
     // main loop: STAGES fully visible tiles per trip, so that every ring stage index is a constant
 #pragma unroll 1
     for (; j + STAGES <= n_unm_tiles; j += STAGES) {
@@ -710,7 +730,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // remaining visible tiles and the partly masked ones (masking a fully visible tile changes nothing)
     int sj = 0;  // j is a multiple of STAGES here (even, where that matters)
     bool owed_in_a = false;  // one block per tile only: the last step left its probabilities in pA, not pB
-    if (KB >= 2) {
+    if (KB >= 2 || kWide) {
 #pragma unroll 1
         for (; j < n_unm_tiles; ++j) {
             tile_steps(j, sj, false, false);
@@ -745,8 +765,9 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     }
 #pragma unroll 1
     for (; j < n_tiles; ++j) {
-        sync_and_stream(j, sj);
-        sj = sj + 1 == STAGES ? 0 : sj + 1;
+        if (kWide) sj = sj + 1 == STAGES ? 0 : sj + 1;
+        sync_and_stream(j + (kWide ? 1 : 0), sj);
+        if (!kWide) sj = sj + 1 == STAGES ? 0 : sj + 1;
     }
 
     // ---- key groups: the partial results (reference maximum, row sum, accumulators) of a row's wavefronts meet in the ring's
