@@ -76,6 +76,12 @@ __device__ __forceinline__ float halves_sum(float x) {
     return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
+// The lower half's value in both halves.
+__device__ __forceinline__ float lower_half(float x) {
+    uint32_t u = __builtin_bit_cast(uint32_t, x);
+    return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
+}
+
 // One wave-wide global -> LDS copy, 16 bytes per lane: lane l's bytes land at lds_base + 16 l.
 // Issued as inline asm so that the compiler does not serialise later LDS reads of OTHER stages
 // behind it; completion is awaited explicitly with wait_vm<n>() before the stage is published by

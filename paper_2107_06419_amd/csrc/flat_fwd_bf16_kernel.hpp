@@ -18,8 +18,9 @@
 // max and sum are carried as running values, so on-chip state is independent of N.
 //
 // Reference max and optimistic exponentiation.  softmax is invariant to the constant subtracted per
-// row, so m need not be the exact running maximum.  It starts as the (scaled) logit of key 0, which
-// every query sees, so the row sum is at least 1 relative to it and can never underflow.  The steady
+// row, so m need not be the exact running maximum.  It starts as the (scaled) logit of the first key of the
+// wavefront's first block: key 0, which every query sees, so the row sum is at least 1 relative to it and can never
+// underflow (where keys are divided, a share of which the row sees nothing has sum 0 and is left out).  The steady
 // state exponentiates against the current m WITHOUT computing the block maximum; a logit far above m
 // shows up as a jump of the fp32 row sum (more than kSumJump per lane and block, i.e. some
 // probability above 2^10), and only then the block takes the exact path: row maximum, raise m,
@@ -29,6 +30,8 @@
 #pragma once
 #include "flat_common.hpp"
 #include "flat_launch.hpp"
+
+#include <float.h>
 
 namespace flat {
 
@@ -424,27 +427,15 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     else
         wait_vm<0>();
     __syncthreads();
-    // Reference max of each row = c * (q . k_first), k_first = the first key the row block sees: row 0 of its first tile.
-    {
+    bf16x8 kf[DS];  // K fragments of one block
+    read_k(0, 0, kf);
+    if (kQThroughLds) {
         typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
-        float k0[DS][8];
 #pragma unroll
-        for (int ds = 0; ds < DS; ++ds) {
-            const bf16x8 kb8 = *(lds_frag_ptr)(uintptr_t)(smem_base + (2 * ds + half) * 16);
+        for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) k0[ds][e] = (float)kb8[e];
-        }
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float dot = 0.f;
-#pragma unroll
-            for (int ds = 0; ds < DS; ++ds) {
-                if (kQThroughLds) qf[qb][ds] = *(lds_frag_ptr)(uintptr_t)(smem_base + kQAt + (rg * QW + 32 * qb + l32) * C::ROWB + (((2 * ds + half) ^ C::swz(l32)) << 4));
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dot = __builtin_fmaf((float)qf[qb][ds][e], k0[ds][e], dot);
-            }
-            m[qb] = n_tiles > 0 ? halves_sum(dot) * c : 0.f;
-        }
+            for (int ds = 0; ds < DS; ++ds)
+                qf[qb][ds] = *(lds_frag_ptr)(uintptr_t)(smem_base + kQAt + (rg * QW + 32 * qb + l32) * C::ROWB + (((2 * ds + half) ^ C::swz(l32)) << 4));
     }
     if (kQThroughLds) __syncthreads();  // every wavefront has its fragments: the ring takes their place
 #pragma unroll
@@ -460,7 +451,6 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     floatx16 xA[QB], xB[QB];
     uint32_t pA[QB][8], pB[QB][8];
     bf16x8 vfA[2][DB], vfB[2][DB];  // vfB stays unused with one set; the wide form uses vfA[0] only
-    bf16x8 kf[DS];                  // the wide form uses the first KFN
     float mx[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
@@ -502,8 +492,12 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         }
         if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
     };
-    read_k(0, 0, kf);
     logits(kf, xA);
+    // Reference max of each row: its scaled logit with the first key of its first block, which is row 0 of S^T: register 0 of the lower half.
+    // (A dot product of its own, taken before, was a chain of d products in the start of every workgroup: 12 heads x 512, d = 64, 5.64 -> 5.42
+    // us, 768 causal heads x 512, d = 96, 90.8 -> 85.0, 8 x 512, d = 256, 17.5 -> 16.5.)
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) m[qb] = n_tiles > 0 ? lower_half(xA[qb][0]) * c : 0.f;
 
     // One step = one block b:   matrix pipe: Attend(b-1) and S(b+1);   vector ALU: softmax(b).
     // Stage bookkeeping (tile j = blocks 2j, 2j+1; reads of step b touch K of block b+1 and V of block b):
@@ -781,7 +775,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const float total = halves_sum(lsum[qb]);
-            stat[slot(kg, qb) * 64] = half ? total : m[qb];
+            // a group none of whose keys the row sees weighs nothing, whatever its first key's logit was
+            stat[slot(kg, qb) * 64] = half ? total : total > 0.f ? m[qb] : -INFINITY;
 #pragma unroll
             for (int q = 0; q < QUADS; ++q) {
                 const int db = q / 4, rq = q % 4;
@@ -792,7 +787,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         __syncthreads();
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float mk[KG], w[KG], M = -INFINITY, L = 0.f;
+            float mk[KG], w[KG], M = -FLT_MAX, L = 0.f;
 #pragma unroll
             for (int k = 0; k < KG; ++k) {
                 mk[k] = stat[slot(k, qb) * 64 - 32 * half];

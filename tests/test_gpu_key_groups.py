@@ -71,3 +71,22 @@ def test_groups_with_very_different_maxima_merge(d, rising):
     v = rounded((B, H, Nk, d), 9, 2)
     for mask in (0, 1):
         check_close(run_both(q, k, v, 0.125, mask, None), oracle.attention_cross(q, k, v, 0.125, mask), "bf16", "ramp")
+
+
+@pytest.mark.parametrize("Nq,Nk", [(100, 100), (64, 161), (32, 160), (1, 33)])
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
+def test_a_group_whose_keys_a_row_does_not_see_weighs_nothing(d, Nq, Nk):
+    """Causal, with logits of hundreds of log2 units from a row's first unseen key on: each group takes its reference maximum from the
+    first key of its share, which must not count in the merge where the row sees none of the share.  The split form, too."""
+    import torch
+    q, k, v = np.abs(rounded((1, 2, Nq, d), 77, 0)), rounded((1, 2, Nk, d), 77, 1), rounded((1, 2, Nk, d), 77, 2)
+    k[:, :, Nk - Nq + 1:] = np.abs(k[:, :, Nk - Nq + 1:]) * 16.0  # exact in bf16; visible to the last rows only
+    scale = float(np.float32(d ** -0.5))
+    ref = oracle.attention_cross(q, k, v, scale, 1)
+    check_close(run_both(q, k, v, scale, 1, None), ref, "bf16", "unseen shares")
+    dq, dk, dv = (to_device(x, "bf16") for x in (q, k, v))
+    out = torch.full_like(dq, float("nan"))
+    ws = torch.empty(fa.flat_attn_fwd_splitkv_workspace_bytes(1, 2, Nq, Nk, d, 2) // 4 + 1, dtype=torch.float32, device="cuda")
+    fa.flat_attn_fwd_splitkv(dq, dk, dv, out, scale, 1, None, 2, ws)
+    torch.cuda.synchronize()
+    check_close(to_host_f64(out), ref, "bf16", "unseen shares, two splits")
