@@ -76,6 +76,20 @@ __device__ __forceinline__ float halves_sum(float x) {
     return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
+// Quotients n / d of 0 <= n < 2^31 by a divisor known when the kernel is launched: mul = ceil(2^(32+shift) / d) with 2^shift < d <=
+// 2^(shift+1), so mul < 2^32, mul d - 2^(32+shift) < d <= 2^(shift+1), and the error n (mul d - 2^(32+shift)) / (d 2^(32+shift)) stays below 1 / d.
+// A division by a kernel argument takes about 40 dependent scalar instructions (200 cycles at the start of every workgroup), this five.
+struct Divisor {
+    uint32_t mul;  // 0: d = 1
+    int shift;
+    explicit Divisor(int d) : mul(0), shift(0) {
+        if (d <= 1) return;
+        while ((2ll << shift) < d) ++shift;
+        mul = (uint32_t)(((1ull << (32 + shift)) + (uint64_t)d - 1) / (uint64_t)d);
+    }
+    __host__ __device__ int quotient(int n) const { return (int)((uint32_t)(((uint64_t)(uint32_t)n * mul) >> 32) >> shift) + (mul ? 0 : n); }
+};
+
 // The lower half's value in both halves.
 __device__ __forceinline__ float lower_half(float x) {
     uint32_t u = __builtin_bit_cast(uint32_t, x);

@@ -102,11 +102,16 @@ constexpr int kMaxSparseTiles = 2048;  // block-sparse: listed tiles per row blo
 // unnormalised result (reference maximum, row sum, accumulators) in a workspace for split_merge_kernel.
 constexpr int kDense = 0, kSparse = 1, kSplit = 2;
 
+// How the workgroups of a launch are numbered: n_blocks = n_heads * n_qtiles, n_qtiles = row blocks (times splits) per head.
+struct LaunchGrid {
+    int n_qtiles, n_blocks, blocks_per_xcd, n_heads, n_row_blocks;
+    Divisor by_qtiles, by_heads, by_splits, by_heads_per_batch;
+};
+
 template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0, int KG = 1>
 __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 2) void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                           const bf16* __restrict__ V, bf16* __restrict__ O,
-                                                          const Bf16Problem prob, int n_qtiles, int n_blocks,
-                                                          int blocks_per_xcd, float c) {
+                                                          const Bf16Problem prob, const LaunchGrid grid, float c) {
     using C = Bf16Cfg<D, STAGES, NW, BCX>;
     constexpr bool SPARSE = MODE == kSparse, SPLIT = MODE == kSplit;
     constexpr int DP = C::DP, QW = 32 * QB, BR = NW / KG * QW, BC = C::BC, DS = D / 16, DB = D / 32;
@@ -136,11 +141,17 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // sequence on the same unit in the first round; the second half of every 64 positions is therefore taken in
     // reverse, which pairs the k-th heaviest of the 64 with the k-th lightest.
     static_assert(!(CAUSAL && SPARSE), "the block-sparse variant has no causal form");
+    // All arguments in one round trip: left alone, the compiler fetches some, waits, divides, and fetches the rest (a first workgroup
+    // of a compute unit pays about 600 cycles for each).
+    const int n_qtiles = grid.n_qtiles, blocks_per_xcd = grid.blocks_per_xcd;
+    int n_blocks = grid.n_blocks;
+    asm("" : "+s"(n_blocks) : "s"(Q), "s"(K), "s"(V), "s"(O), "s"(prob.Nq), "s"(prob.Nk), "s"((uint64_t)prob.kv_lens), "s"(prob.causal_offset), "s"(n_qtiles),
+        "s"(blocks_per_xcd), "s"(grid.by_qtiles.mul), "s"(grid.by_qtiles.shift), "s"(grid.by_heads_per_batch.mul), "s"(grid.by_heads_per_batch.shift), "s"(c));
     int bh, qt;
     if (!CAUSAL) {
         const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
         if (logical >= n_blocks) return;
-        bh = logical / n_qtiles;
+        bh = grid.by_qtiles.quotient(logical);
         qt = logical - bh * n_qtiles;
     } else {
         constexpr int kByLds = (160 * 1024) / bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG), kByRegs = 8 / NW;  // two wavefronts per SIMD
@@ -150,23 +161,23 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         if (kTwoPerUnit && (t | 63) < blocks_per_xcd && (t & 32)) r = (t & ~31) + 31 - (t & 31);
         const int g = 8 * r + x;
         if (g >= n_blocks) return;
-        const int heads = n_blocks / n_qtiles;
-        const int from_end = g / heads;
-        bh = g - from_end * heads;
+        const int from_end = grid.by_heads.quotient(g);
+        bh = g - from_end * grid.n_heads;
         qt = n_qtiles - 1 - from_end;
     }
 
     int split = 0;
     if (SPLIT) {  // the launch counts (row block, split) pairs per head; the splits of a row block are neighbours
-        split = qt % prob.n_splits;
-        qt /= prob.n_splits;
+        const int block = grid.by_splits.quotient(qt);
+        split = qt - block * prob.n_splits;
+        qt = block;
     }
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     // Nq query rows per head; N = number of keys of this head that count (the padded tail of a shorter batch
     // entry is masked like the tail of a ragged tile); causal: query i sees keys 0 .. i + off.
     const int Nq = prob.Nq, off = prob.causal_offset;
     int N = prob.Nk;
-    if (prob.kv_lens) N = max(1, min(prob.Nk, prob.kv_lens[bh / prob.heads_per_batch]));
+    if (prob.kv_lens) N = max(1, min(prob.Nk, prob.kv_lens[grid.by_heads_per_batch.quotient(bh)]));
     const size_t head_q = (size_t)bh * Nq * D, head_k = (size_t)bh * prob.Nk * D;
     const char* Qh = (const char*)(Q + head_q);
     const char* Kh = (const char*)(K + head_k);
@@ -547,7 +558,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         bool jump = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) jump |= !(bsum[qb] <= kSumJump);
-        if (__builtin_amdgcn_ballot_w64(jump) != 0) {  // exact path: xc still holds c S - m of this block
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(jump) != 0, 0)) {  // exact path: xc still holds c S - m of this block
             row_max(xc, mx);
             rescale(xc, mx);
             softmax_b(xc, pc, bsum);
@@ -615,7 +626,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_amdgcn_ballot_w64(!(bsum <= kSumJump)) != 0) {  // exact path, before this block's Attend
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(bsum <= kSumJump)) != 0, 0)) {  // exact path, before this block's Attend
             float top = xv[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, xv[r]);
@@ -802,7 +813,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
             const float inv = SPLIT ? 1.f : 1.0f / L;
             float* ws = nullptr;
             if (SPLIT) {
-                ws = prob.split_ws + ((size_t)(bh * (n_qtiles / prob.n_splits) + qt) * prob.n_splits + split) * (size_t)(BR * (DP + 2));
+                ws = prob.split_ws + ((size_t)(bh * grid.n_row_blocks + qt) * prob.n_splits + split) * (size_t)(BR * (DP + 2));
                 if (row < Nq && kg == 0 && half == 0) {
                     ws[BR * DP + r_wg] = M;
                     ws[BR * DP + BR + r_wg] = L;
@@ -835,8 +846,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // ---- split keys: leave the unnormalised partial result in the workspace.  Per (head, row block, split):
     // BR rows x DP accumulators, then BR reference maxima, then BR row sums, all fp32.
     if (SPLIT) {
-        const int n_row_blocks = n_qtiles / prob.n_splits;  // per head
-        float* part = prob.split_ws + ((size_t)(bh * n_row_blocks + qt) * prob.n_splits + split) * (size_t)(BR * (DP + 2));
+        float* part = prob.split_ws + ((size_t)(bh * grid.n_row_blocks + qt) * prob.n_splits + split) * (size_t)(BR * (DP + 2));
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const float total = halves_sum(lsum[qb]);
@@ -890,17 +900,18 @@ inline hipError_t launch_cfg(const void* Q, const void* K, const void* V, void* 
                              hipStream_t stream) {
     constexpr int BR = 32 * QB * (NW / KG);
     // split keys: the kernel sees (row block, split) pairs where the other modes see row blocks
-    const int n_qtiles = (prob.Nq + BR - 1) / BR * (MODE == kSplit ? prob.n_splits : 1);
-    const int n_blocks = BH * n_qtiles;
-    const int blocks_per_xcd = (n_blocks + 7) / 8;
+    const int n_row_blocks = (prob.Nq + BR - 1) / BR, n_splits = MODE == kSplit ? prob.n_splits : 1;
+    const int n_qtiles = n_row_blocks * n_splits, n_blocks = BH * n_qtiles;
+    const LaunchGrid grid{n_qtiles, n_blocks, (n_blocks + 7) / 8, BH, n_row_blocks, Divisor(n_qtiles), Divisor(BH), Divisor(n_splits),
+                          Divisor(prob.heads_per_batch)};
     auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, CAUSAL, MODE, BCX, KG>;
     constexpr int lds = bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
     static_assert(lds <= 160 * 1024, "more LDS than a compute unit has");
     static std::atomic<uint64_t> attr_done{0};  // one flag per kernel instantiation
     hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(blocks_per_xcd * 8), dim3(64 * NW), lds, stream, (const bf16*)Q, (const bf16*)K,
-                       (const bf16*)V, (bf16*)O, prob, n_qtiles, n_blocks, blocks_per_xcd, scale * kLog2e);
+    hipLaunchKernelGGL(kern, dim3(grid.blocks_per_xcd * 8), dim3(64 * NW), lds, stream, (const bf16*)Q, (const bf16*)K,
+                       (const bf16*)V, (bf16*)O, prob, grid, scale * kLog2e);
     return hipGetLastError();
 }
 
