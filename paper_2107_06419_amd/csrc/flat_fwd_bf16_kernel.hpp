@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     static_assert(NW % KG == 0 && KBT % KG == 0 && D / 8 % KG == 0, "key groups share wavefronts, keys and output columns evenly");
     static_assert(KG == 1 || (!SPARSE && BC % 64 == 0), "the block-sparse variant has one key group");
     static_assert(KB == 1 || KB == 2 || KB == 4, "a wavefront takes one, two or four 32-key blocks of a tile");
-    static_assert(KB != 1 || STAGES % 2 == 0, "with one block per tile the unrolled loop needs an even ring");
+    static_assert(KB != 1 || QB == 1 || STAGES % 2 == 0, "with one block per tile the unrolled loop needs an even ring");
     static_assert(!SPARSE || KB64 >= 1, "block-sparse lists name 64-key tiles");
     constexpr int LOADS_PER_TILE = 2 * C::LOADS;  // DMA instructions per wavefront per tile (K and V)
     // With one block per wavefront and tile, a step is done with its V tile and with the NEXT K tile, so K runs one tile
@@ -455,13 +455,15 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // With d = 128 two sets of V fragments do not fit the register file next to the accumulators: then one
     // set is used, refilled in the middle of each step right after the MFMAs that consumed it were issued.
     constexpr bool kTwoVSets = (DP <= 64);
-    // d = 256 (one wavefront per SIMD, the accumulators and Q in the upper half of its 512 registers) has steps of its own, wide_step below.
-    constexpr bool kWide = (DP == 256);
+    // One 32-key block per wavefront and tile: the steps are two_phase_step, below.
+    constexpr bool kTwoPhase = KB == 1 && QB == 1;
+    constexpr bool kHigh = DP == 256;  // one wavefront per SIMD: the accumulators and Q live in the upper half of its 512 registers
+    static_assert(!kHigh || kTwoPhase, "d = 256 is built for 32 rows per wavefront");
     // Pipeline state: xA/xB hold the logits of the current / next block, pA/pB and vfA/vfB the
     // probabilities and V fragments of the block whose Attend is still owed.
     floatx16 xA[QB], xB[QB];
     uint32_t pA[QB][8], pB[QB][8];
-    bf16x8 vfA[2][DB], vfB[2][DB];  // vfB stays unused with one set; the wide form uses vfA[0] only
+    bf16x8 vfA[2][DB], vfB[2][DB];  // vfB stays unused with one set
     float mx[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
@@ -471,21 +473,22 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int db = 0; db < DB; ++db) vfA[t][db] = vfB[t][db] = __builtin_bit_cast(bf16x8, (uint4v){0, 0, 0, 0});
-    // ---- pieces of a d = 256 step
-    float xv[16];  // logits of the current block, the vector ALU's copy of an accumulator
-    // Kept in the upper half of the register file by name: left to itself the compiler carries all 128 accumulators through the lower half
-    // in every step, for the rescaling that hardly ever happens.
+    // ---- pieces of a two-phase step
+    float xv[16];  // logits of the current block
+    // d = 256: kept in the upper half of the register file by name.  Left to itself the compiler carries all 128 accumulators through the
+    // lower half in every step, for the rescaling that hardly ever happens.
     auto keep_high = [&]() __attribute__((always_inline)) {
+        if (!kHigh) return;
 #pragma unroll
         for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[0][db]));
     };
-    auto wide_visible = [&](int blk, int r) __attribute__((always_inline)) {
+    auto is_visible = [&](int blk, int r) __attribute__((always_inline)) {
         const int key = blk * 32 + acc_row(r, half);
         return key < N && (!CAUSAL || key <= q0w + l32 + off);
     };
-    // V^T fragments of 32 columns (both 16-key halves), and two of the sixteen K fragments
+    // V^T fragments of 32 columns (both 16-key halves), and one of the K fragments
     auto read_v_block = [&](int stage, int db) __attribute__((always_inline)) {
-        const int at = stage * C::K_STEP;
+        const int at = stage * C::K_STEP + (C::SPLIT_RING ? 0 : C::V_AT);
         asm volatile("" : "+v"(voff[db][0]), "+v"(voff[db][1]));
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -494,13 +497,10 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         }
         if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
     };
-    auto read_k_pair = [&](int stage, int g) __attribute__((always_inline)) {
+    auto read_k_frag = [&](int stage, int ds) __attribute__((always_inline)) {
         typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
-#pragma unroll
-        for (int ds = 2 * g; ds < 2 * g + 2; ++ds) {
-            asm volatile("" : "+v"(koff[ds]));
-            kf[ds] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[ds] + stage * C::K_STEP);
-        }
+        asm volatile("" : "+v"(koff[ds]));
+        kf[ds] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[ds] + stage * C::K_STEP);
         if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
     };
     logits(kf, xA);
@@ -595,15 +595,18 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
             __syncthreads();
         }
     };
-    // d = 256.  One wavefront per SIMD has nobody to hide its waits behind, so a step is two phases, each multiplying operands that are
-    // in registers already while the operands of the other one are read from LDS:
-    //   A: S(b+1), sixteen MFMAs over kf, with the softmax of block b and the reads of V(b) between them;
-    //   B: Attend(b), sixteen MFMAs over vfA, with the reads of K(b+2) and the logits of b+1 on their way to the vector ALU.
-    // The ring moves on between the phases: V(b) and K(b+1) have left LDS by then.  Between two MFMAs (32 cycles) at most three vector
-    // instructions and four LDS reads are issued, so the matrix pipe is what bounds a step (1024 cycles), and then power: 16 heads of 8192
-    // positions without a mask 1340 -> 1010-1030 us (1070-1090 TFLOP/s), 2 x 8 causal heads of 3001 130 -> 93 us.  Before, a step read its
-    // operands at its start and moved the accumulators twice between the halves of the register file.
-    auto wide_step = [&](int blk, int j, int stage, bool masked) __attribute__((always_inline)) {
+    // One block per wavefront and tile: launches of few rows, split keys and d = 256, where a SIMD has few wavefronts or one, and nobody to
+    // hide the waits of a step behind.  So a step is two phases, each multiplying operands that are in registers already while the operands
+    // of the other one are read from LDS:
+    //   A: S(b+1) over kf, with the softmax of block b and the reads of V(b) between its MFMAs;
+    //   B: Attend(b) over vfA, with the reads of K(b+2) between its MFMAs.
+    // The ring moves on between the phases: V(b) and K(b+1) have left LDS by then.
+    // d = 256: at most three vector instructions and four LDS reads between two MFMAs (32 cycles), so the matrix pipe is what bounds a step
+    // (1024 cycles), and then power: 16 heads of 8192 positions without a mask 1340 -> 1010-1030 us (1070-1090 TFLOP/s), 2 x 8 causal heads of
+    // 3001 130 -> 93 us.  Before, a step read its operands at its start and moved the accumulators twice between the halves of the register file.
+    // Key groups: 12 heads x 512, d = 64, 5.31 -> 5.06 us; 4 causal heads x 8192 58.1 -> 50.4; 8 causal x 1024, d = 128, 11.9 -> 10.8; a step of
+    // a workgroup alone on its compute unit 900 -> 790 cycles (256 of matrix pipe).  Split keys: 16 heads x 65536 45.7 -> 44.4.
+    auto two_phase_step = [&](int blk, int j, int stage, bool masked) __attribute__((always_inline)) {
         const int stage1 = (stage + 1) % STAGES, stage2 = (stage + 2) % STAGES;
         __builtin_amdgcn_s_waitcnt(kLgkm0);
         __builtin_amdgcn_sched_barrier(0);
@@ -612,17 +615,20 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         uint32_t(&p)[8] = pA[0];
         float bsum = 0.f, e = 0.f;
 #pragma unroll
-        for (int g = 0; g < 16; ++g) {
-            asm volatile("" : "+a"(qf[0][g]));
+        for (int g = 0; g < DS; ++g) {
+            if (kHigh) asm volatile("" : "+a"(qf[0][g]));
             xA[0] = mfma_bf16_32x32x16(kf[g], qf[0][g], xA[0]);
-            if (g < 8) read_v_block(stage, g);
-            xv[g] = __builtin_fmaf(xv[g], c, -m[0]);
-            if (masked) xv[g] = wide_visible(blk, g) ? xv[g] : -INFINITY;
-            if (g & 1) {
-                p[g >> 1] = pack_bf16(e, __builtin_amdgcn_exp2f(xv[g]));
-                bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[g >> 1]), ones, bsum, false);
-            } else {
-                e = __builtin_amdgcn_exp2f(xv[g]);
+            if (g < DB) read_v_block(stage, g);
+#pragma unroll
+            for (int r = 16 * g / DS; r < 16 * (g + 1) / DS; ++r) {
+                xv[r] = __builtin_fmaf(xv[r], c, -m[0]);
+                if (masked) xv[r] = is_visible(blk, r) ? xv[r] : -INFINITY;  // exp2 -> probability exactly 0
+                if (r & 1) {
+                    p[r >> 1] = pack_bf16(e, __builtin_amdgcn_exp2f(xv[r]));
+                    bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[r >> 1]), ones, bsum, false);
+                } else {
+                    e = __builtin_amdgcn_exp2f(xv[r]);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -651,13 +657,13 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         sync_and_stream(j + 1, stage1);
         keep_high();
 #pragma unroll
-        for (int g = 0; g < 16; ++g) {
+        for (int g = 0; g < 2 * DB; ++g) {
             const int t = g / DB, db = g % DB;
             const uint4v pw = {p[4 * t], p[4 * t + 1], p[4 * t + 2], p[4 * t + 3]};
             oacc[0][db] = mfma_bf16_32x32x16(vfA[t][db], __builtin_bit_cast(bf16x8, pw), oacc[0][db]);
-            if (g < 8) read_k_pair(stage2, g);
-            if (g == 4) asm volatile("" : "+a"(xA[0]));  // the copies below stay below: the last MFMA of S has its latency behind it
-            if (g >= 4 && g < 12) {
+            if (g < DS / 2) read_k_frag(stage2, 2 * g), read_k_frag(stage2, 2 * g + 1);
+            if (kHigh && g == 4) asm volatile("" : "+a"(xA[0]));  // the copies below stay below: the last MFMA of S has its latency behind it
+            if (kHigh && g >= 4 && g < 12) {
 #pragma unroll
                 for (int r = 2 * (g - 4); r < 2 * (g - 3); ++r) {
                     xv[r] = xA[0][r];
@@ -665,6 +671,10 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!kHigh) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) xv[r] = xA[0][r];
         }
     };
     // Two or four blocks per tile: the last step already reads K of the next tile, so the synchronisation sits
@@ -688,8 +698,8 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
                 else
                     step(kb0 + i + 1, sj, last ? sn : sj, masked, xB, xA, pA, vfA, pB, vfA);
             }
-        } else if (kWide) {
-            wide_step(kb0, j, sj, masked);
+        } else if (kTwoPhase) {
+            two_phase_step(kb0, j, sj, masked);
         } else {
             sync_and_stream(j, sj);
             if (!odd) {
@@ -719,7 +729,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     const int n_unm_tiles = SPARSE ? max(n_tiles - KB64, 0) : max(0, min(n_unm_all - t0, n_tiles));
     const int n_act_tiles = SPARSE ? n_tiles : max(0, min(n_act_all - t0, n_tiles));
     int j = 0;
-    if (kWide) {
+    if (kTwoPhase) {
         sync_and_stream(0, 0);
         read_k(1, 0, kf);
 #pragma unroll
@@ -735,7 +745,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // remaining visible tiles and the partly masked ones (masking a fully visible tile changes nothing)
     int sj = 0;  // j is a multiple of STAGES here (even, where that matters)
     bool owed_in_a = false;  // one block per tile only: the last step left its probabilities in pA, not pB
-    if (KB >= 2 || kWide) {
+    if (KB >= 2 || kTwoPhase) {
 #pragma unroll 1
         for (; j < n_unm_tiles; ++j) {
             tile_steps(j, sj, false, false);
@@ -761,7 +771,7 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         if (j > n_act_tiles) j = n_act_tiles;
     }
     // the Attend still owed for the last block
-    if (kWide) {
+    if (kTwoPhase) {
         // nothing is owed: every step ran its own Attend
     } else if (owed_in_a) {
         attend(vfA, pA);
@@ -770,9 +780,9 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     }
 #pragma unroll 1
     for (; j < n_tiles; ++j) {
-        if (kWide) sj = sj + 1 == STAGES ? 0 : sj + 1;
-        sync_and_stream(j + (kWide ? 1 : 0), sj);
-        if (!kWide) sj = sj + 1 == STAGES ? 0 : sj + 1;
+        if (kTwoPhase) sj = sj + 1 == STAGES ? 0 : sj + 1;
+        sync_and_stream(j + (kTwoPhase ? 1 : 0), sj);
+        if (!kTwoPhase) sj = sj + 1 == STAGES ? 0 : sj + 1;
     }
 
     // ---- key groups: the partial results (reference maximum, row sum, accumulators) of a row's wavefronts meet in the ring's
