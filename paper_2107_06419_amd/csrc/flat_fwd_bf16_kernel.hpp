@@ -109,7 +109,7 @@ struct LaunchGrid {
 };
 
 template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0, int KG = 1>
-__global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 2) void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
+__global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 2) void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                           const bf16* __restrict__ V, bf16* __restrict__ O,
                                                           const Bf16Problem prob, const LaunchGrid grid, float c) {
     using C = Bf16Cfg<D, STAGES, NW, BCX>;
@@ -120,13 +120,20 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     static_assert(NW % KG == 0 && KBT % KG == 0 && D / 8 % KG == 0, "key groups share wavefronts, keys and output columns evenly");
     static_assert(KG == 1 || (!SPARSE && BC % 64 == 0), "the block-sparse variant has one key group");
     static_assert(KB == 1 || KB == 2 || KB == 4, "a wavefront takes one, two or four 32-key blocks of a tile");
-    static_assert(KB != 1 || QB == 1 || STAGES % 2 == 0, "with one block per tile the unrolled loop needs an even ring");
     static_assert(!SPARSE || KB64 >= 1, "block-sparse lists name 64-key tiles");
     constexpr int LOADS_PER_TILE = 2 * C::LOADS;  // DMA instructions per wavefront per tile (K and V)
     // With one block per wavefront and tile, a step is done with its V tile and with the NEXT K tile, so K runs one tile
     // ahead of V in the ring: one more tile in flight for the same LDS, and two stages are enough.
-    constexpr bool kStagger = KB == 1;
-    static_assert(STAGES >= (kStagger ? 2 : 3), "the ring is too short to keep a tile in flight");
+    constexpr bool kHigh = D == 256 || (D == 128 && QB == 2);  // one wavefront per SIMD: the accumulators and Q live in the upper half of its 512 registers
+    // Which shapes take two_phase_step (below) and which the step that spreads all MFMAs of a block through the softmax of its neighbour.  Two
+    // wavefronts of 64 rows per SIMD, or eight wavefronts in lock step, fill each other's gaps in the latter: there two phases are slower (d = 64,
+    // 16 heads x 16384 1110 -> 1141 us; d = 96, 768 causal heads x 512 82.1 -> 86.6).  With less to fill gaps with they win: 128-row shapes of d = 64,
+    // 64 causal heads x 2048 48.6 -> 46.5, d = 128, 16 heads x 8192 566 -> 551, d = 96 471 -> 463; 64 rows per wavefront at d = 32, 16 heads x 8192
+    // 183 -> 178, and at d = 128 (one wavefront per SIMD) 618 -> 490.
+    constexpr bool kTwoPhase = KB == 1 ? QB == 1 || kHigh : KB == 2 && (kHigh || (NW > 1 && (D == 32 || (QB == 1 && NW <= 4))));
+    static_assert(KB != 1 || kTwoPhase || STAGES % 2 == 0, "with one block per tile the unrolled loop needs an even ring");
+    constexpr bool kStagger = KB == 1 || kTwoPhase;
+    static_assert(STAGES >= (KB == 1 ? 2 : 3), "the ring is too short to keep a tile in flight");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // Which (head, row block) this workgroup takes.  Workgroup ids are dealt round-robin to the 8 XCDs, so XCD x
@@ -455,10 +462,6 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // With d = 128 two sets of V fragments do not fit the register file next to the accumulators: then one
     // set is used, refilled in the middle of each step right after the MFMAs that consumed it were issued.
     constexpr bool kTwoVSets = (DP <= 64);
-    // One 32-key block per wavefront and tile: the steps are two_phase_step, below.
-    constexpr bool kTwoPhase = KB == 1 && QB == 1;
-    constexpr bool kHigh = DP == 256;  // one wavefront per SIMD: the accumulators and Q live in the upper half of its 512 registers
-    static_assert(!kHigh || kTwoPhase, "d = 256 is built for 32 rows per wavefront");
     // Pipeline state: xA/xB hold the logits of the current / next block, pA/pB and vfA/vfB the
     // probabilities and V fragments of the block whose Attend is still owed.
     floatx16 xA[QB], xB[QB];
@@ -474,21 +477,23 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
 #pragma unroll
         for (int db = 0; db < DB; ++db) vfA[t][db] = vfB[t][db] = __builtin_bit_cast(bf16x8, (uint4v){0, 0, 0, 0});
     // ---- pieces of a two-phase step
-    float xv[16];  // logits of the current block
+    float xv[QB][16];  // logits of the current block
     // d = 256: kept in the upper half of the register file by name.  Left to itself the compiler carries all 128 accumulators through the
     // lower half in every step, for the rescaling that hardly ever happens.
     auto keep_high = [&]() __attribute__((always_inline)) {
         if (!kHigh) return;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[0][db]));
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[qb][db]));
     };
-    auto is_visible = [&](int blk, int r) __attribute__((always_inline)) {
+    auto is_visible = [&](int blk, int qb, int r) __attribute__((always_inline)) {
         const int key = blk * 32 + acc_row(r, half);
-        return key < N && (!CAUSAL || key <= q0w + l32 + off);
+        return key < N && (!CAUSAL || key <= q0w + 32 * qb + l32 + off);
     };
     // V^T fragments of 32 columns (both 16-key halves), and one of the K fragments
-    auto read_v_block = [&](int stage, int db) __attribute__((always_inline)) {
-        const int at = stage * C::K_STEP + (C::SPLIT_RING ? 0 : C::V_AT);
+    auto read_v_block = [&](int stage, int kb, int db) __attribute__((always_inline)) {
+        const int at = stage * C::K_STEP + (C::SPLIT_RING ? 0 : C::V_AT) + kb * 32 * C::ROWB;
         asm volatile("" : "+v"(voff[db][0]), "+v"(voff[db][1]));
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -497,10 +502,10 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         }
         if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
     };
-    auto read_k_frag = [&](int stage, int ds) __attribute__((always_inline)) {
+    auto read_k_frag = [&](int stage, int kb, int ds) __attribute__((always_inline)) {
         typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
         asm volatile("" : "+v"(koff[ds]));
-        kf[ds] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[ds] + stage * C::K_STEP);
+        kf[ds] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[ds] + stage * C::K_STEP + kb * 32 * C::ROWB);
         if (kSyncEveryPhase) __builtin_amdgcn_s_waitcnt(kLgkm0);
     };
     logits(kf, xA);
@@ -574,11 +579,11 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     auto sync_and_stream = [&](int j, int sj) __attribute__((always_inline)) {
         // A single wavefront has no barrier to wait at: its reads of the stage that is refilled below must be back first.
         if (NW == 1) __builtin_amdgcn_s_waitcnt(kLgkm0);
-        if (kStagger) {  // the step needs V of tile j and K of tile j+1, which were started together
+        if (kStagger) {  // the step needs V of tile j and K of tile j+1, which were started together; two blocks per tile: both of tile j+1
             if (kSyncEveryPhase || j + STAGES - 1 >= n_tiles)
                 wait_vm<0>();
             else
-                wait_vm<(STAGES - 2) * LOADS_PER_TILE>();
+                wait_vm<KB == 1 ? (STAGES - 2) * LOADS_PER_TILE : STAGES < 3 ? 0 : (STAGES - 3) * LOADS_PER_TILE + C::LOADS>();
             __syncthreads();
             if (j + STAGES - 1 < n_tiles) issue_tile_loads(j + STAGES - 1, sj == 0 ? STAGES - 1 : sj - 1, false, true);
             if (j + STAGES < n_tiles) issue_tile_loads(j + STAGES, sj, true, false);
@@ -606,75 +611,102 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     // 3001 130 -> 93 us.  Before, a step read its operands at its start and moved the accumulators twice between the halves of the register file.
     // Key groups: 12 heads x 512, d = 64, 5.31 -> 5.06 us; 4 causal heads x 8192 58.1 -> 50.4; 8 causal x 1024, d = 128, 11.9 -> 10.8; a step of
     // a workgroup alone on its compute unit 900 -> 790 cycles (256 of matrix pipe).  Split keys: 16 heads x 65536 45.7 -> 44.4.
-    auto two_phase_step = [&](int blk, int j, int stage, bool masked) __attribute__((always_inline)) {
-        const int stage1 = (stage + 1) % STAGES, stage2 = (stage + 2) % STAGES;
+    auto two_phase_step = [&](int blk, int j, int stage, int kb, bool masked) __attribute__((always_inline)) {  // block kb of tile j
+        const int stage1 = (stage + 1) % STAGES, stage_k = KB == 1 ? (stage + 2) % STAGES : stage1;
         __builtin_amdgcn_s_waitcnt(kLgkm0);
         __builtin_amdgcn_sched_barrier(0);
+        float bsum[QB], e[QB];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xA[0][r] = 0.f;
-        uint32_t(&p)[8] = pA[0];
-        float bsum = 0.f, e = 0.f;
+        for (int qb = 0; qb < QB; ++qb) {
+            bsum[qb] = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) xA[qb][r] = 0.f;
+        }
 #pragma unroll
         for (int g = 0; g < DS; ++g) {
-            if (kHigh) asm volatile("" : "+a"(qf[0][g]));
-            xA[0] = mfma_bf16_32x32x16(kf[g], qf[0][g], xA[0]);
-            if (g < DB) read_v_block(stage, g);
 #pragma unroll
-            for (int r = 16 * g / DS; r < 16 * (g + 1) / DS; ++r) {
-                xv[r] = __builtin_fmaf(xv[r], c, -m[0]);
-                if (masked) xv[r] = is_visible(blk, r) ? xv[r] : -INFINITY;  // exp2 -> probability exactly 0
-                if (r & 1) {
-                    p[r >> 1] = pack_bf16(e, __builtin_amdgcn_exp2f(xv[r]));
-                    bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[r >> 1]), ones, bsum, false);
-                } else {
-                    e = __builtin_amdgcn_exp2f(xv[r]);
+            for (int qb = 0; qb < QB; ++qb) {
+                if (kHigh) asm volatile("" : "+a"(qf[qb][g]));
+                xA[qb] = mfma_bf16_32x32x16(kf[g], qf[qb][g], xA[qb]);
+                if (qb == 0 && g < DB) read_v_block(stage, kb, g);
+#pragma unroll
+                for (int r = 16 * g / DS; r < 16 * (g + 1) / DS; ++r) {
+                    xv[qb][r] = __builtin_fmaf(xv[qb][r], c, -m[qb]);
+                    if (masked) xv[qb][r] = is_visible(blk, qb, r) ? xv[qb][r] : -INFINITY;  // exp2 -> probability exactly 0
+                    if (r & 1) {
+                        pA[qb][r >> 1] = pack_bf16(e[qb], __builtin_amdgcn_exp2f(xv[qb][r]));
+                        bsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pA[qb][r >> 1]), ones, bsum[qb], false);
+                    } else {
+                        e[qb] = __builtin_amdgcn_exp2f(xv[qb][r]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        bool jump = false;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) jump |= !(bsum[qb] <= kSumJump);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(jump) != 0, 0)) {  // exact path, before this block's Attend
+            keep_high();
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                float top = xv[qb][0];
+#pragma unroll
+                for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, xv[qb][r]);
+                const float delta = __builtin_fmaxf(halves_max(top), 0.f), alpha = __builtin_amdgcn_exp2f(-delta);
+                m[qb] += delta;
+                lsum[qb] *= alpha;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) oacc[qb][db][r] *= alpha;
+                bsum[qb] = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) {
+                    pA[qb][r >> 1] = pack_bf16(__builtin_amdgcn_exp2f(xv[qb][r] - delta), __builtin_amdgcn_exp2f(xv[qb][r + 1] - delta));
+                    bsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pA[qb][r >> 1]), ones, bsum[qb], false);
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(bsum <= kSumJump)) != 0, 0)) {  // exact path, before this block's Attend
-            float top = xv[0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, xv[r]);
-            const float delta = __builtin_fmaxf(halves_max(top), 0.f), alpha = __builtin_amdgcn_exp2f(-delta);
-            m[0] += delta;
-            lsum[0] *= alpha;
             keep_high();
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[0][db][r] *= alpha;
-            keep_high();
-            bsum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                p[r >> 1] = pack_bf16(__builtin_amdgcn_exp2f(xv[r] - delta), __builtin_amdgcn_exp2f(xv[r + 1] - delta));
-                bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[r >> 1]), ones, bsum, false);
-            }
         }
-        lsum[0] += bsum;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) lsum[qb] += bsum[qb];
         __builtin_amdgcn_s_waitcnt(kLgkm0);
-        sync_and_stream(j + 1, stage1);
+        if (KB == 1)
+            sync_and_stream(j + 1, stage1);
+        else if (kb == 0)
+            sync_and_stream(j, stage);
         keep_high();
 #pragma unroll
         for (int g = 0; g < 2 * DB; ++g) {
             const int t = g / DB, db = g % DB;
-            const uint4v pw = {p[4 * t], p[4 * t + 1], p[4 * t + 2], p[4 * t + 3]};
-            oacc[0][db] = mfma_bf16_32x32x16(vfA[t][db], __builtin_bit_cast(bf16x8, pw), oacc[0][db]);
-            if (g < DS / 2) read_k_frag(stage2, 2 * g), read_k_frag(stage2, 2 * g + 1);
-            if (kHigh && g == 4) asm volatile("" : "+a"(xA[0]));  // the copies below stay below: the last MFMA of S has its latency behind it
-            if (kHigh && g >= 4 && g < 12) {
 #pragma unroll
-                for (int r = 2 * (g - 4); r < 2 * (g - 3); ++r) {
-                    xv[r] = xA[0][r];
-                    asm volatile("" : "+v"(xv[r]));
-                }
+            for (int qb = 0; qb < QB; ++qb) {
+                const uint4v pw = {pA[qb][4 * t], pA[qb][4 * t + 1], pA[qb][4 * t + 2], pA[qb][4 * t + 3]};
+                oacc[qb][db] = mfma_bf16_32x32x16(vfA[t][db], __builtin_bit_cast(bf16x8, pw), oacc[qb][db]);
+            }
+            if (g < DS / 2) read_k_frag(stage_k, kb, 2 * g), read_k_frag(stage_k, kb, 2 * g + 1);
+            // the logits move to the vector ALU's half of the registers when the last MFMA of S has had its latency
+            if (kHigh && g == DB / 2) {
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) asm volatile("" : "+a"(xA[qb]));
+            }
+            if (kHigh && g >= DB / 2 && g < DB / 2 + DB) {
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                    for (int r = 16 * (g - DB / 2) / DB; r < 16 * (g - DB / 2 + 1) / DB; ++r) {
+                        xv[qb][r] = xA[qb][r];
+                        asm volatile("" : "+v"(xv[qb][r]));
+                    }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         if (!kHigh) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) xv[r] = xA[0][r];
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xv[qb][r] = xA[qb][r];
         }
     };
     // Two or four blocks per tile: the last step already reads K of the next tile, so the synchronisation sits
@@ -684,7 +716,10 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
         const int sn = sj + 1 == STAGES ? 0 : sj + 1;       // stage of tile j+1
         // first 32-key block of the tile, as a key position / 32 (only the masked form of a step looks at it)
         const int kb0 = KBT * (((SPARSE && masked) || SPLIT) ? tile_of(j) : j) + kg * KB;
-        if (KB >= 2) {
+        if (kTwoPhase) {
+#pragma unroll
+            for (int i = 0; i < KB; ++i) two_phase_step(kb0 + i, j, sj, i, masked);
+        } else if (KB >= 2) {
 #pragma unroll
             for (int i = 0; i < KB; i += 2) {
                 if (kTwoVSets)
@@ -698,8 +733,6 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
                 else
                     step(kb0 + i + 1, sj, last ? sn : sj, masked, xB, xA, pA, vfA, pB, vfA);
             }
-        } else if (kTwoPhase) {
-            two_phase_step(kb0, j, sj, masked);
         } else {
             sync_and_stream(j, sj);
             if (!odd) {
@@ -730,10 +763,12 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     const int n_act_tiles = SPARSE ? n_tiles : max(0, min(n_act_all - t0, n_tiles));
     int j = 0;
     if (kTwoPhase) {
-        sync_and_stream(0, 0);
-        read_k(1, 0, kf);
+        if (KB == 1) sync_and_stream(0, 0);
+        read_k(KB == 1 ? 1 : 0, KB - 1, kf);  // of the second block
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xv[r] = xA[0][r];
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) xv[qb][r] = xA[qb][r];
         __builtin_amdgcn_sched_barrier(0);
     }
     // main loop: STAGES fully visible tiles per trip, so that every ring stage index is a constant
@@ -780,9 +815,10 @@ __global__ __launch_bounds__(64 * NW, ((D == 128 && QB == 2) || D == 256) ? 1 : 
     }
 #pragma unroll 1
     for (; j < n_tiles; ++j) {
-        if (kTwoPhase) sj = sj + 1 == STAGES ? 0 : sj + 1;
-        sync_and_stream(j + (kTwoPhase ? 1 : 0), sj);
-        if (!kTwoPhase) sj = sj + 1 == STAGES ? 0 : sj + 1;
+        constexpr bool kAhead = kTwoPhase && KB == 1;  // a tile's step has gone past the synchronisation of the next one
+        if (kAhead) sj = sj + 1 == STAGES ? 0 : sj + 1;
+        sync_and_stream(j + (kAhead ? 1 : 0), sj);
+        if (!kAhead) sj = sj + 1 == STAGES ? 0 : sj + 1;
     }
 
     // ---- key groups: the partial results (reference maximum, row sum, accumulators) of a row's wavefronts meet in the ring's
