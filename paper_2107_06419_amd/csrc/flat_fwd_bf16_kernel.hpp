@@ -101,10 +101,14 @@ constexpr int kMaxSparseTiles = 2048;  // block-sparse: listed tiles per row blo
 // kSplit = the keys of one row block are divided over prob.n_splits workgroups, each of which leaves its
 // unnormalised result (reference maximum, row sum, accumulators) in a workspace for split_merge_kernel.
 constexpr int kDense = 0, kSparse = 1, kSplit = 2;
+constexpr bool loops_over_blocks(int d, bool causal, int mode, int key_groups) {
+    return mode == kDense && !causal && key_groups == 1 && (d == 96 || d == 128);
+}
 
-// How the workgroups of a launch are numbered: n_blocks = n_heads * n_qtiles, n_qtiles = row blocks (times splits) per head.
+// How the workgroups of a launch are numbered: n_blocks = n_heads * n_qtiles, n_qtiles = row blocks (times splits) per head.  stride:
+// workgroups launched per XCD; the workgroup in position t of an XCD takes blocks t, t + stride, ... of it.
 struct LaunchGrid {
-    int n_qtiles, n_blocks, blocks_per_xcd, n_heads, n_row_blocks;
+    int n_qtiles, n_blocks, blocks_per_xcd, stride, n_heads, n_row_blocks;
     Divisor by_qtiles, by_heads, by_splits, by_heads_per_batch;
 };
 
@@ -147,14 +151,20 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     // heads.  When two workgroups fit a compute unit the hardware places positions t and t+32 of an XCD's
     // sequence on the same unit in the first round; the second half of every 64 positions is therefore taken in
     // reverse, which pairs the k-th heaviest of the 64 with the k-th lightest.
+    // Without a mask all blocks are equal, and a workgroup that has its compute unit to itself goes on to another one: nothing else covers the
+    // fetch of a block's Q rows and first tile (8000 of 41000 cycles at d = 128 and 512 keys), so the next block's go out before the results of
+    // this one are put together.  512 heads x 512, d = 128, 92.4 -> 87.2 us; 768 x 512, d = 96, 112.5 -> 106.5; 16 x 8192, d = 128, 467.6 -> 466.3.
+    // At d = 64 and 32 a second workgroup covers it, and the loop costs registers (16 x 16384, d = 64, 977 -> 1019 us); at d = 256 Q goes to
+    // registers the accumulators' store still needs (256 x 128 16.5 -> 17.2 us).  Key counts that differ leave the dealing to the hardware.
+    constexpr bool kLoop = loops_over_blocks(D, CAUSAL, MODE, KG);
     static_assert(!(CAUSAL && SPARSE), "the block-sparse variant has no causal form");
     // All arguments in one round trip: left alone, the compiler fetches some, waits, divides, and fetches the rest (a first workgroup
     // of a compute unit pays about 600 cycles for each).
     const int n_qtiles = grid.n_qtiles, blocks_per_xcd = grid.blocks_per_xcd;
     int n_blocks = grid.n_blocks;
     asm("" : "+s"(n_blocks) : "s"(Q), "s"(K), "s"(V), "s"(O), "s"(prob.Nq), "s"(prob.Nk), "s"((uint64_t)prob.kv_lens), "s"(prob.causal_offset), "s"(n_qtiles),
-        "s"(blocks_per_xcd), "s"(grid.by_qtiles.mul), "s"(grid.by_qtiles.shift), "s"(grid.by_heads_per_batch.mul), "s"(grid.by_heads_per_batch.shift), "s"(c));
-    int bh, qt;
+        "s"(blocks_per_xcd), "s"(grid.stride), "s"(grid.by_qtiles.mul), "s"(grid.by_qtiles.shift), "s"(grid.by_heads_per_batch.mul), "s"(grid.by_heads_per_batch.shift), "s"(c));
+    int bh, qt, block_of_xcd = blockIdx.x >> 3;
     if (!CAUSAL) {
         const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
         if (logical >= n_blocks) return;
@@ -183,16 +193,22 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     // Nq query rows per head; N = number of keys of this head that count (the padded tail of a shorter batch
     // entry is masked like the tail of a ragged tile); causal: query i sees keys 0 .. i + off.
     const int Nq = prob.Nq, off = prob.causal_offset;
-    int N = prob.Nk;
-    if (prob.kv_lens) N = max(1, min(prob.Nk, prob.kv_lens[grid.by_heads_per_batch.quotient(bh)]));
-    const size_t head_q = (size_t)bh * Nq * D, head_k = (size_t)bh * prob.Nk * D;
-    const char* Qh = (const char*)(Q + head_q);
-    const char* Kh = (const char*)(K + head_k);
-    const char* Vh = (const char*)(V + head_k);
-    bf16* Oh = O + head_q;
     // Key groups: wavefronts rg * KG + kg, kg = 0 .. KG-1, own the same QW query rows and take KB of every tile's blocks each.
     const int kg = KG == 1 ? 0 : wave % KG, rg = KG == 1 ? wave : wave / KG;
-    const int q0w = qt * BR + rg * QW;
+    int N, q0w;
+    const char *Qh, *Kh, *Vh;
+    bf16* Oh;
+    auto place = [&]() __attribute__((always_inline)) {  // of block (bh, qt)
+        N = prob.Nk;
+        if (prob.kv_lens) N = max(1, min(prob.Nk, prob.kv_lens[grid.by_heads_per_batch.quotient(bh)]));
+        const size_t head_q = (size_t)bh * Nq * D, head_k = (size_t)bh * prob.Nk * D;
+        Qh = (const char*)(Q + head_q);
+        Kh = (const char*)(K + head_k);
+        Vh = (const char*)(V + head_k);
+        Oh = O + head_q;
+        q0w = qt * BR + rg * QW;
+    };
+    place();
 
     // Block-sparse: copy this row block's tile list into LDS (ids forced into range; a wrong list can give a
     // wrong result but no stray access).
@@ -223,17 +239,9 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
 
     floatx16 oacc[QB][DB];
     float lsum[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        lsum[qb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[qb][db][r] = 0.f;
-    }
 
     const int n_tiles_seen = (kv_len + BC - 1) / BC;  // tiles the row block sees
-    const int n_tiles = SPARSE ? sp_count * KB64                                              // tiles this workgroup visits
+    int n_tiles = SPARSE ? sp_count * KB64                                              // tiles this workgroup visits
                         : SPLIT ? max(0, min(n_tiles_seen - t0, prob.tiles_per_split)) : n_tiles_seen;
 
     // ---- global -> LDS streaming.  Wave w issues load i of a tile for the 1024-byte LDS block
@@ -407,28 +415,33 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     static_assert(kQAt + kQBytes <= bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG), "the Q rows must fit the LDS a launch asks for");
     static_assert(!SPARSE || kQAt + kQBytes <= C::LDS_BYTES, "the Q rows must not reach the block-sparse list behind the ring");
     constexpr int kEarlyTiles = kQAt / C::STAGE < STAGES - 1 ? kQAt / C::STAGE : STAGES - 1;
-    if (kQThroughLds) {
-        constexpr int kQLoads = BR / C::ROWS_PER_LOAD;
+    auto load_q = [&]() __attribute__((always_inline)) {
+        // (addresses from a lane index the compiler cannot follow, or it keeps them all in registers for the next block)
+        int ln = lane;
+        if (kLoop) asm volatile("" : "+v"(ln));
+        if (kQThroughLds) {
+            constexpr int kQLoads = BR / C::ROWS_PER_LOAD;
 #pragma unroll
-        for (int i = 0; i < (kQLoads + NW - 1) / NW; ++i) {
-            const int blk = NW * i + wave;  // 1024-byte block of the Q rows
-            if (kQLoads % NW != 0 && blk >= kQLoads) break;
-            const int r = blk * C::ROWS_PER_LOAD + lane / C::CHUNKS, chunk = (lane % C::CHUNKS) ^ C::swz(r);
-            const int row = min(qt * BR + r, Nq - 1);  // rows past the end repeat the last one; they are never stored
-            const uint32_t off_q = (uint32_t)row * C::GROWB + (chunk < C::GCHUNKS ? chunk : chunk - (C::CHUNKS - C::GCHUNKS)) * 16;
-            dma16(Qh, off_q, __builtin_amdgcn_readfirstlane(smem_base + kQAt + blk * 1024));
-        }
-    } else {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int ds = 0; ds < DS; ++ds) {
-                const int row = q0w + 32 * qb + l32;
-                uint4v z = {0, 0, 0, 0};
-                if (row < Nq) z = *(const uint4v*)(Qh + (size_t)row * C::GROWB + ds * 32 + half * 16);
-                qf[qb][ds] = __builtin_bit_cast(bf16x8, z);
+            for (int i = 0; i < (kQLoads + NW - 1) / NW; ++i) {
+                const int blk = NW * i + wave;  // 1024-byte block of the Q rows
+                if (kQLoads % NW != 0 && blk >= kQLoads) break;
+                const int r = blk * C::ROWS_PER_LOAD + ln / C::CHUNKS, chunk = (ln % C::CHUNKS) ^ C::swz(r);
+                const int row = min(qt * BR + r, Nq - 1);  // rows past the end repeat the last one; they are never stored
+                const uint32_t off_q = (uint32_t)row * C::GROWB + (chunk < C::GCHUNKS ? chunk : chunk - (C::CHUNKS - C::GCHUNKS)) * 16;
+                dma16(Qh, off_q, __builtin_amdgcn_readfirstlane(smem_base + kQAt + blk * 1024));
             }
-    }
+        } else {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int ds = 0; ds < DS; ++ds) {
+                    const int row = q0w + 32 * qb + (ln & 31);
+                    uint4v z = {0, 0, 0, 0};
+                    if (row < Nq) z = *(const uint4v*)(Qh + (size_t)row * C::GROWB + ds * 32 + (ln >> 5) * 16);
+                    qf[qb][ds] = __builtin_bit_cast(bf16x8, z);
+                }
+        }
+    };
     auto fill = [&](int t) __attribute__((always_inline)) {
         if (t >= n_tiles) return;
         if (kStagger) {  // K first, in the order the loop goes on with and its wait counts: K(t), V(t), K(t+1), ...
@@ -438,22 +451,40 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
             issue_tile_loads(t, t);
         }
     };
+    auto start_loads = [&]() __attribute__((always_inline)) {
+        load_q();
 #pragma unroll
-    for (int t = 0; t < kEarlyTiles; ++t) fill(t);
-    if (kQThroughLds && !kSyncEveryPhase && n_tiles >= kEarlyTiles)
-        wait_vm<(kEarlyTiles - 1) * LOADS_PER_TILE>();
-    else
-        wait_vm<0>();
+        for (int t = 0; t < kEarlyTiles; ++t) fill(t);
+    };
+    auto await_first = [&]() __attribute__((always_inline)) {
+        if (kQThroughLds && !kSyncEveryPhase && n_tiles >= kEarlyTiles)
+            wait_vm<(kEarlyTiles - 1) * LOADS_PER_TILE>();
+        else
+            wait_vm<0>();
+    };
+    start_loads();
+    await_first();
+    for (;;) {  // over the blocks of this workgroup
     __syncthreads();
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        lsum[qb] = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[qb][db][r] = 0.f;
+    }
     bf16x8 kf[DS];  // K fragments of one block
     read_k(0, 0, kf);
     if (kQThroughLds) {
         typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
+        int ln = lane;
+        if (kLoop) asm volatile("" : "+v"(ln));
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
             for (int ds = 0; ds < DS; ++ds)
-                qf[qb][ds] = *(lds_frag_ptr)(uintptr_t)(smem_base + kQAt + (rg * QW + 32 * qb + l32) * C::ROWB + (((2 * ds + half) ^ C::swz(l32)) << 4));
+                qf[qb][ds] = *(lds_frag_ptr)(uintptr_t)(smem_base + kQAt + (rg * QW + 32 * qb + (ln & 31)) * C::ROWB + (((2 * ds + (ln >> 5)) ^ C::swz(ln & 31)) << 4));
     }
     if (kQThroughLds) __syncthreads();  // every wavefront has its fragments: the ring takes their place
 #pragma unroll
@@ -916,11 +947,29 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     // 4; two quads are swapped across the halves so that every lane stores 8 consecutive columns.  Short sequences are bound by
     // memory and by their start and end: half as many stores of twice the width, 768 heads x 512, d = 64: 66 -> 62 us; 1024 x 128
     // 16.3 -> 15.0; d = 128, 768 x 512: 158 -> 147.
+    // Where the workgroup has another block, its first loads go out before the results of this one are put together, and are awaited
+    // before they are stored.
+    bf16* const O_done = Oh;
+    const int row_done = q0w + l32;
+    bool more = false;
+    if (kLoop) {
+        block_of_xcd += grid.stride;
+        const int logical = (blockIdx.x & 7) * blocks_per_xcd + block_of_xcd;
+        more = block_of_xcd < blocks_per_xcd && logical < n_blocks;
+        if (more) {
+            bh = grid.by_qtiles.quotient(logical);
+            qt = logical - bh * n_qtiles;
+            place();
+            n_tiles = (N + BC - 1) / BC;
+            __syncthreads();  // every wavefront is past its last read of the ring
+            start_loads();
+        }
+    }
+    uint4v out[QB][DB][2];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const float total = halves_sum(lsum[qb]);
         const float inv = (SPARSE && n_tiles == 0) ? 0.f : 1.0f / total;  // a row block with an empty list yields zeros
-        const int row = q0w + 32 * qb + l32;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -935,9 +984,24 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
                     }
                 const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
                 const auto hi = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-                const uint4v o8 = {(uint32_t)lo[0], (uint32_t)hi[0], (uint32_t)lo[1], (uint32_t)hi[1]};
-                if (row < Nq) *(uint4v*)(Oh + (size_t)row * D + 32 * db + 16 * rp + 8 * half) = o8;
+                out[qb][db][rp] = uint4v{(uint32_t)lo[0], (uint32_t)hi[0], (uint32_t)lo[1], (uint32_t)hi[1]};
+                if (!kLoop && row_done + 32 * qb < Nq)
+                    *(uint4v*)(O_done + (size_t)(row_done + 32 * qb) * D + 32 * db + 16 * rp + 8 * half) = out[qb][db][rp];
             }
+    }
+    if (!kLoop) return;
+    if (more) await_first();
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int row = row_done + 32 * qb;
+        if (row < Nq) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int rp = 0; rp < 2; ++rp) *(uint4v*)(O_done + (size_t)row * D + 32 * db + 16 * rp + 8 * half) = out[qb][db][rp];
+        }
+    }
+    if (!more) return;
     }
 }
 
@@ -948,15 +1012,28 @@ inline hipError_t launch_cfg(const void* Q, const void* K, const void* V, void* 
     // split keys: the kernel sees (row block, split) pairs where the other modes see row blocks
     const int n_row_blocks = (prob.Nq + BR - 1) / BR, n_splits = MODE == kSplit ? prob.n_splits : 1;
     const int n_qtiles = n_row_blocks * n_splits, n_blocks = BH * n_qtiles;
-    const LaunchGrid grid{n_qtiles, n_blocks, (n_blocks + 7) / 8, BH, n_row_blocks, Divisor(n_qtiles), Divisor(BH), Divisor(n_splits),
-                          Divisor(prob.heads_per_batch)};
     auto kern = fwd_bf16_kernel<D, QB, NW, STAGES, CAUSAL, MODE, BCX, KG>;
     constexpr int lds = bf16_lds_bytes(D, QB, NW, STAGES, BCX, KG) + (MODE == kSparse ? kMaxSparseTiles * (int)sizeof(int) : 0);
     static_assert(lds <= 160 * 1024, "more LDS than a compute unit has");
     static std::atomic<uint64_t> attr_done{0};  // one flag per kernel instantiation
     hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid.blocks_per_xcd * 8), dim3(64 * NW), lds, stream, (const bf16*)Q, (const bf16*)K,
+    const int blocks_per_xcd = (n_blocks + 7) / 8;
+    int stride = blocks_per_xcd;
+    if (loops_over_blocks(D, CAUSAL, MODE, KG) && !prob.kv_lens) {
+        static std::atomic<int> per_cu{0};
+        int n = per_cu.load(std::memory_order_relaxed);
+        if (n == 0) {
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, 64 * NW, lds);
+            if (e != hipSuccess) return e;
+            if (n < 1) n = 1;
+            per_cu.store(n, std::memory_order_relaxed);
+        }
+        if (stride > 32 * n) stride = 32 * n;
+    }
+    const LaunchGrid grid{n_qtiles, n_blocks, blocks_per_xcd, stride, BH, n_row_blocks, Divisor(n_qtiles), Divisor(BH), Divisor(n_splits),
+                          Divisor(prob.heads_per_batch)};
+    hipLaunchKernelGGL(kern, dim3(stride * 8), dim3(64 * NW), lds, stream, (const bf16*)Q, (const bf16*)K,
                        (const bf16*)V, (bf16*)O, prob, grid, scale * kLog2e);
     return hipGetLastError();
 }

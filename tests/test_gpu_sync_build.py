@@ -115,3 +115,28 @@ def test_release_and_fully_synchronised_builds_agree_for_every_tile_shape(d):
             torch.cuda.synchronize()
             assert torch.isfinite(rel.float()).all()
             assert torch.equal(rel.view(torch.int16), chk.view(torch.int16))
+
+
+# more blocks than the launch has workgroups, by one, two rounds and a rest, and three; one tile (and less), a ragged tail, and as many tiles
+# as the ring has stages
+@pytest.mark.parametrize("H,Nq,Nk", [(257, 256, 64), (257, 17, 33), (300, 300, 129), (128, 700, 192), (200, 900, 1000)])
+@pytest.mark.parametrize("d", [96, 128])
+def test_workgroups_with_several_blocks(d, H, Nq, Nk):
+    """Against the fully synchronised build, bit for bit, and against fp32 attention: without a mask a workgroup goes on to its next block,
+    whose loads overlap the results of the one before."""
+    import torch
+    lib = _sync_lib()
+    gen = torch.Generator(device="cuda").manual_seed(d + H + Nq + Nk)
+    q, k, v = (torch.randn(1, H, n, d, generator=gen, device="cuda").to(torch.bfloat16) for n in (Nq, Nk, Nk))
+    rel, chk = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    scale = float(np.float32(d ** -0.5))
+    print(f"case several blocks d={d} H={H} Nq={Nq} Nk={Nk}", flush=True)
+    fa.flat_attn_fwd_cross(q, k, v, rel, scale, 0, None)
+    assert lib.flat_attn_fwd_cross(q.data_ptr(), k.data_ptr(), v.data_ptr(), chk.data_ptr(), 1, H, Nq, Nk, d, scale, 0, None,
+                                   torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(rel.view(torch.int16), chk.view(torch.int16))
+    qf, kf, vf = (x.float() for x in (q, k, v))
+    ref = torch.softmax(torch.matmul(qf, kf.transpose(-1, -2).contiguous()) * scale, dim=-1) @ vf
+    # bf16 rounding of probabilities and results: 2^-9 of the result each, and of the largest results at most 2e-2 as elsewhere
+    assert (rel.float() - ref).abs().max() <= 2e-2 and (rel.float() - ref).abs().sum() <= 5e-3 * ref.abs().sum()
