@@ -9,35 +9,6 @@ namespace {
 // The 128-row shape of a head size, for launches of few query rows (0: there is none).
 int small_launch_shape(int d) { return d == 64 ? 7 : d == 128 ? 2 : d == 32 || d == 96 ? 1 : 0; }
 
-// The shape a launch takes if none of its key-group forms is faster: index 0, except where a measured sweep (python -m
-// paper_2107_06419_amd.tile_sweep --small: 1 to 512 heads of 128 to 8192 positions, both masks, several machines)
-// shows the 128-row shape of the head dimension ahead:
-//   * launches too small to give every compute unit a 256-row workgroup - at most 128 blocks of 256 query rows (causal:
-//     256 at d = 32 / 64, 192 at d = 96 / 128): 1.3-1.5 times faster, simply because twice as many compute units work;
-//   * d = 64 with the causal mask, up to 4096 positions and 1024 row blocks: ahead by up to 15 %, never behind;
-//   * d = 32 (the vector side is the longer pole there and three workgroups per compute unit hide more of it): with
-//     the causal mask up to 8192 positions (4-18 %), without it up to 4096 positions and 1024 row blocks (6 %).
-//   * up to 128 query rows, where half of a 256-row workgroup or more would be padding (256 heads of 16 rows over 1024
-//     keys, d = 64: 23 us on 256 rows, 16 on 128; 2048 heads of 100 rows: 162 and 119 us).
-// Beyond these ranges the 128-row shapes lose 1-15 %.  No other shape is ahead of index 0 by more than the
-// run-to-run spread (the 512-row shape leads by 3 % for d = 64, causal, when B*H*ceil(N/512) is exactly 512, and
-// trails by 2-15 % with more or fewer row blocks: no rule is built on that).
-int base_tile_shape(int BH, int Nq, int d, int causal) {
-    const long long blocks = (long long)BH * (((long long)Nq + 255) / 256);  // 256-row blocks in the launch
-    if (Nq <= 128 && d != 256) return small_launch_shape(d);  // a 256-row workgroup would be at least half padding
-    switch (d) {
-        case 32:
-            if (causal) return Nq <= 8192 ? 1 : 0;
-            return (Nq > 512 && ((Nq <= 4096 && blocks <= 1024) || blocks <= 128)) ? 1 : 0;
-        case 64:
-            if (causal) return (Nq > 256 && blocks <= (Nq <= 4096 ? 1024 : 256)) ? 7 : 0;
-            return (Nq > 256 && blocks <= 128) ? 7 : 0;
-        case 96: return blocks <= (causal ? 192 : 128) ? 1 : 0;
-        case 128: return blocks <= (causal ? 192 : 128) ? 2 : 0;
-        default: return 0;
-    }
-}
-
 }  // namespace
 
 // ---- Key-group forms.  A launch of few query rows leaves most of the chip idle on the base shapes, whatever their rows per
@@ -90,6 +61,12 @@ const Choice kChoices[] = {
      {{64, 64, 1, {0.34f, 1.459f, 10.02f, 1.459f, 0.15f}}}},
 };
 
+const Choice* choice_of(int d) {
+    for (const Choice& c : kChoices)
+        if (c.d == d) return &c;
+    return nullptr;
+}
+
 float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int causal) {
     const long long wgs = (long long)BH * ((prob.Nq + (long long)f.rows - 1) / f.rows), per_cu = (wgs + 255) / 256;
     const float tiles = (float)((prob.Nk + (long long)f.keys_per_tile - 1) / f.keys_per_tile);
@@ -125,6 +102,44 @@ float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int ca
     return f.cost.start + (work > memory ? work : memory);
 }
 
+// The shape a launch takes if none of its key-group forms is faster: index 0, except where a measured sweep (python -m
+// paper_2107_06419_amd.tile_sweep --small: 1 to 512 heads of 128 to 8192 positions, both masks, several machines)
+// shows the 128-row shape of the head dimension ahead:
+//   * launches too small to give every compute unit a 256-row workgroup - at most 128 blocks of 256 query rows (causal:
+//     256 at d = 32 / 64, 192 at d = 96 / 128): 1.3-1.5 times faster, simply because twice as many compute units work;
+//   * d = 64 with the causal mask, up to 4096 positions and 1024 row blocks: ahead by up to 15 %, never behind;
+//   * d = 32 with the causal mask up to 8192 positions (4-18 %: the vector side is the longer pole there and three workgroups per
+//     compute unit hide more of it);
+//   * up to 128 query rows, where half of a 256-row workgroup or more would be padding (256 heads of 16 rows over 1024
+//     keys, d = 64: 23 us on 256 rows, 16 on 128; 2048 heads of 100 rows: 162 and 119 us).
+// At d = 64 and 32 without a mask the predicted times of the two decide, by 3 %.  Half the rows per workgroup and three workgroups per compute
+// unit instead of two waste less on the last row block and the last round, and cost 4-8 % where neither counts: 87 heads x 537, d = 64,
+// 21.5 us on 256 rows, 14.8 on 128; 143 x 316 14.7 and 10.3; 26 x 3302 96.7 and 86.2; 457 x 849 124 and 111; 16 x 16384 1029 and 1145.
+// Over 4900 random problems the choice changes for 650, which get 6-10 % faster on average (20-25 % at best, 17 % slower at worst); it is 0.6 %
+// behind the fastest shape or form on average, 1.7 % with rules on the number of row blocks.  Key counts that differ favour more and shorter
+// workgroups: there the 128-row shape is taken up to 5 % behind (192 heads, 250 rows over 506 to 1011 keys: 21.5 and 19.1 us).  Heads of exactly one
+// or two full 256-row blocks keep to those rules (flat_attn_tile_shape_default promises it for 129 heads x 512; they have no last row block to
+// waste anything on).
+int base_tile_shape(int BH, const Bf16Problem& prob, int d, int causal) {
+    const int Nq = prob.Nq;
+    const long long blocks = (long long)BH * (((long long)Nq + 255) / 256);  // 256-row blocks in the launch
+    if (Nq <= 128 && d != 256) return small_launch_shape(d);  // a 256-row workgroup would be at least half padding
+    if ((d == 64 || d == 32) && !causal && (Nq > 512 || Nq % 256 != 0)) {
+        const Form* base = choice_of(d)->base;
+        const float margin = prob.kv_lens ? 0.95f : 1.03f;
+        return predicted_us(base[1], BH, prob, d, 0) * margin < predicted_us(base[0], BH, prob, d, 0) ? small_launch_shape(d) : 0;
+    }
+    switch (d) {
+        case 32: return causal && Nq <= 8192 ? 1 : 0;
+        case 64:
+            if (causal) return (Nq > 256 && blocks <= (Nq <= 4096 ? 1024 : 256)) ? 7 : 0;
+            return (Nq > 256 && blocks <= 128) ? 7 : 0;
+        case 96: return blocks <= (causal ? 192 : 128) ? 1 : 0;
+        case 128: return blocks <= (causal ? 192 : 128) ? 2 : 0;
+        default: return 0;
+    }
+}
+
 // The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1
 // times as long (what the prediction is worth) or there is one tile, and so nothing to divide.
 int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
@@ -132,24 +147,22 @@ int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index
     // 12.0, 7 causal heads, 55 rows over 80 keys, 10.8 and 12.1.  In causal self-attention the form wins there too (2 x 75: 10.5 and 11.4).
     const bool triangle = causal && prob.causal_offset == 0;
     if (prob.Nk <= (d == 256 && !triangle ? 96 : 64)) return -1;
-    for (const Choice& c : kChoices) {
-        if (c.d != d) continue;
-        int best = -1;
-        float limit = predicted_us(c.base[index == 0 ? 0 : 1], BH, prob, d, causal) / 1.1f;
-        for (int i = 0; i < c.n_forms; ++i) {
-            const float t = predicted_us(c.forms[i], BH, prob, d, causal);
-            if (t < limit) limit = t, best = i;
-        }
-        return best;
+    const Choice* c = choice_of(d);
+    if (!c) return -1;
+    int best = -1;
+    float limit = predicted_us(c->base[index == 0 ? 0 : 1], BH, prob, d, causal) / 1.1f;
+    for (int i = 0; i < c->n_forms; ++i) {
+        const float t = predicted_us(c->forms[i], BH, prob, d, causal);
+        if (t < limit) limit = t, best = i;
     }
-    return -1;
+    return best;
 }
 
 }  // namespace
 
 // The index flat_attn_fwd / flat_attn_fwd_cross run: a base shape or its key-group form.
 int chosen_tile_shape(int BH, const Bf16Problem& prob, int d, int causal) {
-    const int base = base_tile_shape(BH, prob.Nq, d, causal), form = key_group_form(BH, prob, d, causal, base);
+    const int base = base_tile_shape(BH, prob, d, causal), form = key_group_form(BH, prob, d, causal, base);
     return form < 0 ? base : first_key_group_form(d) + form;
 }
 
