@@ -90,3 +90,14 @@ def test_a_group_whose_keys_a_row_does_not_see_weighs_nothing(d, Nq, Nk):
     fa.flat_attn_fwd_splitkv(dq, dk, dv, out, scale, 1, None, 2, ws)
     torch.cuda.synchronize()
     check_close(to_host_f64(out), ref, "bf16", "unseen shares, two splits")
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk", [(2, 65, 40, 90), (3, 43, 300, 310), (1, 8, 33, 100), (15, 16, 129, 140)])
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
+def test_heads_dealt_over_the_xcds(B, H, Nq, Nk, d):
+    """Key counts over fewer than 16 batch entries, with head counts that eight divides and (from 128 heads on) does not."""
+    q, k, v = rounded((B, H, Nq, d), 88, 0), rounded((B, H, Nk, d), 88, 1), rounded((B, H, Nk, d), 88, 2)
+    lens = np.linspace(1, Nk, B).astype(np.int64) if B > 1 else np.array([Nk - 7])
+    scale = float(np.float32(d ** -0.5))
+    print(f"case dealt heads B={B} H={H} Nq={Nq} Nk={Nk} d={d}", flush=True)
+    check_close(run_both(q, k, v, scale, 0, [int(x) for x in lens]), oracle.attention_cross(q, k, v, scale, 0, kv_lens=lens), "bf16", "dealt heads")
