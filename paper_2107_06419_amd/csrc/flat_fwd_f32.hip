@@ -58,7 +58,8 @@ constexpr float kF32Headroom = 4.0f;  // of the reference maximum above the row 
 template <int D, int NW, bool CAUSAL>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                                           const float* __restrict__ V, float* __restrict__ O, int N,
-                                                                          int n_qtiles, int n_blocks, int blocks_per_xcd, float c) {
+                                                                          int n_qtiles, int n_blocks, int blocks_per_xcd, int n_heads,
+                                                                          const Divisor by_qtiles, const Divisor by_heads, float c) {
     using C = F32Cfg<D>;
     constexpr int G = C::G, DB = C::DB, LOADS = C::LOADS;
     typedef float floatdb __attribute__((ext_vector_type(DB)));
@@ -68,18 +69,20 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
 
     // Without a mask an XCD takes a contiguous range of (head, row block) pairs, so that a head's K and V stay in one L2; with the
     // causal mask the blocks are ranked heaviest first over all heads and dealt to the XCDs in turn.
+    // (all arguments in one round trip, as in the bf16 kernel)
+    asm("" : "+s"(n_blocks), "+s"(blocks_per_xcd) : "s"(Q), "s"(K), "s"(V), "s"(O), "s"(N), "s"(n_qtiles), "s"(n_heads), "s"(by_qtiles.mul), "s"(by_qtiles.shift),
+        "s"(by_heads.mul), "s"(by_heads.shift), "s"(c));
     int bh, qt;
     if (!CAUSAL) {
         const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
         if (logical >= n_blocks) return;
-        bh = logical / n_qtiles;
+        bh = by_qtiles.quotient(logical);
         qt = logical - bh * n_qtiles;
     } else {
         const int rank = blockIdx.x;
         if (rank >= n_blocks) return;
-        const int heads = n_blocks / n_qtiles;
-        const int from_end = rank / heads;
-        bh = rank - from_end * heads;
+        const int from_end = by_heads.quotient(rank);
+        bh = rank - from_end * n_heads;
         qt = n_qtiles - 1 - from_end;
     }
 
@@ -284,7 +287,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (risen) rescale(top);
+            if (__builtin_expect(risen, 0)) rescale(top);
         };
         int i = 0;
 #pragma unroll 1
@@ -378,8 +381,8 @@ static hipError_t launch_shape(const float* Q, const float* K, const float* V, f
     static std::atomic<uint64_t> attr_done{0};
     hipError_t e = allow_dynamic_lds((const void*)kern, lds, &attr_done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(blocks_per_xcd * 8), dim3(64 * NW), lds, stream, Q, K, V, O, N, n_qtiles, n_blocks, blocks_per_xcd,
-                       scale * kLog2e);
+    hipLaunchKernelGGL(kern, dim3(blocks_per_xcd * 8), dim3(64 * NW), lds, stream, Q, K, V, O, N, n_qtiles, n_blocks, blocks_per_xcd, BH,
+                       Divisor(n_qtiles), Divisor(BH), scale * kLog2e);
     return hipGetLastError();
 }
 
