@@ -470,7 +470,7 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     };
     start_loads();
     await_first();
-    for (;;) {  // over the blocks of this workgroup
+    for (;;) {  // over the blocks of this workgroup, to the end of the kernel (not indented)
     __syncthreads();
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {

@@ -17,18 +17,18 @@ int small_launch_shape(int d) { return d == 64 ? 7 : d == 128 ? 2 : d == 32 || d
 // and V from L2 more often per flop, so large launches keep the base shapes.  Each holds a step of K and V per wavefront in
 // a ring of two stages (K runs one tile ahead of V); deeper rings measured 3-25 % slower where they cost a workgroup per
 // compute unit, so only d = 32, whose tiles are small, has four.
-// Measured, us, best base shape -> form: 12 heads x 512, d = 64, 9.8 -> 6.5; 4 x 4096, d = 64, 47.6 -> 26.4; 2 causal
-// x 8192, d = 64, 86.7 -> 39.2; 8 x 1024, d = 128, 22.2 -> 13.3; 4 x 4096, d = 256, 175 -> 109; 64 x 16 rows over 4096 keys,
-// d = 64, 46 -> 24.
+// Measured, us, best base shape -> form: 12 heads x 512, d = 64, 7.8 -> 5.1; 4 x 4096, d = 64, 40.1 -> 24.8, causal 40.0 -> 20.4;
+// 4 x 4096, d = 256, 110.7 -> 86.7, causal 109.3 -> 76.1; 64 x 16 rows over 4096 keys, d = 64, 46 -> 22.
 //
 // The choice is by predicted time.  A form (and each base shape) has five measured costs: us to launch, start and drain (`start`),
 // us per tile and per workgroup when a workgroup runs alone (`step`, `fixed`), us per tile when the compute unit holds as
 // many workgroups as fit (`busy`), and the share of its longest workgroup that a causal launch ends late (`skew`).  They were
 // fitted by hand-run least squares to 1750 timings (1 to 2048 heads, 16 to 300 query rows over 300 to 4096 keys and 64 to 16384
-// positions, both masks, five head sizes, inputs that stay in the caches), before the epilogue and the start of a workgroup
-// took their present form.  What the choice is worth on the kernels as they are, python -m paper_2107_06419_amd.tile_sweep --forms
-// says: over 1050 self-attention problems it is 0-2 % behind the fastest on average, 32 % at worst, where the better base
-// shape is 13-22 % behind on average, and no form that runs is more than 8 % slower than the base shape it replaces.
+// positions, both masks, five head sizes, inputs that stay in the caches), before the steps, the epilogue and the start of a workgroup
+// took their present form.  (Refitted to 21671 timings of the kernels as they are, the choice was no better: 1.0 % behind the fastest on average
+// against 0.9 %.)  What it is worth on the kernels as they are, python -m paper_2107_06419_amd.tile_sweep --forms
+// says: over 1050 self-attention problems it is 0-2 % behind the fastest on average, 35 % at worst, where the better base
+// shape is 9-24 % behind on average, and no form that runs is more than 8 % slower than the base shape it replaces.
 namespace {
 
 struct Cost {
