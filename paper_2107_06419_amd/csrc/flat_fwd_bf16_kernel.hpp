@@ -24,8 +24,9 @@
 // state exponentiates against the current m WITHOUT computing the block maximum; a logit far above m
 // shows up as a jump of the fp32 row sum (more than kSumJump per lane and block, i.e. some
 // probability above 2^10), and only then the block takes the exact path: row maximum, raise m,
-// rescale O and l, recompute the block's probabilities.  Probabilities therefore stay below 2^14
-// relative to m, far inside bf16/fp32 range, and for typical data the exact path runs in the first
+// rescale O and l, recompute the block's probabilities from its logits (not from what is left of them in c S - m: the
+// first key may be one whose logit says it does not count, -1e9 say, and c S + 1e9 is a multiple of 64).  Probabilities
+// therefore stay below 2^14 relative to m, far inside bf16/fp32 range, and for typical data the exact path runs in the first
 // blocks only.
 #pragma once
 #include "flat_common.hpp"
@@ -37,6 +38,8 @@ namespace flat {
 
 constexpr int kLgkm0 = (63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8);  // s_waitcnt: lgkmcnt(0), the other counters left alone
 constexpr float kSumJump = 16384.0f;  // per lane and 32-key block: 16 probabilities
+constexpr float kFar = 1024.0f;  // log2 units: for reference maxima, and keys above them, no larger than this, c S - m holds the logits to 2^-13
+constexpr float kLargestExponent = 96.0f;  // 2^31 probabilities of 2^96 are still a number
 
 // Checking build (-DFLAT_SYNC_EVERY_PHASE): nothing is left in flight across a phase of the ring.  Every
 // streaming load is awaited in full and fenced by a barrier on both sides, and every LDS operand read is awaited
@@ -93,7 +96,8 @@ constexpr int kMaxSparseTiles = 2048;  // block-sparse: listed tiles per row blo
 // depth of the K/V ring, CAUSAL mask, MODE: kDense, kSparse = block-sparse variant (the workgroup visits only the 64-key tiles
 // listed for its row block, ids ascending, staged in LDS behind the ring; everything else as in the dense kernel).
 // Two wavefronts per SIMD (256 registers each), except 64 rows per wavefront at d = 128 and every shape at d = 256,
-// whose accumulators alone need more: those run one wavefront per SIMD with the full 512 registers.
+// whose accumulators alone need more: those run one wavefront per SIMD with the full 512 registers.  The 128-row shapes of d = 32 leave
+// room in LDS for five and are held to the 96 registers that five need.
 
 // Key groups (KG > 1): NW / KG wavefronts' worth of rows per workgroup, the keys of every tile divided over KG wavefronts per row
 // block.  For launches of few rows, which are bound by the chain of steps of one workgroup: KG times fewer steps, paid for
@@ -114,7 +118,7 @@ struct LaunchGrid {
 };
 
 template <int D, int QB, int NW, int STAGES, bool CAUSAL, int MODE = kDense, int BCX = 0, int KG = 1>
-__global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 2) void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
+__global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : D == 32 && QB == 1 && NW == 4 && KG == 1 ? 5 : 2) void fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                           const bf16* __restrict__ V, bf16* __restrict__ O,
                                                           const Bf16Problem prob, const LaunchGrid grid, float c) {
     using C = Bf16Cfg<D, STAGES, NW, BCX>;
@@ -135,9 +139,9 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     // 16 heads x 16384 1110 -> 1141 us; d = 96, 768 causal heads x 512 82.1 -> 86.6).  With less to fill gaps with they win: 128-row shapes of d = 64,
     // 64 causal heads x 2048 48.6 -> 46.5, d = 128, 16 heads x 8192 566 -> 551, d = 96 471 -> 463; 64 rows per wavefront at d = 32, 16 heads x 8192
     // 183 -> 178, and at d = 128 (one wavefront per SIMD) 618 -> 490.
-    constexpr bool kTwoPhase = KB == 1 ? QB == 1 || kHigh : KB == 2 && (kHigh || (NW > 1 && (D == 32 || (QB == 1 && NW <= 4))));
-    static_assert(KB != 1 || kTwoPhase || STAGES % 2 == 0, "with one block per tile the unrolled loop needs an even ring");
-    constexpr bool kStagger = KB == 1 || kTwoPhase;
+    // With one block per wavefront and tile there is no choice: K of a block is gone from the ring when the exact path of the other step asks for it.
+    constexpr bool kTwoPhase = KB == 1 || (KB == 2 && (kHigh || (NW > 1 && (D == 32 || (QB == 1 && NW <= 4)))));
+    constexpr bool kStagger = kTwoPhase;
     static_assert(STAGES >= (KB == 1 ? 2 : 3), "the ring is too short to keep a tile in flight");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -343,6 +347,11 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
                     oacc[qb][db] = mfma_bf16_32x32x16(vf[t][db], __builtin_bit_cast(bf16x8, pw), oacc[qb][db]);
                 }
     };
+    auto first_key = [&](int blk) __attribute__((always_inline)) { return blk * 32 + acc_row(0, half); };  // of a lane's 16 of a block
+    auto is_visible = [&](int first, int qb, int r) __attribute__((always_inline)) {
+        const int key = first + acc_row(r, 0);
+        return key < N && (!CAUSAL || key <= q0w + 32 * qb + l32 + off);
+    };
     // x <- c S - m (masked keys -> -inf)
     auto shift = [&](int blk, bool masked, floatx16 (&x)[QB]) __attribute__((always_inline)) {
 #pragma unroll
@@ -351,29 +360,15 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
 #pragma unroll
             for (int r = 0; r < 16; ++r) x[qb][r] = __builtin_fmaf(x[qb][r], c, -mref);
             if (masked) {
-                const int qidx = q0w + 32 * qb + l32;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = blk * 32 + acc_row(r, half);
-                    const bool ok = key < N && (!CAUSAL || key <= qidx + off);
-                    x[qb][r] = ok ? x[qb][r] : -INFINITY;  // exp2 -> probability exactly 0
-                }
+                for (int r = 0; r < 16; ++r) x[qb][r] = is_visible(first_key(blk), qb, r) ? x[qb][r] : -INFINITY;  // exp2 -> probability exactly 0
             }
-        }
-    };
-    auto row_max = [&](const floatx16 (&x)[QB], float (&mx)[QB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float a = x[qb][0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) a = __builtin_fmaxf(a, x[qb][r]);
-            mx[qb] = halves_max(a);
         }
     };
     // p <- bf16(exp2(x)); bsum <- this block's sum of the ROUNDED probabilities (so that the row sum and the
     // Attend operand agree).  One accumulator chain per query block: its links are spread through the step
     // anyway, and a second chain costs more in merging than it gains.
-    auto softmax_b = [&](floatx16 (&x)[QB], uint32_t (&p)[QB][8], float (&bsum)[QB]) __attribute__((always_inline)) {
+    auto softmax_b = [&](const auto (&x)[QB], uint32_t (&p)[QB][8], float (&bsum)[QB]) __attribute__((always_inline)) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             float l0 = 0.f;
@@ -391,21 +386,43 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
             bsum[qb] = l0;
         }
     };
-    // Rare path: raise the reference max of every row whose block maximum lies above it, rescale O and l,
-    // and shift the block's exponents accordingly.
-    auto rescale = [&](floatx16 (&x)[QB], const float (&mx)[QB]) __attribute__((always_inline)) {
+    // Rare path: raise the reference max of every row whose block maximum lies above it, rescale O and l (by alpha), and leave the block's
+    // exponents in x.  This one starts from the logits S: c S - m has lost them if m is the logit of a key far below the others, -1e9 say.  Where
+    // c S has steps so coarse (from 1e9) that a key's exponent against its own rounded logit overflows, m is the next step up.
+    auto block_max = [&](const auto &x) __attribute__((always_inline)) {
+        float top = x[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, x[r]);
+        return halves_max(top);
+    };
+    auto raise_from_logits = [&](int blk, bool masked, auto (&x)[QB], float (&alpha)[QB]) __attribute__((always_inline)) {
+        int first = first_key(blk);
+        asm("" : "+v"(first));  // or the compiler keeps the comparisons of the step for here
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const float delta = __builtin_fmaxf(mx[qb], 0.f);
-            const float alpha = __builtin_amdgcn_exp2f(-delta);
-            m[qb] += delta;
-            lsum[qb] *= alpha;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) x[qb][r] -= delta;
+            for (int r = 0; r < 16; ++r)
+                if (masked) x[qb][r] = is_visible(first, qb, r) ? x[qb][r] : -INFINITY;
+            const float top = block_max(x[qb]);
+            float raised = __builtin_fmaxf(__builtin_fmaxf(m[qb], top * c), -FLT_MAX);
+            if (__builtin_fmaf(top, c, -raised) > kLargestExponent) raised = __builtin_fmaf(__builtin_fabsf(raised), FLT_EPSILON, raised);
+            alpha[qb] = __builtin_amdgcn_exp2f(m[qb] - raised);
+            m[qb] = raised;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float e = __builtin_fmaf(x[qb][r], c, -raised);
+                x[qb][r] = masked && x[qb][r] == -INFINITY ? -INFINITY : e;  // (c may be 0)
+            }
+        }
+    };
+    auto rescale = [&](const float (&alpha)[QB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            lsum[qb] *= alpha[qb];
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[qb][db][r] *= alpha;
+                for (int r = 0; r < 16; ++r) oacc[qb][db][r] *= alpha[qb];
         }
     };
     // ---- prologue.  The workgroup's Q rows arrive through LDS like the tiles: whole rows, 1024 contiguous bytes per load, where
@@ -504,7 +521,6 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     floatx16 xA[QB], xB[QB];
     uint32_t pA[QB][8], pB[QB][8];
     bf16x8 vfA[2][DB], vfB[2][DB];  // vfB stays unused with one set
-    float mx[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -523,10 +539,6 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
             for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[qb][db]));
-    };
-    auto is_visible = [&](int blk, int qb, int r) __attribute__((always_inline)) {
-        const int key = blk * 32 + acc_row(r, half);
-        return key < N && (!CAUSAL || key <= q0w + 32 * qb + l32 + off);
     };
     // V^T fragments of 32 columns (both 16-key halves), and one of the K fragments
     auto read_v_block = [&](int stage, int kb, int db) __attribute__((always_inline)) {
@@ -600,9 +612,29 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
         bool jump = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) jump |= !(bsum[qb] <= kSumJump);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(jump) != 0, 0)) {  // exact path: xc still holds c S - m of this block
-            row_max(xc, mx);
-            rescale(xc, mx);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(jump) != 0, 0)) {  // exact path: xc holds c S - m of this block
+            float by[QB], alpha[QB];
+            bool far = false;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                by[qb] = __builtin_fmaxf(block_max(xc[qb]), 0.f);
+                alpha[qb] = __builtin_amdgcn_exp2f(-by[qb]);
+                far |= by[qb] > kFar || __builtin_fabsf(m[qb]) > kFar;
+            }
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {
+                read_k(stage, blk & (KB - 1), kf);  // S once more: the block's K is still in the ring
+                logits(kf, xc);
+                raise_from_logits(blk, masked, xc, alpha);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) by[qb] = 0.f;
+            }
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                m[qb] += by[qb];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xc[qb][r] -= by[qb];
+            }
+            rescale(alpha);
             softmax_b(xc, pc, bsum);
         }
 #pragma unroll
@@ -668,13 +700,13 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
                 if (qb == 0 && g < DB) read_v_block(stage, kb, g);
 #pragma unroll
                 for (int r = 16 * g / DS; r < 16 * (g + 1) / DS; ++r) {
-                    xv[qb][r] = __builtin_fmaf(xv[qb][r], c, -m[qb]);
-                    if (masked) xv[qb][r] = is_visible(blk, qb, r) ? xv[qb][r] : -INFINITY;  // exp2 -> probability exactly 0
+                    float x = __builtin_fmaf(xv[qb][r], c, -m[qb]);
+                    if (masked) x = is_visible(first_key(blk), qb, r) ? x : -INFINITY;  // exp2 -> probability exactly 0
                     if (r & 1) {
-                        pA[qb][r >> 1] = pack_bf16(e[qb], __builtin_amdgcn_exp2f(xv[qb][r]));
+                        pA[qb][r >> 1] = pack_bf16(e[qb], __builtin_amdgcn_exp2f(x));
                         bsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pA[qb][r >> 1]), ones, bsum[qb], false);
                     } else {
-                        e[qb] = __builtin_amdgcn_exp2f(xv[qb][r]);
+                        e[qb] = __builtin_amdgcn_exp2f(x);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -685,25 +717,10 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
         for (int qb = 0; qb < QB; ++qb) jump |= !(bsum[qb] <= kSumJump);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(jump) != 0, 0)) {  // exact path, before this block's Attend
             keep_high();
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                float top = xv[qb][0];
-#pragma unroll
-                for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, xv[qb][r]);
-                const float delta = __builtin_fmaxf(halves_max(top), 0.f), alpha = __builtin_amdgcn_exp2f(-delta);
-                m[qb] += delta;
-                lsum[qb] *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[qb][db][r] *= alpha;
-                bsum[qb] = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    pA[qb][r >> 1] = pack_bf16(__builtin_amdgcn_exp2f(xv[qb][r] - delta), __builtin_amdgcn_exp2f(xv[qb][r + 1] - delta));
-                    bsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pA[qb][r >> 1]), ones, bsum[qb], false);
-                }
-            }
+            float alpha[QB];
+            raise_from_logits(blk, masked, xv, alpha);
+            rescale(alpha);
+            softmax_b(xv, pA, bsum);
             keep_high();
         }
 #pragma unroll
@@ -746,17 +763,16 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
                 for (int r = 0; r < 16; ++r) xv[qb][r] = xA[qb][r];
         }
     };
-    // Two or four blocks per tile: the last step already reads K of the next tile, so the synchronisation sits
-    // before it.  One block per tile: it sits before the tile's only step, and consecutive tiles alternate the
-    // roles of the two logit / probability register sets (`odd`).
-    auto tile_steps = [&](int j, int sj, bool masked, bool odd) __attribute__((always_inline)) {  // sj = j % STAGES
+    // Where MFMAs are spread through the neighbour's softmax, the last step of a tile already reads K of the next tile, so the
+    // synchronisation sits before it.
+    auto tile_steps = [&](int j, int sj, bool masked) __attribute__((always_inline)) {  // sj = j % STAGES
         const int sn = sj + 1 == STAGES ? 0 : sj + 1;       // stage of tile j+1
         // first 32-key block of the tile, as a key position / 32 (only the masked form of a step looks at it)
         const int kb0 = KBT * (((SPARSE && masked) || SPLIT) ? tile_of(j) : j) + kg * KB;
         if (kTwoPhase) {
 #pragma unroll
             for (int i = 0; i < KB; ++i) two_phase_step(kb0 + i, j, sj, i, masked);
-        } else if (KB >= 2) {
+        } else {
 #pragma unroll
             for (int i = 0; i < KB; i += 2) {
                 if (kTwoVSets)
@@ -769,19 +785,6 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
                     step(kb0 + i + 1, sj, last ? sn : sj, masked, xB, xA, pA, vfA, pB, vfB);
                 else
                     step(kb0 + i + 1, sj, last ? sn : sj, masked, xB, xA, pA, vfA, pB, vfA);
-            }
-        } else {
-            sync_and_stream(j, sj);
-            if (!odd) {
-                if (kTwoVSets)
-                    step(kb0, sj, sn, masked, xA, xB, pB, vfB, pA, vfA);
-                else
-                    step(kb0, sj, sn, masked, xA, xB, pB, vfA, pA, vfA);
-            } else {
-                if (kTwoVSets)
-                    step(kb0, sj, sn, masked, xB, xA, pA, vfA, pB, vfB);
-                else
-                    step(kb0, sj, sn, masked, xB, xA, pA, vfA, pB, vfA);
             }
         }
     };
@@ -812,44 +815,21 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
 #pragma unroll 1
     for (; j + STAGES <= n_unm_tiles; j += STAGES) {
 #pragma unroll
-        for (int sj = 0; sj < STAGES; ++sj) tile_steps(j + sj, sj, false, (sj & 1) != 0);
+        for (int sj = 0; sj < STAGES; ++sj) tile_steps(j + sj, sj, false);
     }
     // remaining visible tiles and the partly masked ones (masking a fully visible tile changes nothing)
-    int sj = 0;  // j is a multiple of STAGES here (even, where that matters)
-    bool owed_in_a = false;  // one block per tile only: the last step left its probabilities in pA, not pB
-    if (KB >= 2 || kTwoPhase) {
+    int sj = 0;  // j is a multiple of STAGES here
 #pragma unroll 1
-        for (; j < n_unm_tiles; ++j) {
-            tile_steps(j, sj, false, false);
-            sj = sj + 1 == STAGES ? 0 : sj + 1;
-        }
-#pragma unroll 1
-        for (; j < n_act_tiles; ++j) {
-            tile_steps(j, sj, true, false);
-            sj = sj + 1 == STAGES ? 0 : sj + 1;
-        }
-    } else {
-#pragma unroll 1
-        for (; j < n_act_tiles; j += 2) {
-            tile_steps(j, sj, true, false);
-            sj = sj + 1 == STAGES ? 0 : sj + 1;
-            if (j + 1 < n_act_tiles) {
-                tile_steps(j + 1, sj, true, true);
-                sj = sj + 1 == STAGES ? 0 : sj + 1;
-            } else {
-                owed_in_a = true;
-            }
-        }
-        if (j > n_act_tiles) j = n_act_tiles;
+    for (; j < n_unm_tiles; ++j) {
+        tile_steps(j, sj, false);
+        sj = sj + 1 == STAGES ? 0 : sj + 1;
     }
-    // the Attend still owed for the last block
-    if (kTwoPhase) {
-        // nothing is owed: every step ran its own Attend
-    } else if (owed_in_a) {
-        attend(vfA, pA);
-    } else {
-        attend(kTwoVSets ? vfB : vfA, pB);
+#pragma unroll 1
+    for (; j < n_act_tiles; ++j) {
+        tile_steps(j, sj, true);
+        sj = sj + 1 == STAGES ? 0 : sj + 1;
     }
+    if (!kTwoPhase) attend(kTwoVSets ? vfB : vfA, pB);  // still owed for the last block; a two-phase step runs its own
 #pragma unroll 1
     for (; j < n_tiles; ++j) {
         constexpr bool kAhead = kTwoPhase && KB == 1;  // a tile's step has gone past the synchronisation of the next one
