@@ -54,6 +54,7 @@ struct F32Cfg {
 };
 
 constexpr float kF32Headroom = 4.0f;  // of the reference maximum above the row maximum, log2 units
+constexpr float kF32LargestExponent = 96.0f;  // 2^31 probabilities of 2^96 are still a number
 
 template <int D, int NW, bool CAUSAL>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
@@ -170,9 +171,15 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
             for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[db]));
         }
     };
-    // raise the reference maximum where the row maximum `top` (log2 units) is above it, and bring O and l to it
-    auto rescale = [&](float top) __attribute__((always_inline)) {
-        const float m_new = top > m ? top + kF32Headroom : m;
+    // Reference maximum of a row maximum S.  Where c S has steps so coarse (from 1e9) that the headroom is lost and a key's exponent against its
+    // own rounded logit overflows, it is the next step up.
+    auto reference = [&](float s) __attribute__((always_inline)) {
+        const float above = __builtin_fmaxf(s * c + kF32Headroom, -FLT_MAX);  // finite, so that a first tile of -infinity only has weight 0
+        return __builtin_fmaf(s, c, -above) > kF32LargestExponent ? __builtin_fmaf(__builtin_fabsf(above), FLT_EPSILON, above) : above;
+    };
+    // raise the reference maximum where the row maximum s is above it, and bring O and l to it
+    auto rescale = [&](float s) __attribute__((always_inline)) {
+        const float m_new = s * c > m ? reference(s) : m;
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         lsum *= alpha;
 #pragma unroll
@@ -215,7 +222,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
             asm volatile("" : "+v"(x[r]));
             mx = __builtin_fmaxf(mx, x[r]);
         }
-        m = __builtin_fmaxf(halves_max(mx) * c + kF32Headroom, -FLT_MAX);  // finite, so that a first tile of -infinity only has weight 0
+        m = reference(halves_max(mx));
         if (n_mine > 1) {
             wait_vm<0>();
             fence();
@@ -270,8 +277,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
                     }
                 }
                 if (r == 13) {
-                    top = halves_max(mx) * c;
-                    risen = __builtin_amdgcn_ballot_w64(top > m) != 0;
+                    top = halves_max(mx);
+                    risen = __builtin_amdgcn_ballot_w64(top * c > m) != 0;
                 }
                 if (r < 8) {
 #pragma unroll

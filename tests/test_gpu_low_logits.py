@@ -76,3 +76,13 @@ def test_keys_of_one_low_logit_weigh_the_same(d, low):
         agree(lambda *t: fa.flat_attn_fwd_tile(*t, scale, 0, index), dev, ref, f"one low logit, tile shape {index}")
     if d in (64, 128):
         agree(lambda *t: fa.flat_attn_fwd_f32(*t, scale, 0), [x.float() for x in dev], ref, "one low logit", "f32")
+
+
+@pytest.mark.parametrize("low", LOW)
+@pytest.mark.parametrize("d", [64, 128])
+def test_keys_of_low_logits_weigh_nothing_fp32(d, low):
+    scale = float(np.float32(d ** -0.5))
+    for place, keys in PLACES.items():
+        print(f"case low logits fp32 d={d} low={low} keys {place}", flush=True)
+        dev, host = inputs(N, N, d, low, keys, "f32")
+        agree(lambda *t: fa.flat_attn_fwd_f32(*t, scale, 0), dev, oracle.attention(*host, scale, 0), f"low keys {place}", "f32")
