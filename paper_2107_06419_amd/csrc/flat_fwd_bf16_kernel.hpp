@@ -158,8 +158,7 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
     // reverse, which pairs the k-th heaviest of the 64 with the k-th lightest.
     // Without a mask all blocks are equal, and a workgroup that has its compute unit to itself goes on to another one: nothing else covers the
     // fetch of a block's Q rows and first tile (8000 of 41000 cycles at d = 128 and 512 keys), so the next block's go out before the results of
-    // this one are put together.  512 heads x 512, d = 128, 92.4 -> 87.2 us; 768 x 512, d = 96, 112.5 -> 106.5; 16 x 8192, d = 128, 467.6 -> 466.3.
-    // At d = 64 and 32 a second workgroup covers it, and the loop costs registers (16 x 16384, d = 64, 977 -> 1019 us); at d = 256 Q goes to
+    // this one are put together.  (How many: launch_cfg.)  At d = 64 and 32 a second workgroup covers it, and the loop costs registers (16 x 16384, d = 64, 977 -> 1019 us); at d = 256 Q goes to
     // registers the accumulators' store still needs (256 x 128 16.5 -> 17.2 us).  Key counts that differ leave the dealing to the hardware.
     constexpr bool kLoop = loops_over_blocks(D, CAUSAL, MODE, KG);
     static_assert(!(CAUSAL && SPARSE), "the block-sparse variant has no causal form");
@@ -1016,7 +1015,12 @@ inline hipError_t launch_cfg(const void* Q, const void* K, const void* V, void* 
             if (n < 1) n = 1;
             per_cu.store(n, std::memory_order_relaxed);
         }
-        if (stride > 32 * n) stride = 32 * n;
+        // A workgroup takes two blocks where the launch has four rounds of them or more.  Blocks that belong to a workgroup do not move to a unit
+        // that is free: beside another stream's launch that holds 32 of the 256 units, 512 heads x 512, d = 128 (four rounds; alone 97 us with a
+        // workgroup for every block) takes 116 us with one block per workgroup, 128 with two and 156 with four, and alone 97, 92 and 89;
+        // 1024 x 256 89, 91, 108 and alone 71, 63, 62; 2048 x 512 (16 rounds) 414 with one, 416 with two, 591 with 16, and alone 362, 350,
+        // 343; 16 x 8192 (two rounds) 666 with one, 838 with two, and alone no difference.
+        if (blocks_per_xcd >= 4 * 32 * n) stride = (blocks_per_xcd + 1) / 2;
     }
     const LaunchGrid grid{n_qtiles, n_blocks, blocks_per_xcd, stride, BH, n_row_blocks, deal_heads ? 0 : blocks_per_xcd, deal_heads ? 8 : 1, deal_heads, Divisor(n_qtiles), Divisor(BH), Divisor(n_splits),
                           Divisor(prob.heads_per_batch)};

@@ -117,13 +117,12 @@ def test_release_and_fully_synchronised_builds_agree_for_every_tile_shape(d):
             assert torch.equal(rel.view(torch.int16), chk.view(torch.int16))
 
 
-# more blocks than the launch has workgroups, by one, two rounds and a rest, and three; one tile (and less), a ragged tail, and as many tiles
-# as the ring has stages
+# from one round of workgroups to a few; one tile (and less), a ragged tail, and as many tiles as the ring has stages
 @pytest.mark.parametrize("H,Nq,Nk", [(257, 256, 64), (257, 17, 33), (300, 300, 129), (128, 700, 192), (200, 900, 1000)])
 @pytest.mark.parametrize("d", [96, 128])
 def test_workgroups_with_several_blocks(d, H, Nq, Nk):
-    """Against the fully synchronised build, bit for bit, and against fp32 attention: without a mask a workgroup goes on to its next block,
-    whose loads overlap the results of the one before."""
+    """Against the fully synchronised build, bit for bit, and against fp32 attention: launches without a mask of about as many blocks as there
+    are compute units."""
     import torch
     lib = _sync_lib()
     gen = torch.Generator(device="cuda").manual_seed(d + H + Nq + Nk)
@@ -134,6 +133,34 @@ def test_workgroups_with_several_blocks(d, H, Nq, Nk):
     fa.flat_attn_fwd_cross(q, k, v, rel, scale, 0, None)
     assert lib.flat_attn_fwd_cross(q.data_ptr(), k.data_ptr(), v.data_ptr(), chk.data_ptr(), 1, H, Nq, Nk, d, scale, 0, None,
                                    torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(rel.view(torch.int16), chk.view(torch.int16))
+    qf, kf, vf = (x.float() for x in (q, k, v))
+    ref = torch.softmax(torch.matmul(qf, kf.transpose(-1, -2).contiguous()) * scale, dim=-1) @ vf
+    # bf16 rounding of probabilities and results: 2^-9 of the result each, and of the largest results at most 2e-2 as elsewhere
+    assert (rel.float() - ref).abs().max() <= 2e-2 and (rel.float() - ref).abs().sum() <= 5e-3 * ref.abs().sum()
+
+
+# keys: less than a tile, one, two, and as many as every ring has stages and more; heads: four rounds and an odd number of blocks, and more
+@pytest.mark.parametrize("H,N", [(1025, 33), (1031, 64), (1500, 129), (2050, 128), (1027, 250), (1100, 300)])
+@pytest.mark.parametrize("d,index", [(96, 0), (96, 1), (128, 0), (128, 1), (128, 2), (128, 3)])
+def test_workgroups_that_go_on_to_a_second_block(d, index, H, N):
+    """Every shape whose workgroups take two blocks in a launch of four rounds or more: against the fully synchronised build, bit for bit,
+    and against fp32 attention."""
+    import torch
+    lib = _sync_lib()
+    vp, i, f = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
+    lib.flat_attn_fwd_tile.argtypes = [vp, vp, vp, vp, i, i, i, i, f, i, i, vp]
+    rows = fa.flat_attn_tile_shape_get(d, index).as_dict()["rows_per_workgroup"]
+    assert H * -(-N // rows) >= 4 * 256 * fa.flat_attn_tile_shape_occupancy(d, index)
+    gen = torch.Generator(device="cuda").manual_seed(d + index + H + N)
+    q, k, v = (torch.randn(1, H, N, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    rel, chk = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    scale = float(np.float32(d ** -0.5))
+    print(f"case second block d={d} index={index} H={H} N={N}", flush=True)
+    fa.flat_attn_fwd_tile(q, k, v, rel, scale, 0, index)
+    assert lib.flat_attn_fwd_tile(q.data_ptr(), k.data_ptr(), v.data_ptr(), chk.data_ptr(), 1, H, N, d, scale, 0, index,
+                                  torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert torch.equal(rel.view(torch.int16), chk.view(torch.int16))
     qf, kf, vf = (x.float() for x in (q, k, v))
