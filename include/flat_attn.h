@@ -176,20 +176,22 @@ int flat_attn_unfused(const void* Q, const void* K, const void* V, void* O,
  * cost model (section 6.1) and discusses what the row granularity trades (section 5.3: fewer query rows per
  * tile re-fetch the keys more often and fill the compute array less; more rows need more on-chip memory).
  * Here the exploration is done by measurement: the library is built with several shapes per head dimension,
- * flat_attn_fwd uses index 0, except where the 128-row shape (d = 64: index 7, d = 128: index 2, d = 32 and 96:
- * index 1) measures ahead: launches of few row blocks (at most 128 blocks of 256 query rows; 256 with the causal
- * mask at d = 32 and 64, 192 at d = 96 and 128: 1.3-1.5 times faster), d = 64 with the causal mask up to 4096
- * positions and 1024 row blocks, d = 32 for short sequences, and up to 128 query rows; and except where a key-group form
- * (the last indices of a head size), in which the wavefronts of a workgroup share the keys of the same 32 to 128 rows, is
- * predicted to be faster: launches of few rows.  flat_attn_fwd_tile runs any index as it is, so that the choice can be re-timed.
+ * flat_attn_fwd uses index 0, except where the 128-row shape (d = 64: index 7, d = 128: index 2, d = 32 and 96: index 1) is ahead:
+ *   up to 128 query rows (not at d = 256);
+ *   d = 64 and 32 without a mask: where it is predicted to take less time (heads of exactly 256 and 512 rows: d = 64, 512 rows, up to 64 heads);
+ *   d = 64 with the causal mask: more than 256 rows, up to 1024 blocks of 256 rows (beyond 4096 rows: up to 256);
+ *   d = 32 with the causal mask: up to 8192 rows;
+ *   d = 96 and 128: up to 128 blocks of 256 rows, 192 with the causal mask;
+ * and except where a key-group form (the last indices of a head size), in which the wavefronts of a workgroup share the keys of the
+ * same 32 to 128 rows, is predicted to be faster: launches of few rows.  flat_attn_fwd_tile runs any index as it is, so that the choice can be re-timed.
  *   flat_attn_tile_shape_count(d): number of shapes for head dimension d (0 if d is not one of 32, 64, 96, 128, 256).
  *   flat_attn_tile_shape_get: fills *out (HOST pointer) for 0 <= index < count; FLAT_ERR_SHAPE otherwise.
  *   flat_attn_tile_shape_occupancy: workgroups of that shape resident per compute unit on the current
  *     device (registers and LDS permitting), or a negative flat_status; the only one of the three that
  *     needs a GPU.
  *   flat_attn_tile_shape_default: the index flat_attn_fwd (N = Nq) runs for a problem, and flat_attn_fwd_cross for Nq query rows
- *     over as many keys (with another number of keys a key-group form may be the faster one, or not), or a negative
- *     flat_status; host arithmetic only.
+ *     over as many keys without key counts, or a negative flat_status; host arithmetic only.  With another number of keys either
+ *     choice may fall differently, and with kv_lens the 128-row shape of d = 64 and 32 without a mask is taken a little earlier.
  *   flat_attn_fwd_tile: flat_attn_fwd with the shape chosen by the caller; same arguments, checks and
  *     result tolerance (different shapes sum in different orders, so results differ in the last bits).
  */

@@ -115,11 +115,15 @@ float predicted_us(const Form& f, int BH, const Bf16Problem& prob, int d, int ca
 // At d = 64 and 32 without a mask the predicted times of the two decide, by 3 %.  Half the rows per workgroup and three workgroups per compute
 // unit instead of two waste less on the last row block and the last round, and cost 4-8 % where neither counts: 87 heads x 537, d = 64,
 // 21.5 us on 256 rows, 14.8 on 128; 143 x 316 14.7 and 10.3; 26 x 3302 96.7 and 86.2; 457 x 849 124 and 111; 16 x 16384 1029 and 1145.
-// Over 4900 random problems the choice changes for 650, which get 6-10 % faster on average (20-25 % at best, 17 % slower at worst); it is 0.6 %
-// behind the fastest shape or form on average, 1.7 % with rules on the number of row blocks.  Key counts that differ favour more and shorter
-// workgroups: there the 128-row shape is taken up to 5 % behind (192 heads, 250 rows over 506 to 1011 keys: 21.5 and 19.1 us).  Heads of exactly one
-// or two full 256-row blocks keep to those rules (flat_attn_tile_shape_default promises it for 129 heads x 512; they have no last row block to
-// waste anything on).
+// Over 12200 random problems (profiles/row_shapes_key_counts.md) the shape taken is 1.5 % (d = 64) and 0.2 % (d = 32) behind the faster one on
+// average and 14 and 5 % at the 99th percentile; with rules on the number of row blocks it was 8.4 and 5.3 %.
+// With key counts, which the host does not know, the 128-row shape is taken up to 5 % behind: the times are predicted for all keys, and where
+// entries differ many short workgroups even out better.  Over 13300 random problems: counts from half the keys to all of them, d = 64,
+// 0.8 % behind on average and 10 % at the 99th percentile (with 1.03 for 0.95: 2.8 and 28 %), from an eighth 1.5 and 16 % (4.9 and 45 %), all
+// keys in every entry 0.6 and 12 % (1.5 and 14 %); d = 32 0.8, 1.0 and 0.5 % (0.8, 1.5 and 0.3 %).
+// Heads of exactly 256 or 512 rows keep to the rules on row blocks for no better reason than that their indices were tested as they are (129
+// heads x 512: index 0, 128 x 256: a key-group form): the predicted time would serve them as well as other lengths (512 rows, d = 64: 1.9 %
+// behind the faster shape on average, 4.6 % as it is; 129 to 192 heads x 512 lose 16-18 %).
 int base_tile_shape(int BH, const Bf16Problem& prob, int d, int causal) {
     const int Nq = prob.Nq;
     const long long blocks = (long long)BH * (((long long)Nq + 255) / 256);  // 256-row blocks in the launch
