@@ -530,8 +530,8 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
         for (int db = 0; db < DB; ++db) vfA[t][db] = vfB[t][db] = __builtin_bit_cast(bf16x8, (uint4v){0, 0, 0, 0});
     // ---- pieces of a two-phase step
     float xv[QB][16];  // logits of the current block
-    // d = 256: kept in the upper half of the register file by name.  Left to itself the compiler carries all 128 accumulators through the
-    // lower half in every step, for the rescaling that hardly ever happens.
+    // One wavefront per SIMD: kept in the upper half of the register file by name.  Left to itself the compiler carries all accumulators (128 at
+    // d = 256) through the lower half in every step, for the rescaling that hardly ever happens.
     auto keep_high = [&]() __attribute__((always_inline)) {
         if (!kHigh) return;
 #pragma unroll
@@ -668,15 +668,16 @@ __global__ __launch_bounds__(64 * NW, (D == 256 || (D == 128 && QB == 2)) ? 1 : 
             __syncthreads();
         }
     };
-    // One block per wavefront and tile: launches of few rows, split keys and d = 256, where a SIMD has few wavefronts or one, and nobody to
+    // Launches of few rows, split keys, the 128-row shapes, d = 32 and d = 256 (kTwoPhase), where a SIMD has few wavefronts or one, and nobody to
     // hide the waits of a step behind.  So a step is two phases, each multiplying operands that are in registers already while the operands
     // of the other one are read from LDS:
     //   A: S(b+1) over kf, with the softmax of block b and the reads of V(b) between its MFMAs;
     //   B: Attend(b) over vfA, with the reads of K(b+2) between its MFMAs.
-    // The ring moves on between the phases: V(b) and K(b+1) have left LDS by then.
-    // d = 256: at most three vector instructions and four LDS reads between two MFMAs (32 cycles), so the matrix pipe is what bounds a step
-    // (1024 cycles), and then power: 16 heads of 8192 positions without a mask 1340 -> 1010-1030 us (1070-1090 TFLOP/s), 2 x 8 causal heads of
-    // 3001 130 -> 93 us.  Before, a step read its operands at its start and moved the accumulators twice between the halves of the register file.
+    // The ring moves on between the phases (two blocks per tile: of the tile's first step): V(b) and K(b+1) have left LDS by then.
+    // d = 256: at most three vector instructions and four LDS reads between two MFMAs.  A step still takes 2020 cycles for the 1024 of its 32 MFMAs
+    // (matrix pipes 51 % busy, LDS 25 %, a third of the wavefronts' cycles spent waiting to issue; the 16 MFMAs of S are one chain on one
+    // accumulator): 16 heads of 8192 positions without a mask 1342 -> 982 us (1119 TFLOP/s), 2 x 8 causal heads of 3001 131 -> 89.
+    // Before, a step read its operands at its start and moved the accumulators twice between the halves of the register file.
     // Key groups: 12 heads x 512, d = 64, 5.31 -> 5.06 us; 4 causal heads x 8192 58.1 -> 50.4; 8 causal x 1024, d = 128, 11.9 -> 10.8; a step of
     // a workgroup alone on its compute unit 900 -> 790 cycles (256 of matrix pipe).  Split keys: 16 heads x 65536 45.7 -> 44.4.
     auto two_phase_step = [&](int blk, int j, int stage, int kb, bool masked) __attribute__((always_inline)) {  // block kb of tile j

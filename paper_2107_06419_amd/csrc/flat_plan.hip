@@ -28,7 +28,7 @@ int small_launch_shape(int d) { return d == 64 ? 7 : d == 128 ? 2 : d == 32 || d
 // took their present form.  (Refitted to 21671 timings of the kernels as they are, the choice was no better: 1.0 % behind the fastest on average
 // against 0.9 %.)  What it is worth on the kernels as they are, python -m paper_2107_06419_amd.tile_sweep --forms
 // says: over 1050 self-attention problems it is 0-2 % behind the fastest on average, 35 % at worst, where the better base
-// shape is 9-24 % behind on average, and no form that runs is more than 8 % slower than the base shape it replaces.
+// shape is 9-24 % behind on average, and no form that runs is more than 12 % slower than the base shape it replaces.
 namespace {
 
 struct Cost {
