@@ -114,6 +114,15 @@ __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((CNT & 15) | ((CNT >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// Slot of 16-byte chunk c of row r in an LDS tile of ROWB-byte rows: c ^ lds_swizzle(r).  The LDS serves 256 bytes per clock: a ds_read_b128
+// touches 16 rows at one chunk index per clock, a ds_read_b64_tr_b16 4 rows x 64 bytes; both then hit every bank once.
+template <int ROWB>
+__device__ __forceinline__ int lds_swizzle(int r) {
+    if (ROWB == 64) return (r >> 2) & 3;                                                    // 4 rows per 256 B
+    if (ROWB == 128) return (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1);  // 2 rows per 256 B
+    return ((r & 3) << 2) | ((r >> 2) & 3);                                                 // rows of 256 B or more
+}
+
 // XCD-aware remap of a 1-D grid.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs;
 // this makes each XCD own a contiguous range of logical ids, so that the workgroups sharing one
 // head's K/V also share one L2.

@@ -84,9 +84,7 @@ struct Bf16Cfg {
     static_assert(LOADS >= 1 && LOADS * ROWS_PER_LOAD * NW == BC, "the wavefronts must share a tile's rows evenly");
     static constexpr int LDS_BYTES = STAGES * STAGE;
     __device__ static __forceinline__ int swz(int r) {
-        if (ROWB == 64) return (r >> 2) & 3;                                                    // 4 rows per 256 B
-        if (ROWB == 128) return (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1);  // 2 rows per 256 B
-        return ((r & 3) << 2) | ((r >> 2) & 3);                                                 // rows of 256 B or more
+        return lds_swizzle<ROWB>(r);
     }
 };
 

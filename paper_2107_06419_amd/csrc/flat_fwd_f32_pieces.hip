@@ -1,0 +1,571 @@
+// fp32 attention on the 16-bit matrix pipe: every factor is split into two fp16 pieces.
+#include "flat_fwd_f32_rows.hpp"
+#include "flat_launch.hpp"
+
+namespace flat {
+
+// x = h + l: h the nearest fp16 to x, l the nearest fp16 to x - h, which has at most 13 significant bits: h + l is x to 2^-23 of it at worst, 2^-25 in
+// the root mean square.  A product of two floats is hh' + (hl' + lh'); ll', left out, is below 2^-22 of it with either sign and 2^-25 in the mean.
+// Three fp16 MFMAs of 32x32x16 take 96 cycles for what 8 fp32 MFMAs of 32x32x2 take 512 for.  Their sums are rounded less often than those of the
+// latter: every 16 products instead of every two, and products with a lower piece are summed apart.
+// Measured error against 64 bits, 2-norm, normal inputs: six heads, d = 64, 130 positions causal 2.04e-7 (fp32 MFMAs 2.13e-7 to 2.25e-7 by their key
+// groups), 1000 without a mask 3.9e-7 (4.3e-7 to 6.9e-7); d = 128 2.0e-7 (2.7e-7), 4.0e-7 (5.0e-7 to 7.3e-7); with Q three times as large and
+// uniform values 1.5e-7 to 2.8e-7 (1.8e-7 to 6.1e-7).  Below 128 positions there is little to gain and at d = 64 little difference in error (32 causal
+// ones 1.7e-7 against 1.6e-7), so f32_rows keeps them.  Where all logits are almost equal f32_rows is the more accurate: 1000 causal positions, Q times
+// 1e-6, 2.2e-7 against 1.6e-7 to 2.5e-7, without a mask 3.7e-7 against 3.2e-7 to 6.2e-7; 130 causal ones 1.9e-7 against 1.2e-7.
+//
+// One workgroup = four wavefronts = RG = 4 / KG blocks of 32 query rows times KG groups of keys.  A step takes 32 KG keys.  All four wavefronts
+// fetch them to registers, split them and leave the pieces in LDS, where the layouts and operand reads are those of the bf16 kernel
+// (chunks of 16 bytes swizzled by row, V through ds_read_b64_tr_b16), so the splitting (6 vector instructions for two floats) is shared by RG
+// wavefronts.  There are two buffers for each tensor and one barrier per step, which has two phases:
+//   A: S(i + 1) from the K pieces, with the exponentials of tile i, the pieces of its probabilities, and V(i + 1) on its way into LDS;
+//   B: Attend(i) from the V pieces, with the row maximum of tile i + 1 and K(i + 2) on its way into LDS.
+// A chunk's next fetch goes out when its registers have been split, one step ahead.  Masks and the reference maximum are those of f32_rows.
+//
+// What bounds it: the issue of one wavefront's instructions at d = 128, where the registers (O and its small part 128, Q 64) leave room for one
+// wavefront per SIMD: 16 heads x 4096 429 us, of it 240 with the MFMAs taken out and 260 with nothing but them and the operand reads; at d = 64
+// (two per SIMD) 32 x 4096 420, 231 and 243.  Before, with fp32 MFMAs: 1087 and 1050.  16 causal heads x 2049, d = 128, 162 -> 91; 256 x 700, d = 64, 280 -> 123.
+// Tried: three bf16 pieces and six products (exact splits of any float, 679 and 665 us; errors like these); one accumulator for S with a third piece of Q
+// (2^-11 h: 424 and 419, but spills with two key groups); the left-out product added (no smaller error); one buffer per tensor and two barriers per step (439, 442).
+//
+// What the pieces cannot hold goes to f32_rows, for the 32 RG rows of the workgroup:
+//   infinities and NaN, and |x| beyond 65504 (h is infinite, x - h infinite or a NaN, and the result no number);
+//   logits where |q|max c d^1/2 >= 2^10 (a key below 2^-14 is off by up to 2^-36, which then moves a logit by 2^-26; q is scaled by row);
+//   columns of V whose largest element is below 2^-10 (elements below 2^-14 are off by up to 2^-36), except columns of zeros: where the first tile has
+//   small values only, before any work, else when the results are there.
+// Probabilities are held times 2^15 below the reference maximum, so those off by 2^-25 of that are below 2^-25 of the largest.
+constexpr float kPieceStep = 2048.0f;        // the lower piece is held times this
+constexpr float kTopExponent = 15.0f;        // probabilities are held times 2^15
+constexpr float kSmallestValue = 0x1p-10f;
+
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ floatx16 mfma_f16_32x32x16(half8 a, half8 b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ half2v pack_f16(float a, float b) {  // to nearest
+    const floatx2 v = {a, b};
+    return __builtin_convertvector(v, half2v);
+}
+
+template <int D, int KG>
+struct F32PiecesCfg {
+    static constexpr int RG = 4 / KG, BR = 32 * RG, BC = 32 * KG;
+    static constexpr int GROWB = 4 * D, ROWB = 2 * D;        // bytes of a row in memory, and of one piece of it in LDS
+    static constexpr int CHUNKS = D / 8;                     // of 8 elements
+    static constexpr int ROWS = 256 / CHUNKS, CH = BC / ROWS;  // a thread fetches the same chunk of CH rows, ROWS apart
+    static constexpr int PIECE = BC * ROWB;
+    static constexpr int BUF = 2 * PIECE;                    // both pieces of a tile; buffers: K of even tiles, of odd ones, V of even, of odd
+    static constexpr int V_AT = 2 * BUF, LDS_TILES = 4 * BUF;
+    static constexpr int LDS_ROWS = 4 * F32Cfg<D>::WAVE_LDS;  // what f32_rows uses
+    static constexpr int LDS_BYTES = (LDS_TILES > LDS_ROWS ? LDS_TILES : LDS_ROWS) + 32;  // and two flags of each wavefront
+    static constexpr int COLUMNS_AT = KG == 1 ? 0 : 4 * D * 128 + 4 * 256;  // largest values by column, behind the partial results that meet in the tiles' place
+    static_assert(COLUMNS_AT + ROWS * D * 4 <= LDS_BYTES - 32, "no room for them");
+};
+
+template <int D, int KG, bool CAUSAL>
+__global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                                                       const float* __restrict__ V, float* __restrict__ O, int N,
+                                                                                       int n_qtiles, int n_blocks, int blocks_per_xcd, int n_heads,
+                                                                                       const Divisor by_qtiles, const Divisor by_heads, float c) {
+    using C = F32PiecesCfg<D, KG>;
+    constexpr int RG = C::RG, BR = C::BR, BC = C::BC, CH = C::CH, DS = D / 16, DB = D / 32, ROWB = C::ROWB;
+    typedef const half8 __attribute__((address_space(3))) * lds_frag_ptr;
+    typedef uint4v __attribute__((address_space(3))) * lds_u4_ptr;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    asm("" : "+s"(n_blocks), "+s"(blocks_per_xcd) : "s"(Q), "s"(K), "s"(V), "s"(O), "s"(N), "s"(n_qtiles), "s"(n_heads), "s"(by_qtiles.mul), "s"(by_qtiles.shift),
+        "s"(by_heads.mul), "s"(by_heads.shift), "s"(c));
+    int bh, qt;
+    if (!CAUSAL) {
+        const int logical = xcd_logical_block(blockIdx.x, blocks_per_xcd);
+        if (logical >= n_blocks) return;
+        bh = by_qtiles.quotient(logical);
+        qt = logical - bh * n_qtiles;
+    } else {
+        const int rank = blockIdx.x;
+        if (rank >= n_blocks) return;
+        const int from_end = by_heads.quotient(rank);
+        bh = rank - from_end * n_heads;
+        qt = n_qtiles - 1 - from_end;
+    }
+
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave % KG, rg = wave / KG;
+    const size_t head = (size_t)bh * N * D;
+    const char* const Kh = (const char*)(K + head);
+    const char* const Vh = (const char*)(V + head);
+    const int q0w = qt * BR + 32 * rg, qrow = q0w + l32;
+    const int kv_len = CAUSAL ? min(N, qt * BR + BR) : N;
+    const int n_tiles = (kv_len + BC - 1) / BC;
+
+    auto fence = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    // Barrier for LDS alone: loads to registers stay in flight across it.
+    auto meet = [&]() __attribute__((always_inline)) {
+        fence();
+        __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0), the rest left alone
+        __builtin_amdgcn_s_barrier();
+        fence();
+    };
+
+    // ---- memory -> registers -> pieces in LDS.  Keys past the last one repeat it; they are masked.
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    const int ld_row = tid / C::CHUNKS, ld_chunk = tid % C::CHUNKS;
+    const uint32_t st = lds0 + ld_row * ROWB + ((ld_chunk ^ lds_swizzle<ROWB>(ld_row)) << 4);  // (the swizzle looks at row bits below 16)
+    floatx4 rk[CH][2], rv[CH][2];
+    auto fetch_chunk = [&](const char* base, int tile, int i, floatx4 (&raw)[2]) __attribute__((always_inline)) {
+        const int first = min(tile, n_tiles - 1) * BC;
+        const char* const from = base + (size_t)first * C::GROWB;
+        const uint32_t at = (uint32_t)min(C::ROWS * i + ld_row, N - 1 - first) * C::GROWB + (uint32_t)ld_chunk * 32;
+        raw[0] = *(const floatx4*)(from + at);
+        raw[1] = *(const floatx4*)(from + at + 16);
+    };
+    auto fetch = [&](const char* base, int tile, floatx4 (&raw)[CH][2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) fetch_chunk(base, tile, i, raw[i]);
+    };
+    auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(uint32_t, x); };
+    auto split2 = [&](float a, float b, half2v& h, half2v& l) __attribute__((always_inline)) {
+        h = pack_f16(a, b);
+        // (x - h, which is exact, as 2^11 x - 2^11 h)
+        l = pack_f16(__builtin_fmaf((float)h[0], -kPieceStep, a * kPieceStep), __builtin_fmaf((float)h[1], -kPieceStep, b * kPieceStep));
+    };
+    auto split_pair = [&](const floatx4& a, const floatx4& b, int e, uint4v (&piece)[2]) __attribute__((always_inline)) {  // pair e of a chunk's four
+        half2v h, l;
+        split2(e < 2 ? a[2 * e] : b[2 * e - 4], e < 2 ? a[2 * e + 1] : b[2 * e - 3], h, l);
+        piece[0][e] = __builtin_bit_cast(uint32_t, h);
+        piece[1][e] = __builtin_bit_cast(uint32_t, l);
+    };
+    auto split8 = [&](const floatx4& a, const floatx4& b, uint4v (&piece)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) split_pair(a, b, e, piece);
+    };
+    auto store_pieces = [&](const uint4v (&piece)[2], int i, int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) *(lds_u4_ptr)(uintptr_t)(uint32_t)(st + at + p * C::PIECE + i * C::ROWS * ROWB) = piece[p];
+    };
+    auto store_chunk = [&](const floatx4 (&raw)[2], int i, int at) __attribute__((always_inline)) {
+        uint4v piece[2];
+        split8(raw[0], raw[1], piece);
+        store_pieces(piece, i, at);
+    };
+    floatx4 vmax[2];  // largest of the values fetched, by column
+#pragma unroll
+    for (int e = 0; e < 4; ++e) vmax[0][e] = vmax[1][e] = 0.f;
+    auto largest_pair = [&](const floatx4 (&raw)[2], int e) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            asm("v_max_f32 %0, %0, |%1|" : "+v"(vmax[e / 2][2 * (e % 2) + k]) : "v"(raw[e / 2][2 * (e % 2) + k]));  // (fmaxf is two instructions)
+    };
+
+    // ---- operands
+    half8 qf[2][DS], kf[3][2], vf[3][2];
+    uint32_t koff[DS];
+    int voff[DB][2];
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) koff[ds] = lds0 + (kg * 32 + l32) * ROWB + (((2 * ds + half) ^ lds_swizzle<ROWB>(l32)) << 4);
+    const int i16 = lane & 15, g16 = lane >> 4;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {
+            const int r = 8 * hi + 4 * (g16 >> 1) + (i16 >> 2);        // row within 16 keys
+            const int ch = 4 * db + 2 * (g16 & 1) + ((i16 >> 1) & 1);  // chunk that holds this lane's 4 columns
+            voff[db][hi] = (int)lds0 + C::V_AT + (kg * 32 + r) * ROWB + ((ch ^ lds_swizzle<ROWB>(r)) << 4) + (i16 & 1) * 8;
+        }
+    auto read_k = [&](int ds, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) kf[ds % 3][p] = *(lds_frag_ptr)(uintptr_t)(uint32_t)(koff[ds] + buf * C::BUF + p * C::PIECE);
+    };
+    auto read_v = [&](int g, int buf) __attribute__((always_inline)) {  // group g: 16 keys g / DB, 32 columns g mod DB
+        const int t = g / DB, db = g % DB;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int at = buf * C::BUF + p * C::PIECE + t * 16 * ROWB;
+            vf[g % 3][p] = __builtin_bit_cast(half8, concat(lds_read_tr16_at(voff[db][0] + at), lds_read_tr16_at(voff[db][1] + at)));
+        }
+    };
+
+    // S = xa + 2^-11 xb and O = oacc + 2^-11 osmall: the products of the upper pieces, and those with a lower one.
+    floatx16 oacc[DB], osmall[DB], xa, xb;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[db][r] = osmall[db][r] = 0.f;
+    float m, lsum = 0.f, x[16], cq;
+    half2v pf[2][8];  // pieces of the probabilities
+
+    auto keep_high = [&]() __attribute__((always_inline)) {  // with 512 registers: see f32_rows
+        if (D == 128) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(oacc[db]), "+a"(osmall[db]));
+        }
+    };
+    auto logit_group = [&](int ds) __attribute__((always_inline)) {
+        if (D == 128) asm volatile("" : "+a"(qf[0][ds]), "+a"(qf[1][ds]));
+        xb = mfma_f16_32x32x16(kf[ds % 3][1], qf[0][ds], xb);
+        xa = mfma_f16_32x32x16(kf[ds % 3][0], qf[0][ds], xa);
+        xb = mfma_f16_32x32x16(kf[ds % 3][0], qf[1][ds], xb);
+    };
+    auto attend_group = [&](int g) __attribute__((always_inline)) {
+        const int t = g / DB, db = g % DB;
+        half8 p[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[i][e] = pf[i][4 * t + e / 2][e % 2];
+        oacc[db] = mfma_f16_32x32x16(vf[g % 3][0], p[1], oacc[db]);
+        osmall[db] = mfma_f16_32x32x16(vf[g % 3][1], p[0], osmall[db]);
+        oacc[db] = mfma_f16_32x32x16(vf[g % 3][0], p[0], oacc[db]);
+    };
+    uint32_t one_one = 0x3c003c00;  // (in a register: not as an inline constant, which does not fill both halves)
+    float minus_one = -1.0f;  // (in a register: the compiler makes one instruction of the product and the sum then)
+    asm("" : "+s"(one_one), "+s"(minus_one));
+    const half2v ones = __builtin_bit_cast(half2v, one_one);
+    float psum;  // of a tile's probabilities
+    float ex[8][2];
+    auto exponentiate = [&](int j) __attribute__((always_inline)) {  // probabilities 2 j and 2 j + 1 of a lane
+        ex[j][0] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * j], cq, -m));
+        ex[j][1] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * j + 1], cq, -m));
+    };
+    auto split_probabilities = [&](int j) __attribute__((always_inline)) {
+        const half2v h = pack_f16(ex[j][0], ex[j][1]);
+        const half2v l = pack_f16(__builtin_fmaf((float)h[0], minus_one, ex[j][0]), __builtin_fmaf((float)h[1], minus_one, ex[j][1]));
+        pf[0][j] = h;
+        pf[1][j] = l;
+        // the sum of what is multiplied, so that an error common to a row's probabilities cancels
+        psum = __builtin_amdgcn_fdot2(l, ones, j == 0 ? 0.f : psum, false);
+        psum = __builtin_amdgcn_fdot2(h, ones, psum, false);
+        asm volatile("" : "+v"(pf[0][j]), "+v"(pf[1][j]), "+v"(psum));  // here, between the MFMAs, not where they are used
+    };
+    auto first_key = [&](int i) __attribute__((always_inline)) { return i * BC + kg * 32; };
+    auto mask = [&](int i) __attribute__((always_inline)) {
+        const int first = first_key(i);
+        if (first + 32 > N || (CAUSAL && first + 31 > q0w)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = first + acc_row(r, half);
+                const bool visible = key < N && (!CAUSAL || key <= qrow);
+                xa[r] = visible ? xa[r] : -INFINITY;
+                xb[r] = visible ? xb[r] : 0.f;
+            }
+        }
+    };
+    auto reference = [&](float s) __attribute__((always_inline)) {  // as in f32_rows
+        const float above = __builtin_fmaxf(s * cq + (kF32Headroom - kTopExponent), -FLT_MAX);
+        return __builtin_fmaf(s, cq, -above) > kF32LargestExponent ? __builtin_fmaf(__builtin_fabsf(above), FLT_EPSILON, above) : above;
+    };
+    auto rescale = [&](float s) __attribute__((always_inline)) {
+        keep_high();
+        const float m_new = s * cq > m + kTopExponent ? reference(s) : m;
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        lsum *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha, osmall[db][r] *= alpha;
+        keep_high();
+        m = m_new;
+    };
+    // The vector work of a group of MFMAs, spread evenly through it.
+    auto spread = [&](auto per_mfma) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x002, per_mfma, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int GA = DS, GB = 2 * DB;  // groups of three MFMAs in phase A and B
+    using PerA = std::integral_constant<int, (8 * 9 + 4 * CH * 8 + 3 * GA - 1) / (3 * GA)>;
+    using PerB = std::integral_constant<int, (4 * CH * 6 + 24 + 3 * GB - 1) / (3 * GB)>;
+
+    // ---- prologue
+    fetch(Kh, 0, rk);
+    floatx4 rq[DS][2];
+    {
+        const float* const Qr = Q + head + (size_t)min(qrow, N - 1) * D + 8 * half;
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            rq[ds][0] = *(const floatx4*)(Qr + 16 * ds);
+            rq[ds][1] = *(const floatx4*)(Qr + 16 * ds + 4);
+        }
+    }
+    fetch(Vh, 0, rv);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) store_chunk(rk[i], i, 0);
+    fetch(Kh, 1, rk);
+    float qmax = 0.f;
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qmax = __builtin_fmaxf(__builtin_fmaxf(qmax, __builtin_fabsf(rq[ds][0][e])), __builtin_fabsf(rq[ds][1][e]));
+    qmax = halves_max(qmax);
+    // each row times the power of two that brings its largest element to 2^12 .. 2^13
+    const int shift = min(100, max(-100, 139 - (int)(bits(qmax) >> 23)));
+    const float up = __builtin_bit_cast(float, (uint32_t)(127 + shift) << 23);
+    cq = c * __builtin_bit_cast(float, (uint32_t)(127 - shift) << 23);
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) {
+        uint4v piece[2];
+        split8(rq[ds][0] * up, rq[ds][1] * up, piece);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) qf[p][ds] = __builtin_bit_cast(half8, piece[p]);
+    }
+    float v0 = 0.f;
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v0 = __builtin_fmaxf(__builtin_fmaxf(v0, __builtin_fabsf(rv[i][0][e])), __builtin_fabsf(rv[i][1][e]));
+    bool unfit = !(qmax * c < (D == 64 ? 128.0f : 90.5f));
+    int* const flags = (int*)(smem + C::LDS_BYTES - 32);
+    auto any_unfit = [&]() __attribute__((always_inline)) {  // of the workgroup; the flags are written on the way into a barrier
+        return (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+    };
+    auto raise_flag = [&]() __attribute__((always_inline)) {
+        const bool any = __builtin_amdgcn_ballot_w64(unfit) != 0;
+        if (lane == 0) flags[wave] = any;
+    };
+    // a first tile of small values only: flags 4 .. 7 say where there is a value, and where there is one large enough
+    const bool any_value = __builtin_amdgcn_ballot_w64(v0 > 0.f) != 0, any_large = __builtin_amdgcn_ballot_w64(v0 >= kSmallestValue) != 0;
+    if (lane == 0) flags[4 + wave] = (any_value ? 1 : 0) | (any_large ? 2 : 0);
+    raise_flag();
+    meet();
+    unfit = any_unfit() || (flags[4] | flags[5] | flags[6] | flags[7]) == 1;
+    if (!unfit) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xa[r] = xb[r] = 0.f;
+        read_k(0, 0);
+        read_k(1, 0);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) largest_pair(rv[i], e);
+            store_chunk(rv[i], i, C::V_AT);
+            store_chunk(rk[i], i, C::BUF);
+        }
+        fetch(Vh, 1, rv);
+        fetch(Kh, 2, rk);
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            if (ds + 2 < DS) read_k(ds + 2, 0);
+            logit_group(ds);
+        }
+        mask(0);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            x[r] = __builtin_fmaf(xb[r], 1.0f / kPieceStep, xa[r]);
+            mx = __builtin_fmaxf(mx, x[r]);
+        }
+        m = reference(halves_max(mx));
+        meet();
+
+        auto trip = [&](int i, auto odd, auto more) __attribute__((always_inline)) {  // odd: i is; more: there is a tile i + 1
+            // ---- A
+            keep_high();
+            if (more) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xa[r] = xb[r] = 0.f;
+                read_k(0, 1 - odd);
+                read_k(1, 1 - odd);
+            }
+            constexpr int EXPS = 8 / GA, PAIRS_A = 4 * CH / GA, PAIRS_B = 4 * CH / GB;  // pairs of probabilities, and of V and K, per group
+            uint4v piece[2];
+#pragma unroll
+            for (int j = 0; j < EXPS; ++j) exponentiate(j);
+#pragma unroll
+            for (int g = 0; g < GA; ++g) {
+                if (more) {
+                    if (g + 2 < GA)
+                        read_k(g + 2, 1 - odd);
+                    else
+                        read_v(g + 2 - GA, odd);
+                    logit_group(g);
+                }
+#pragma unroll
+                for (int j = EXPS * g; j < EXPS * (g + 1); ++j) {
+                    if (j + EXPS < 8) exponentiate(j + EXPS);
+                    split_probabilities(j);
+                }
+                if (more) {
+#pragma unroll
+                    for (int k = PAIRS_A * g; k < PAIRS_A * (g + 1); ++k) {
+                        largest_pair(rv[k / 4], k % 4);
+                        split_pair(rv[k / 4][0], rv[k / 4][1], k % 4, piece);
+                        if (k % 4 == 3) {
+                            store_pieces(piece, k / 4, C::V_AT + (1 - odd) * C::BUF);
+                            fetch_chunk(Vh, i + 2, k / 4, rv[k / 4]);
+                        }
+                    }
+                    spread(PerA{});
+                } else {
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (more) {
+                mask(i + 1);
+            } else {
+                read_v(0, odd);
+                read_v(1, odd);
+            }
+            // ---- B
+            lsum += psum;
+            keep_high();
+            float mx = -INFINITY, top = 0.f;
+            bool risen = false;
+#pragma unroll
+            for (int g = 0; g < GB; ++g) {
+                if (g + 2 < GB) read_v(g + 2, odd);
+                attend_group(g);
+                if (more) {
+#pragma unroll
+                    for (int k = PAIRS_B * g; k < PAIRS_B * (g + 1); ++k) {
+                        split_pair(rk[k / 4][0], rk[k / 4][1], k % 4, piece);
+                        if (k % 4 == 3) {
+                            store_pieces(piece, k / 4, odd * C::BUF);
+                            fetch_chunk(Kh, i + 3, k / 4, rk[k / 4]);
+                        }
+                    }
+                    if (g >= 1 && g <= GB / 2) {  // the last MFMAs of S have had their latency
+#pragma unroll
+                        for (int r = 16 * (g - 1) / (GB / 2); r < 16 * g / (GB / 2); ++r) {
+                            x[r] = __builtin_fmaf(xb[r], 1.0f / kPieceStep, xa[r]);
+                            mx = __builtin_fmaxf(mx, x[r]);
+                        }
+                    }
+                    if (g == GB - 1) {
+                        top = halves_max(mx);
+                        risen = __builtin_amdgcn_ballot_w64(top * cq > m + kTopExponent) != 0;
+                    }
+                    spread(PerB{});
+                }
+            }
+            if (more) {
+                keep_high();
+                if (__builtin_expect(risen, 0)) rescale(top);
+            }
+            meet();
+        };
+        using Even = std::integral_constant<int, 0>;
+        using Odd = std::integral_constant<int, 1>;
+        int i = 0;
+#pragma unroll 1
+        for (; i + 2 < n_tiles; i += 2) {
+            trip(i, Even{}, std::true_type{});
+            trip(i + 1, Odd{}, std::true_type{});
+        }
+        if (i + 1 < n_tiles) {
+            trip(i, Even{}, std::true_type{});
+            trip(i + 1, Odd{}, std::false_type{});
+        } else {
+            trip(i, Even{}, std::false_type{});
+        }
+
+        // ---- results: key groups meet in LDS, in the lane layout they have; each merges its share of the columns
+        constexpr int QUADS = D / 8, OQ = QUADS / KG;
+        const float total = halves_sum(lsum);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[db][r] = __builtin_fmaf(osmall[db][r], 1.0f / kPieceStep, oacc[db][r]);
+        float* const columns = (float*)(smem + C::COLUMNS_AT);
+        *(floatx4*)(columns + ld_row * D + 8 * ld_chunk) = vmax[0];
+        *(floatx4*)(columns + ld_row * D + 8 * ld_chunk + 4) = vmax[1];
+        floatx4 out[OQ];
+        if (KG > 1) {
+            floatx4* const part = (floatx4*)smem + lane;
+            float* const stat = (float*)(smem + 4 * QUADS * 1024) + lane;
+#pragma unroll
+            for (int q = 0; q < QUADS; ++q) part[(wave * QUADS + q) * 64] = floatx4{oacc[q / 4][4 * (q % 4)], oacc[q / 4][4 * (q % 4) + 1], oacc[q / 4][4 * (q % 4) + 2], oacc[q / 4][4 * (q % 4) + 3]};
+            stat[wave * 64] = half ? total : m;
+        }
+        meet();
+        if (KG > 1) {
+            const floatx4* const part = (const floatx4*)smem + lane;
+            const float* const stat = (const float*)(smem + 4 * QUADS * 1024) + lane;
+            float M = -FLT_MAX, L = 0.f, w[KG];
+#pragma unroll
+            for (int k = 0; k < KG; ++k) {
+                w[k] = stat[(rg * KG + k) * 64 - 32 * half];
+                M = __builtin_fmaxf(M, w[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < KG; ++k) {
+                w[k] = __builtin_amdgcn_exp2f(w[k] - M);
+                L += w[k] * stat[(rg * KG + k) * 64 + 32 * (1 - half)];
+            }
+            const float inv = 1.0f / L;
+#pragma unroll
+            for (int i = 0; i < OQ; ++i) {
+                floatx4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < KG; ++k) {
+                    const floatx4 o = part[((rg * KG + k) * QUADS + kg * OQ + i) * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[e] += w[k] * o[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[i][e] = a[e] * inv;
+            }
+        } else {
+            const float inv = 1.0f / total;
+#pragma unroll
+            for (int q = 0; q < OQ; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[q][e] = oacc[q / 4][4 * (q % 4) + e] * inv;
+        }
+#pragma unroll
+        for (int q = 0; q < OQ; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) unfit |= !(__builtin_fabsf(out[q][e]) < INFINITY);
+        if (tid < D) {
+            float top = 0.f;
+#pragma unroll
+            for (int r = 0; r < C::ROWS; ++r) top = __builtin_fmaxf(top, columns[r * D + tid]);
+            unfit |= top > 0.f && top < kSmallestValue;
+        }
+        raise_flag();
+        meet();
+        unfit = any_unfit();
+        if (!unfit && qrow < N) {
+            float* const Or = O + head + (size_t)qrow * D + 4 * half;
+#pragma unroll
+            for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = out[q];
+        }
+    }
+    if (__builtin_expect(unfit, 0)) {  // of the whole workgroup
+#pragma unroll 1
+        for (int rb = 0; rb < RG; ++rb) {
+            if (qt * BR + 32 * rb >= N) break;
+            __syncthreads();
+            f32_rows<D, 4, CAUSAL>(smem, Q, K, V, O, N, bh, qt * RG + rb, c);
+        }
+    }
+}
+
+template <int D, int KG, bool CAUSAL>
+hipError_t launch_fwd_f32_pieces(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream) {
+    using C = F32PiecesCfg<D, KG>;
+    const int n_qtiles = (N + C::BR - 1) / C::BR;
+    if ((long long)BH * n_qtiles > 0x7ffffff0LL) return hipErrorInvalidValue;
+    const int n_blocks = BH * n_qtiles, blocks_per_xcd = (n_blocks + 7) / 8;
+    auto kern = fwd_f32_pieces_kernel<D, KG, CAUSAL>;
+    static std::atomic<uint64_t> attr_done{0};
+    const hipError_t e = allow_dynamic_lds((const void*)kern, C::LDS_BYTES, &attr_done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(blocks_per_xcd * 8), dim3(256), C::LDS_BYTES, stream, Q, K, V, O, N, n_qtiles, n_blocks, blocks_per_xcd, BH,
+                       Divisor(n_qtiles), Divisor(BH), scale * kLog2e);
+    return hipGetLastError();
+}
+
+#define FLAT_INSTANTIATE_F32_PIECES(D, KG)                                                                                              \
+    template hipError_t launch_fwd_f32_pieces<D, KG, false>(const float*, const float*, const float*, float*, int, int, float, hipStream_t); \
+    template hipError_t launch_fwd_f32_pieces<D, KG, true>(const float*, const float*, const float*, float*, int, int, float, hipStream_t);
+FLAT_INSTANTIATE_F32_PIECES(64, 1)
+FLAT_INSTANTIATE_F32_PIECES(64, 2)
+FLAT_INSTANTIATE_F32_PIECES(128, 1)
+FLAT_INSTANTIATE_F32_PIECES(128, 2)
+
+}  // namespace flat

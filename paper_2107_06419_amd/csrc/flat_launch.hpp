@@ -109,6 +109,9 @@ hipError_t launch_fwd_bf16_groups(const void* Q, const void* K, const void* V, v
 template <int D, int QB, int NW, int STAGES, int BCX = 0, int KG = 1>
 hipError_t fwd_bf16_shape_occupancy(int* workgroups_per_cu);
 
+// (flat_fwd_f32_pieces.hip) KG key groups
+template <int D, int KG, bool CAUSAL>
+hipError_t launch_fwd_f32_pieces(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream);
 hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale,
                           int causal, hipStream_t stream);
 
