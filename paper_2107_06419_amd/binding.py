@@ -142,41 +142,65 @@ def _check(status: int) -> None:
         raise FlatAttnError(status, flat_attn_status_string(status))
 
 
+_torch = _raw_stream = _device = None
+
+
+def _load_torch():
+    """torch, and the two calls behind torch.cuda.current_stream(), looked up once: an import statement costs 0.2 us each time it runs."""
+    global _torch, _raw_stream, _device
+    import torch
+    _raw_stream, _device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    _torch = torch
+    return torch
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
         # The handle of torch.cuda.current_stream() without building the Stream object around it: 0.1 us against 2.7, a third
         # of what a call on a small problem costs the host (8.6 -> 6.0 us, where the kernel of 12 heads x 512 takes 6).
-        import torch
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _torch is None:
+            _load_torch()
+        return _raw_stream(_device())
     return int(stream.cuda_stream)
 
 
 def _dev_args(dtype, first, *others):
+    # One test per tensor; which of its parts failed is looked up afterwards.  (What a call costs the host is what a small problem takes.)
     shape = first.shape
+    ok = len(shape) == 4 and first.is_cuda and first.dtype is dtype and first.is_contiguous()
+    for t in others:
+        ok = ok and t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous()
+    if not ok:
+        _explain(dtype, shape, (first, *others))
+    return shape
+
+
+def _explain(dtype, shape, tensors):
     if len(shape) != 4:
         raise ValueError("expected [B, H, N, d] tensors")
-    for t in (first, *others):
+    for t in tensors:
         if not t.is_cuda:
             raise ValueError("tensors must live on the GPU")
         if t.dtype != dtype:
             raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
         if t.shape != shape or not t.is_contiguous():
             raise ValueError("tensors must be contiguous and share one [B, H, N, d] shape")
-    return tuple(shape)
 
 
 def flat_attn_fwd(Q, K, V, O, scale: float, mask_kind: int = FLAT_MASK_NONE, stream=None) -> None:
     """Fused attention, bf16 [B,H,N,d] device tensors; O is overwritten. Enqueues on `stream`."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, d = _dev_args(torch.bfloat16, Q, K, V, O)
-    _check(load_library().flat_attn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
-                                        float(scale), int(mask_kind), _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
+                                                    float(scale), int(mask_kind), _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 def flat_attn_fwd_cross(Q, K, V, O, scale: float, mask_kind: int = FLAT_MASK_NONE, kv_lens=None, stream=None) -> None:
     """Fused attention with Nq queries and Nk keys: Q, O bf16 [B,H,Nq,d], K, V bf16 [B,H,Nk,d] device tensors;
     kv_lens: optional int32 device tensor of B key counts (padding beyond them is ignored)."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, Nq, d = _dev_args(torch.bfloat16, Q, O)
     Bk, Hk, Nk, dk = _dev_args(torch.bfloat16, K, V)
     if (Bk, Hk, dk) != (B, H, d):
@@ -186,24 +210,26 @@ def flat_attn_fwd_cross(Q, K, V, O, scale: float, mask_kind: int = FLAT_MASK_NON
         if not kv_lens.is_cuda or kv_lens.dtype != torch.int32 or not kv_lens.is_contiguous() or kv_lens.numel() != B:
             raise ValueError("kv_lens must be a contiguous int32 GPU tensor with one entry per batch")
         lens_ptr = kv_lens.data_ptr()
-    _check(load_library().flat_attn_fwd_cross(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, Nq, Nk, d,
-                                              float(scale), int(mask_kind), lens_ptr, _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd_cross(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, Nq, Nk, d,
+                                                          float(scale), int(mask_kind), lens_ptr, _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 def flat_attn_fwd_splitkv_splits(B: int, H: int, Nq: int, Nk: int, d: int, n_splits: int = 0) -> int:
     """Number of splits a flat_attn_fwd_splitkv call with these arguments uses (n_splits <= 0: the library's choice)."""
-    n = int(load_library().flat_attn_fwd_splitkv_splits(int(B), int(H), int(Nq), int(Nk), int(d), int(n_splits)))
+    n = int((_lib or load_library()).flat_attn_fwd_splitkv_splits(int(B), int(H), int(Nq), int(Nk), int(d), int(n_splits)))
     if n < 0:
         _check(n)
     return n
 
 
 def flat_attn_fwd_splitkv_workspace_bytes(B: int, H: int, Nq: int, Nk: int, d: int, n_splits: int = 0) -> int:
-    return int(load_library().flat_attn_fwd_splitkv_workspace_bytes(int(B), int(H), int(Nq), int(Nk), int(d), int(n_splits)))
+    return int((_lib or load_library()).flat_attn_fwd_splitkv_workspace_bytes(int(B), int(H), int(Nq), int(Nk), int(d), int(n_splits)))
 
 
 def _cross_args(Q, K, V, O, kv_lens):
-    import torch
+    torch = _torch or _load_torch()
     B, H, Nq, d = _dev_args(torch.bfloat16, Q, O)
     Bk, Hk, Nk, dk = _dev_args(torch.bfloat16, K, V)
     if (Bk, Hk, dk) != (B, H, d):
@@ -222,9 +248,11 @@ def flat_attn_fwd_splitkv(Q, K, V, O, scale: float, mask_kind: int, kv_lens, n_s
     B, H, Nq, Nk, d, lens_ptr = _cross_args(Q, K, V, O, kv_lens)
     if not workspace.is_cuda or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous GPU tensor")
-    _check(load_library().flat_attn_fwd_splitkv(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, Nq, Nk, d,
-                                                float(scale), int(mask_kind), lens_ptr, int(n_splits), workspace.data_ptr(),
-                                                workspace.numel() * workspace.element_size(), _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd_splitkv(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, Nq, Nk, d,
+                                                            float(scale), int(mask_kind), lens_ptr, int(n_splits), workspace.data_ptr(),
+                                                            workspace.numel() * workspace.element_size(), _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 FLAT_SPLITKV_STATIC_BYTES = 64 << 20
@@ -233,8 +261,10 @@ FLAT_SPLITKV_STATIC_BYTES = 64 << 20
 def flat_attn_fwd_splitkv_static(Q, K, V, O, scale: float, mask_kind: int, kv_lens=None, n_splits: int = 0, stream=None) -> None:
     """flat_attn_fwd_splitkv out of the library's built-in scratch buffer (FLAT_SPLITKV_STATIC_BYTES): allocates nothing."""
     B, H, Nq, Nk, d, lens_ptr = _cross_args(Q, K, V, O, kv_lens)
-    _check(load_library().flat_attn_fwd_splitkv_static(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, Nq, Nk, d,
-                                                       float(scale), int(mask_kind), lens_ptr, int(n_splits), _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd_splitkv_static(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, Nq, Nk, d,
+                                                                   float(scale), int(mask_kind), lens_ptr, int(n_splits), _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 FLAT_SPARSE_BLOCK_ROWS = 256
@@ -244,7 +274,7 @@ FLAT_SPARSE_BLOCK_KEYS = 64
 def flat_attn_fwd_blocksparse(Q, K, V, O, scale: float, tile_offsets, tile_ids, stream=None) -> None:
     """Block-sparse fused attention: int32 device tensors `tile_offsets` (B*H*ceil(N/256) + 1) and `tile_ids` list,
     per block of 256 query rows, the 64-key tiles it sees (CSR, ids ascending)."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, d = _dev_args(torch.bfloat16, Q, K, V, O)
     for t in (tile_offsets, tile_ids):
         if not t.is_cuda or t.dtype != torch.int32 or not t.is_contiguous():
@@ -252,17 +282,21 @@ def flat_attn_fwd_blocksparse(Q, K, V, O, scale: float, tile_offsets, tile_ids, 
     n_row_blocks = B * H * ((N + FLAT_SPARSE_BLOCK_ROWS - 1) // FLAT_SPARSE_BLOCK_ROWS)
     if tile_offsets.numel() != n_row_blocks + 1:
         raise ValueError(f"tile_offsets must have {n_row_blocks + 1} entries")
-    _check(load_library().flat_attn_fwd_blocksparse(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
-                                                    float(scale), tile_offsets.data_ptr(), tile_ids.data_ptr(),
-                                                    int(tile_ids.numel()), _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd_blocksparse(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
+                                                                float(scale), tile_offsets.data_ptr(), tile_ids.data_ptr(),
+                                                                int(tile_ids.numel()), _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 def flat_attn_fwd_f32(Q, K, V, O, scale: float, mask_kind: int = FLAT_MASK_NONE, stream=None) -> None:
     """Fused attention in fp32, float32 [B,H,N,d] device tensors."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, d = _dev_args(torch.float32, Q, K, V, O)
-    _check(load_library().flat_attn_fwd_f32(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
-                                            float(scale), int(mask_kind), _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd_f32(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
+                                                        float(scale), int(mask_kind), _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 def flat_attn_unfused_workspace_bytes(B: int, H: int, N: int, d: int, dtype: int = FLAT_DTYPE_BF16) -> int:
@@ -271,7 +305,7 @@ def flat_attn_unfused_workspace_bytes(B: int, H: int, N: int, d: int, dtype: int
 
 def flat_attn_unfused(Q, K, V, O, scale: float, mask_kind: int, workspace, stream=None) -> None:
     """Unfused baseline; `workspace` is a device tensor of at least flat_attn_unfused_workspace_bytes() bytes."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, d = _dev_args(torch.bfloat16, Q, K, V, O)
     if not workspace.is_cuda or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous GPU tensor")
@@ -310,10 +344,12 @@ def flat_attn_tile_shape_default(B: int, H: int, Nq: int, d: int, mask_kind: int
 
 def flat_attn_fwd_tile(Q, K, V, O, scale: float, mask_kind: int, tile_shape: int, stream=None) -> None:
     """flat_attn_fwd with tile shape `tile_shape` of the library's table instead of the default (index 0)."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, d = _dev_args(torch.bfloat16, Q, K, V, O)
-    _check(load_library().flat_attn_fwd_tile(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
-                                             float(scale), int(mask_kind), int(tile_shape), _stream_handle(stream)))
+    status = (_lib or load_library()).flat_attn_fwd_tile(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), B, H, N, d,
+                                                         float(scale), int(mask_kind), int(tile_shape), _stream_handle(stream))
+    if status != 0:
+        _check(status)
 
 
 def flat_attn_mfma_probe_sink_bytes() -> int:
