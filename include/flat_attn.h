@@ -193,8 +193,7 @@ int flat_attn_unfused(const void* Q, const void* K, const void* V, void* O,
  *     needs a GPU.
  *   flat_attn_tile_shape_default: the index flat_attn_fwd (N = Nq) runs for a problem, and flat_attn_fwd_cross for Nq query rows
  *     over as many keys without key counts, or a negative flat_status; host arithmetic only.  With another number of keys either
- *     choice may fall differently, and with kv_lens the 128-row shape of d = 64 and 32 without a mask and the key-group forms are taken a little
- *     earlier.
+ *     choice may fall differently, and with kv_lens the 128-row shape of d = 64 and 32 without a mask is taken a little earlier.
  *   flat_attn_fwd_tile: flat_attn_fwd with the shape chosen by the caller; same arguments, checks and
  *     result tolerance (different shapes sum in different orders, so results differ in the last bits).
  */

@@ -144,13 +144,8 @@ int base_tile_shape(int BH, const Bf16Problem& prob, int d, int causal) {
     }
 }
 
-// The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than `margin`
-// times as long, or there is one tile, and so nothing to divide.  1.1 is what the prediction is worth.  With key counts entries differ, short workgroups even
-// out better than predicted, and more was lost by not taking a form than by taking a wrong one: 1 there, for launches of up to 200 us, which is what was
-// timed, and not at d = 256, whose one form is a third slower where it is wrong.  Of 13800 random problems, counts from half the keys to all of them, 940 take another
-// shape than with 1.1, 710 of them more than 3 % faster for it, 58 more than 3 % slower (31 % at worst); 2.0 -> 1.4 % behind the fastest shape on average.
-// 16 x 12 heads, 250 rows over 506 to 1011 keys, d = 64: 21.3 us on 128 rows, 19.1 in a form of 64.  Without key counts 1.05 gains as much on 300 of 9000
-// problems and loses on longer ones (4 x 10245, d = 128, 229 us, 248 in the form).
+// The key-group form for this problem, as its position in the table, or -1 where the shape `index` is predicted to take no more than 1.1
+// times as long (what the prediction is worth) or there is one tile, and so nothing to divide.
 int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index) {
     // At d = 256 three tiles of the base shape are no more work than two of the form's: 8 x 65 without a mask 10.6 us, in the form
     // 12.0, 7 causal heads, 55 rows over 80 keys, 10.8 and 12.1.  In causal self-attention the form wins there too (2 x 75: 10.5 and 11.4).
@@ -159,8 +154,7 @@ int key_group_form(int BH, const Bf16Problem& prob, int d, int causal, int index
     const Choice* c = choice_of(d);
     if (!c) return -1;
     int best = -1;
-    float limit = predicted_us(c->base[index == 0 ? 0 : 1], BH, prob, d, causal);
-    if (!prob.kv_lens || d == 256 || limit > 200.0f) limit /= 1.1f;
+    float limit = predicted_us(c->base[index == 0 ? 0 : 1], BH, prob, d, causal) / 1.1f;
     for (int i = 0; i < c->n_forms; ++i) {
         const float t = predicted_us(c->forms[i], BH, prob, d, causal);
         if (t < limit) limit = t, best = i;

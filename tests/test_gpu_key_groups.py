@@ -101,3 +101,19 @@ def test_heads_dealt_over_the_xcds(B, H, Nq, Nk, d):
     scale = float(np.float32(d ** -0.5))
     print(f"case dealt heads B={B} H={H} Nq={Nq} Nk={Nk} d={d}", flush=True)
     check_close(run_both(q, k, v, scale, 0, [int(x) for x in lens]), oracle.attention_cross(q, k, v, scale, 0, kv_lens=lens), "bf16", "dealt heads")
+
+
+# (B, H, Nq, Nk, d, mask): launches on the edge of a key-group form, which a rule of its own for key counts would take
+@pytest.mark.parametrize("B,H,Nq,Nk,d,mask", [(6, 16, 300, 900, 64, 1), (16, 12, 250, 1011, 128, 1), (12, 16, 160, 600, 128, 1), (8, 16, 200, 500, 32, 1),
+                                              (8, 12, 250, 700, 96, 0), (8, 12, 250, 700, 96, 1)])
+def test_counts_of_all_keys_change_nothing(B, H, Nq, Nk, d, mask):
+    """Key counts that name every key divide the keys as no counts do: the same sums in the same order."""
+    import torch
+    q, k, v = (to_device(rounded((B, H, n, d), 53000 + Nq + d + mask, t), "bf16") for n, t in ((Nq, 0), (Nk, 1), (Nk, 2)))
+    counts = torch.full((B,), Nk, dtype=torch.int32, device="cuda")
+    with_counts, without = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    print(f"case all keys counted B={B} H={H} Nq={Nq} Nk={Nk} d={d} mask={mask}", flush=True)
+    fa.flat_attn_fwd_cross(q, k, v, with_counts, float(np.float32(d ** -0.5)), mask, counts)
+    fa.flat_attn_fwd_cross(q, k, v, without, float(np.float32(d ** -0.5)), mask, None)
+    torch.cuda.synchronize()
+    assert torch.isfinite(without).all() and torch.equal(with_counts.view(torch.int16), without.view(torch.int16))
