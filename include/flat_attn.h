@@ -152,7 +152,8 @@ int flat_attn_fwd_blocksparse(const void* Q, const void* K, const void* V, void*
 /*
  * Same dataflow in fp32: fp32 inputs, probabilities, sums and results.  Products are those of the fp32 matrix instructions, or (128 to 4096
  * positions, where it is faster) of factors split into two fp16 pieces each, whose error against 64 bits is the smaller one for logits of ordinary spread;
- * inputs that the pieces cannot hold (beyond 65504, infinite, NaN, columns of V below 2^-10, very large logits) are taken through the former.
+ * inputs that the pieces cannot hold (K beyond 65504, infinities, NaN, very large logits, V that grows to more than 8 times its first values, results
+ * made of values of 2^-26 of those) are taken through the former.
  *   Q, K, V: device, const float [B,H,N,d].  O: device, float [B,H,N,d].
  */
 int flat_attn_fwd_f32(const float* Q, const float* K, const float* V, float* O,

@@ -76,6 +76,18 @@ __device__ __forceinline__ float halves_sum(float x) {
     return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
+// Largest x of a wavefront, in every lane.  (row_ror 8, 4, 2, 1 within 16 lanes)
+__device__ __forceinline__ float wave_max(float x) {
+    x = halves_max(x);
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = __builtin_fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+    x = __builtin_fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xf, 0xf, true)));
+    x = __builtin_fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x124, 0xf, 0xf, true)));
+    x = __builtin_fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x122, 0xf, 0xf, true)));
+    return __builtin_fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x121, 0xf, 0xf, true)));
+}
+
 // Quotients n / d of 0 <= n < 2^31 by a divisor known when the kernel is launched: mul = ceil(2^(32+shift) / d) with 2^shift < d <=
 // 2^(shift+1), so mul < 2^32, mul d - 2^(32+shift) < d <= 2^(shift+1), and the error n (mul d - 2^(32+shift)) / (d 2^(32+shift)) stays below 1 / d.
 // A division by a kernel argument takes about 40 dependent scalar instructions (200 cycles at the start of every workgroup), this five.

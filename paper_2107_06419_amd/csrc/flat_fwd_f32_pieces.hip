@@ -31,12 +31,17 @@ namespace flat {
 // What the pieces cannot hold goes to f32_rows, for the 32 RG rows of the workgroup:
 //   infinities and NaN, and |x| beyond 65504 (h is infinite, x - h infinite or a NaN, and the result no number);
 //   logits where |q|max c d^1/2 >= 2^10 (a key below 2^-14 is off by up to 2^-36, which then moves a logit by 2^-26; q is scaled by row);
-//   columns of V whose largest element is below 2^-10 (elements below 2^-14 are off by up to 2^-36), except columns of zeros: where the first tile has
-//   small values only, before any work, else when the results are there.
+//   V whose largest element in the first tile is infinite or below 2^-104, or which grows to 8 to 16 times that later on.
+// V is held times the power of two that brings that element to 2^12 .. 2^13.  Elements that are then below 2^-14, a part in 2^26 of it, are off by up to
+// 2^-36, so a result that is made of those alone would not be what it was, whatever the keys hold that its row does not see or barely.  Results of 2^-14 and
+// more are at most 2^-22 away through them, and so are those of rows that have half of their weight on other keys.  The loop keeps the smallest and the largest
+// value by pair of columns (zeros count as small); only if a smaller result stands in a pair with both, V is read once more for the number of small values in
+// each column, and the rows go to f32_rows if that many keys may have half of the weight.  Of 16 x 4096, d = 128, 430 us, a column of zeros beside an
+// ordinary one takes 476 then, a column 1e-4 of the others 960, a few small values 432 to 458.
 // Probabilities are held times 2^15 below the reference maximum, so those off by 2^-25 of that are below 2^-25 of the largest.
 constexpr float kPieceStep = 2048.0f;        // the lower piece is held times this
 constexpr float kTopExponent = 15.0f;        // probabilities are held times 2^15
-constexpr float kSmallestValue = 0x1p-10f;
+constexpr float kSmallestExact = 0x1p-14f;   // what the pieces hold to all of their bits
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -57,8 +62,10 @@ struct F32PiecesCfg {
     static constexpr int V_AT = 2 * BUF, LDS_TILES = 4 * BUF;
     static constexpr int LDS_ROWS = 4 * F32Cfg<D>::WAVE_LDS;  // what f32_rows uses
     static constexpr int LDS_BYTES = (LDS_TILES > LDS_ROWS ? LDS_TILES : LDS_ROWS) + 32;  // and two flags of each wavefront
-    static constexpr int COLUMNS_AT = KG == 1 ? 0 : 4 * D * 128 + 4 * 256;  // largest values by column, behind the partial results that meet in the tiles' place
-    static_assert(COLUMNS_AT + ROWS * D * 4 <= LDS_BYTES - 32, "no room for them");
+    // in the tiles' place, behind the loop: the largest value of each column and the smallest, or the number of small ones, as each row of threads has found
+    // them, and what columns are suspected of
+    static constexpr int LARGEST_AT = 0, SMALL_AT = LARGEST_AT + ROWS * D * 4, SUSPECTS_AT = SMALL_AT + ROWS * D * 4;
+    static_assert(SUSPECTS_AT + D * 4 <= LDS_BYTES - 32, "no room for them");
 };
 
 template <int D, int KG, bool CAUSAL>
@@ -150,13 +157,21 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         split8(raw[0], raw[1], piece);
         store_pieces(piece, i, at);
     };
-    floatx4 vmax[2];  // largest of the values fetched, by column
+    float v_up = 1.f, v_up_step = kPieceStep;  // V is held times v_up
+    auto split_values = [&](const floatx4 (&raw)[2], int e, uint4v (&piece)[2]) __attribute__((always_inline)) {  // as split_pair, scaled
+        const float a = raw[e / 2][2 * (e % 2)], b = raw[e / 2][2 * (e % 2) + 1];
+        const half2v h = pack_f16(a * v_up, b * v_up);
+        const half2v l = pack_f16(__builtin_fmaf((float)h[0], -kPieceStep, a * v_up_step), __builtin_fmaf((float)h[1], -kPieceStep, b * v_up_step));
+        piece[0][e] = __builtin_bit_cast(uint32_t, h);
+        piece[1][e] = __builtin_bit_cast(uint32_t, l);
+    };
+    floatx4 vmax, vmin;  // largest and smallest of the values fetched, by pair of columns
 #pragma unroll
-    for (int e = 0; e < 4; ++e) vmax[0][e] = vmax[1][e] = 0.f;
-    auto largest_pair = [&](const floatx4 (&raw)[2], int e) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            asm("v_max_f32 %0, %0, |%1|" : "+v"(vmax[e / 2][2 * (e % 2) + k]) : "v"(raw[e / 2][2 * (e % 2) + k]));  // (fmaxf is two instructions)
+    for (int e = 0; e < 4; ++e) vmax[e] = 0.f, vmin[e] = INFINITY;
+    auto extremes_of_pair = [&](const floatx4 (&raw)[2], int e) __attribute__((always_inline)) {
+        const float a = raw[e / 2][2 * (e % 2)], b = raw[e / 2][2 * (e % 2) + 1];
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(vmax[e]) : "v"(a), "v"(b));  // (fmaxf is two instructions)
+        asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(vmin[e]) : "v"(a), "v"(b));
     };
 
     // ---- operands
@@ -278,7 +293,7 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         __builtin_amdgcn_sched_barrier(0);
     };
     constexpr int GA = DS, GB = 2 * DB;  // groups of three MFMAs in phase A and B
-    using PerA = std::integral_constant<int, (8 * 9 + 4 * CH * 8 + 3 * GA - 1) / (3 * GA)>;
+    using PerA = std::integral_constant<int, (8 * 9 + 4 * CH * 10 + 3 * GA - 1) / (3 * GA)>;
     using PerB = std::integral_constant<int, (4 * CH * 6 + 24 + 3 * GB - 1) / (3 * GB)>;
 
     // ---- prologue
@@ -327,12 +342,16 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         const bool any = __builtin_amdgcn_ballot_w64(unfit) != 0;
         if (lane == 0) flags[wave] = any;
     };
-    // a first tile of small values only: flags 4 .. 7 say where there is a value, and where there is one large enough
-    const bool any_value = __builtin_amdgcn_ballot_w64(v0 > 0.f) != 0, any_large = __builtin_amdgcn_ballot_w64(v0 >= kSmallestValue) != 0;
-    if (lane == 0) flags[4 + wave] = (any_value ? 1 : 0) | (any_large ? 2 : 0);
+    v0 = wave_max(v0);
+    if (lane == 0) flags[4 + wave] = (int)bits(v0);
     raise_flag();
     meet();
-    unfit = any_unfit() || (flags[4] | flags[5] | flags[6] | flags[7]) == 1;
+    // V times the power of two that brings the largest value of the first tile to 2^12 .. 2^13 (4 if there are zeros only)
+    const int v0_exponent = __builtin_amdgcn_readfirstlane(max(max(flags[4], flags[5]), max(flags[6], flags[7]))) >> 23;
+    const int v_shift = 139 - (v0_exponent ? v0_exponent : 129);
+    v_up = __builtin_bit_cast(float, (127 + v_shift) << 23);
+    v_up_step = __builtin_bit_cast(float, (127 + 11 + v_shift) << 23);
+    unfit = any_unfit() || (v0_exponent && v0_exponent < 23) || v0_exponent == 255;
     if (!unfit) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) xa[r] = xb[r] = 0.f;
@@ -340,9 +359,10 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         read_k(1, 0);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
+            uint4v piece[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) largest_pair(rv[i], e);
-            store_chunk(rv[i], i, C::V_AT);
+            for (int e = 0; e < 4; ++e) extremes_of_pair(rv[i], e), split_values(rv[i], e, piece);
+            store_pieces(piece, i, C::V_AT);
             store_chunk(rk[i], i, C::BUF);
         }
         fetch(Vh, 1, rv);
@@ -392,8 +412,8 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
                 if (more) {
 #pragma unroll
                     for (int k = PAIRS_A * g; k < PAIRS_A * (g + 1); ++k) {
-                        largest_pair(rv[k / 4], k % 4);
-                        split_pair(rv[k / 4][0], rv[k / 4][1], k % 4, piece);
+                        extremes_of_pair(rv[k / 4], k % 4);
+                        split_values(rv[k / 4], k % 4, piece);
                         if (k % 4 == 3) {
                             store_pieces(piece, k / 4, C::V_AT + (1 - odd) * C::BUF);
                             fetch_chunk(Vh, i + 2, k / 4, rv[k / 4]);
@@ -465,23 +485,21 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
 
         // ---- results: key groups meet in LDS, in the lane layout they have; each merges its share of the columns
         constexpr int QUADS = D / 8, OQ = QUADS / KG;
-        const float total = halves_sum(lsum);
+        const float total = halves_sum(lsum), v_down = __builtin_bit_cast(float, (127 - v_shift) << 23);
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[db][r] = __builtin_fmaf(osmall[db][r], 1.0f / kPieceStep, oacc[db][r]);
-        float* const columns = (float*)(smem + C::COLUMNS_AT);
-        *(floatx4*)(columns + ld_row * D + 8 * ld_chunk) = vmax[0];
-        *(floatx4*)(columns + ld_row * D + 8 * ld_chunk + 4) = vmax[1];
         floatx4 out[OQ];
+        float weights = total;  // of a row's keys, the largest at most 2^kTopExponent
         if (KG > 1) {
             floatx4* const part = (floatx4*)smem + lane;
             float* const stat = (float*)(smem + 4 * QUADS * 1024) + lane;
 #pragma unroll
             for (int q = 0; q < QUADS; ++q) part[(wave * QUADS + q) * 64] = floatx4{oacc[q / 4][4 * (q % 4)], oacc[q / 4][4 * (q % 4) + 1], oacc[q / 4][4 * (q % 4) + 2], oacc[q / 4][4 * (q % 4) + 3]};
             stat[wave * 64] = half ? total : m;
+            meet();
         }
-        meet();
         if (KG > 1) {
             const floatx4* const part = (const floatx4*)smem + lane;
             const float* const stat = (const float*)(smem + 4 * QUADS * 1024) + lane;
@@ -496,6 +514,7 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
                 w[k] = __builtin_amdgcn_exp2f(w[k] - M);
                 L += w[k] * stat[(rg * KG + k) * 64 + 32 * (1 - half)];
             }
+            weights = L;
             const float inv = 1.0f / L;
 #pragma unroll
             for (int i = 0; i < OQ; ++i) {
@@ -520,19 +539,85 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         for (int q = 0; q < OQ; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e) unfit |= !(__builtin_fabsf(out[q][e]) < INFINITY);
-        if (tid < D) {
-            float top = 0.f;
-#pragma unroll
-            for (int r = 0; r < C::ROWS; ++r) top = __builtin_fmaxf(top, columns[r * D + tid]);
-            unfit |= top > 0.f && top < kSmallestValue;
-        }
-        raise_flag();
+        const float limit = kSmallestExact * v_down;
+        const bool suspect = __builtin_fminf(__builtin_fminf(vmin[0], vmin[1]), __builtin_fminf(vmin[2], vmin[3])) < limit;
+        const int state = (__builtin_amdgcn_ballot_w64(unfit) != 0 ? 1 : 0) | (__builtin_amdgcn_ballot_w64(suspect) != 0 ? 2 : 0);
+        if (lane == 0) flags[wave] = state;
         meet();
-        unfit = any_unfit();
+        const int states = flags[0] | flags[1] | flags[2] | flags[3];
+        unfit = (states & 1) != 0;
+        if (__builtin_expect(states == 2, 0)) {
+            float* const largest = (float*)(smem + C::LARGEST_AT);
+            float* const small = (float*)(smem + C::SMALL_AT);
+            float* const suspects = (float*)(smem + C::SUSPECTS_AT);
+            auto leave = [&](float* at, const floatx4& lo, const floatx4& hi) __attribute__((always_inline)) {
+                *(floatx4*)(at + ld_row * D + 8 * ld_chunk) = lo;
+                *(floatx4*)(at + ld_row * D + 8 * ld_chunk + 4) = hi;
+            };
+            // a small result in a column whose n small values may have half of the row's weight between them (n: suspects[column])
+            auto any_harmed = [&](int at) __attribute__((always_inline)) {
+                bool mine = false;
+#pragma unroll
+                for (int q = 0; q < OQ; ++q) {
+                    const floatx4 n = *(const floatx4*)(suspects + 8 * (kg * OQ + q) + 4 * half);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) mine |= __builtin_fabsf(out[q][e]) < kSmallestExact && n[e] * 0x1p16f > weights;
+                }
+                const bool any = __builtin_amdgcn_ballot_w64(mine) != 0;
+                if (lane == 0) flags[at + wave] = any;
+                meet();
+                return (flags[at] | flags[at + 1] | flags[at + 2] | flags[at + 3]) != 0;
+            };
+            leave(largest, vmax.xxyy, vmax.zzww);
+            leave(small, vmin.xxyy, vmin.zzww);
+            meet();
+            if (tid < D) {
+                float top = 0.f, low = INFINITY;
+#pragma unroll
+                for (int r = 0; r < C::ROWS; ++r) {
+                    top = __builtin_fmaxf(top, largest[r * D + tid]);
+                    low = __builtin_fminf(low, small[r * D + tid]);
+                }
+                suspects[tid] = top > 0.f && low < limit ? INFINITY : 0.f;
+            }
+            meet();
+            if (any_harmed(4)) {
+                floatx4 hi[2], n[2];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) hi[0][e] = hi[1][e] = n[0][e] = n[1][e] = 0.f;
+#pragma unroll 4
+                for (int key = ld_row; key < kv_len; key += C::ROWS) {
+                    const char* const from = Vh + (size_t)key * C::GROWB + ld_chunk * 32;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const floatx4 x = *(const floatx4*)(from + 16 * i);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            hi[i][e] = __builtin_fmaxf(hi[i][e], __builtin_fabsf(x[e]));
+                            n[i][e] += __builtin_fabsf(x[e]) < limit ? 1.f : 0.f;
+                        }
+                    }
+                }
+                leave(largest, hi[0], hi[1]);
+                leave(small, n[0], n[1]);
+                meet();
+                if (tid < D) {
+                    float top = 0.f, all = 0.f;
+#pragma unroll
+                    for (int r = 0; r < C::ROWS; ++r) {
+                        top = __builtin_fmaxf(top, largest[r * D + tid]);
+                        all += small[r * D + tid];
+                    }
+                    suspects[tid] = top > 0.f ? all : 0.f;
+                }
+                meet();
+                unfit = any_harmed(0);
+            }
+        }
         if (!unfit && qrow < N) {
             float* const Or = O + head + (size_t)qrow * D + 4 * half;
 #pragma unroll
-            for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = out[q];
+            for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = out[q] * v_down;
         }
     }
     if (__builtin_expect(unfit, 0)) {  // of the whole workgroup

@@ -96,3 +96,36 @@ def test_low_keys_and_infinite_values(heads, d, low):
     assert torch.isposinf(out[:, some][:, :, rows][..., 3]).all()
     ref = oracle.attention_cross(q[:, some], k[:, some, :200], v[:, some, :200], scale, 0)
     check_close(to_host_f64(out[:, some][:, :, rows])[..., rest], ref[:, :, rows][..., rest], "f32", f"low keys {low}")
+
+
+def elementwise_excess(got, q, k, v, scale, mask, bound):
+    """How far the worst element is off, in units of `bound` times the sum of |p v| that makes it up (64 bits)."""
+    x = [t.astype(np.float64) for t in (q, k, v)]
+    s = np.matmul(x[0], x[1].swapaxes(-1, -2)) * scale
+    if mask:
+        s = np.where(np.tri(s.shape[-2], dtype=bool), s, -np.inf)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    made_of = np.matmul(p, np.abs(x[2]))
+    return float((np.abs(got - np.matmul(p, x[2])) / np.maximum(made_of * bound, 1e-300)).max())
+
+
+# A row's own exponents, up to 16 here (64 with one heavy key), are off by 2^-25 of that and the sums by a few 2^-24: 3e-6 and 1e-5.
+@pytest.mark.parametrize("heads", HEADS)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("small", [1e-7, 1e-12])
+@pytest.mark.parametrize("where", ["first keys", "first keys of a column", "heavy key", "heavy key in a column"])
+def test_rows_that_see_small_values(heads, d, small, where):
+    """What a row gets keeps its relative precision, element by element, also where keys that it does not see, or barely, have far larger values."""
+    N, scale, causal = 390, float(np.float32(d ** -0.5)), where.startswith("first")
+    q, k, v = inputs(heads, N, d, 5000 + d)
+    columns = slice(9, 10) if where.endswith("column") else slice(None)
+    if causal:
+        v[:, :, :40, columns] *= np.float32(small)
+    else:
+        q[..., 0], k[..., 0] = 8.0, 0.0
+        k[:, :, 200, :], k[:, :, 200, 0] = 0.0, 5.0 / scale
+        v[:, :, 200, columns] *= np.float32(small)
+    out = to_host_f64(run(*(to_device(x, "f32") for x in (q, k, v)), scale, int(causal)))
+    some = [0, heads - 1]
+    assert elementwise_excess(out[:, some], q[:, some], k[:, some], v[:, some], scale, causal, 3e-6 if causal else 1e-5) <= 1.0
