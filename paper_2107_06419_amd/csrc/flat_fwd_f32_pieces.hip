@@ -38,7 +38,9 @@ namespace flat {
 // value by pair of columns (zeros count as small); only if a smaller result stands in a pair with both, V is read once more for the number of small values in
 // each column, and the rows go to f32_rows if that many keys may have half of the weight.  Of 16 x 4096, d = 128, 430 us, a column of zeros beside an
 // ordinary one takes 476 then, a column 1e-4 of the others 960, a few small values 432 to 458.
-// Probabilities are held times 2^15 below the reference maximum, so those off by 2^-25 of that are below 2^-25 of the largest.
+// Probabilities are held times 2^15 below the reference maximum, the lower piece times 2^11 as those of K and V: weights above 2^-25 of a row's largest have
+// all of their bits, smaller ones a step of 2^-48 of it.  Where such weights are all that a column gets (values that select keys) the result is small for
+// its zeros, and the rows go to f32_rows as above.
 constexpr float kPieceStep = 2048.0f;        // the lower piece is held times this
 constexpr float kTopExponent = 15.0f;        // probabilities are held times 2^15
 constexpr float kSmallestExact = 0x1p-14f;   // what the pieces hold to all of their bits
@@ -230,14 +232,13 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e) p[i][e] = pf[i][4 * t + e / 2][e % 2];
-        oacc[db] = mfma_f16_32x32x16(vf[g % 3][0], p[1], oacc[db]);
-        osmall[db] = mfma_f16_32x32x16(vf[g % 3][1], p[0], osmall[db]);
+        osmall[db] = mfma_f16_32x32x16(vf[g % 3][0], p[1], osmall[db]);
         oacc[db] = mfma_f16_32x32x16(vf[g % 3][0], p[0], oacc[db]);
+        osmall[db] = mfma_f16_32x32x16(vf[g % 3][1], p[0], osmall[db]);
     };
-    uint32_t one_one = 0x3c003c00;  // (in a register: not as an inline constant, which does not fill both halves)
-    float minus_one = -1.0f;  // (in a register: the compiler makes one instruction of the product and the sum then)
-    asm("" : "+s"(one_one), "+s"(minus_one));
-    const half2v ones = __builtin_bit_cast(half2v, one_one);
+    uint32_t one_one = 0x3c003c00, steps = 0x10001000;  // (in registers: not as inline constants, which do not fill both halves)
+    asm("" : "+s"(one_one), "+s"(steps));
+    const half2v ones = __builtin_bit_cast(half2v, one_one), small_ones = __builtin_bit_cast(half2v, steps);  // 1 and 1 / kPieceStep
     float psum;  // of a tile's probabilities
     float ex[8][2];
     auto exponentiate = [&](int j) __attribute__((always_inline)) {  // probabilities 2 j and 2 j + 1 of a lane
@@ -245,12 +246,12 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         ex[j][1] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * j + 1], cq, -m));
     };
     auto split_probabilities = [&](int j) __attribute__((always_inline)) {
-        const half2v h = pack_f16(ex[j][0], ex[j][1]);
-        const half2v l = pack_f16(__builtin_fmaf((float)h[0], minus_one, ex[j][0]), __builtin_fmaf((float)h[1], minus_one, ex[j][1]));
+        half2v h, l;
+        split2(ex[j][0], ex[j][1], h, l);
         pf[0][j] = h;
         pf[1][j] = l;
         // the sum of what is multiplied, so that an error common to a row's probabilities cancels
-        psum = __builtin_amdgcn_fdot2(l, ones, j == 0 ? 0.f : psum, false);
+        psum = __builtin_amdgcn_fdot2(l, small_ones, j == 0 ? 0.f : psum, false);
         psum = __builtin_amdgcn_fdot2(h, ones, psum, false);
         asm volatile("" : "+v"(pf[0][j]), "+v"(pf[1][j]), "+v"(psum));  // here, between the MFMAs, not where they are used
     };
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         __builtin_amdgcn_sched_barrier(0);
     };
     constexpr int GA = DS, GB = 2 * DB;  // groups of three MFMAs in phase A and B
-    using PerA = std::integral_constant<int, (8 * 9 + 4 * CH * 10 + 3 * GA - 1) / (3 * GA)>;
+    using PerA = std::integral_constant<int, (8 * 11 + 4 * CH * 10 + 3 * GA - 1) / (3 * GA)>;
     using PerB = std::integral_constant<int, (4 * CH * 6 + 24 + 3 * GB - 1) / (3 * GB)>;
 
     // ---- prologue

@@ -129,3 +129,18 @@ def test_rows_that_see_small_values(heads, d, small, where):
     out = to_host_f64(run(*(to_device(x, "f32") for x in (q, k, v)), scale, int(causal)))
     some = [0, heads - 1]
     assert elementwise_excess(out[:, some], q[:, some], k[:, some], v[:, some], scale, causal, 3e-6 if causal else 1e-5) <= 1.0
+
+
+@pytest.mark.parametrize("heads", HEADS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_that_select_keys(heads, d):
+    """V of zeros and one 1 per key: a result is the weight of some keys, from all of it to 1e-13, and keeps its relative precision.  (Exponents up to 64 are off by 2^-19.)"""
+    N = 390
+    q, k, v = (np.zeros((1, heads, N, d), np.float32) for _ in range(3))
+    of = np.arange(N) % d
+    v[:, :, np.arange(N), of] = 1.0
+    q[..., 0] = 1.0 + 0.1 * np.arange(N, dtype=np.float32) / N
+    k[..., 0] = -27.0 * of.astype(np.float32) / d
+    out = to_host_f64(run(*(to_device(x, "f32") for x in (q, k, v)), 1.0, 0))
+    some = [0, heads - 1]
+    assert elementwise_excess(out[:, some], q[:, some], k[:, some], v[:, some], 1.0, 0, 1e-5) <= 1.0
