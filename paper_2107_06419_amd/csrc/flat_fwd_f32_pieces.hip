@@ -31,7 +31,11 @@ namespace flat {
 // What the pieces cannot hold goes to f32_rows, for the 32 RG rows of the workgroup:
 //   infinities and NaN, and |x| beyond 65504 (h is infinite, x - h infinite or a NaN, and the result no number);
 //   logits where |q|max c d^1/2 >= 2^10 (a key below 2^-14 is off by up to 2^-36, which then moves a logit by 2^-26; q is scaled by row);
-//   V whose largest element in the first tile is infinite or below 2^-104, or which grows to 8 to 16 times that later on.
+//   V whose largest element in the first tile and the last keys is infinite or below 2^-104, or which grows to 8 to 16 times that in between;
+//   a scale of 0 with masked keys.
+// f32_rows then takes the workgroup's RG row blocks at once, with KG wavefronts each.  Logits, and what the first tile and the last four keys show, are known before
+// any work: 16 x 4096, d = 128, padding of -1e5 at the end 1086 us with fp32 MFMAs alone, 1084; 16 causal x 2049 160 and 143, but 256 x 300 130 and 154, for the
+// rows that a workgroup of 128 has too many.  What else comes up costs the pass on top, where the results are seen: an infinity in the middle 1069 and 1481.
 // V is held times the power of two that brings that element to 2^12 .. 2^13.  Elements that are then below 2^-14, a part in 2^26 of it, are off by up to
 // 2^-36, so a result that is made of those alone would not be what it was, whatever the keys hold that its row does not see or barely.  Results of 2^-14 and
 // more are at most 2^-22 away through them, and so are those of rows that have half of their weight on other keys.  The loop keeps the smallest and the largest
@@ -309,6 +313,18 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         }
     }
     fetch(Vh, 0, rv);
+    // the last four keys, one per wavefront: keys marked as padding by a large number, and values that have grown, are mostly to be seen there
+    const size_t last_at = (size_t)max(kv_len - 1 - wave, 0) * C::GROWB + lane * (C::GROWB / 64);
+    typedef float lane_part __attribute__((ext_vector_type(D / 64)));
+    const lane_part last_k = *(const lane_part*)(Kh + last_at), last_v = *(const lane_part*)(Vh + last_at);
+    float kmax = 0.f, v0 = 0.f;
+    auto largest_of = [&](const floatx4 (&raw)[CH][2], float& top) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(raw[i][0][e]), "v"(raw[i][1][e]));
+    };
+    largest_of(rk, kmax);
 #pragma unroll
     for (int i = 0; i < CH; ++i) store_chunk(rk[i], i, 0);
     fetch(Kh, 1, rk);
@@ -329,12 +345,14 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
 #pragma unroll
         for (int p = 0; p < 2; ++p) qf[p][ds] = __builtin_bit_cast(half8, piece[p]);
     }
-    float v0 = 0.f;
+    largest_of(rv, v0);
 #pragma unroll
-    for (int i = 0; i < CH; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v0 = __builtin_fmaxf(__builtin_fmaxf(v0, __builtin_fabsf(rv[i][0][e])), __builtin_fabsf(rv[i][1][e]));
-    bool unfit = !(qmax * c < (D == 64 ? 128.0f : 90.5f));
+    for (int e = 0; e < D / 64; ++e) {
+        kmax = __builtin_fmaxf(kmax, __builtin_fabsf(last_k[e]));
+        v0 = __builtin_fmaxf(v0, __builtin_fabsf(last_v[e]));
+    }
+    // (a scale of 0 makes a NaN of the exponents of masked keys)
+    bool unfit = !(qmax * c < (D == 64 ? 128.0f : 90.5f)) || kmax > 65504.0f || (c == 0.f && (CAUSAL || N % BC != 0));
     int* const flags = (int*)(smem + C::LDS_BYTES - 32);
     auto any_unfit = [&]() __attribute__((always_inline)) {  // of the workgroup; the flags are written on the way into a barrier
         return (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
@@ -347,7 +365,7 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
     if (lane == 0) flags[4 + wave] = (int)bits(v0);
     raise_flag();
     meet();
-    // V times the power of two that brings the largest value of the first tile to 2^12 .. 2^13 (4 if there are zeros only)
+    // V times the power of two that brings the largest value of the first tile and the last keys to 2^12 .. 2^13 (4 if there are zeros only)
     const int v0_exponent = __builtin_amdgcn_readfirstlane(max(max(flags[4], flags[5]), max(flags[6], flags[7]))) >> 23;
     const int v_shift = 139 - (v0_exponent ? v0_exponent : 129);
     v_up = __builtin_bit_cast(float, (127 + v_shift) << 23);
@@ -622,12 +640,11 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         }
     }
     if (__builtin_expect(unfit, 0)) {  // of the whole workgroup
-#pragma unroll 1
-        for (int rb = 0; rb < RG; ++rb) {
-            if (qt * BR + 32 * rb >= N) break;
-            __syncthreads();
-            f32_rows<D, 4, CAUSAL>(smem, Q, K, V, O, N, bh, qt * RG + rb, c);
-        }
+        __syncthreads();
+        if (q0w < N)
+            f32_rows<D, KG, CAUSAL>(smem + rg * KG * F32Cfg<D>::WAVE_LDS, Q, K, V, O, N, bh, qt * RG + rg, c, kg);
+        else if (KG > 1)
+            __syncthreads();  // the one in f32_rows
     }
 }
 

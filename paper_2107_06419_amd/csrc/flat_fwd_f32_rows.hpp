@@ -56,17 +56,17 @@ struct F32Cfg {
 constexpr float kF32Headroom = 4.0f;  // of the reference maximum above the row maximum, log2 units
 constexpr float kF32LargestExponent = 96.0f;  // 2^31 probabilities of 2^96 are still a number
 
-// 32 query rows, row block qt of head bh, by the NW wavefronts of a workgroup.
+// 32 query rows, row block qt of head bh, by NW wavefronts of a workgroup, this one the wave-th of them, in their part of LDS.  With NW > 1 there
+// is one barrier, for the whole workgroup: every other group of NW has to come to one as well.
 template <int D, int NW, bool CAUSAL>
 __device__ __forceinline__ void f32_rows(char* const smem, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-                                         float* __restrict__ O, int N, int bh, int qt, float c) {
+                                         float* __restrict__ O, int N, int bh, int qt, float c, int wave) {
     using C = F32Cfg<D>;
     constexpr int G = C::G, DB = C::DB, LOADS = C::LOADS;
     typedef float floatdb __attribute__((ext_vector_type(DB)));
     typedef const floatx4 __attribute__((address_space(3))) * lds_f4_ptr;
     typedef const floatdb __attribute__((address_space(3))) * lds_fdb_ptr;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     const size_t head = (size_t)bh * N * D;
     const char* const Kh = (const char*)(K + head);
     const char* const Vh = (const char*)(V + head);
