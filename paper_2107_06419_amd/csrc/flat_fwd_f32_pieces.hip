@@ -31,6 +31,7 @@ namespace flat {
 // What the pieces cannot hold goes to f32_rows, for the 32 RG rows of the workgroup:
 //   infinities and NaN, and |x| beyond 65504 (h is infinite, x - h infinite or a NaN, and the result no number);
 //   logits where |q|max c d^1/2 >= 2^10 (a key below 2^-14 is off by up to 2^-36, which then moves a logit by 2^-26; q is scaled by row);
+//   rows of Q below 2^-88 where the scale is above 2^30 (their power of two would be above 2^100);
 //   V whose largest element in the first tile and the last keys is infinite or below 2^-104, or which grows to 8 to 16 times that in between;
 //   a scale of 0 with masked keys.
 // f32_rows then takes the workgroup's RG row blocks at once, with KG wavefronts each.  Logits, and what the first tile and the last four keys show, are known before
@@ -351,8 +352,9 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         kmax = __builtin_fmaxf(kmax, __builtin_fabsf(last_k[e]));
         v0 = __builtin_fmaxf(v0, __builtin_fabsf(last_v[e]));
     }
-    // (a scale of 0 makes a NaN of the exponents of masked keys)
-    bool unfit = !(qmax * c < (D == 64 ? 128.0f : 90.5f)) || kmax > 65504.0f || (c == 0.f && (CAUSAL || N % BC != 0));
+    // (a scale of 0 makes a NaN of the exponents of masked keys; with a scale below 2^30 rows too small for `up` have logits below 2^-35)
+    bool unfit = !(qmax * c < (D == 64 ? 128.0f : 90.5f)) || kmax > 65504.0f || (c == 0.f && (CAUSAL || N % BC != 0)) ||
+                 (qmax > 0.f && qmax < 0x1p-88f && c > 0x1p30f);
     int* const flags = (int*)(smem + C::LDS_BYTES - 32);
     auto any_unfit = [&]() __attribute__((always_inline)) {  // of the workgroup; the flags are written on the way into a barrier
         return (flags[0] | flags[1] | flags[2] | flags[3]) != 0;

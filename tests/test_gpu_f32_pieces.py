@@ -144,3 +144,21 @@ def test_values_that_select_keys(heads, d):
     out = to_host_f64(run(*(to_device(x, "f32") for x in (q, k, v)), 1.0, 0))
     some = [0, heads - 1]
     assert elementwise_excess(out[:, some], q[:, some], k[:, some], v[:, some], 1.0, 0, 1e-5) <= 1.0
+
+
+@pytest.mark.parametrize("heads", HEADS)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("q_by", [1e-30, 1e-36])
+def test_small_queries_and_a_large_scale(heads, d, q_by):
+    """The logits are ordinary ones, however far apart Q and the scale are.  (Bound: as for the magnitudes above.)"""
+    N = 390
+    q, k, v = inputs(heads, N, d, 5200 + d)
+    q *= np.float32(q_by)
+    scale = float(np.float32(d ** -0.5 / q_by))
+    out = run(*(to_device(x, "f32") for x in (q, k, v)), scale, 0)
+    some = [0, heads - 1]
+    x = [t[:, some].astype(np.float64) for t in (q, k, v)]
+    s = np.matmul(x[0], x[1].swapaxes(-1, -2)) * scale
+    p = np.exp(s - s.max(-1, keepdims=True))
+    ref = np.matmul(p / p.sum(-1, keepdims=True), x[2])
+    assert np.linalg.norm(out[:, some].double().cpu().numpy() - ref) <= 1.5e-6 * np.linalg.norm(ref)
