@@ -637,8 +637,14 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
         }
         if (!unfit && qrow < N) {
             float* const Or = O + head + (size_t)qrow * D + 4 * half;
+            if (CAUSAL && qrow == 0) {  // of its one key, which the pieces may hold to a bit less
+                const float* const Vr = V + head + 4 * half;
 #pragma unroll
-            for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = out[q] * v_down;
+                for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = *(const floatx4*)(Vr + 8 * (kg * OQ + q));
+            } else {
+#pragma unroll
+                for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = out[q] * v_down;
+            }
         }
     }
     if (__builtin_expect(unfit, 0)) {  // of the whole workgroup

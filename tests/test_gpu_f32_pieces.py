@@ -162,3 +162,12 @@ def test_small_queries_and_a_large_scale(heads, d, q_by):
     p = np.exp(s - s.max(-1, keepdims=True))
     ref = np.matmul(p / p.sum(-1, keepdims=True), x[2])
     assert np.linalg.norm(out[:, some].double().cpu().numpy() - ref) <= 1.5e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("heads", HEADS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_row_of_one_key_is_its_value(heads, d):
+    """The causal mask leaves query 0 one key, of weight 1: its result is that key's value, bit for bit."""
+    q, k, v = (to_device(x, "f32") for x in inputs(heads, 390, d, 5300 + d))
+    out = run(q, k, v, float(np.float32(d ** -0.5)), 1)
+    assert torch.equal(out[:, :, 0], v[:, :, 0])
