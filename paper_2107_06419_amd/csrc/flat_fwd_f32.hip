@@ -30,7 +30,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void fwd_f32_kernel(const
         qt = n_qtiles - 1 - from_end;
     }
 
-    f32_rows<D, NW, CAUSAL>(smem, Q, K, V, O, N, bh, qt, c, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    f32_rows<D, NW, CAUSAL>(smem, Q, K, V, O, N, bh, qt, c, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
 }
 
 template <int D, int NW, bool CAUSAL>

@@ -76,7 +76,7 @@ struct F32PiecesCfg {
 };
 
 template <int D, int KG, bool CAUSAL>
-__global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_f32_pieces_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                                                        const float* __restrict__ V, float* __restrict__ O, int N,
                                                                                        int n_qtiles, int n_blocks, int blocks_per_xcd, int n_heads,
                                                                                        const Divisor by_qtiles, const Divisor by_heads, float c) {
@@ -111,6 +111,12 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
     const int kv_len = CAUSAL ? min(N, qt * BR + BR) : N;
     const int n_tiles = (kv_len + BC - 1) / BC;
 
+    // The lane's number for what follows the loop; with `lane` what that has in common with the start is kept through the loop, some of it in scratch memory.
+    auto lane_again = [&]() __attribute__((always_inline)) {
+        int l = threadIdx.x & 63;
+        asm("" : "+v"(l));
+        return l;
+    };
     auto fence = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -635,9 +641,10 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
                 unfit = any_harmed(0);
             }
         }
-        if (!unfit && qrow < N) {
-            float* const Or = O + head + (size_t)qrow * D + 4 * half;
-            if (CAUSAL && qrow == 0) {  // of its one key, which the pieces may hold to a bit less
+        const int row = q0w + (lane_again() & 31);
+        if (!unfit && row < N) {
+            float* const Or = O + head + (size_t)row * D + 4 * half;
+            if (CAUSAL && row == 0) {  // of its one key, which the pieces may hold to a bit less
                 const float* const Vr = V + head + 4 * half;
 #pragma unroll
                 for (int q = 0; q < OQ; ++q) *(floatx4*)(Or + 8 * (kg * OQ + q)) = *(const floatx4*)(Vr + 8 * (kg * OQ + q));
@@ -650,7 +657,7 @@ __global__ __launch_bounds__(256, D == 64 && KG < 4 ? 2 : 1) void fwd_f32_pieces
     if (__builtin_expect(unfit, 0)) {  // of the whole workgroup
         __syncthreads();
         if (q0w < N)
-            f32_rows<D, KG, CAUSAL>(smem + rg * KG * F32Cfg<D>::WAVE_LDS, Q, K, V, O, N, bh, qt * RG + rg, c, kg);
+            f32_rows<D, KG, CAUSAL>(smem + rg * KG * F32Cfg<D>::WAVE_LDS, Q, K, V, O, N, bh, qt * RG + rg, c, kg, lane_again());
         else if (KG > 1)
             __syncthreads();  // the one in f32_rows
     }

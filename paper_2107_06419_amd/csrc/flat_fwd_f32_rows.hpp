@@ -60,13 +60,13 @@ constexpr float kF32LargestExponent = 96.0f;  // 2^31 probabilities of 2^96 are 
 // is one barrier, for the whole workgroup: every other group of NW has to come to one as well.
 template <int D, int NW, bool CAUSAL>
 __device__ __forceinline__ void f32_rows(char* const smem, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-                                         float* __restrict__ O, int N, int bh, int qt, float c, int wave) {
+                                         float* __restrict__ O, int N, int bh, int qt, float c, int wave, int lane) {
     using C = F32Cfg<D>;
     constexpr int G = C::G, DB = C::DB, LOADS = C::LOADS;
     typedef float floatdb __attribute__((ext_vector_type(DB)));
     typedef const floatx4 __attribute__((address_space(3))) * lds_f4_ptr;
     typedef const floatdb __attribute__((address_space(3))) * lds_fdb_ptr;
-    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int l32 = lane & 31, half = lane >> 5;
     const size_t head = (size_t)bh * N * D;
     const char* const Kh = (const char*)(K + head);
     const char* const Vh = (const char*)(V + head);

@@ -229,3 +229,26 @@ def test_streaming_asm_is_the_only_user_of_m0():
                     uses.append(t)
     assert dmas > 0, "no streaming load found: the check looks at the wrong file"
     assert not uses, f"m0 is used outside the streaming asm: {uses[:5]}"
+
+
+@pytest.mark.parametrize("source", ["flat_fwd_f32.hip", "flat_fwd_f32_pieces.hip"])
+def test_fp32_kernels_use_no_scratch_memory_and_no_m0_beside_the_streaming_asm(source):
+    """As above for the fp32 kernels, and their registers have to do: a spill is scratch memory, which a launch may have to wait for."""
+    import shutil
+    import subprocess
+    import tempfile
+    from paper_2107_06419_amd import build as fb
+    hipcc = fb._hipcc()
+    if shutil.which(hipcc) is None and not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "k.s")
+        subprocess.run([hipcc, *fb.FLAGS, "-S", "--cuda-device-only", "-o", out, os.path.join(ROOT, "paper_2107_06419_amd", "csrc", source)],
+                       check=True, capture_output=True)
+        text = open(out).read()
+    scratch = re.findall(r"\.private_segment_fixed_size: *(\d+)", text)
+    assert scratch and set(scratch) == {"0"}, f"scratch bytes of the kernels of {source}: {scratch}"
+    outside = re.sub(r";;#ASMSTART.*?;;#ASMEND", "", text, flags=re.S)
+    assert "s_mov_b32 m0" in text, "no streaming load found: the check looks at the wrong file"
+    uses = [line for line in outside.splitlines() if re.search(r"\bm0\b", line.split(";")[0])]
+    assert not uses, f"m0 is used outside the streaming asm: {uses[:5]}"
