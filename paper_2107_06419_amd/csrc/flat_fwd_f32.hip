@@ -109,27 +109,45 @@ static int key_groups_of_pieces(int BH, int N, bool causal) {
     return best;
 }
 
+// A form of the fp32 entry point by number: 1, 2 and 4 are fwd_f32_kernel with that many wavefronts per workgroup, -1 and -2 the split products with that
+// many key groups.
+template <int D>
+static int form_of(int BH, int N, bool causal) {
+    const int key_groups = key_groups_of_pieces<D>(BH, N, causal);
+    return key_groups ? -key_groups : wavefronts_per_workgroup<D>(BH, N, causal);
+}
+
 template <int D, bool CAUSAL>
-static hipError_t launch_cfg(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream) {
-    switch (key_groups_of_pieces<D>(BH, N, CAUSAL)) {
-        case 1: return launch_fwd_f32_pieces<D, 1, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
-        case 2: return launch_fwd_f32_pieces<D, 2, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
-        default: break;
-    }
-    switch (wavefronts_per_workgroup<D>(BH, N, CAUSAL)) {
+static hipError_t launch_form(int form, const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream) {
+    switch (form) {
+        case -2: return launch_fwd_f32_pieces<D, 2, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
+        case -1: return launch_fwd_f32_pieces<D, 1, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
         case 1: return launch_shape<D, 1, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
         case 2: return launch_shape<D, 2, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
-        default: return launch_shape<D, 4, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
+        case 4: return launch_shape<D, 4, CAUSAL>(Q, K, V, O, BH, N, scale, stream);
+        default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale,
-                          int causal, hipStream_t stream) {
+int f32_form(int BH, int N, int d, int causal) { return d == 64 ? form_of<64>(BH, N, causal) : form_of<128>(BH, N, causal); }
+
+hipError_t launch_fwd_f32_form(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale, int causal, int form,
+                               hipStream_t stream) {
     if (d == 64)
-        return causal ? launch_cfg<64, true>(Q, K, V, O, BH, N, scale, stream)
-                      : launch_cfg<64, false>(Q, K, V, O, BH, N, scale, stream);
-    return causal ? launch_cfg<128, true>(Q, K, V, O, BH, N, scale, stream)
-                  : launch_cfg<128, false>(Q, K, V, O, BH, N, scale, stream);
+        return causal ? launch_form<64, true>(form, Q, K, V, O, BH, N, scale, stream) : launch_form<64, false>(form, Q, K, V, O, BH, N, scale, stream);
+    return causal ? launch_form<128, true>(form, Q, K, V, O, BH, N, scale, stream) : launch_form<128, false>(form, Q, K, V, O, BH, N, scale, stream);
+}
+
+hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale, int causal, hipStream_t stream) {
+    return launch_fwd_f32_form(Q, K, V, O, BH, N, d, scale, causal, f32_form(BH, N, d, causal), stream);
 }
 
 }  // namespace flat
+
+// For tests, which have to reach every form at its edges: the form a problem takes, and a call with a given one (d 64 or 128, device pointers as
+// flat_attn_fwd_f32 takes them; nothing is checked).  Not part of the interface.
+extern "C" int flat_internal_f32_form(int BH, int N, int d, int causal) { return flat::f32_form(BH, N, d, causal); }
+extern "C" int flat_internal_fwd_f32_form(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale, int causal, int form,
+                                          void* stream) {
+    return (int)flat::launch_fwd_f32_form(Q, K, V, O, BH, N, d, scale, causal, form, static_cast<hipStream_t>(stream));
+}

@@ -114,6 +114,9 @@ template <int D, int KG, bool CAUSAL>
 hipError_t launch_fwd_f32_pieces(const float* Q, const float* K, const float* V, float* O, int BH, int N, float scale, hipStream_t stream);
 hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale,
                           int causal, hipStream_t stream);
+int f32_form(int BH, int N, int d, int causal);  // the form launch_fwd_f32 takes (flat_fwd_f32.hip has their numbers)
+hipError_t launch_fwd_f32_form(const float* Q, const float* K, const float* V, float* O, int BH, int N, int d, float scale, int causal, int form,
+                               hipStream_t stream);
 
 // GEMM -> row softmax -> GEMM through an fp32 [B*H, N, N] workspace.
 hipError_t launch_unfused_bf16(const void* Q, const void* K, const void* V, void* O, int BH, int N, int d, float scale,

@@ -252,3 +252,11 @@ def test_fp32_kernels_use_no_scratch_memory_and_no_m0_beside_the_streaming_asm(s
     assert "s_mov_b32 m0" in text, "no streaming load found: the check looks at the wrong file"
     uses = [line for line in outside.splitlines() if re.search(r"\bm0\b", line.split(";")[0])]
     assert not uses, f"m0 is used outside the streaming asm: {uses[:5]}"
+
+
+@pytest.mark.parametrize("heads,N,d,mask,form", [(16, 2049, 128, 1, -2), (128, 512, 128, 1, -1), (16, 4096, 128, 0, -1), (32, 4096, 64, 0, -1), (16, 1000, 64, 1, -2),
+                                                 (24, 390, 64, 0, -2), (600, 390, 64, 0, -1), (12, 512, 64, 0, 4), (1100, 127, 64, 0, 2), (1100, 127, 128, 0, 1),
+                                                 (16, 4097, 128, 0, 4), (16, 8192, 128, 0, 1)])
+def test_forms_of_the_fp32_entry_point(heads, N, d, mask, form):
+    """Split products (negative: minus the key groups) from 128 to 4096 positions where they are predicted to be faster, else fp32 MFMAs (wavefronts per workgroup)."""
+    assert fa.load_library().flat_internal_f32_form(heads, N, d, mask) == form
