@@ -371,6 +371,18 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_f32_pieces_kernel(co
     };
     v0 = wave_max(v0);
     if (lane == 0) flags[4 + wave] = (int)bits(v0);
+    // A column that has nothing but values below 2^-20 of that, and not only zeros, in the rows of this wavefront: its results would be found too small.
+    // (Of a pair of columns the smaller value: either of them.)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float top = 0.f;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) top = __builtin_fmaxf(top, __builtin_fminf(__builtin_fabsf(rv[i][e / 2][2 * (e % 2)]), __builtin_fabsf(rv[i][e / 2][2 * (e % 2) + 1])));
+        uint64_t low = __builtin_amdgcn_ballot_w64(top < v0 * 0x1p-20f), some = __builtin_amdgcn_ballot_w64(top > 0.f);
+#pragma unroll
+        for (int by = 32; by >= C::CHUNKS; by /= 2) low &= low >> by, some |= some >> by;
+        unfit |= (low & some & ((1ull << C::CHUNKS) - 1)) != 0;
+    }
     raise_flag();
     meet();
     // V times the power of two that brings the largest value of the first tile and the last keys to 2^12 .. 2^13 (4 if there are zeros only)

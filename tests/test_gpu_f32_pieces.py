@@ -171,3 +171,17 @@ def test_a_row_of_one_key_is_its_value(heads, d):
     q, k, v = (to_device(x, "f32") for x in inputs(heads, 390, d, 5300 + d))
     out = run(q, k, v, float(np.float32(d ** -0.5)), 1)
     assert torch.equal(out[:, :, 0], v[:, :, 0])
+
+
+@pytest.mark.parametrize("heads", HEADS)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("weak", [1e-3, 1e-4, 1e-5, 1e-6])
+@pytest.mark.parametrize("mask", [0, 1])
+def test_a_weak_column(heads, d, weak, mask):
+    """A column of V far below the others keeps its relative precision, whether that shows in the first keys or in the results.  (Bound: as for rows above.)"""
+    N, scale = 390, float(np.float32(d ** -0.5))
+    q, k, v = inputs(heads, N, d, 5400 + d + mask)
+    v[..., 11] *= np.float32(weak)
+    out = to_host_f64(run(*(to_device(x, "f32") for x in (q, k, v)), scale, mask))
+    some = [0, heads - 1]
+    assert elementwise_excess(out[:, some], q[:, some], k[:, some], v[:, some], scale, mask, 3e-6) <= 1.0
