@@ -150,10 +150,11 @@ int flat_attn_fwd_blocksparse(const void* Q, const void* K, const void* V, void*
                               const int* tile_offsets, const int* tile_ids, int n_tile_ids, void* stream);
 
 /*
- * Same dataflow in fp32: fp32 inputs, probabilities, sums and results.  Products are those of the fp32 matrix instructions, or (128 to 4096
- * positions, where it is faster) of factors split into two fp16 pieces each, whose error against 64 bits is the smaller one for logits of ordinary spread;
- * inputs that the pieces cannot hold (K beyond 65504, infinities, NaN, very large logits, V that grows to more than 8 times its first values, results
- * made of values of 2^-26 of those) are taken through the former.
+ * Same dataflow in fp32: fp32 inputs, exponentials, sums and results.  Products are those of the fp32 matrix instructions, or (128 to 4096
+ * positions, where it is faster) of factors (Q, K, V and the probabilities) split into two fp16 pieces each: 23 of 24 bits, and sums that are rounded less often.  Their
+ * error against 64 bits is the smaller one for logits of ordinary spread; an element of a row that one key decides, or whose logits are all almost equal, may be off by a bit more.
+ * Probabilities below 2^-25 of a row's largest have a step of 2^-48 of it.  Inputs that the pieces cannot hold (K beyond 65504, infinities, NaN, very large logits, V that
+ * grows to more than 8 times its first values, columns of V or results made of values of 2^-20 to 2^-26 of those) are taken through the former.
  *   Q, K, V: device, const float [B,H,N,d].  O: device, float [B,H,N,d].
  */
 int flat_attn_fwd_f32(const float* Q, const float* K, const float* V, float* O,

@@ -80,13 +80,14 @@ static int wavefronts_per_workgroup(int BH, int N, bool causal) {
 // arithmetic in us: a workgroup takes its steps and 6.5 us for its start and end; a step 1.65 us with one key group and 2.03 with two at d = 128, 1.64 and
 // 1.9 at d = 64, where two workgroups share a compute unit and one alone takes half of that.  So at d = 64 a round that is partly filled counts
 // half at least, and with the causal mask the heaviest workgroup is alone for half of its time; at d = 128 what is left of a second round follows a first
-// one, if only of the lightest blocks.  A unit of the other kernel is 4.2 us.  Fewer than 128 positions: see there.  More than 4096: the results of the two
-// would differ by more than the 1.5e-6 in the 2-norm and 1.5e-5 in an element to which results of this precision are held (6 x 5953, d = 64, 1.7e-6, nearly all
-// of it the error of the fp32 sums, 1.5e-6 against 0.75e-6; 6 causal x 5953, d = 128, 1.4e-5 in an element).
-// Measured, one group / two / the other kernel (the rule's choice in brackets): d = 128, 16 x 2049 causal 103 / 91 / 162 [2], 128 x 512 causal 52 / 69 / 84 [1],
-// 4 x 3000 135 / 93 / 203 [2], 256 x 300 75 / 87 / 131 [1]; d = 64, 12 x 512 18.5 / 14.2 / 13.4 [0], 1 x 2000 53 / 37 / 39 [0], 16 x 1000 causal 32 / 23 / 30
-// [2], 1024 x 128 29 / 34 / 44 [1].  Over 150 random problems 1.3 % behind the best of all on average, 33 % at worst (36 x 226, d = 64: 14.0 [0], two 10.5), and
-// none slower than the other kernel; without the margin of 5 % two are, by 4 and 8 %.
+// one, if only of the lightest blocks.  A unit of the other kernel is 4.2 us.  Fewer than 128 positions: see there.  4096 is where the
+// comparison of the two over random problems ends, in time and in error; no limit of the split products is known beyond it (32 x 4097, d = 64, 506 us and 5.1e-7 against 1134
+// and 6.7e-7; 16 x 8192, d = 128, 1679 and 6.6e-7 against 4302 and 1.8e-6).
+// Measured, one group / two / the other kernel (the rule's choice in brackets): d = 128, 16 x 2049 causal 104 / 93 / 162 [2], 128 x 512 causal 53 / 71 / 85 [1],
+// 4 x 3000 141 / 95 / 202 [2], 256 x 300 71 / 88 / 131 [1]; d = 64, 12 x 512 18.3 / 13.6 / 12.6 [0], 1 x 2000 55 / 38 / 39 [0], 16 x 1000 causal 32 / 23 / 29
+// [2], 1024 x 128 28 / 35 / 44 [1].  Over 500 random problems of 128 to 4096 positions 1.7 % behind the best of all on average, 69 % at worst (216 x 131, d = 64: 24.7 [0], one
+// 14.0; 15 x 602, 25.3 [0], two 16.0).  Of the 355 that take the split products 12 are slower than with the other kernel, by up to 6 % (161 to 192 positions of few heads, d =
+// 128: 16 x 163 14.7 against 14.4); the rest take 0.4 to 1.0 of its time, 0.7 on average.
 template <int D>
 static int key_groups_of_pieces(int BH, int N, bool causal) {
     if (N < 128 || N > 4096) return 0;

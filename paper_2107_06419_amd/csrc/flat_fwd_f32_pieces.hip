@@ -4,15 +4,17 @@
 
 namespace flat {
 
-// x = h + l: h the nearest fp16 to x, l the nearest fp16 to x - h, which has at most 13 significant bits: h + l is x to 2^-23 of it at worst, 2^-25 in
-// the root mean square.  A product of two floats is hh' + (hl' + lh'); ll', left out, is below 2^-22 of it with either sign and 2^-25 in the mean.
+// x = h + l: h the nearest fp16 to x, l the nearest fp16 to x - h, which has at most 13 significant bits: h + l is x to 2^-23 of it at worst,
+// 2^-24.4 in the root mean square (three floats of four are held exactly).  A product of two floats is hh' + (hl' + lh'); ll', left out, is below 2^-22 of it with either sign and 2^-25 in the mean.
 // Three fp16 MFMAs of 32x32x16 take 96 cycles for what 8 fp32 MFMAs of 32x32x2 take 512 for.  Their sums are rounded less often than those of the
 // latter: every 16 products instead of every two, and products with a lower piece are summed apart.
-// Measured error against 64 bits, 2-norm, normal inputs: six heads, d = 64, 130 positions causal 2.04e-7 (fp32 MFMAs 2.13e-7 to 2.25e-7 by their key
-// groups), 1000 without a mask 3.9e-7 (4.3e-7 to 6.9e-7); d = 128 2.0e-7 (2.7e-7), 4.0e-7 (5.0e-7 to 7.3e-7); with Q three times as large and
-// uniform values 1.5e-7 to 2.8e-7 (1.8e-7 to 6.1e-7).  Below 128 positions there is little to gain and at d = 64 little difference in error (32 causal
-// ones 1.7e-7 against 1.6e-7), so f32_rows keeps them.  Where all logits are almost equal f32_rows is the more accurate: 1000 causal positions, Q times
-// 1e-6, 2.2e-7 against 1.6e-7 to 2.5e-7, without a mask 3.7e-7 against 3.2e-7 to 6.2e-7; 130 causal ones 1.9e-7 against 1.2e-7.
+// Measured error against 64 bits, 86 random problems of 128 to 4096 positions, normal inputs, fp32 MFMAs and this: 2-norm 4.3e-7 and 2.7e-7 on average, the
+// smaller one in all of them (0.90 of the other at most); worst row 1.3e-6 and 6.7e-7 (0.84 at most); largest element over the root mean square 7.3e-6 and 4.3e-6
+// (in 8 of the 86 the larger one, 1.26 times at most).  With Q three times as large and uniform values 4.6e-7 and 2.2e-7, Q four and K twice as large 1.3e-6 and
+// 6.1e-7.  Below 128 positions there is little to gain and at d = 64 little difference in error (32 causal ones 1.7e-7 against 1.6e-7), so f32_rows
+// keeps them.  Where it is the less accurate one: rows of few keys or of one heavy key (an element off by a bit more), logits that are almost equal (24 heads, Q
+// times 1e-6: 130 to 390 causal positions 1.8e-7 against 1.2e-7 to 1.3e-7; from 1000 on the better one), and values that are (1 +- 0.001, d = 128, 1000 and 2049
+// positions without a mask, 1.9e-7 and 2.6e-7 against 1.5e-7 and 2.0e-7).  Query 0 of a causal call, which sees one key, gets that key's value itself.
 //
 // One workgroup = four wavefronts = RG = 4 / KG blocks of 32 query rows times KG groups of keys.  A step takes 32 KG keys.  All four wavefronts
 // fetch them to registers, split them and leave the pieces in LDS, where the layouts and operand reads are those of the bf16 kernel
@@ -23,9 +25,10 @@ namespace flat {
 // A chunk's next fetch goes out when its registers have been split, one step ahead.  Masks and the reference maximum are those of f32_rows.
 //
 // What bounds it: the issue of one wavefront's instructions at d = 128, where the registers (O and its small part 128, Q 64) leave room for one
-// wavefront per SIMD: 16 heads x 4096 429 us, of it 240 with the MFMAs taken out and 260 with nothing but them and the operand reads; at d = 64
-// (two per SIMD) 32 x 4096 420, 231 and 243.  Before, with fp32 MFMAs: 1087 and 1050.  16 causal heads x 2049, d = 128, 162 -> 91; 256 x 700, d = 64, 280 -> 123.
-// Tried: three bf16 pieces and six products (exact splits of any float, 679 and 665 us; errors like these); one accumulator for S with a third piece of Q
+// wavefront per SIMD: 16 heads x 4096 433 us; at d = 64 (two per SIMD) 32 x 4096 431.  Before, with fp32 MFMAs: 1087 and 1050.  16 causal heads x 2049, d = 128,
+// 161 -> 93; 256 x 700, d = 64, 279 -> 120.  (Before values were scaled and small ones looked for, 429 and 420: of it 240 and 231 with the MFMAs taken out, 260 and 243 with
+// nothing but them and the operand reads.)
+// Tried on that: three bf16 pieces and six products (exact splits of any float, 679 and 665 us; errors like these); one accumulator for S with a third piece of Q
 // (2^-11 h: 424 and 419, but spills with two key groups); the left-out product added (no smaller error); one buffer per tensor and two barriers per step (439, 442).
 //
 // What the pieces cannot hold goes to f32_rows, for the 32 RG rows of the workgroup:
@@ -33,16 +36,18 @@ namespace flat {
 //   logits where |q|max c d^1/2 >= 2^10 (a key below 2^-14 is off by up to 2^-36, which then moves a logit by 2^-26; q is scaled by row);
 //   rows of Q below 2^-88 where the scale is above 2^30 (their power of two would be above 2^100);
 //   V whose largest element in the first tile and the last keys is infinite or below 2^-104, or which grows to 8 to 16 times that in between;
+//   a column of V with nothing but values below 2^-20 of that element in the rows of the first tile that one wavefront fetches;
 //   a scale of 0 with masked keys.
 // f32_rows then takes the workgroup's RG row blocks at once, with KG wavefronts each.  Logits, and what the first tile and the last four keys show, are known before
 // any work: 16 x 4096, d = 128, padding of -1e5 at the end 1086 us with fp32 MFMAs alone, 1084; 16 causal x 2049 160 and 143, but 256 x 300 130 and 154, for the
-// rows that a workgroup of 128 has too many.  What else comes up costs the pass on top, where the results are seen: an infinity in the middle 1069 and 1481.
+// rows that a workgroup of 128 has too many; 128 causal x 512, scale 0, 85 and 102.  What else comes up costs the pass on top, where the results are seen: an infinity in
+// the middle 1056 and 1477, 128 causal x 512 85 and 118.  A column at 1e-6 of the others, 16 x 4096, 1076 (1588 before it was looked for in the first tile).
 // V is held times the power of two that brings that element to 2^12 .. 2^13.  Elements that are then below 2^-14, a part in 2^26 of it, are off by up to
 // 2^-36, so a result that is made of those alone would not be what it was, whatever the keys hold that its row does not see or barely.  Results of 2^-14 and
 // more are at most 2^-22 away through them, and so are those of rows that have half of their weight on other keys.  The loop keeps the smallest and the largest
 // value by pair of columns (zeros count as small); only if a smaller result stands in a pair with both, V is read once more for the number of small values in
 // each column, and the rows go to f32_rows if that many keys may have half of the weight.  Of 16 x 4096, d = 128, 430 us, a column of zeros beside an
-// ordinary one takes 476 then, a column 1e-4 of the others 960, a few small values 432 to 458.
+// ordinary one takes 530 then, a column 1e-4 of the others 1045 (fp32 MFMAs alone 1086), zeros for half of the values 436.
 // Probabilities are held times 2^15 below the reference maximum, the lower piece times 2^11 as those of K and V: weights above 2^-25 of a row's largest have
 // all of their bits, smaller ones a step of 2^-48 of it.  Where such weights are all that a column gets (values that select keys) the result is small for
 // its zeros, and the rows go to f32_rows as above.

@@ -1,5 +1,6 @@
 """fp32 path at the sizes where its key split can go wrong: one to a few 32-key tiles per wavefront, tails of a tile, wavefronts
-without a tile, and enough or too few heads for each number of wavefronts per workgroup (1, 2, 4)."""
+without a tile, and enough or too few heads for each number of wavefronts per workgroup (1, 2, 4).  From 129 positions on most of these
+problems take the split products; test_gpu_f32_forms.py runs every form by name."""
 import numpy as np
 import pytest
 
